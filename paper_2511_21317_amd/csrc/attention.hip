@@ -133,36 +133,50 @@ __device__ __forceinline__ f32x16 splat16(float x) {
   return r;
 }
 
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+// keys 16j .. 16j+15 of a step's P^T as the B operand of a 32x32x16 MFMA
+__device__ __forceinline__ bf16x8 p_half(const u32x8& p, int j) {
+  return __builtin_bit_cast(bf16x8, j ? __builtin_shufflevector(p, p, 4, 5, 6, 7) : __builtin_shufflevector(p, p, 0, 1, 2, 3));
+}
+
 // Per-wave softmax state and accumulators.
 template <int QT>
 struct WaveState {
   bf16x8 qf[QT][4];      // Q^T fragments
   f32x16 o_acc[2][QT];   // O^T accumulators, [channel tile][query tile]
   f32x16 s_cur[QT];      // raw scores of the current step
-  u32x4 p_old[QT][2];    // bf16 P^T of the previous step, packed as MFMA B operands
+  u32x8 p_old[QT];       // bf16 P^T of the previous step: two 32x32x16 MFMA B operands, one 16x16x64 one
   float mc[QT];          // shift m in log2 units
   float c;               // factor from raw scores to log2 units (kernel with per-row shifts only)
   float l_run[QT];       // per-lane partial row sums (kernel with per-row shifts)
   f32x4 l_acc[QT];       // row sums of the fast kernel, from the matrix cores: see row_sum_operand()
-  bf16x8 ones_a;
+  bf16x8 ones_a;         // A operand and index operand of the row sums
+  int ones_idx;
 };
 
-// Row sums on the matrix cores (fast kernel).  The P^T registers of a lane (query l%32, keys of
-// half l/32) read as the B operand of a 16x16x32 MFMA put query l%32 in column l%16 and its
-// 8 keys in k-group l/16: column n collects query n from k-groups 0 and 2 and query n+16 from
-// k-groups 1 and 3.  An A operand with ones in row 0 over k-groups {0, 2} and in row 1 over {1, 3}
-// therefore gives D[0][n] = sum over the 16 keys of query n and D[1][n] = the same for query n+16:
-// registers 0 and 1 of lanes 0..15.
+// Row sums on the matrix cores (fast kernel).  A sum does not need the zeros of a structured-sparse A
+// operand: v_smfmac_f32_16x16x64_bf16 takes 64 dense k per instruction in the time the dense
+// 16x16x32 takes 32 (18 cycles each in a register-only loop), and the two k of every four that a row of A
+// drops are taken by another row.  The eight P^T registers of a lane (query l%32, 16 keys of half l/32)
+// are its B operand: query l%32 sits in column l%16, and the hardware pairs the 8 values of A lane
+// group g with B lane group 2g%4 (values 0..3) and 2g%4 + 1 (values 4..7).  So rows 0 and 1 of A hold
+// ones in values 0..3 - the even lane groups of B, queries 0..15 - and rows 2 and 3 in values 4..7 - the
+// odd ones, queries 16..31; rows 0 and 2 keep the k 0, 1 of every four (index 0x4), rows 1 and 3 the k 2, 3
+// (0xE).  D[0][n] + D[1][n] is the sum of query n, D[2][n] + D[3][n] that of query n + 16: registers 0..3
+// of lanes 0..15.  A step's 16 products take 512 matrix-core cycles; its row sums
+// take 36 instead of the 64 of four dense 16x16x32.  Stage 3 is bound by those cycles and the power they
+// draw: 16 heads x 16384 x 16384 878 -> 860 us.
 __device__ __forceinline__ bf16x8 row_sum_operand(int lane) {
-  const int m = lane & 15, kg = lane >> 4;
-  const bool one = (m == 0 && (kg & 1) == 0) || (m == 1 && (kg & 1) == 1);
-  const uint32_t w = one ? 0x3F803F80u : 0u;
-  return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
+  const int m = lane & 15;
+  const uint32_t lo = m < 2 ? 0x3F803F80u : 0u, hi = m == 2 || m == 3 ? 0x3F803F80u : 0u;
+  return __builtin_bit_cast(bf16x8, u32x4{lo, lo, hi, hi});
 }
+__device__ __forceinline__ int row_sum_index(int lane) { return (lane & 1) ? (int)0xEEEEEEEEu : 0x44444444; }
 
 // exp2(s*c - m) (SHIFT) or exp2(s), bf16 pack and row sum of one query tile.
 template <bool SHIFT>
-__device__ __forceinline__ float exp_pack(const f32x16& s, float c, float m, u32x4 (&p)[2]) {
+__device__ __forceinline__ float exp_pack(const f32x16& s, float c, float m, u32x8& p) {
   const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
   float ps = 0.f;
 #pragma unroll
@@ -172,7 +186,7 @@ __device__ __forceinline__ float exp_pack(const f32x16& s, float c, float m, u32
       const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[8 * j + 2 * e], c, -m) : s[8 * j + 2 * e]);
       const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[8 * j + 2 * e + 1], c, -m) : s[8 * j + 2 * e + 1]);
       const uint32_t w = pack_bf16x2(p0, p1);
-      p[j][e] = w;
+      p[4 * j + e] = w;
       if (SHIFT) ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones2, ps, false);
     }
   return ps;
@@ -252,14 +266,12 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
           w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              op.av[dt * 2 + j], __builtin_bit_cast(bf16x8, w.p_old[qt][j]), w.o_acc[dt][qt], 0, 0, 0);
+              op.av[dt * 2 + j], p_half(w.p_old[qt], j), w.o_acc[dt][qt], 0, 0, 0);
     if (!SHIFT) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
-          w.l_acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              w.ones_a, __builtin_bit_cast(bf16x8, w.p_old[qt][j]), w.l_acc[qt], 0, 0, 0);
+      for (int qt = 0; qt < QT; ++qt)
+        w.l_acc[qt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+            w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[qt]), w.l_acc[qt], w.ones_idx, 0, 0);
     }
   }
   if (DO_SM) {
@@ -274,7 +286,7 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
         }
       }
     }
-    u32x4 p_new[QT][2];
+    u32x8 p_new[QT];
     float psum[QT];
     if (!SHIFT) {
 #pragma unroll
@@ -320,8 +332,7 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
       if (SHIFT) w.l_run[qt] += psum[qt];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) w.p_old[qt][j] = p_new[qt][j];
+      w.p_old[qt] = p_new[qt];
     }
   }
   if (DO_QK) {
@@ -334,7 +345,7 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
 // share of the softmax of the current step (two exp2, one bf16 pack of the pair before), fenced so
 // that the compiler keeps the interleave.  PV of step t-1 first (the V operands retire, their
 // successors are requested), then QK^T of step t+1 and the K operands; a row-sum MFMA after every
-// fourth product.  `between` runs after the step's last LDS read: the global->LDS requests of the
+// eighth product.  `between` runs after the step's last LDS read: the global->LDS requests of the
 // iteration go there, because the compiler makes every LDS read wait for all requests issued
 // before it in program order.
 template <int QT, bool SHIFT, bool PREFETCH, typename Between>
@@ -344,7 +355,7 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   constexpr int NG = 8 * QT;
   f32x16 s_next[QT];
   float ex[16 * QT];
-  u32x4 p_new[QT][2];
+  u32x8 p_new[QT];
   float psum[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) psum[qt] = 0.f;
@@ -361,17 +372,17 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   auto pack = [&](int p) {
     uint32_t r = pack_bf16x2(ex[2 * p], ex[2 * p + 1]);
     asm volatile("" : "+v"(r));
-    p_new[p >> 3][(p & 7) >> 2][p & 3] = r;
+    p_new[p >> 3][p & 7] = r;
     if (SHIFT) {
       psum[p >> 3] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r), ones2, psum[p >> 3], false);
       asm volatile("" : "+v"(psum[p >> 3]));
     }
   };
-  auto row_sum = [&](int g) {   // a row-sum MFMA after every fourth product: 2 * QT per step, (query tile, j)
-    if (!SHIFT && (g & 3) == 3) {
-      const int r = g >> 2, rq = r % QT, rj = r / QT;
-      w.l_acc[rq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-          w.ones_a, __builtin_bit_cast(bf16x8, w.p_old[rq][rj]), w.l_acc[rq], 0, 0, 0);
+  auto row_sum = [&](int g) {   // a row-sum MFMA after every eighth product: QT per step
+    if (!SHIFT && (g & 7) == 3) {
+      const int rq = g >> 3;
+      w.l_acc[rq] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[rq]), w.l_acc[rq], w.ones_idx, 0, 0);
     }
   };
   // PV of step t-1 first: the V operands retire and their successors are requested ...
@@ -379,7 +390,7 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   for (int g = 0; g < NG / 2; ++g) {
     const int qt = g % QT, dt = (g / QT) & 1, j = g / (2 * QT);
     w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-        op.av[dt * 2 + j], __builtin_bit_cast(bf16x8, w.p_old[qt][j]), w.o_acc[dt][qt], 0, 0, 0);
+        op.av[dt * 2 + j], p_half(w.p_old[qt], j), w.o_acc[dt][qt], 0, 0, 0);
     soft(g);
     if (g > 0) pack(g - 1);
     row_sum(g);
@@ -435,8 +446,7 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     w.s_cur[qt] = s_next[qt];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) w.p_old[qt][j] = p_new[qt][j];
+    w.p_old[qt] = p_new[qt];
   }
 }
 
@@ -552,6 +562,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
 
   w.c = a.scale_log2;
   w.ones_a = row_sum_operand(lane);
+  w.ones_idx = row_sum_index(lane);
   const int n_tiles = (Mk + kKvTile - 1) / kKvTile;
 
   // Steps are numbered t = 0 .. 2*n_tiles-1 (32 keys each).  Outer iteration j runs the pipeline
@@ -648,7 +659,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     if (SHIFT) {
       l_tot[qt] = w.l_run[qt] + __shfl_xor(w.l_run[qt], 32);
     } else {
-      const float s0 = __shfl(w.l_acc[qt][0], l32 & 15), s1 = __shfl(w.l_acc[qt][1], l32 & 15);
+      const float s0 = __shfl(w.l_acc[qt][0] + w.l_acc[qt][1], l32 & 15);
+      const float s1 = __shfl(w.l_acc[qt][2] + w.l_acc[qt][3], l32 & 15);
       l_tot[qt] = l32 < 16 ? s0 : s1;
     }
   }
