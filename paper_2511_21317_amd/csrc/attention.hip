@@ -40,24 +40,17 @@
 //
 // Softmax without a running maximum.  softmax is invariant to the per-row shift m, and fp32 /
 // bf16 keep their relative precision over the whole exponent range, so m only has to keep
-// exp2(s - m) inside that range - it does not have to be the maximum.  Per row, m is the exact
-// maximum of the first 32 keys and is then left alone; the vector ALU does one fma (scale and
-// shift), exp2, the bf16 conversion and the row sum (a bf16 dot2 against ones) per score, and no
-// max, no rescaling of O.  Because the first block's maximum contributes exp2(0) = 1, the row
-// sum can never underflow.  Overflow is caught: if a lane's partial row sum of a step is not
-// below 2^60 (this also catches inf / NaN), the wave redoes that step's softmax with m raised to
-// the step's true maximum and rescales its O and l accumulators - the classic online-softmax
-// update, taken only when needed.
-//
-// Two kernels.  The one described so far (SHIFT = true) takes any keys and any scale.  When stage 2
-// has left the merged keys multiplied by scale * log2(e) ("log2 keys": the factor goes into the
-// fp32 mean before its one rounding to bf16, so nothing is rounded twice), the raw MFMA scores are
-// the base-2 logits, and the fast kernel (SHIFT = false) uses the weights exp2(s) as they are: no
-// fma, no shift - a quarter of the vector work per score gone - and takes the row sums from the
-// matrix cores as well (row_sum_operand()).  That is safe while a row's sum
-// stays well inside the fp32 range; every workgroup checks its final row sums against
-// [2^-64, 2^64] and, if a row is outside (or inf / NaN), writes a mark instead of its tile.  The
-// SHIFT kernel is launched right behind on the same grid and redoes exactly the marked tiles.
+// exp2(s - m) inside that range - it does not have to be the maximum.  When stage 2 has left the
+// merged keys multiplied by scale * log2(e) ("log2 keys": the factor goes into the fp32 mean before its
+// one rounding to bf16, so nothing is rounded twice), the raw MFMA scores are the base-2 logits and the
+// kernel (SHIFT = false) uses the weights exp2(s) as they are.  With any other keys (SHIFT = true) it
+// takes one fma per score, scale and shift, with m the row's exact maximum over the first 32 keys, left
+// alone from there on.  Neither looks at the sums inside the loop: the row sums come from the matrix
+// cores (row_sum_operand()), and a tile is checked once, at its end.  If a row's sum is outside
+// [2^-64, 2^64] (or inf / NaN), the workgroup takes the tile again with running maxima
+// (running_max_step(): the classic online softmax, not pipelined).  Measured against a guard inside the loop for plain keys (a dot2
+// against ones and a compare per score pair) and a second launch that redid marked tiles for log2 keys:
+// 16 ragged heads of 5500 x 9000 plain keys 219 -> 201 us, two 16 x 16 frames 27.3 -> 24.3 us a layer.
 //
 // End of a launch.  A CU runs its 256-row tiles two at a time, but one alone nearly twice as fast,
 // so the launch time follows the largest number of whole tiles a CU gets.  When the caller has given
@@ -78,8 +71,6 @@ namespace {
 
 constexpr int kKvTile = 64;
 constexpr int kStep = 32;                               // keys per pipeline step
-constexpr float kSumLimit = 1.152921504606846976e18f;  // 2^60
-constexpr float kShiftLimit = 60.0f;
 
 struct AttnArgs {
   const bf16_t* q;
@@ -87,7 +78,6 @@ struct AttnArgs {
   const bf16_t* v;
   bf16_t* o;
   float scale_log2;  // scale * log2(e); 1 when the keys carry that factor already
-  int32_t marked_only;  // the kernel with per-row shifts redoes only the tiles the fast kernel marked
   int32_t H;
   int32_t n_full;                             // tiles with all BQ query rows
   int32_t n_ragged;                           // heads whose last tile is partial
@@ -149,13 +139,12 @@ struct WaveState {
   u32x8 p_old[QT];       // bf16 P^T of the previous step: two 32x32x16 MFMA B operands, one 16x16x64 one
   float mc[QT];          // shift m in log2 units
   float c;               // factor from raw scores to log2 units (kernel with per-row shifts only)
-  float l_run[QT];       // per-lane partial row sums (kernel with per-row shifts)
-  f32x4 l_acc[QT];       // row sums of the fast kernel, from the matrix cores: see row_sum_operand()
+  f32x4 l_acc[QT];       // row sums, from the matrix cores: see row_sum_operand()
   bf16x8 ones_a;         // A operand and index operand of the row sums
   int ones_idx;
 };
 
-// Row sums on the matrix cores (fast kernel).  A sum does not need the zeros of a structured-sparse A
+// Row sums on the matrix cores.  A sum does not need the zeros of a structured-sparse A
 // operand: v_smfmac_f32_16x16x64_bf16 takes 64 dense k per instruction in the time the dense
 // 16x16x32 takes 32 (18 cycles each in a register-only loop), and the two k of every four that a row of A
 // drops are taken by another row.  The eight P^T registers of a lane (query l%32, 16 keys of half l/32)
@@ -174,22 +163,23 @@ __device__ __forceinline__ bf16x8 row_sum_operand(int lane) {
 }
 __device__ __forceinline__ int row_sum_index(int lane) { return (lane & 1) ? (int)0xEEEEEEEEu : 0x44444444; }
 
-// exp2(s*c - m) (SHIFT) or exp2(s), bf16 pack and row sum of one query tile.
+// exp2(s*c - m) (SHIFT) or exp2(s) and bf16 pack of one query tile.
 template <bool SHIFT>
-__device__ __forceinline__ float exp_pack(const f32x16& s, float c, float m, u32x8& p) {
-  const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
-  float ps = 0.f;
+__device__ __forceinline__ void exp_pack(const f32x16& s, float c, float m, u32x8& p) {
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int e = 0; e < 8; ++e) {
+    const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[2 * e], c, -m) : s[2 * e]);
+    const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[2 * e + 1], c, -m) : s[2 * e + 1]);
+    p[e] = pack_bf16x2(p0, p1);
+  }
+}
+
+// The largest score of a query column among the 32 keys of a step (both half-waves).
+__device__ __forceinline__ float step_max(const f32x16& s) {
+  float t = s[0];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[8 * j + 2 * e], c, -m) : s[8 * j + 2 * e]);
-      const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[8 * j + 2 * e + 1], c, -m) : s[8 * j + 2 * e + 1]);
-      const uint32_t w = pack_bf16x2(p0, p1);
-      p[4 * j + e] = w;
-      if (SHIFT) ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones2, ps, false);
-    }
-  return ps;
+  for (int r = 1; r < 16; ++r) t = fmaxf(t, s[r]);
+  return fmaxf(t, __shfl_xor(t, 32));
 }
 
 // MFMA A operands of one step: 4 K fragments (32 key rows x 64 channels) and 4 V^T fragments
@@ -267,12 +257,10 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
         for (int qt = 0; qt < QT; ++qt)
           w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               op.av[dt * 2 + j], p_half(w.p_old[qt], j), w.o_acc[dt][qt], 0, 0, 0);
-    if (!SHIFT) {
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-        w.l_acc[qt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-            w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[qt]), w.l_acc[qt], w.ones_idx, 0, 0);
-    }
+    for (int qt = 0; qt < QT; ++qt)
+      w.l_acc[qt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[qt]), w.l_acc[qt], w.ones_idx, 0, 0);
   }
   if (DO_SM) {
     // s_cur[qt][r]: key kv_first + 8*(r/4) + 4*half + r%4, query column l32 of tile qt
@@ -286,53 +274,10 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
         }
       }
     }
-    u32x8 p_new[QT];
-    float psum[QT];
-    if (!SHIFT) {
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) psum[qt] = exp_pack<false>(w.s_cur[qt], 1.f, 0.f, p_new[qt]);
-    } else if (FIRST) {
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        float tmax = w.s_cur[qt][0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, w.s_cur[qt][r]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        w.mc[qt] = tmax * w.c;
-        psum[qt] = exp_pack<true>(w.s_cur[qt], w.c, w.mc[qt], p_new[qt]);
-      }
-    } else {
-      bool redo = false;
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        psum[qt] = exp_pack<true>(w.s_cur[qt], w.c, w.mc[qt], p_new[qt]);
-        redo = redo || !(psum[qt] < kSumLimit);
-      }
-      // rare: raise m to this step's maximum where needed and redo the step's softmax
-      if (__any(redo)) {
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-          float tmax = w.s_cur[qt][0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, w.s_cur[qt][r]);
-          tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-          const float rel = fmaf(tmax, w.c, -w.mc[qt]);  // log2 units above the current m
-          const float delta = rel > kShiftLimit ? rel : 0.f;
-          const float sc = __builtin_amdgcn_exp2f(-delta);
-          w.l_run[qt] *= sc;
-#pragma unroll
-          for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) w.o_acc[dt][qt][r] *= sc;
-          w.mc[qt] += delta;
-          psum[qt] = exp_pack<true>(w.s_cur[qt], w.c, w.mc[qt], p_new[qt]);
-        }
-      }
-    }
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
-      if (SHIFT) w.l_run[qt] += psum[qt];
-      w.p_old[qt] = p_new[qt];
+      if (SHIFT && FIRST) w.mc[qt] = step_max(w.s_cur[qt]) * w.c;
+      exp_pack<SHIFT>(w.s_cur[qt], w.c, w.mc[qt], w.p_old[qt]);
     }
   }
   if (DO_QK) {
@@ -341,7 +286,7 @@ __device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk
   }
 }
 
-// The steady-state step (of both kernels) with the order of issue written out: one MFMA, then its
+// The steady-state step with the order of issue written out: one MFMA, then its
 // share of the softmax of the current step (two exp2, one bf16 pack of the pair before), fenced so
 // that the compiler keeps the interleave.  PV of step t-1 first (the V operands retire, their
 // successors are requested), then QK^T of step t+1 and the K operands; a row-sum MFMA after every
@@ -356,10 +301,6 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   f32x16 s_next[QT];
   float ex[16 * QT];
   u32x8 p_new[QT];
-  float psum[QT];
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) psum[qt] = 0.f;
-  const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
   auto soft = [&](int g) {   // values 2g, 2g+1 of the 32 scores of this lane
     // (the empty asm after a result only pins where the instruction is issued)
     const int qt = (2 * g) >> 4;
@@ -373,13 +314,9 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
     uint32_t r = pack_bf16x2(ex[2 * p], ex[2 * p + 1]);
     asm volatile("" : "+v"(r));
     p_new[p >> 3][p & 7] = r;
-    if (SHIFT) {
-      psum[p >> 3] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r), ones2, psum[p >> 3], false);
-      asm volatile("" : "+v"(psum[p >> 3]));
-    }
   };
   auto row_sum = [&](int g) {   // a row-sum MFMA after every eighth product: QT per step
-    if (!SHIFT && (g & 7) == 3) {
+    if ((g & 7) == 3) {
       const int rq = g >> 3;
       w.l_acc[rq] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
           w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[rq]), w.l_acc[rq], w.ones_idx, 0, 0);
@@ -416,33 +353,6 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   __builtin_amdgcn_sched_barrier(0);
   between();        // requests that must follow the step's last LDS read in program order
   __builtin_amdgcn_sched_barrier(0);
-  if (SHIFT) {
-    // rare: raise m to this step's maximum where a row sum left the range, redo the step's weights
-    bool redo = false;
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) redo = redo || !(psum[qt] < kSumLimit);
-    if (__any(redo)) {
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        float tmax = w.s_cur[qt][0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, w.s_cur[qt][r]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        const float rel = fmaf(tmax, w.c, -w.mc[qt]);
-        const float delta = rel > kShiftLimit ? rel : 0.f;
-        const float sc = __builtin_amdgcn_exp2f(-delta);
-        w.l_run[qt] *= sc;
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) w.o_acc[dt][qt][r] *= sc;
-        w.mc[qt] += delta;
-        psum[qt] = exp_pack<true>(w.s_cur[qt], w.c, w.mc[qt], p_new[qt]);
-      }
-    }
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) w.l_run[qt] += psum[qt];
-  }
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     w.s_cur[qt] = s_next[qt];
@@ -450,14 +360,47 @@ __device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, 
   }
 }
 
-// bf16 bit pattern (a NaN with a payload that arithmetic does not produce) that the fast kernel
-// leaves in channel 0 of a tile's first output row when the tile has to be redone.
-constexpr uint16_t kRedoMark = 0x7FA5;
-// Row sums the fast kernel accepts (inf and NaN fail the test as well): inside, the weights of a
+// Row sums the pipelined pass accepts (inf and NaN fail the test as well): inside, the weights of a
 // row's best keys are far from both ends of the fp32 range, and no weight exceeds 2^64, so that the
 // unnormalised products with V stay finite for |v| below 1e19.
 constexpr float kFastSumMin = 5.421010862427522e-20f;    // 2^-64
 constexpr float kFastSumMax = 1.8446744073709552e19f;    // 2^64
+
+// One step of 32 keys with a running maximum per row (the classic online softmax), for tiles whose
+// rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.
+template <int QT>
+__device__ __forceinline__ void running_max_step(WaveState<QT>& w, float (&l)[QT], const bf16_t* sk, const bf16_t* sv,
+                                                 int kv_first, int Mk, int l32, int half) {
+  const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
+  StepOperands op;
+  load_k_operands(op, sk, l32, half);
+  load_v_operands(op, sv, l32, half);
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    f32x16 s = splat16(0.f);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.ak[ks], w.qf[qt][ks], s, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (kv_first + 8 * (r >> 2) + 4 * half + (r & 3) >= Mk) s[r] = -INFINITY;
+    const float m = fmaxf(w.mc[qt], step_max(s) * w.c);
+    const float sc = __builtin_amdgcn_exp2f(w.mc[qt] - m);
+    w.mc[qt] = m;
+    u32x8 p;
+    exp_pack<true>(s, w.c, m, p);
+    l[qt] *= sc;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) l[qt] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)p[e]), ones2, l[qt], false);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) w.o_acc[dt][qt][r] *= sc;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.av[dt * 2 + j], p_half(p, j), w.o_acc[dt][qt], 0, 0, 0);
+    }
+  }
+}
 
 // One query tile (or one segment of it) of a workgroup: see attention_kernel.
 //   h, q0          : head and first query row of the tile
@@ -478,8 +421,6 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   const bf16_t* __restrict__ q_rows = dev_tile ? a.q2 : a.q;
   bf16_t* __restrict__ o_rows = dev_tile ? a.o2 : a.o;
   int Mk = (int)(a.k_off[h + 1] - k_base);
-  uint16_t* mark = (uint16_t*)(o_rows + (q_base + q0) * kDHead);
-  if (SHIFT && a.marked_only && (Mk == 0 || *(volatile const uint16_t*)mark != kRedoMark)) return;
 
   // (the empty asm keeps per-lane values that derive from the thread index from being computed once
   // in front of the loop over a share's segments and held in registers across the whole tile)
@@ -518,7 +459,6 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) w.qf[qt][ks] = *(const bf16x8*)(p + ks * 16);
     w.mc[qt] = 0.f;
-    w.l_run[qt] = 0.f;
     w.l_acc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt) w.o_acc[dt][qt] = splat16(0.f);
@@ -654,18 +594,45 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   }
 
   float l_tot[QT];
+  bool bad = false;
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
-    if (SHIFT) {
-      l_tot[qt] = w.l_run[qt] + __shfl_xor(w.l_run[qt], 32);
-    } else {
-      const float s0 = __shfl(w.l_acc[qt][0] + w.l_acc[qt][1], l32 & 15);
-      const float s1 = __shfl(w.l_acc[qt][2] + w.l_acc[qt][3], l32 & 15);
-      l_tot[qt] = l32 < 16 ? s0 : s1;
-    }
+    const float s0 = __shfl(w.l_acc[qt][0] + w.l_acc[qt][1], l32 & 15);
+    const float s1 = __shfl(w.l_acc[qt][2] + w.l_acc[qt][3], l32 & 15);
+    l_tot[qt] = l32 < 16 ? s0 : s1;
+    bad = bad || !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax);
   }
+  // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
+  // stages its tiles together) takes the tile again with running maxima.
+  if (__syncthreads_or(active && bad)) {
+    if (active) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        w.mc[qt] = -1e30f;
+        l_tot[qt] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) w.o_acc[dt][qt] = splat16(0.f);
+      }
+    }
+#pragma unroll 1
+    for (int kv0 = 0; kv0 < Mk; kv0 += kKvTile) {
+      load_k(kv0, 0);
+      load_v(kv0, 0);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      if (active) {
+#pragma unroll 1
+        for (int st = 0; st < kKvTile && kv0 + st < Mk; st += kStep)
+          running_max_step<QT>(w, l_tot, &s_k[0][st * kDHead], &s_v[0][st * kDHead], kv0 + st, Mk, l32, half);
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) l_tot[qt] += __shfl_xor(l_tot[qt], 32);
+  }
+
   if (piece) {
-    // a segment: unnormalised sums (and the shifts they are relative to) for attention_split_reduce_kernel
+    // a segment: unnormalised sums and the shifts they are relative to, for attention_split_reduce_kernel
     if (active) {
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
@@ -684,23 +651,12 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
                         w.o_acc[dt][qt][4 * g + 3]};
           if (half == 0) {
             a.split_l[piece_row0 + (row - q0)] = l_tot[qt];
-            if (SHIFT) a.split_m[piece_row0 + (row - q0)] = w.mc[qt];
+            a.split_m[piece_row0 + (row - q0)] = w.mc[qt];
           }
         }
       }
     }
     return;
-  }
-  if (!SHIFT) {
-    // Rare: a row of this tile left the range in which unshifted weights are safe.  The whole
-    // workgroup (its tiles are staged together) leaves the tile to the kernel with per-row shifts.
-    bool bad = false;
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) bad = bad || !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax);
-    if (__syncthreads_or(active && bad)) {
-      if (tid == 0) *mark = kRedoMark;
-      return;
-    }
   }
 
   // ---- normalise and store ---------------------------------------------------------------------
@@ -723,9 +679,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   }
 }
 
-// SHIFT = false: the fast kernel (keys carry the logit scale; weights exp2(s)).  SHIFT = true: per-row
-// shifts and the overflow guard; with a.marked_only it is launched right after the fast kernel on
-// the same grid and a workgroup leaves at once unless the fast kernel marked its tile.
+// SHIFT = false: the keys carry the logit scale, weights exp2(s).  SHIFT = true: any keys and scale.
 template <int QT, int NW, bool SHIFT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, QT == 1 ? 3 : 2)))
 void attention_kernel(const AttnArgs a) {
@@ -785,80 +739,72 @@ void attention_kernel(const AttnArgs a) {
   }
 }
 
-// The split tiles after a kernel ran them in segments: four workgroups per split tile (64 rows each)
-// add its segments in ascending key order (run-to-run identical) and store the normalised rows.
-// After the fast kernel every workgroup tests the row sums of the whole tile like that kernel does (a
-// tile with a row outside the window gets the mark and is redone by the kernel with per-row
-// shifts); after the kernel with per-row shifts every segment is first brought to the largest of
-// the segments' shifts of its row.
+// The split tiles after attention_kernel ran them in segments: four workgroups per split tile (64 rows
+// each) bring its segments to the largest of their shifts of a row (all zero unless a segment had
+// to take running maxima or the keys are plain), add them in ascending key order (run-to-run
+// identical) and store the normalised rows.  Bound by the latency of one chain of loads - 16 to 30 MB
+// over the chip - so every thread fetches the sums and the shifts of its own row next to its
+// values instead of taking them from LDS behind a barrier, kReduceBatch segments at a time.
 constexpr int kReduceRows = 64;
-template <int BQ, bool SHIFT>
+constexpr int kReduceBatch = 3;
 __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnArgs a) {
-  static_assert(BQ == 256, "one thread per row of the tile in the first phase");
-  __shared__ float s_inv[BQ];
-  __shared__ float s_max[SHIFT ? BQ : 1];      // the row's largest shift
+  constexpr int BQ = kAttnTileRows;
   __shared__ __align__(16) uint32_t s_out[kReduceRows * 32];   // the normalised bf16 rows, for whole-line stores
   const int e = blockIdx.x >> 2, part = blockIdx.x & 3, tid = threadIdx.x;
   const SplitTile t = split_tile(a.sp, e);
   const int64_t q_base = a.q_off[t.head];
   const int left = (int)(a.q_off[t.head + 1] - q_base) - t.q0;
   const int rows = left < BQ ? left : BQ;
+  if (part * kReduceRows >= rows) return;
   const int np = t.last_share - t.first_share + 1;
   // consecutive shares of one tile have consecutive slots
   const int64_t row0 = (int64_t)split_slot(t.first_share, e) * BQ;     // segment p: rows from row0 + p * BQ
-  // ---- the row sums of the whole tile (every workgroup of the tile, so that all four decide alike)
-  bool bad = false;
-  if (tid < rows) {
-    float l = 0.f;
-    if (SHIFT) {
-      float m = -1e30f;
-#pragma unroll 4
-      for (int p = 0; p < np; ++p) m = fmaxf(m, a.split_m[row0 + (int64_t)p * BQ + tid]);
-#pragma unroll 4
-      for (int p = 0; p < np; ++p) {
-        const float wgt = __builtin_amdgcn_exp2f(a.split_m[row0 + (int64_t)p * BQ + tid] - m);
-        l = fmaf(a.split_l[row0 + (int64_t)p * BQ + tid], wgt, l);
-      }
-      s_max[tid] = m;
-    } else {
-#pragma unroll 4
-      for (int p = 0; p < np; ++p) l += a.split_l[row0 + (int64_t)p * BQ + tid];
-      bad = !(l >= kFastSumMin && l <= kFastSumMax);
-    }
-    s_inv[tid] = 1.0f / l;
-  }
-  if (__syncthreads_or(bad)) {
-    if (tid == 0 && part == 0) *(uint16_t*)(a.o + (q_base + t.q0) * kDHead) = kRedoMark;
-    return;
-  }
-  // ---- rows part * 64 .. + 63: thread -> row r = tid % 64 and the 16-byte output chunks c, c + 4
+  // thread -> row r = tid % 64 of the part and the 16-byte output chunks c0, c0 + 4
   const int r = part * kReduceRows + (tid & 63), c0 = tid >> 6;
-  if (part * kReduceRows >= rows) return;
   const int rr = r < rows ? r : rows - 1;          // a row past the end reads a valid row and stores nothing
   float acc[2][8];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[i][q] = 0.f;
-  const float m_row = SHIFT ? s_max[rr] : 0.f;
-#pragma unroll 4
-  for (int p = 0; p < np; ++p) {
-    const float* ps = a.split_o + (row0 + (int64_t)p * BQ) * kDHead + rr * 4;
-    f32x4 v[2][2];
+  float m_row = -1e30f, l_row = 0.f;
+  for (int p0 = 0; p0 < np; p0 += kReduceBatch) {
+    f32x4 v[kReduceBatch][2][2];
+    float m[kReduceBatch], l[kReduceBatch];
+#pragma unroll
+    for (int u = 0; u < kReduceBatch; ++u) {
+      const int64_t row = row0 + (int64_t)(p0 + u < np ? p0 + u : np - 1) * BQ + rr;   // past the last one: that one again
+      m[u] = a.split_m[row];
+      l[u] = a.split_l[row];
+      const float* ps = a.split_o + (row - rr) * kDHead + rr * 4;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) v[u][i][hf] = *(const f32x4*)(ps + ((c0 + 4 * i) * 2 + hf) * (BQ * 4));
+    }
+    float m_new = m_row;
+#pragma unroll
+    for (int u = 0; u < kReduceBatch; ++u) m_new = fmaxf(m_new, m[u]);
+    const float old = __builtin_amdgcn_exp2f(m_row - m_new);
+    m_row = m_new;
+    l_row *= old;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) v[i][hf] = *(const f32x4*)(ps + ((c0 + 4 * i) * 2 + hf) * (BQ * 4));
-    const float wgt = SHIFT ? __builtin_amdgcn_exp2f(a.split_m[row0 + (int64_t)p * BQ + rr] - m_row) : 1.0f;
+      for (int q = 0; q < 8; ++q) acc[i][q] *= old;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < kReduceBatch; ++u) {
+      const float wgt = p0 + u < np ? __builtin_amdgcn_exp2f(m[u] - m_row) : 0.f;
+      l_row = fmaf(l[u], wgt, l_row);
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          acc[i][4 * hf + q] = SHIFT ? fmaf(v[i][hf][q], wgt, acc[i][4 * hf + q]) : acc[i][4 * hf + q] + v[i][hf][q];
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[i][4 * hf + q] = fmaf(v[u][i][hf][q], wgt, acc[i][4 * hf + q]);
+    }
   }
-  const float inv = s_inv[rr];
+  const float inv = 1.0f / l_row;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     u32x4 o;
@@ -892,9 +838,16 @@ constexpr int64_t kSmallTileRound = 768;
 
 // `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
 // `scratch` (fp32 words, or nullptr): room for the tiles that run in segments (attention_split.hpp).
-// a.marked_only != 0: the fast kernel, then the kernel with per-row shifts on the marked tiles.
 template <int QT, int NW>
-hipError_t launch_cfg(AttnArgs& a, const int64_t* q_off_host, const int64_t* k_off_host, int H,
+void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t stream) {
+  if (log2_keys)
+    hipLaunchKernelGGL((attention_kernel<QT, NW, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
+  else
+    hipLaunchKernelGGL((attention_kernel<QT, NW, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
+}
+
+template <int QT, int NW>
+hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, const int64_t* k_off_host, int H,
                       hipStream_t stream, int extra_tiles = 0, float* scratch = nullptr, int64_t scratch_words = 0) {
   constexpr int BQ = 32 * QT * NW;
   int64_t full = 0;
@@ -925,46 +878,32 @@ hipError_t launch_cfg(AttnArgs& a, const int64_t* q_off_host, const int64_t* k_o
   a.split_m = nullptr;
   a.sp.n_tiles = 0;
   a.sp.slots = 0;
-  const unsigned grid = (unsigned)a.main_blocks + (unsigned)extra_tiles;
-  AttnArgs f = a;   // the first launch when tiles are split
-  unsigned fgrid = grid;
-  bool split = false;
   if (BQ == kAttnTileRows && scratch) {
     int64_t kept_full = full;
     int split_ragged = 0;
-    plan_attention_split(q_off_host, k_off_host, H, compute_units(), &f.sp, &kept_full, &split_ragged);
-    const int64_t slots = split_slots(f.sp);
-    split = f.sp.n_tiles > 0 && slots * kAttnSlotWords <= scratch_words;
-    if (split) {
+    plan_attention_split(q_off_host, k_off_host, H, compute_units(), &a.sp, &kept_full, &split_ragged);
+    const int64_t slots = split_slots(a.sp);
+    if (a.sp.n_tiles > 0 && slots * kAttnSlotWords <= scratch_words) {
       // the first partial tiles (in head order) and the last full tiles run in segments; the others
       // keep their order: partial tiles in front of the full tiles
-      f.n_full = (int32_t)kept_full;
-      f.full_per_xcd = (int32_t)((kept_full + 7) / 8);
-      f.n_ragged = ragged - split_ragged;
-      f.ragged_per_xcd = (f.n_ragged + 7) / 8;
-      for (int i = 0; i < f.n_ragged; ++i) f.ragged_head[i] = a.ragged_head[split_ragged + i];
-      f.split_per_xcd = (f.sp.shares + 7) / 8;
-      f.main_blocks = 8 * (f.full_per_xcd + f.ragged_per_xcd + f.split_per_xcd);
-      f.split_o = scratch;
-      f.split_l = scratch + slots * kAttnTileRows * kDHead;
-      f.split_m = f.split_l + slots * kAttnTileRows;
-      fgrid = (unsigned)f.main_blocks + (unsigned)extra_tiles;
+      a.n_full = (int32_t)kept_full;
+      a.full_per_xcd = (int32_t)((kept_full + 7) / 8);
+      a.n_ragged = ragged - split_ragged;
+      a.ragged_per_xcd = (a.n_ragged + 7) / 8;
+      for (int i = 0; i < a.n_ragged; ++i) a.ragged_head[i] = a.ragged_head[split_ragged + i];
+      a.split_per_xcd = (a.sp.shares + 7) / 8;
+      a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd + a.split_per_xcd);
+      a.split_o = scratch;
+      a.split_l = scratch + slots * kAttnTileRows * kDHead;
+      a.split_m = a.split_l + slots * kAttnTileRows;
     } else {
-      f.sp.n_tiles = 0;
-      f.sp.slots = 0;
+      a.sp.n_tiles = 0;
+      a.sp.slots = 0;
     }
   }
-  if (a.marked_only) {
-    // the fast kernel (and the sum of its segments), then the kernel with per-row shifts on the marked tiles
-    hipLaunchKernelGGL((attention_kernel<QT, NW, false>), dim3(fgrid), dim3(64 * NW), 0, stream, f);
-    if (split)
-      hipLaunchKernelGGL((attention_split_reduce_kernel<kAttnTileRows, false>), dim3(4u * (unsigned)f.sp.n_tiles), dim3(256), 0, stream, f);
-    hipLaunchKernelGGL((attention_kernel<QT, NW, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL((attention_kernel<QT, NW, true>), dim3(fgrid), dim3(64 * NW), 0, stream, f);
-    if (split)
-      hipLaunchKernelGGL((attention_split_reduce_kernel<kAttnTileRows, true>), dim3(4u * (unsigned)f.sp.n_tiles), dim3(256), 0, stream, f);
-  }
+  launch_kernel<QT, NW>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
+  if (a.sp.n_tiles > 0)
+    hipLaunchKernelGGL(attention_split_reduce_kernel, dim3(4u * (unsigned)a.sp.n_tiles), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -991,7 +930,6 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
   a.v = (const bf16_t*)v;
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.marked_only = log2_keys ? 1 : 0;
   a.H = H;
   for (int h = 0; h <= kAttnMaxHeads; ++h) a.k_off[h] = k_off_host[h < H ? h : H];
   a.dev_q_off = q_off_dev;
@@ -999,9 +937,7 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
   a.q2 = a.q;
   a.o2 = a.o;
   a.main_blocks = 0;        // no whole tiles, no segments: every workgroup takes the device-side list
-  if (a.marked_only)
-    hipLaunchKernelGGL((attention_kernel<2, 4, false>), dim3((unsigned)max_tiles), dim3(256), 0, stream, a);
-  hipLaunchKernelGGL((attention_kernel<2, 4, true>), dim3((unsigned)max_tiles), dim3(256), 0, stream, a);
+  launch_kernel<2, 4>(a, log2_keys, (unsigned)max_tiles, stream);
   return hipGetLastError();
 }
 
@@ -1017,13 +953,12 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.v = (const bf16_t*)v;
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.marked_only = log2_keys ? 1 : 0;
   a.H = H;
   a.dev_q_off = q2_off_dev;
   a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
   a.o2 = (bf16_t*)o2;
-  return launch_cfg<2, 4>(a, q_off_host, k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
+  return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
                           scratch_bytes / 4);
 }
 
@@ -1037,7 +972,6 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   a.v = (const bf16_t*)v;
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.marked_only = log2_keys ? 1 : 0;
   a.H = H;
   // Tiles of 256 query rows (two workgroups per CU) are the efficient shape, and with scratch memory
   // the tiles in excess of a multiple of the CU count run in segments, so that any tile count fills
@@ -1050,9 +984,9 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   if (tiles128 <= kSmallTileRound) {
     const bool splits = scratch && attention_scratch_need(q_off_host, k_off_host, H) > 0 &&
                         attention_scratch_need(q_off_host, k_off_host, H) <= scratch_bytes;
-    if (!splits) return launch_cfg<1, 4>(a, q_off_host, k_off_host, H, stream);
+    if (!splits) return launch_cfg<1, 4>(a, log2_keys, q_off_host, k_off_host, H, stream);
   }
-  return launch_cfg<2, 4>(a, q_off_host, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
+  return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------

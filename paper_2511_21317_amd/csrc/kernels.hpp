@@ -134,9 +134,9 @@ hipError_t launch_match_f32(const float* xbar, const int32_t* pi, const WorkItem
 // ---- stage 3 -------------------------------------------------------------------------------
 constexpr int kAttnMaxHeads = HTTM_MAX_HEADS;
 // log2_keys: the keys carry the factor scale * log2(e) already (stage 2 with
-// MatchMergeStream.xm_scale), `scale` is ignored and the fast kernel runs first.
+// MatchMergeStream.xm_scale), `scale` is ignored and the weights are exp2 of the raw scores.
 constexpr float kLog2KeyScale = 0.125f * 1.4426950408889634f;   // log2(e) / sqrt(d_head)
-// `scratch` (device, 16-byte aligned, or nullptr): room for the fast kernel to run the partial last
+// `scratch` (device, 16-byte aligned, or nullptr): room to run the partial last
 // tile of every head in pieces over the keys (attention_scratch_bytes(H) bytes cover any lengths);
 // without it, or when the launch is short, the partial tiles run whole.
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,
