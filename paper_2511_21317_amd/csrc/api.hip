@@ -36,6 +36,12 @@ struct httm_plan {
 
 namespace {
 
+// tokens of the largest work item: a merging block or a pseudo-block of the special prefix
+int32_t plan_max_item(const httm_plan* p) {
+  const int64_t chunk = prefix_chunk((int64_t)p->geom.T * p->geom.b * ((p->geom.flags & HTTM_FLAG_CHUNKED_BLOCKS) ? 1 : p->geom.b));
+  return (int32_t)(p->sizes.max_block < chunk ? chunk : p->sizes.max_block);
+}
+
 thread_local int g_last_hip_error = 0;
 
 int hip_fail(hipError_t e) {
@@ -103,7 +109,7 @@ int run_match_merge(const httm_plan_t* p, const int32_t* pi, const void* q, cons
   a.row_len = (g.flags & HTTM_FLAG_CHUNKED_BLOCKS) ? g.Hp * g.Wp : g.Wp;
   a.N = p->sizes.N;
   a.H = g.H;
-  a.max_block = (int32_t)(p->sizes.max_block < kPrefixChunk ? kPrefixChunk : p->sizes.max_block);
+  a.max_block = plan_max_item(p);
   a.max_k = p->max_k;
   a.top_r = p->geom.dst_frac > 0.0 && p->geom.variant != HTTM_VARIANT_NONE;
   if (p->d_score) {
@@ -163,7 +169,7 @@ int run_match_merge_filtered(const httm_plan_t* p, const void* q, const void* k,
   r.row_len = (p->geom.flags & HTTM_FLAG_CHUNKED_BLOCKS) ? p->geom.Hp * p->geom.Wp : p->geom.Wp;
   r.N = p->sizes.N;
   r.H = p->geom.H;
-  r.max_block = (int32_t)(p->sizes.max_block < kPrefixChunk ? kPrefixChunk : p->sizes.max_block);
+  r.max_block = plan_max_item(p);
   r.eager = (double)p->outlier_cap * (double)p->sizes.max_block >= (double)p->geom.H * (double)p->sizes.N;
   r.b = p->ob;
   if (r.max_block > kSmallBlockMax)

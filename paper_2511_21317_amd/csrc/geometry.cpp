@@ -98,8 +98,9 @@ int build_tables(const httm_geom_t& g, bool with_pi, HostTables* out) {
   // Pseudo-blocks over the prefix: identity clusters.
   t.items_q.clear();
   t.items_k.clear();
-  for (int64_t p = 0; p < t.n_prefix; p += kPrefixChunk) {
-    const int32_t n = (int32_t)((t.n_prefix - p) < kPrefixChunk ? (t.n_prefix - p) : kPrefixChunk);
+  const int32_t chunk = prefix_chunk((int64_t)g.T * g.b * (chunked ? 1 : g.b));
+  for (int64_t p = 0; p < t.n_prefix; p += chunk) {
+    const int32_t n = (int32_t)((t.n_prefix - p) < chunk ? (t.n_prefix - p) : chunk);
     t.items_q.push_back({(int32_t)p, n, n, (int32_t)p, 0, n, 0, 0});
     t.items_k.push_back({(int32_t)p, n, n, (int32_t)p, 0, n, 0, 0});
   }

@@ -46,7 +46,9 @@ struct HostTables {
   std::vector<WorkItem> items_q, items_k;  // prefix pseudo-blocks followed by the real blocks
 };
 
-constexpr int kPrefixChunk = 64;  // tokens per pseudo-block of the special prefix
+// tokens per pseudo-block of the special prefix, in a plan whose merging blocks have at most
+// `block` tokens
+inline int32_t prefix_chunk(int64_t block) { return block <= 32 ? 32 : 64; }
 
 // Validate a geometry (returns an HTTM_E_* code).
 int check_geom(const httm_geom_t& g);

@@ -162,24 +162,34 @@ __device__ __forceinline__ void request_rows(const void* head_base, uint32_t hea
 // Sec. 3.2, where only the n - k src tokens with the highest best-match similarity merge and the
 // other src tokens stay clusters of their own (a separate instantiation, so that the usual one
 // pays nothing for it).
-template <int NW, int MAXN, bool TOPR = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 8)))
+//
+// Instances (NW waves, items of at most MAXN tokens, one thread per token): the smallest that takes the
+// plan's largest block.  Every wave of an item too many costs its share of the barriers and of the
+// resident waves, and rows past the end are staged like the others.  Fused launch, 16 heads x 44280
+// tokens, us with the instances of 64, 256 and 512 tokens alone -> with these: blocks of 16 tokens 158 ->
+// 108, 32: 98 -> 76, 75: 153 -> 108, 100: 102 -> 73, 128: 113 -> 79, 150: 96 -> 87, 192: 89 -> 79, 294:
+// 147 -> 107, 320: 177 -> 118, 384: 155 -> 137; 64 and 256 tokens unchanged.
+template <int NW, int MAXN, bool TOPR>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MAXN == 32 ? 6 : 4, 8)))
 void match_merge_kernel(const MatchMergeArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int ITER = MAXN * kRowChunks / NT;
-  static_assert(MAXN * kRowChunks % NT == 0, "tile must divide among the threads");
-  static_assert(NT == MAXN, "one thread per token");
+  constexpr int SUB = ITER / 4;                       // 32-token tiles of a wave
+  static_assert(MAXN <= NT && (ITER == 4 || ITER == 8), "a thread per token, one or two 32-token tiles per wave");
 
-  // (row MAXN stays zero: the aggregation reads it for the slots of a round that have no member)
-  __shared__ __align__(16) unsigned char tile[(MAXN + 1) * kLdsRowBytes];
   // phase A (matching): inverse norms of all tokens / of the dst tokens
   // phase B (aggregation): member lists - the same storage, the phases are separated by barriers
   // (TOPR: the selection's 256-bin histogram and a few words, between the two phases)
   constexpr int kUnionA = MAXN * 8, kUnionB = MAXN * 4 + 8 + NW * MAXN, kUnionT = TOPR ? 1024 + 8 + 4 * NW : 0;
   constexpr int kUnionAB = kUnionA > kUnionB ? kUnionA : kUnionB;
-  __shared__ __align__(16) unsigned char s_union[kUnionAB > kUnionT ? kUnionAB : kUnionT];
+  constexpr int kUnionT0 = kUnionT > kUnionA ? kUnionT : kUnionA;   // (the table s_cl lives through A and T, behind them)
+  constexpr int kUnion = kUnionT0 + 16 + MAXN * 2 > kUnionAB ? kUnionT0 + 16 + MAXN * 2 : kUnionAB;
+  constexpr int kUnionBytes = (kUnion + 15) & ~15;
+  // (row MAXN stays zero: the aggregation reads it for the slots of a round that have no member)
+  __shared__ __align__(16) unsigned char tile[(MAXN + 1) * kLdsRowBytes];
+  __shared__ __align__(16) unsigned char s_union[kUnionBytes];
   __shared__ uint16_t s_dpos[MAXN];
-  __shared__ int16_t s_cl[MAXN];
+  int16_t* s_cl = (int16_t*)(s_union + ((kUnionT0 + 15) & ~15));
   float* s_invn = (float*)s_union;                    // [MAXN]
   float* s_dinv = s_invn + MAXN;                      // [MAXN]
   uint16_t* s_list = (uint16_t*)s_union;              // [MAXN]    tokens ordered by (cluster, position)
@@ -234,7 +244,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
 
   // ---- 1. the table of the dst tokens, while the rows are on their way ------------------------------
   const int kd = TOPR ? it.kd : k;   // dst tokens = clusters 0 .. kd-1
-  s_cl[tid] = -1;
+  if (MAXN == NT || tid < MAXN) s_cl[tid] = -1;
   if (tid < kLdsRowBytes / 16) *(u32x4*)(tile + MAXN * kLdsRowBytes + tid * 16) = u32x4{0, 0, 0, 0};
   __syncthreads();
   for (int m = tid; m < kd; m += NT) {
@@ -259,7 +269,6 @@ void match_merge_kernel(const MatchMergeArgs a) {
     // inverse norms, from the registers: the 8 lanes that hold the chunks of a row add their sums
     // of squares; of the ITER rows a group of 8 lanes holds, lane c finishes the c-th (one square
     // root and one division per thread) and, if the row is a dst token, files it under its cluster
-    static_assert(ITER == kRowChunks, "one row per lane of a group");
     float mine = 0.f;
 #pragma unroll
     for (int i = 0; i < ITER; ++i) {
@@ -273,7 +282,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
       if ((tid & 7) == i) mine = ss;
     }
     const int row = (tid >> 3) + (NT >> 3) * (tid & 7);
-    if (row < n) {
+    if ((ITER == 8 || (tid & 7) < ITER) && row < n) {
       const float invn = 1.0f / fmaxf(sqrtf(mine), 1e-12f);
       s_invn[row] = invn;
       const int c = s_cl[row];
@@ -304,27 +313,34 @@ void match_merge_kernel(const MatchMergeArgs a) {
     const int ndt = (kd + 31) >> 5;
     float my_sc = 1.0f;                // similarity of token `tid` to the dst it would join
     if (wave * 64 < n) {
-      int tok[2];
-      const unsigned char* xrow[2];
+      int tok[SUB];
+      const unsigned char* xrow[SUB];
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        tok[sub] = (wave * 2 + sub) * 32 + l32;
+      for (int sub = 0; sub < SUB; ++sub) {
+        tok[sub] = (wave * SUB + sub) * 32 + l32;
         xrow[sub] = tile + (tok[sub] < n ? tok[sub] : n - 1) * kLdsRowBytes + half * 16;
       }
-      float best[2] = {-INFINITY, -INFINITY};
-      int bm[2] = {0, 0};
+      float best[SUB];
+      int bm[SUB];
+#pragma unroll
+      for (int sub = 0; sub < SUB; ++sub) {
+        best[sub] = -INFINITY;
+        bm[sub] = 0;
+      }
       for (int dt = 0; dt < ndt; ++dt) {
         asm volatile("" ::: "memory");   // keeps the reads of the token operands inside the loop: registers
         const int m = dt * 32 + l32;
         const int drow = s_dpos[m < kd ? m : kd - 1];
-        f32x16 acc[2];
+        f32x16 acc[SUB];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+        for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[sub][r] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
           const bf16x8 ad = *(const bf16x8*)(tile + drow * kLdsRowBytes + ks * 32 + half * 16);
 #pragma unroll
-          for (int sub = 0; sub < 2; ++sub)
+          for (int sub = 0; sub < SUB; ++sub)
             acc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, *(const bf16x8*)(xrow[sub] + ks * 32), acc[sub], 0, 0, 0);
         }
         // acc[sub][r] = <dst row, token>, dst row = dt*32 + 8*(r/4) + 4*half + r%4, token = l32 of the tile.
@@ -335,7 +351,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
+            for (int sub = 0; sub < SUB; ++sub) {
               const float sc = acc[sub][4 * g + q] * dv[q];
               if (sc > best[sub]) {
                 best[sub] = sc;
@@ -346,7 +362,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
         }
       }
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+      for (int sub = 0; sub < SUB; ++sub) {
         const float ob = __shfl_xor(best[sub], 32);
         const int om = __shfl_xor(bm[sub], 32);
         if (ob > best[sub] || (ob == best[sub] && om < bm[sub])) {
@@ -356,13 +372,13 @@ void match_merge_kernel(const MatchMergeArgs a) {
       }
       // lanes 0..31 publish tile 0 and lanes 32..63 tile 1, so that afterwards thread `tid` holds
       // the result of token `tid`
-      const int t = half ? tok[1] : tok[0];
-      if (t < n) {
+      const int t = SUB == 2 && half ? tok[SUB - 1] : tok[0];
+      if (t < n && (SUB == 2 || half == 0)) {
         int c = s_cl[t];
         float sc = 1.0f;
         if (c < 0) {
-          c = half ? bm[1] : bm[0];
-          sc = (half ? best[1] : best[0]) * s_invn[t];
+          c = SUB == 2 && half ? bm[SUB - 1] : bm[0];
+          sc = (SUB == 2 && half ? best[SUB - 1] : best[0]) * s_invn[t];
         }
         my_cl = c;
         my_sc = sc;
@@ -628,12 +644,12 @@ void match_merge_kernel(const MatchMergeArgs a) {
 // aggregation), a merged token that loses all of them becomes a zero row, and every outlier gets a
 // row of its own in q_out; its assign entry becomes -1 - row.  Work items without an outlier
 // return before they load a single token row.
-template <int NW, int MAXN>
+template <int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void outlier_refine_kernel(const RefineArgs a) {
   constexpr int NT = 64 * NW;
+  constexpr int MAXN = NT;                            // one thread per token
   constexpr int ITER = MAXN * kRowChunks / NT;
-  static_assert(NT == MAXN, "one thread per token");
   __shared__ __align__(16) unsigned char tile[MAXN * kLdsRowBytes];
   __shared__ uint16_t s_list[MAXN];
   __shared__ uint16_t s_off[MAXN + 4];
@@ -893,39 +909,51 @@ __global__ __launch_bounds__(256) void match_f32_kernel(const float* __restrict_
 
 }  // namespace
 
+template <int NW, int MAXN, bool TOPR>
+static void launch_match_merge_as(const MatchMergeArgs& a, int n_items, hipStream_t stream) {
+  const dim3 grid((unsigned)n_items, (unsigned)a.H, (unsigned)a.n_streams);
+  hipLaunchKernelGGL((match_merge_kernel<NW, MAXN, TOPR>), grid, dim3(64 * NW), 0, stream, a);
+}
+template <bool TOPR>
+static void launch_match_merge_sized(const MatchMergeArgs& a, int n_items, hipStream_t stream) {
+  if (a.max_block <= 32) return launch_match_merge_as<1, 32, TOPR>(a, n_items, stream);
+  switch ((a.max_block + 63) / 64) {
+    case 1: return launch_match_merge_as<1, 64, TOPR>(a, n_items, stream);
+    case 2: return launch_match_merge_as<2, 128, TOPR>(a, n_items, stream);
+    case 3: return launch_match_merge_as<3, 192, TOPR>(a, n_items, stream);
+    case 4: return launch_match_merge_as<4, 256, TOPR>(a, n_items, stream);
+    case 5: return launch_match_merge_as<5, 320, TOPR>(a, n_items, stream);
+    case 6: return launch_match_merge_as<6, 384, TOPR>(a, n_items, stream);
+    case 7: return launch_match_merge_as<7, 448, TOPR>(a, n_items, stream);
+    default: return launch_match_merge_as<8, 512, TOPR>(a, n_items, stream);
+  }
+}
+
 hipError_t launch_match_merge(const MatchMergeArgs& a, hipStream_t stream) {
   int n_items = 0;
   for (int i = 0; i < a.n_streams; ++i) n_items = a.s[i].n_items > n_items ? a.s[i].n_items : n_items;
   if (n_items == 0 || a.H == 0) return hipSuccess;
   if (a.max_block > kSmallBlockMax) return launch_match_merge_big(a, stream);
-  dim3 grid((unsigned)n_items, (unsigned)a.H, (unsigned)a.n_streams);
-  if (a.top_r) {
-    if (a.max_block <= 64)
-      hipLaunchKernelGGL((match_merge_kernel<1, 64, true>), grid, dim3(64), 0, stream, a);
-    else if (a.max_block <= 256)
-      hipLaunchKernelGGL((match_merge_kernel<4, 256, true>), grid, dim3(256), 0, stream, a);
-    else
-      hipLaunchKernelGGL((match_merge_kernel<8, 512, true>), grid, dim3(512), 0, stream, a);
-    return hipGetLastError();
-  }
-  if (a.max_block <= 64)
-    hipLaunchKernelGGL((match_merge_kernel<1, 64>), grid, dim3(64), 0, stream, a);
-  else if (a.max_block <= 256)
-    hipLaunchKernelGGL((match_merge_kernel<4, 256>), grid, dim3(256), 0, stream, a);
+  if (a.top_r)
+    launch_match_merge_sized<true>(a, n_items, stream);
   else
-    hipLaunchKernelGGL((match_merge_kernel<8, 512>), grid, dim3(512), 0, stream, a);
+    launch_match_merge_sized<false>(a, n_items, stream);
   return hipGetLastError();
 }
 
 hipError_t launch_outlier_refine(const RefineArgs& a, hipStream_t stream) {
   if (a.n_items == 0 || a.H == 0) return hipSuccess;
   dim3 grid((unsigned)a.n_items, (unsigned)a.H);
-  if (a.max_block <= 64)
-    hipLaunchKernelGGL((outlier_refine_kernel<1, 64>), grid, dim3(64), 0, stream, a);
-  else if (a.max_block <= 256)
-    hipLaunchKernelGGL((outlier_refine_kernel<4, 256>), grid, dim3(256), 0, stream, a);
-  else
-    hipLaunchKernelGGL((outlier_refine_kernel<8, 512>), grid, dim3(512), 0, stream, a);
+  switch ((a.max_block + 63) / 64) {
+    case 1: hipLaunchKernelGGL((outlier_refine_kernel<1>), grid, dim3(64), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((outlier_refine_kernel<2>), grid, dim3(128), 0, stream, a); break;
+    case 3: hipLaunchKernelGGL((outlier_refine_kernel<3>), grid, dim3(192), 0, stream, a); break;
+    case 4: hipLaunchKernelGGL((outlier_refine_kernel<4>), grid, dim3(256), 0, stream, a); break;
+    case 5: hipLaunchKernelGGL((outlier_refine_kernel<5>), grid, dim3(320), 0, stream, a); break;
+    case 6: hipLaunchKernelGGL((outlier_refine_kernel<6>), grid, dim3(384), 0, stream, a); break;
+    case 7: hipLaunchKernelGGL((outlier_refine_kernel<7>), grid, dim3(448), 0, stream, a); break;
+    default: hipLaunchKernelGGL((outlier_refine_kernel<8>), grid, dim3(512), 0, stream, a); break;
+  }
   return hipGetLastError();
 }
 
@@ -941,7 +969,7 @@ hipError_t launch_match_f32(const float* xbar, const int32_t* pi, const WorkItem
                             int32_t n_items, int32_t max_block, int32_t* slot, float* score,
                             hipStream_t stream) {
   if (n_items == 0) return hipSuccess;
-  const int mb = max_block < kPrefixChunk ? kPrefixChunk : max_block;
+  const int mb = max_block;
   hipLaunchKernelGGL(match_f32_kernel, dim3((unsigned)n_items, (unsigned)((mb + 255) / 256)), dim3(256), 0, stream,
                      xbar, pi, items, slot, score);
   return hipGetLastError();
