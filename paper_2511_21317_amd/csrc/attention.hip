@@ -1,27 +1,34 @@
 // Stage 3: attention over the reduced per-head sequences (paper Sec. 3.2 Eq. 3-4):
 //   O = softmax(Q K^T * scale) V, per head, no mask, ragged (M_q[h], M_k[h]).
 //
-// Flash-style single pass with bf16 MFMA (v_mfma_f32_32x32x16_bf16) and fp32 softmax state.
+// Flash-style single pass with bf16 MFMA (v_mfma_f32_16x16x32_bf16) and fp32 softmax state.
 // The kernel is bound by the matrix cores (4*M_q*M_k*64 flop per head against a few MB of
 // K/V that stay in L2 / Infinity Cache); with d_head = 64 the softmax needs about as many
 // vector-ALU cycles as the two matrix products need MFMA cycles, so the design is about
 // (a) taking vector instructions out of the inner loop and (b) giving every wave independent
 // MFMA and vector work in the same stretch of code so that both pipes run at once.
 //
+// Why 16x16x32.  Under these kernels the chip is at its power limit and the clock follows the energy of an
+// instruction: a register-only loop of 16x16x32 products sustains 1.95 PFLOP/s (2.0 GHz), one of
+// 32x32x16 products - same nominal rate, half the instructions - 1.76 (1.77 GHz).  With the instruction
+// mix of a step (products, exp2, packs) in registers a step takes 307 against 330 ns, although the finer
+// products leave less room between them for vector instructions (595 against 527 cycles).  This kernel:
+// 16 heads x 16384 x 16384 860 -> 807 us, x 28700 x 28700 2.51 -> 2.45 ms.
+//
 // Work decomposition
-//   * workgroup = NW waves = one tile of 32*QT*NW query rows of one head; a wave owns 32*QT rows;
+//   * workgroup = NW waves = one tile of 16*NQ*NW query rows of one head; a wave owns 16*NQ rows;
 //   * K/V are streamed in tiles of 64 rows through LDS, double buffered, one barrier per tile;
 //   * blockIdx -> tile mapping is XCD-aware: workgroups are dispatched round-robin over the 8
 //     XCDs, so tile = (bid % 8) * (grid/8) + bid / 8 gives every XCD a contiguous range of
 //     tiles, i.e. about two heads, whose K/V then stay in that XCD's L2.
 //
 // Transposed formulation.  Each wave computes S^T = K Q^T (A = K tile from LDS, B = Q^T from
-// registers) so that in the 32x32 accumulator layout a lane owns ONE query column and 16 of the
-// 32 key rows: the softmax reductions are sums inside a lane plus one exchange with lane^32 at
-// the very end, and every per-row quantity is a per-lane scalar for the O^T = V^T P^T
+// registers) so that in the 16x16 accumulator layout a lane owns ONE query column and 4 of the
+// 16 key rows: the softmax reductions are sums inside a lane plus two exchanges between the four lane
+// groups at the very end, and every per-row quantity is a per-lane scalar for the O^T = V^T P^T
 // accumulators as well.  P^T goes from the accumulator registers straight into the B operand of
 // the second MFMA (fp32 -> bf16 in registers, no LDS round trip).  That fixes which 8 keys a lane
-// supplies per MFMA step: {16j + 4*half + 0..3, 16j + 8 + 4*half + 0..3}.  The matching A operand
+// group g supplies per step of 32: {4g + 0..3, 16 + 4g + 0..3}.  The matching A operand
 // (V^T: a lane's channel, those 8 keys) comes out of the row-major V tile through two transposing
 // LDS reads (ds_read_b64_tr_b16), so V is never transposed in memory or in registers.
 //
@@ -31,10 +38,11 @@
 //
 // Software pipeline.  Work is cut into steps of 32 keys.  In step t a wave issues, in one
 // basic block, the QK^T MFMAs of step t+1, the PV MFMAs of step t-1 and the softmax of step t:
-// the 16 MFMAs do not depend on the ~100 vector instructions next to them, so the matrix core
+// the 32 MFMAs do not depend on the ~50 vector instructions next to them, so the matrix core
 // and the vector ALU overlap inside a single wave (two waves per SIMD then fill what is left).
 // V lags K by one tile in LDS because of the t-1.  In the steady state the order of issue is
-// written out (steady_step(): one MFMA, then two exp2 and a pack, behind a scheduling fence), the
+// written out (steady_step(): one MFMA, then an exp2 and at times a pack, behind a scheduling fence; two
+// MFMAs and then their vector instructions together take 40 % more cycles), the
 // loop runs two tiles per trip so that the LDS buffer indices are constants, and the global->LDS
 // requests of an iteration are issued behind the last LDS read of its first step.
 //
@@ -48,8 +56,8 @@
 // alone from there on.  Neither looks at the sums inside the loop: the row sums come from the matrix
 // cores (row_sum_operand()), and a tile is checked once, at its end.  If a row's sum is outside
 // [2^-64, 2^64] (or inf / NaN), the workgroup takes the tile again with running maxima
-// (running_max_step(): the classic online softmax, not pipelined).  Measured against a guard inside the loop for plain keys (a dot2
-// against ones and a compare per score pair) and a second launch that redid marked tiles for log2 keys:
+// (running_max_step(): the classic online softmax, not pipelined).  Measured against a guard inside the
+// loop for plain keys (a dot2 against ones and a compare per score pair) and a second launch that redid marked tiles for log2 keys:
 // 16 ragged heads of 5500 x 9000 plain keys 219 -> 201 us, two 16 x 16 frames 27.3 -> 24.3 us a layer.
 //
 // End of a launch.  A CU runs its 256-row tiles two at a time, but one alone nearly twice as fast,
@@ -112,78 +120,72 @@ struct AttnArgs {
 static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 // V tile in LDS: 64 rows of 128 bytes, written by global->LDS loads like the K tile; the 16-byte
-// chunk c of row r sits at chunk position c ^ (2 * (r & 3)), so that the four rows a transposing read
-// touches (32 bytes each, same channels) fall into four different 32-byte bank groups.
-__device__ __forceinline__ int v_swizzle(int row) { return (row & 3) << 1; }
-
-__device__ __forceinline__ f32x16 splat16(float x) {
-  f32x16 r;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) r[i] = x;
-  return r;
-}
+// chunk c of row r sits at chunk position c ^ (2 * ((r >> 1) & 3)), so that the eight rows which half a
+// transposing read touches (32 bytes each, same channels) fall into eight different 32-byte bank groups.
+__device__ __forceinline__ int v_swizzle(int row) { return ((row >> 1) & 3) << 1; }
 
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
-// keys 16j .. 16j+15 of a step's P^T as the B operand of a 32x32x16 MFMA
+// One half of a pair of query tiles' P^T: the B operand of a 16x16x32 MFMA
 __device__ __forceinline__ bf16x8 p_half(const u32x8& p, int j) {
   return __builtin_bit_cast(bf16x8, j ? __builtin_shufflevector(p, p, 4, 5, 6, 7) : __builtin_shufflevector(p, p, 0, 1, 2, 3));
 }
 
-// Per-wave softmax state and accumulators.
-template <int QT>
+// Per-wave softmax state and accumulators; a wave owns NQ query tiles of 16 rows.
+template <int NQ>
 struct WaveState {
-  bf16x8 qf[QT][4];      // Q^T fragments
-  f32x16 o_acc[2][QT];   // O^T accumulators, [channel tile][query tile]
-  f32x16 s_cur[QT];      // raw scores of the current step
-  u32x8 p_old[QT];       // bf16 P^T of the previous step: two 32x32x16 MFMA B operands, one 16x16x64 one
-  float mc[QT];          // shift m in log2 units
+  bf16x8 qf[NQ][2];      // Q^T fragments, 32 channels each
+  f32x4 o_acc[4][NQ];    // O^T accumulators, [16 channels][query tile]
+  f32x4 s_cur[2][NQ];    // raw scores of the current step, [16 keys][query tile]
+  u32x8 p_old[NQ / 2];   // bf16 P^T of the previous step, two query tiles each: two 16x16x32 B operands, one 16x16x64 one
+  float mc[NQ];          // shift m in log2 units
   float c;               // factor from raw scores to log2 units (kernel with per-row shifts only)
-  f32x4 l_acc[QT];       // row sums, from the matrix cores: see row_sum_operand()
+  f32x4 l_acc[NQ / 2];   // row sums, from the matrix cores: see row_sum_operand()
   bf16x8 ones_a;         // A operand and index operand of the row sums
   int ones_idx;
 };
 
 // Row sums on the matrix cores.  A sum does not need the zeros of a structured-sparse A
 // operand: v_smfmac_f32_16x16x64_bf16 takes 64 dense k per instruction in the time the dense
-// 16x16x32 takes 32 (18 cycles each in a register-only loop), and the two k of every four that a row of A
-// drops are taken by another row.  The eight P^T registers of a lane (query l%32, 16 keys of half l/32)
-// are its B operand: query l%32 sits in column l%16, and the hardware pairs the 8 values of A lane
-// group g with B lane group 2g%4 (values 0..3) and 2g%4 + 1 (values 4..7).  So rows 0 and 1 of A hold
-// ones in values 0..3 - the even lane groups of B, queries 0..15 - and rows 2 and 3 in values 4..7 - the
-// odd ones, queries 16..31; rows 0 and 2 keep the k 0, 1 of every four (index 0x4), rows 1 and 3 the k 2, 3
-// (0xE).  D[0][n] + D[1][n] is the sum of query n, D[2][n] + D[3][n] that of query n + 16: registers 0..3
-// of lanes 0..15.  A step's 16 products take 512 matrix-core cycles; its row sums
-// take 36 instead of the 64 of four dense 16x16x32.  Stage 3 is bound by those cycles and the power they
-// draw: 16 heads x 16384 x 16384 878 -> 860 us.
+// 16x16x32 takes 32 (18 against 16 cycles in a register-only loop), and the two k of every four that a row
+// of A drops are taken by another row.  Its B operand are the eight P^T registers of two query tiles
+// (query l%16 of both): the first tile's values are the k below 32 and the second one's the others,
+// which are multiplied by lanes 0..31 and lanes 32..63 of A.  So rows 0 and 1 of A hold ones in lanes below
+// 32 and rows 2 and 3 in the others; rows 0 and 2 keep the k 0, 1 of every four (index 0x4), rows 1 and 3
+// the k 2, 3 (0xE).  D[0][n] + D[1][n] is the sum of query n of the first tile, D[2][n] + D[3][n] that of
+// the second: registers 0..3 of lanes 0..15.  A step's 32 products take 512 matrix-core cycles; its
+// row sums take 36 instead of the 64 of four dense 16x16x32.  Stage 3 is bound by those cycles and the
+// power they draw: 16 heads x 16384 x 16384 878 -> 860 us.
 __device__ __forceinline__ bf16x8 row_sum_operand(int lane) {
   const int m = lane & 15;
-  const uint32_t lo = m < 2 ? 0x3F803F80u : 0u, hi = m == 2 || m == 3 ? 0x3F803F80u : 0u;
-  return __builtin_bit_cast(bf16x8, u32x4{lo, lo, hi, hi});
+  const uint32_t w = m < 4 && (m >> 1) == (lane >> 5) ? 0x3F803F80u : 0u;
+  return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
 }
 __device__ __forceinline__ int row_sum_index(int lane) { return (lane & 1) ? (int)0xEEEEEEEEu : 0x44444444; }
 
-// exp2(s*c - m) (SHIFT) or exp2(s) and bf16 pack of one query tile.
+// exp2(s*c - m) (SHIFT) or exp2(s) of a step's 8 scores of one query column, packed to bf16: one half of
+// a pair's P^T operand.
 template <bool SHIFT>
-__device__ __forceinline__ void exp_pack(const f32x16& s, float c, float m, u32x8& p) {
+__device__ __forceinline__ void exp_pack(const f32x4& s0, const f32x4& s1, float c, float m, u32x8& p, int half) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[2 * e], c, -m) : s[2 * e]);
-    const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(s[2 * e + 1], c, -m) : s[2 * e + 1]);
-    p[e] = pack_bf16x2(p0, p1);
+  for (int e = 0; e < 4; ++e) {
+    const f32x4& s = e < 2 ? s0 : s1;
+    const float x0 = s[2 * (e & 1)], x1 = s[2 * (e & 1) + 1];
+    const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x0, c, -m) : x0);
+    const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x1, c, -m) : x1);
+    p[4 * half + e] = pack_bf16x2(p0, p1);
   }
 }
 
-// The largest score of a query column among the 32 keys of a step (both half-waves).
-__device__ __forceinline__ float step_max(const f32x16& s) {
-  float t = s[0];
-#pragma unroll
-  for (int r = 1; r < 16; ++r) t = fmaxf(t, s[r]);
+// The largest score of a query column among the 32 keys of a step (all four lane groups).
+__device__ __forceinline__ float step_max(const f32x4& s0, const f32x4& s1) {
+  float t = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+  t = fmaxf(t, __shfl_xor(t, 16));
   return fmaxf(t, __shfl_xor(t, 32));
 }
 
-// MFMA A operands of one step: 4 K fragments (32 key rows x 64 channels) and 4 V^T fragments
-// (64 channels x 32 key positions), 16 bytes per lane each.
+// MFMA A operands of one step: 4 K fragments (16 key rows x 32 channels, [key tile * 2 + channel half]) and
+// 4 V^T fragments (16 channels x 32 key positions), 16 bytes per lane each.
 struct StepOperands {
   bf16x8 ak[4];
   bf16x8 av[4];
@@ -195,36 +197,36 @@ struct StepOperands {
 __device__ __forceinline__ int k_swizzle(int row) { return (row >> 1) & 7; }
 
 // `sk` points at the first of the 32 rows of this step (row 0 or 32 of the tile).
-__device__ __forceinline__ void load_k_operands(StepOperands& op, const bf16_t* sk, int l32, int half) {
-  const int sw = k_swizzle(l32);
+__device__ __forceinline__ void load_k_operands(StepOperands& op, const bf16_t* sk, int l16, int grp) {
+  const int sw = k_swizzle(l16);
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-    op.ak[ks] = *(const bf16x8*)(sk + l32 * kDHead + ((ks * 2 + half) ^ sw) * 8);
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      op.ak[kt * 2 + ks] = *(const bf16x8*)(sk + (kt * 16 + l16) * kDHead + ((ks * 4 + grp) ^ sw) * 8);
 }
 // A operands of O^T += V^T P^T from the row-major V tile: ds_read_b64_tr_b16 hands lane 4a+e of a
 // 16-lane group element e of the 8 bytes that lane 4r+a of the group addressed, as its r-th value.
 // Lane 4r+a addresses key k0+r, channels c0+4a..c0+4a+3, so lane i receives keys k0..k0+3 of channel
-// c0+i - four consecutive keys of one V^T row.  Two reads (k0 = 16j + 4*half and 8 keys further)
-// give the 8 keys a lane's P^T registers hold; the four groups of a wave are (half, 16 channels).
+// c0+i - four consecutive keys of one V^T row.  Two reads (k0 = 4*grp and 16 keys further) give the 8 keys
+// a lane's P^T registers hold.
 // `sv` points at the first of the 32 key rows of this step.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ void load_v_operands(StepOperands& op, const bf16_t* sv, int l32, int half) {
-  const int i = l32 & 15, chalf = l32 >> 4;
-  const int krow = 4 * half + (i >> 2);
+__device__ __forceinline__ void load_v_operands(StepOperands& op, const bf16_t* sv, int l16, int grp) {
+  const int krow = 4 * grp + (l16 >> 2);
+  const int sw = v_swizzle(krow);
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt) {
-    const int chunk = (4 * dt + 2 * chalf + ((i & 3) >> 1)) ^ v_swizzle(krow);
-    const bf16_t* base = sv + krow * kDHead + chunk * 8 + 4 * (i & 1);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(base + (16 * j) * kDHead));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(base + (16 * j + 8) * kDHead));
-      op.av[dt * 2 + j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+  for (int ct = 0; ct < 4; ++ct) {
+    const bf16_t* base = sv + krow * kDHead + ((2 * ct + ((l16 & 3) >> 1)) ^ sw) * 8 + 4 * (l16 & 1);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)base);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(base + 16 * kDHead));
+    op.av[ct] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
+}
+
+__device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // One pipeline step of a wave outside the steady state (first tile, last tile, drain); the order of
@@ -233,131 +235,129 @@ __device__ __forceinline__ void load_v_operands(StepOperands& op, const bf16_t* 
 //   DO_PV : O^T += V^T P^T of the PREVIOUS step, V rows at `svt`
 //   DO_SM : softmax of the CURRENT step (s_cur -> p_old); its first key is `kv_first`
 //   MASK  : keys >= Mk get weight 0;  FIRST : this is step 0 and fixes m
-template <int QT, bool SHIFT, bool DO_QK, bool DO_PV, bool DO_SM, bool MASK, bool FIRST>
-__device__ __forceinline__ void pipeline_step(WaveState<QT>& w, const bf16_t* sk, const bf16_t* svt,
-                                              int kv_first, int Mk, int l32, int half) {
+template <int NQ, bool SHIFT, bool DO_QK, bool DO_PV, bool DO_SM, bool MASK, bool FIRST>
+__device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk, const bf16_t* svt,
+                                              int kv_first, int Mk, int l16, int grp) {
   StepOperands op;
-  f32x16 s_next[QT];
+  f32x4 s_next[2][NQ];
   if (DO_QK) {
-    load_k_operands(op, sk, l32, half);
+    load_k_operands(op, sk, l16, grp);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-        s_next[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            op.ak[ks], w.qf[qt][ks], ks == 0 ? splat16(0.f) : s_next[qt], 0, 0, 0);
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt)
+          s_next[kt][qt] = mfma16(op.ak[kt * 2 + ks], w.qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s_next[kt][qt]);
   }
   if (DO_PV) {
-    load_v_operands(op, svt, l32, half);
+    load_v_operands(op, svt, l16, grp);
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
+    for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int qt = 0; qt < NQ; ++qt)
+        w.o_acc[ct][qt] = mfma16(op.av[ct], p_half(w.p_old[qt >> 1], qt & 1), w.o_acc[ct][qt]);
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
-          w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              op.av[dt * 2 + j], p_half(w.p_old[qt], j), w.o_acc[dt][qt], 0, 0, 0);
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-      w.l_acc[qt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[qt]), w.l_acc[qt], w.ones_idx, 0, 0);
+    for (int i = 0; i < NQ / 2; ++i)
+      w.l_acc[i] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[i]), w.l_acc[i], w.ones_idx, 0, 0);
   }
   if (DO_SM) {
-    // s_cur[qt][r]: key kv_first + 8*(r/4) + 4*half + r%4, query column l32 of tile qt
+    // s_cur[kt][qt][r]: key kv_first + 16*kt + 4*grp + r, query column l16 of tile qt
     if (MASK) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int kv = kv_first + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (kv >= Mk) {
+      for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-          for (int qt = 0; qt < QT; ++qt) w.s_cur[qt][r] = -INFINITY;
+        for (int r = 0; r < 4; ++r) {
+          const int kv = kv_first + 16 * kt + 4 * grp + r;
+          if (kv >= Mk) {
+#pragma unroll
+            for (int qt = 0; qt < NQ; ++qt) w.s_cur[kt][qt][r] = -INFINITY;
+          }
         }
-      }
     }
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-      if (SHIFT && FIRST) w.mc[qt] = step_max(w.s_cur[qt]) * w.c;
-      exp_pack<SHIFT>(w.s_cur[qt], w.c, w.mc[qt], w.p_old[qt]);
+    for (int qt = 0; qt < NQ; ++qt) {
+      if (SHIFT && FIRST) w.mc[qt] = step_max(w.s_cur[0][qt], w.s_cur[1][qt]) * w.c;
+      exp_pack<SHIFT>(w.s_cur[0][qt], w.s_cur[1][qt], w.c, w.mc[qt], w.p_old[qt >> 1], qt & 1);
     }
   }
   if (DO_QK) {
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) w.s_cur[qt] = s_next[qt];
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) w.s_cur[kt][qt] = s_next[kt][qt];
   }
 }
 
 // The steady-state step with the order of issue written out: one MFMA, then its
-// share of the softmax of the current step (two exp2, one bf16 pack of the pair before), fenced so
-// that the compiler keeps the interleave.  PV of step t-1 first (the V operands retire, their
-// successors are requested), then QK^T of step t+1 and the K operands; a row-sum MFMA after every
-// eighth product.  `between` runs after the step's last LDS read: the global->LDS requests of the
-// iteration go there, because the compiler makes every LDS read wait for all requests issued
-// before it in program order.
-template <int QT, bool SHIFT, bool PREFETCH, typename Between>
-__device__ __forceinline__ void steady_step(WaveState<QT>& w, StepOperands& op, const bf16_t* sk_next,
-                                            const bf16_t* sv_next, int l32, int half, Between between) {
-  // 8 * QT groups: 4 * QT products of each kind, every group with 2 of the 16 * QT scores of the lane
-  constexpr int NG = 8 * QT;
-  f32x16 s_next[QT];
-  float ex[16 * QT];
-  u32x8 p_new[QT];
-  auto soft = [&](int g) {   // values 2g, 2g+1 of the 32 scores of this lane
+// share of the softmax of the current step (an exp2, and behind every second one the bf16 pack of the pair
+// before), fenced so that the compiler keeps the interleave.  PV of step t-1 first (the V operands
+// retire, their successors are requested), then QK^T of step t+1 and the K operands; a row-sum MFMA after
+// every sixteenth product.  Neighbouring products share one operand (the query tiles run forth
+// and back): the sources that toggle cost power, and the clock follows it.  `between` runs after the
+// step's last LDS read: the global->LDS requests of the iteration go there, because the compiler makes
+// every LDS read wait for all requests issued before it in program order.
+template <int NQ, bool SHIFT, bool PREFETCH, typename Between>
+__device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, const bf16_t* sk_next,
+                                            const bf16_t* sv_next, int l16, int grp, Between between) {
+  // 8 * NQ groups: 4 * NQ products of each kind, every group with one of the 8 * NQ scores of the lane
+  constexpr int NG = 8 * NQ;
+  f32x4 s_next[2][NQ];
+  float ex[8 * NQ];
+  u32x8 p_new[NQ / 2];
+  auto soft = [&](int g) {   // value g of the scores of this lane: query tile g / 8, key register g % 8
     // (the empty asm after a result only pins where the instruction is issued)
-    const int qt = (2 * g) >> 4;
-    const float x0 = w.s_cur[qt][(2 * g) & 15], x1 = w.s_cur[qt][(2 * g + 1) & 15];
-    ex[2 * g] = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x0, w.c, -w.mc[qt]) : x0);
-    asm volatile("" : "+v"(ex[2 * g]));
-    ex[2 * g + 1] = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x1, w.c, -w.mc[qt]) : x1);
-    asm volatile("" : "+v"(ex[2 * g + 1]));
+    const int qt = g >> 3;
+    const float x = w.s_cur[(g >> 2) & 1][qt][g & 3];
+    ex[g] = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x, w.c, -w.mc[qt]) : x);
+    asm volatile("" : "+v"(ex[g]));
   };
-  auto pack = [&](int p) {
+  auto pack = [&](int p) {   // values 2p, 2p + 1
     uint32_t r = pack_bf16x2(ex[2 * p], ex[2 * p + 1]);
     asm volatile("" : "+v"(r));
     p_new[p >> 3][p & 7] = r;
   };
-  auto row_sum = [&](int g) {   // a row-sum MFMA after every eighth product: QT per step
-    if ((g & 7) == 3) {
-      const int rq = g >> 3;
-      w.l_acc[rq] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[rq]), w.l_acc[rq], w.ones_idx, 0, 0);
+  auto group_end = [&](int g) {
+    soft(g);
+    if (g >= 2 && (g & 1) == 0) pack((g >> 1) - 1);
+    if ((g & 15) == 7) {
+      const int i = g >> 4;
+      w.l_acc[i] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[i]), w.l_acc[i], w.ones_idx, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
   // PV of step t-1 first: the V operands retire and their successors are requested ...
 #pragma unroll
   for (int g = 0; g < NG / 2; ++g) {
-    const int qt = g % QT, dt = (g / QT) & 1, j = g / (2 * QT);
-    w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-        op.av[dt * 2 + j], p_half(w.p_old[qt], j), w.o_acc[dt][qt], 0, 0, 0);
-    soft(g);
-    if (g > 0) pack(g - 1);
-    row_sum(g);
-    __builtin_amdgcn_sched_barrier(0);
+    const int ct = g / NQ, qt = ct & 1 ? NQ - 1 - g % NQ : g % NQ;
+    w.o_acc[ct][qt] = mfma16(op.av[ct], p_half(w.p_old[qt >> 1], qt & 1), w.o_acc[ct][qt]);
+    group_end(g);
   }
   if (PREFETCH) {
-    load_v_operands(op, sv_next, l32, half);
+    load_v_operands(op, sv_next, l16, grp);
     __builtin_amdgcn_sched_barrier(0);
   }
   // ... then QK^T of step t+1
 #pragma unroll
   for (int g = NG / 2; g < NG; ++g) {
-    const int i = g - NG / 2, ks = i / QT, qt = i % QT;
-    s_next[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.ak[ks], w.qf[qt][ks],
-                                                         ks == 0 ? splat16(0.f) : s_next[qt], 0, 0, 0);
-    soft(g);
-    pack(g - 1);
-    row_sum(g);
-    __builtin_amdgcn_sched_barrier(0);
+    const int i = g - NG / 2, ks = i / (2 * NQ), kt = (i / NQ) & 1, qt = kt ? NQ - 1 - i % NQ : i % NQ;
+    s_next[kt][qt] = mfma16(op.ak[kt * 2 + ks], w.qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s_next[kt][qt]);
+    group_end(g);
   }
-  pack(NG - 1);
-  if (PREFETCH) load_k_operands(op, sk_next, l32, half);
+  pack(NG / 2 - 1);
+  if (PREFETCH) load_k_operands(op, sk_next, l16, grp);
   __builtin_amdgcn_sched_barrier(0);
   between();        // requests that must follow the step's last LDS read in program order
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    w.s_cur[qt] = s_next[qt];
-    w.p_old[qt] = p_new[qt];
+  for (int qt = 0; qt < NQ; ++qt) {
+    w.s_cur[0][qt] = s_next[0][qt];
+    w.s_cur[1][qt] = s_next[1][qt];
   }
+#pragma unroll
+  for (int i = 0; i < NQ / 2; ++i) w.p_old[i] = p_new[i];
 }
 
 // Row sums the pipelined pass accepts (inf and NaN fail the test as well): inside, the weights of a
@@ -368,36 +368,38 @@ constexpr float kFastSumMax = 1.8446744073709552e19f;    // 2^64
 
 // One step of 32 keys with a running maximum per row (the classic online softmax), for tiles whose
 // rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.
-template <int QT>
-__device__ __forceinline__ void running_max_step(WaveState<QT>& w, float (&l)[QT], const bf16_t* sk, const bf16_t* sv,
-                                                 int kv_first, int Mk, int l32, int half) {
+template <int NQ>
+__device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ], const bf16_t* sk, const bf16_t* sv,
+                                                 int kv_first, int Mk, int l16, int grp) {
   const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
   StepOperands op;
-  load_k_operands(op, sk, l32, half);
-  load_v_operands(op, sv, l32, half);
+  load_k_operands(op, sk, l16, grp);
+  load_v_operands(op, sv, l16, grp);
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    f32x16 s = splat16(0.f);
+  for (int qt = 0; qt < NQ; ++qt) {
+    f32x4 s[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.ak[ks], w.qf[qt][ks], s, 0, 0, 0);
+    for (int kt = 0; kt < 2; ++kt) {
+      s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (kv_first + 8 * (r >> 2) + 4 * half + (r & 3) >= Mk) s[r] = -INFINITY;
-    const float m = fmaxf(w.mc[qt], step_max(s) * w.c);
+      for (int ks = 0; ks < 2; ++ks) s[kt] = mfma16(op.ak[kt * 2 + ks], w.qf[qt][ks], s[kt]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (kv_first + 16 * kt + 4 * grp + r >= Mk) s[kt][r] = -INFINITY;
+    }
+    const float m = fmaxf(w.mc[qt], step_max(s[0], s[1]) * w.c);
     const float sc = __builtin_amdgcn_exp2f(w.mc[qt] - m);
     w.mc[qt] = m;
-    u32x8 p;
-    exp_pack<true>(s, w.c, m, p);
+    u32x8 p = {};
+    exp_pack<true>(s[0], s[1], w.c, m, p, 0);
     l[qt] *= sc;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) l[qt] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)p[e]), ones2, l[qt], false);
+    for (int e = 0; e < 4; ++e) l[qt] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)p[e]), ones2, l[qt], false);
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt) {
+    for (int ct = 0; ct < 4; ++ct) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) w.o_acc[dt][qt][r] *= sc;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        w.o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.av[dt * 2 + j], p_half(p, j), w.o_acc[dt][qt], 0, 0, 0);
+      for (int r = 0; r < 4; ++r) w.o_acc[ct][qt][r] *= sc;
+      w.o_acc[ct][qt] = mfma16(op.av[ct], p_half(p, 0), w.o_acc[ct][qt]);
     }
   }
 }
@@ -406,13 +408,13 @@ __device__ __forceinline__ void running_max_step(WaveState<QT>& w, float (&l)[QT
 //   h, q0          : head and first query row of the tile
 //   dev_tile       : the tile comes from the device-side list (rows q_base_dev .. + mq_dev of q2 / o2)
 //   seg.slot >= 0  : only the key tiles [seg.t0, seg.t1) of the head, results into scratch slot seg.slot
-template <int QT, int NW, bool SHIFT>
+template <int NQ, int NW, bool SHIFT>
 __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[kKvTile * kDHead],
                                                bf16_t (*s_v)[kKvTile * kDHead], const int h, const int q0,
                                                const bool dev_tile, const int64_t q_base_dev, const int mq_dev,
                                                const SplitSegment seg) {
   constexpr int NT = 64 * NW;
-  constexpr int BQ = 32 * QT * NW;
+  constexpr int BQ = 16 * NQ * NW;
   constexpr int LDK = 8 / NW;                              // 1 KB global->LDS loads per wave per tile
   const bool piece = seg.slot >= 0;
   const int64_t q_base = dev_tile ? q_base_dev : a.q_off[h];
@@ -434,8 +436,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     Mk = (seg.t1 * kKvTile < Mk ? seg.t1 * kKvTile : Mk) - seg.t0 * kKvTile;
   }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS destinations stay scalar
-  const int l32 = lane & 31, half = lane >> 5;
-  const int wq0 = q0 + wave * 32 * QT;  // first query row of this wave
+  const int l16 = lane & 15, grp = lane >> 4;
+  const int wq0 = q0 + wave * 16 * NQ;  // first query row of this wave
   // A wave of a partial tile that owns no valid row only helps to stage K/V and to keep the
   // barriers; it issues no MFMA and no softmax.
   const bool active = __builtin_amdgcn_readfirstlane((int)(wq0 < Mq)) != 0;   // wave-uniform, and known to be
@@ -449,19 +451,19 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     return;
   }
 
-  WaveState<QT> w;
+  WaveState<NQ> w;
   // ---- Q^T fragments (B operand): lane -> query column, 8 consecutive channels ---------------
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    int row = wq0 + qt * 32 + l32;
+  for (int qt = 0; qt < NQ; ++qt) {
+    int row = wq0 + qt * 16 + l16;
     row = row < Mq ? row : Mq - 1;
-    const bf16_t* p = q_rows + (q_base + row) * kDHead + half * 8;
+    const bf16_t* p = q_rows + (q_base + row) * kDHead + grp * 8;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) w.qf[qt][ks] = *(const bf16x8*)(p + ks * 16);
+    for (int ks = 0; ks < 2; ++ks) w.qf[qt][ks] = *(const bf16x8*)(p + ks * 32);
     w.mc[qt] = 0.f;
-    w.l_acc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    w.l_acc[qt >> 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt) w.o_acc[dt][qt] = splat16(0.f);
+    for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
   // ---- K/V tile staging: global -> registers -> LDS ---------------------------------------------
@@ -517,13 +519,13 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
   __syncthreads();
   if (active) {
-    pipeline_step<QT, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, 0, Mk, l32, half);
+    pipeline_step<NQ, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, 0, Mk, l16, grp);
     if (n_tiles > 1)
-      pipeline_step<QT, SHIFT, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
-                                                        Mk, l32, half);
+      pipeline_step<NQ, SHIFT, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
+                                                        Mk, l16, grp);
     else
-      pipeline_step<QT, SHIFT, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
-                                                       Mk, l32, half);
+      pipeline_step<NQ, SHIFT, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
+                                                       Mk, l16, grp);
   }
   __syncthreads();
 
@@ -545,10 +547,10 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     };
     // (a wave without valid rows runs the loop below instead: no global->LDS request may precede
     // an LDS read on the path of an active wave, the compiler would wait for it before the read)
-    load_k_operands(op, kb, l32, half);
-    load_v_operands(op, vb, l32, half);
-    steady_step<QT, SHIFT, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, l32, half, request);
-    steady_step<QT, SHIFT, false>(w, op, nullptr, nullptr, l32, half, [] {});
+    load_k_operands(op, kb, l16, grp);
+    load_v_operands(op, vb, l16, grp);
+    steady_step<NQ, SHIFT, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, l16, grp, request);
+    steady_step<NQ, SHIFT, false>(w, op, nullptr, nullptr, l16, grp, [] {});
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): K tile jt+1 and V tile jt are in LDS
     __syncthreads();
   };
@@ -577,9 +579,9 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     const bf16_t* kb = &s_k[j & 1][0];
     const bf16_t* vb = &s_v[(j - 1) & 1][0];
     if (active) {
-      pipeline_step<QT, SHIFT, true, true, true, false, false>(w, kb, vb, 0, Mk, l32, half);
-      pipeline_step<QT, SHIFT, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead,
-                                                       2 * j * kStep, Mk, l32, half);
+      pipeline_step<NQ, SHIFT, true, true, true, false, false>(w, kb, vb, 0, Mk, l16, grp);
+      pipeline_step<NQ, SHIFT, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead,
+                                                       2 * j * kStep, Mk, l16, grp);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the last V tile is in LDS
     __syncthreads();
@@ -588,18 +590,17 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   // ---- j = n_tiles: drain ---------------------------------------------------------------------------
   if (active) {
     const bf16_t* vb = &s_v[(n_tiles - 1) & 1][0];
-    pipeline_step<QT, SHIFT, false, true, true, true, false>(w, nullptr, vb, (2 * n_tiles - 1) * kStep, Mk,
-                                                      l32, half);
-    pipeline_step<QT, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, 0, Mk, l32, half);
+    pipeline_step<NQ, SHIFT, false, true, true, true, false>(w, nullptr, vb, (2 * n_tiles - 1) * kStep, Mk,
+                                                      l16, grp);
+    pipeline_step<NQ, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, 0, Mk, l16, grp);
   }
 
-  float l_tot[QT];
+  float l_tot[NQ];
   bool bad = false;
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    const float s0 = __shfl(w.l_acc[qt][0] + w.l_acc[qt][1], l32 & 15);
-    const float s1 = __shfl(w.l_acc[qt][2] + w.l_acc[qt][3], l32 & 15);
-    l_tot[qt] = l32 < 16 ? s0 : s1;
+  for (int qt = 0; qt < NQ; ++qt) {
+    const f32x4& l = w.l_acc[qt >> 1];
+    l_tot[qt] = __shfl(qt & 1 ? l[2] + l[3] : l[0] + l[1], l16);
     bad = bad || !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax);
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
@@ -607,11 +608,11 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   if (__syncthreads_or(active && bad)) {
     if (active) {
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
+      for (int qt = 0; qt < NQ; ++qt) {
         w.mc[qt] = -1e30f;
         l_tot[qt] = 0.f;
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt) w.o_acc[dt][qt] = splat16(0.f);
+        for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
 #pragma unroll 1
@@ -623,33 +624,31 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
       if (active) {
 #pragma unroll 1
         for (int st = 0; st < kKvTile && kv0 + st < Mk; st += kStep)
-          running_max_step<QT>(w, l_tot, &s_k[0][st * kDHead], &s_v[0][st * kDHead], kv0 + st, Mk, l32, half);
+          running_max_step<NQ>(w, l_tot, &s_k[0][st * kDHead], &s_v[0][st * kDHead], kv0 + st, Mk, l16, grp);
       }
       __syncthreads();
     }
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) l_tot[qt] += __shfl_xor(l_tot[qt], 32);
+    for (int qt = 0; qt < NQ; ++qt) {
+      l_tot[qt] += __shfl_xor(l_tot[qt], 16);
+      l_tot[qt] += __shfl_xor(l_tot[qt], 32);
+    }
   }
 
   if (piece) {
     // a segment: unnormalised sums and the shifts they are relative to, for attention_split_reduce_kernel
     if (active) {
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        const int row = wq0 + qt * 32 + l32;
+      for (int qt = 0; qt < NQ; ++qt) {
+        const int row = wq0 + qt * 16 + l16;
         if (row < Mq) {
-          // slot layout [16 channel groups of 4][BQ rows][4]: group (dt * 4 + g) * 2 + half holds the
-          // channels dt * 32 + 8 * g + 4 * half .. + 3, so that the 32 lanes of a half write 512
-          // contiguous bytes and the kernel that adds the segments up reads whole lines
+          // slot layout [16 channel groups of 4][BQ rows][4]: group 4 * ct + grp holds the channels
+          // 16 * ct + 4 * grp .. + 3, so that the 16 lanes of a group write 256 contiguous bytes and the
+          // kernel that adds the segments up reads whole lines
           float* po = a.split_o + piece_row0 * kDHead + (row - q0) * 4;
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              *(f32x4*)(po + ((dt * 4 + g) * 2 + half) * (BQ * 4)) =
-                  f32x4{w.o_acc[dt][qt][4 * g], w.o_acc[dt][qt][4 * g + 1], w.o_acc[dt][qt][4 * g + 2],
-                        w.o_acc[dt][qt][4 * g + 3]};
-          if (half == 0) {
+          for (int ct = 0; ct < 4; ++ct) *(f32x4*)(po + (4 * ct + grp) * (BQ * 4)) = w.o_acc[ct][qt];
+          if (grp == 0) {
             a.split_l[piece_row0 + (row - q0)] = l_tot[qt];
             a.split_m[piece_row0 + (row - q0)] = w.mc[qt];
           }
@@ -661,30 +660,28 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
 
   // ---- normalise and store ---------------------------------------------------------------------
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
+  for (int qt = 0; qt < NQ; ++qt) {
     const float inv = 1.0f / l_tot[qt];
-    const int row = wq0 + qt * 32 + l32;
+    const int row = wq0 + qt * 16 + l16;
     if (row < Mq) {
       bf16_t* orow = o_rows + (q_base + row) * kDHead;
 #pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          u32x2 ow;
-          ow[0] = pack_bf16x2(w.o_acc[dt][qt][4 * g] * inv, w.o_acc[dt][qt][4 * g + 1] * inv);
-          ow[1] = pack_bf16x2(w.o_acc[dt][qt][4 * g + 2] * inv, w.o_acc[dt][qt][4 * g + 3] * inv);
-          *(u32x2*)(orow + dt * 32 + 8 * g + 4 * half) = ow;
-        }
+      for (int ct = 0; ct < 4; ++ct) {
+        u32x2 ow;
+        ow[0] = pack_bf16x2(w.o_acc[ct][qt][0] * inv, w.o_acc[ct][qt][1] * inv);
+        ow[1] = pack_bf16x2(w.o_acc[ct][qt][2] * inv, w.o_acc[ct][qt][3] * inv);
+        *(u32x2*)(orow + 16 * ct + 4 * grp) = ow;
+      }
     }
   }
 }
 
 // SHIFT = false: the keys carry the logit scale, weights exp2(s).  SHIFT = true: any keys and scale.
-template <int QT, int NW, bool SHIFT>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, QT == 1 ? 3 : 2)))
+template <int NQ, int NW, bool SHIFT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2 ? 3 : 2, NQ == 2 ? 3 : 2)))
 void attention_kernel(const AttnArgs a) {
   constexpr int NT = 64 * NW;
-  constexpr int BQ = 32 * QT * NW;
+  constexpr int BQ = 16 * NQ * NW;
   constexpr int LD_ITER = kKvTile * kRowChunks / NT;       // 16-byte K chunks per thread per tile
   static_assert(LD_ITER >= 2 && LD_ITER % 2 == 0, "tile staging needs an even chunk count");
   constexpr int kTileElems = kKvTile * kDHead;
@@ -735,7 +732,7 @@ void attention_kernel(const AttnArgs a) {
       q0 = seg.q0;
       if (i) __syncthreads();                       // the tile buffers in LDS are free again
     }
-    attention_tile<QT, NW, SHIFT>(a, s_k, s_v, h, q0, dev_tile, q_base_dev, mq_dev, seg);
+    attention_tile<NQ, NW, SHIFT>(a, s_k, s_v, h, q0, dev_tile, q_base_dev, mq_dev, seg);
   }
 }
 
@@ -838,18 +835,18 @@ constexpr int64_t kSmallTileRound = 768;
 
 // `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
 // `scratch` (fp32 words, or nullptr): room for the tiles that run in segments (attention_split.hpp).
-template <int QT, int NW>
+template <int NQ, int NW>
 void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t stream) {
   if (log2_keys)
-    hipLaunchKernelGGL((attention_kernel<QT, NW, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
+    hipLaunchKernelGGL((attention_kernel<NQ, NW, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
   else
-    hipLaunchKernelGGL((attention_kernel<QT, NW, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
+    hipLaunchKernelGGL((attention_kernel<NQ, NW, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
 }
 
-template <int QT, int NW>
+template <int NQ, int NW>
 hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, const int64_t* k_off_host, int H,
                       hipStream_t stream, int extra_tiles = 0, float* scratch = nullptr, int64_t scratch_words = 0) {
-  constexpr int BQ = 32 * QT * NW;
+  constexpr int BQ = 16 * NQ * NW;
   int64_t full = 0;
   int ragged = 0;
   for (int h = 0; h < H; ++h) {
@@ -901,7 +898,7 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, co
       a.sp.slots = 0;
     }
   }
-  launch_kernel<QT, NW>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
+  launch_kernel<NQ, NW>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
   if (a.sp.n_tiles > 0)
     hipLaunchKernelGGL(attention_split_reduce_kernel, dim3(4u * (unsigned)a.sp.n_tiles), dim3(256), 0, stream, a);
   return hipGetLastError();
@@ -921,7 +918,7 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
                                       const int32_t* q_off_dev, const int32_t* tiles, int max_tiles,
                                       const int64_t* k_off_host, int H, float scale, bool log2_keys,
                                       hipStream_t stream) {
-  static_assert(kAttnDevTileRows == 32 * 2 * 4, "the device tile list is cut for attention_kernel<2, 4>");
+  static_assert(kAttnDevTileRows == 16 * 4 * 4, "the device tile list is cut for attention_kernel<4, 4>");
   if (max_tiles <= 0) return hipSuccess;
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -937,7 +934,7 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
   a.q2 = a.q;
   a.o2 = a.o;
   a.main_blocks = 0;        // no whole tiles, no segments: every workgroup takes the device-side list
-  launch_kernel<2, 4>(a, log2_keys, (unsigned)max_tiles, stream);
+  launch_kernel<4, 4>(a, log2_keys, (unsigned)max_tiles, stream);
   return hipGetLastError();
 }
 
@@ -958,7 +955,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
   a.o2 = (bf16_t*)o2;
-  return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
+  return launch_cfg<4, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
                           scratch_bytes / 4);
 }
 
@@ -984,9 +981,9 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   if (tiles128 <= kSmallTileRound) {
     const bool splits = scratch && attention_scratch_need(q_off_host, k_off_host, H) > 0 &&
                         attention_scratch_need(q_off_host, k_off_host, H) <= scratch_bytes;
-    if (!splits) return launch_cfg<1, 4>(a, log2_keys, q_off_host, k_off_host, H, stream);
+    if (!splits) return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream);
   }
-  return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
+  return launch_cfg<4, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------
