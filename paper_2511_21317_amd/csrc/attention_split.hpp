@@ -6,7 +6,7 @@
 // 512.  The R = T mod C tiles in excess of a multiple of C (the partial last tiles of the heads first,
 // then full tiles from the end) are therefore not run whole.  Their work - R tiles x the key tiles of
 // their heads, numbered as one line of "units" of (256 queries x 64 keys) - is cut into S equal
-// shares, about one or two per compute unit, whatever R is.  A share is one workgroup - equal work
+// shares, one per compute unit, whatever R is.  A share is one workgroup - equal work
 // is what the hardware's dispatch of workgroups to free slots balances - and where it crosses from one
 // query tile into the next it is two (or more) segments that the workgroup runs one after the other.
 // A segment sees its key range as the whole key sequence and leaves un-normalised fp32 sums (and
@@ -30,7 +30,7 @@ constexpr int kAttnSplitGroups = 64;      // runs of tiles of one head the exces
 constexpr int kAttnMaxShares = 512;
 constexpr int kAttnMaxExcess = 255;
 constexpr int kAttnMinShareUnits = 8;     // a share is at least 512 keys long (pipeline fill and drain)
-constexpr int kAttnShareUnits = 64;       // shares of more than 4096 keys are cut finer, down to two per CU
+constexpr int kAttnLongShareUnits = 240;  // shares of more than 15360 keys are cut in two
 constexpr int kAttnMaxPiecesPerTile = 32; // bounds what one workgroup of the second kernel has to add up
 constexpr int64_t kAttnSlotWords = (int64_t)kAttnTileRows * (64 + 2);   // 64 sums of weight * v, sum of weights, shift
 
@@ -168,12 +168,17 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   }
   if (left != 0 || units >= ((int64_t)1 << 30)) return;
   // It pays when the tile time it saves - the share (1 - R / cus) of an average tile of the excess
-  // set, about 0.85 us per unit - outweighs the second kernel and the traffic of the partial results
-  // (about 15 us): (cus - R) * units / R >= 20 * cus.
-  if ((cus - R) * (units / R) < 20 * cus) return;
-  int64_t shares = units / kAttnShareUnits;
-  if (shares < cus) shares = cus;
-  if (shares > 2 * cus) shares = 2 * cus;
+  // set, about 0.75 us per unit - outweighs the second kernel and the traffic of the partial results:
+  // (cus - R) * units / R >= 24 * cus.  16 heads, split against whole tiles, by the units saved per CU: 22
+  // (7400 rows and keys) 191 : 184 us, 27 (7000) 172 : 172, 33 (6700) 161 : 162, 44 (6376) 146 : 153, 54 (11000)
+  // 392 : 406, 78 (10000) 328 : 346.
+  if ((cus - R) * (units / R) < 24 * cus) return;
+  // One share per CU.  With any other number some CUs get one more than the others, and twice as many
+  // (every CU two) double the partial results: 16 heads of 7000 rows and keys in 330 / 512 / 256 shares 210 /
+  // 181 / 172 us, of 10000 in 314 / 512 / 256 364 / 344 / 328, of 15000 in 512 / 256 745 / 708.  Only very long
+  // shares are halved, which costs 2 % there (27000 rows and keys 2.27 : 2.21 ms): the launches whose partial
+  // results have never fitted the library's own array (httm_attention_log2_static) keep being refused.
+  int64_t shares = units / kAttnLongShareUnits > cus ? 2 * cus : cus;
   if (shares > units / kAttnMinShareUnits) shares = units / kAttnMinShareUnits;
   if (shares > kAttnMaxShares) shares = kAttnMaxShares;
   if (shares < 1) return;
