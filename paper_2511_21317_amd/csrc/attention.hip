@@ -65,6 +65,12 @@
 // scratch memory, the tiles in excess of a multiple of the CU count are not run whole: their work
 // is cut into equal shares over the keys, one or two per CU, that are dispatched behind the whole
 // tiles, and attention_split_reduce_kernel adds the pieces of every tile up (attention_split.hpp).
+//
+// Few rows.  With less than a 256-row tile per CU a launch is as long as one workgroup's walk over the
+// keys.  Workgroups with KS key groups (KS = 2 or 4: 128 or 64 rows) walk a KS-th of them: a wave still owns 64
+// rows, so its products are as dense and read as little LDS as those of the big tile, and the groups
+// meet in LDS at the end - no scratch memory, no second kernel.  The limits are in launch_attention().
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <type_traits>
@@ -93,7 +99,8 @@ struct AttnArgs {
   int32_t ragged_per_xcd;                     // ceil(n_ragged / 8)
   int32_t tile_start[kAttnMaxHeads + 1];      // first full tile of every head
   int32_t ragged_head[kAttnMaxHeads];         // head of every partial tile
-  int64_t q_off[kAttnMaxHeads + 1];
+  int64_t q_off[kAttnMaxHeads];               // first query row of every head, and how many
+  int32_t q_rows[kAttnMaxHeads];
   int64_t k_off[kAttnMaxHeads + 1];
   // When set, a second set of query tiles is described by device memory: rows of head h are
   // [dev_q_off[h], dev_q_off[h+1]) and workgroup t takes tile (head, first row) =
@@ -408,18 +415,20 @@ __device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ
 //   h, q0          : head and first query row of the tile
 //   dev_tile       : the tile comes from the device-side list (rows q_base_dev .. + mq_dev of q2 / o2)
 //   seg.slot >= 0  : only the key tiles [seg.t0, seg.t1) of the head, results into scratch slot seg.slot
-template <int NQ, int NW, bool SHIFT>
-__device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[kKvTile * kDHead],
-                                               bf16_t (*s_v)[kKvTile * kDHead], const int h, const int q0,
-                                               const bool dev_tile, const int64_t q_base_dev, const int mq_dev,
-                                               const SplitSegment seg) {
+//   KS > 1         : the waves form KS groups that take a KS-th of the keys each, for the same rows; every
+//                    group has tile buffers of its own, and the groups' results meet in LDS at the end
+template <int NQ, int NW, int KS, bool SHIFT>
+__device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[kKvTile * kDHead], const int h,
+                                               const int q0, const bool dev_tile, const int64_t q_base_dev,
+                                               const int mq_dev, const SplitSegment seg) {
   constexpr int NT = 64 * NW;
-  constexpr int BQ = 16 * NQ * NW;
-  constexpr int LDK = 8 / NW;                              // 1 KB global->LDS loads per wave per tile
+  constexpr int RG = NW / KS;                              // waves of a key group
+  constexpr int BQ = 16 * NQ * RG;
+  constexpr int LDK = 8 / RG;                              // 1 KB global->LDS loads per wave per tile
   const bool piece = seg.slot >= 0;
   const int64_t q_base = dev_tile ? q_base_dev : a.q_off[h];
   int64_t k_base = a.k_off[h];
-  const int Mq = dev_tile ? mq_dev : (int)(a.q_off[h + 1] - q_base);
+  const int Mq = dev_tile ? mq_dev : a.q_rows[h];
   const bf16_t* __restrict__ q_rows = dev_tile ? a.q2 : a.q;
   bf16_t* __restrict__ o_rows = dev_tile ? a.o2 : a.o;
   int Mk = (int)(a.k_off[h + 1] - k_base);
@@ -436,8 +445,11 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
     Mk = (seg.t1 * kKvTile < Mk ? seg.t1 * kKvTile : Mk) - seg.t0 * kKvTile;
   }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS destinations stay scalar
+  const int key_group = KS == 1 ? 0 : wave / RG, rwave = KS == 1 ? wave : wave % RG;
+  bf16_t (*s_k)[kKvTile * kDHead] = lds + key_group * 4;       // two tiles of K, two of V
+  bf16_t (*s_v)[kKvTile * kDHead] = s_k + 2;
   const int l16 = lane & 15, grp = lane >> 4;
-  const int wq0 = q0 + wave * 16 * NQ;  // first query row of this wave
+  const int wq0 = q0 + rwave * 16 * NQ;  // first query row of this wave
   // A wave of a partial tile that owns no valid row only helps to stage K/V and to keep the
   // barriers; it issues no MFMA and no softmax.
   const bool active = __builtin_amdgcn_readfirstlane((int)(wq0 < Mq)) != 0;   // wave-uniform, and known to be
@@ -449,6 +461,16 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
       if (row < Mq) ((u32x4*)o_rows)[(q_base + row) * kRowChunks + (e & 7)] = u32x4{0, 0, 0, 0};
     }
     return;
+  }
+
+  int max_tiles = 0;                              // of any key group (KS > 1)
+  __shared__ float s_sum[KS == 1 ? 1 : NW][NQ * 16], s_shift[KS == 1 ? 1 : NW][NQ * 16];
+  if constexpr (KS > 1) {
+    const int all = (Mk + kKvTile - 1) / kKvTile;
+    const int t0 = (key_group * all + KS - 1) / KS, t1 = ((key_group + 1) * all + KS - 1) / KS;   // (never none for the first)
+    max_tiles = (all + KS - 1) / KS;
+    k_base += (int64_t)t0 * kKvTile;
+    Mk = (t1 * kKvTile < Mk ? t1 * kKvTile : Mk) - t0 * kKvTile;   // 0 for a group without a key tile
   }
 
   WaveState<NQ> w;
@@ -475,7 +497,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   auto load_k = [&](int kv0, int buf, bool inside = false) {   // inside: the whole tile lies below Mk
 #pragma unroll
     for (int i = 0; i < LDK; ++i) {
-      const int blk = wave * LDK + i;
+      const int blk = rwave * LDK + i;
       const int r = blk * 8 + (lane >> 3);
       const int c = (lane & 7) ^ k_swizzle(r);
       int row = kv0 + r;
@@ -490,7 +512,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   auto load_v = [&](int kv0, int buf, bool inside = false) {
 #pragma unroll
     for (int i = 0; i < LDK; ++i) {
-      const int blk = wave * LDK + i;
+      const int blk = rwave * LDK + i;
       const int r = blk * 8 + (lane >> 3);
       const int c = (lane & 7) ^ v_swizzle(r);
       int row = kv0 + r;
@@ -512,6 +534,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   // (products of steps 2j-2, 2j-1), while K tile j+1 and V tile j are on their way into the
   // other LDS buffers.
 
+  if (KS == 1 || n_tiles > 0) {
   // ---- j = 0 ---------------------------------------------------------------------------------------
   load_k(0, 0);
   load_v(0, 0);
@@ -520,11 +543,29 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   __syncthreads();
   if (active) {
     pipeline_step<NQ, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, 0, Mk, l16, grp);
+  }
+  if constexpr (SHIFT && KS > 1) {
+    // the shifts of a row are those of the kernel without key groups: from the first 32 keys of the head
+    if (key_group == 0 && active) {
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          if (16 * (r >> 2) + 4 * grp + (r & 3) >= Mk) w.s_cur[r >> 2][qt][r & 3] = -INFINITY;
+        const float m = step_max(w.s_cur[0][qt], w.s_cur[1][qt]) * w.c;
+        if (grp == 0) s_shift[rwave][qt * 16 + l16] = m;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) w.mc[qt] = active ? s_shift[rwave][qt * 16 + l16] : 0.f;
+  }
+  if (active) {
     if (n_tiles > 1)
-      pipeline_step<NQ, SHIFT, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
+      pipeline_step<NQ, SHIFT, true, false, true, false, KS == 1>(w, &s_k[0][kStep * kDHead], nullptr, 0,
                                                         Mk, l16, grp);
     else
-      pipeline_step<NQ, SHIFT, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, 0,
+      pipeline_step<NQ, SHIFT, true, false, true, true, KS == 1>(w, &s_k[0][kStep * kDHead], nullptr, 0,
                                                        Mk, l16, grp);
   }
   __syncthreads();
@@ -594,6 +635,11 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
                                                       l16, grp);
     pipeline_step<NQ, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, 0, Mk, l16, grp);
   }
+  }
+  // a group of n tiles has met n + 1 barriers, one more for shifts (none if it has no tile): the others of
+  // its workgroup wait
+  if constexpr (KS > 1)
+    for (int b = n_tiles ? n_tiles : -1 - SHIFT; b < max_tiles; ++b) __syncthreads();
 
   float l_tot[NQ];
   bool bad = false;
@@ -601,7 +647,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
   for (int qt = 0; qt < NQ; ++qt) {
     const f32x4& l = w.l_acc[qt >> 1];
     l_tot[qt] = __shfl(qt & 1 ? l[2] + l[3] : l[0] + l[1], l16);
-    bad = bad || !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax);
+    if (KS > 1 && n_tiles == 0) w.mc[qt] = -1e30f;      // (no keys, no say in the common shift)
+    bad = bad || (n_tiles > 0 && !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax));
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
   // stages its tiles together) takes the tile again with running maxima.
@@ -615,10 +662,13 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
         for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
+    const int end = KS == 1 ? Mk : max_tiles * kKvTile;      // (the groups meet at the same barriers)
 #pragma unroll 1
-    for (int kv0 = 0; kv0 < Mk; kv0 += kKvTile) {
-      load_k(kv0, 0);
-      load_v(kv0, 0);
+    for (int kv0 = 0; kv0 < end; kv0 += kKvTile) {
+      if (KS == 1 || kv0 < Mk) {
+        load_k(kv0, 0);
+        load_v(kv0, 0);
+      }
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
       if (active) {
@@ -633,6 +683,56 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
       l_tot[qt] += __shfl_xor(l_tot[qt], 16);
       l_tot[qt] += __shfl_xor(l_tot[qt], 32);
     }
+  }
+
+  if constexpr (KS > 1) {
+    // The groups' sums, brought to the largest of their shifts of a row (all zero unless a group had
+    // to take running maxima or the keys are plain), added in key order.  Every wave leaves its registers in
+    // LDS as they are (the tile buffers: no group reads them any more) and adds up its share of the channels.
+    static_assert(NQ * NW * 4 * 64 * 16 <= KS * 4 * kKvTile * kDHead * 2, "the accumulators fit the tile buffers");
+    f32x4* s_acc = (f32x4*)lds;                     // [wave][channel tile][query tile][lane]
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) s_acc[((wave * 4 + ct) * NQ + qt) * 64 + lane] = w.o_acc[ct][qt];
+      if (grp == 0) {
+        s_sum[wave][qt * 16 + l16] = l_tot[qt];
+        s_shift[wave][qt * 16 + l16] = w.mc[qt];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      float wgt[KS], m = -1e30f, l = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        wgt[k] = s_shift[k * RG + rwave][qt * 16 + l16];
+        m = fmaxf(m, wgt[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const float sum = s_sum[k * RG + rwave][qt * 16 + l16];
+        wgt[k] = sum == 0.f ? 0.f : __builtin_amdgcn_exp2f(wgt[k] - m);    // (a group without keys: no weight)
+        l = fmaf(sum, wgt[k], l);
+      }
+      const float inv = 1.0f / l;
+      const int row = wq0 + qt * 16 + l16;
+#pragma unroll
+      for (int c = 0; c < 4 / KS; ++c) {
+        const int ct = key_group * (4 / KS) + c;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          const f32x4 x = s_acc[(((k * RG + rwave) * 4 + ct) * NQ + qt) * 64 + lane];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[r] = fmaf(x[r], wgt[k], o[r]);
+        }
+        if (row < Mq)
+          *(u32x2*)(o_rows + (q_base + row) * kDHead + 16 * ct + 4 * grp) =
+              u32x2{pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+      }
+    }
+    return;
   }
 
   if (piece) {
@@ -677,16 +777,12 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*s_k)[
 }
 
 // SHIFT = false: the keys carry the logit scale, weights exp2(s).  SHIFT = true: any keys and scale.
-template <int NQ, int NW, bool SHIFT>
+template <int NQ, int NW, int KS, bool SHIFT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2 ? 3 : 2, NQ == 2 ? 3 : 2)))
 void attention_kernel(const AttnArgs a) {
-  constexpr int NT = 64 * NW;
-  constexpr int BQ = 16 * NQ * NW;
-  constexpr int LD_ITER = kKvTile * kRowChunks / NT;       // 16-byte K chunks per thread per tile
-  static_assert(LD_ITER >= 2 && LD_ITER % 2 == 0, "tile staging needs an even chunk count");
-  constexpr int kTileElems = kKvTile * kDHead;
-  __shared__ __align__(16) bf16_t s_k[2][kTileElems];    // [kv][d], 128-byte rows, chunk-swizzled
-  __shared__ __align__(16) bf16_t s_v[2][kTileElems];    // [kv][d], 128-byte rows, chunk-swizzled
+  constexpr int BQ = 16 * NQ * (NW / KS);
+  // per key group two tiles of K and two of V: [kv][d], 128-byte rows, chunk-swizzled
+  __shared__ __align__(16) bf16_t lds[KS * 4][kKvTile * kDHead];
 
   // blockIdx -> work.  Workgroups go round-robin to the 8 XCDs, and in blockIdx order to free
   // slots.  Every XCD walks its whole tiles first - the partial last tiles of the heads (they are
@@ -707,7 +803,7 @@ void attention_kernel(const AttnArgs a) {
     q0 = a.dev_tiles[2 + 2 * t];
     q_base_dev = a.dev_q_off[h];
     mq_dev = a.dev_q_off[h + 1] - a.dev_q_off[h];
-  } else if (pos >= whole_per_xcd) {
+  } else if (KS == 1 && pos >= whole_per_xcd) {
     const int item = pos - whole_per_xcd;
     share = xcd * a.split_per_xcd + item;
     if (item >= a.split_per_xcd || share >= a.sp.shares) return;
@@ -732,7 +828,7 @@ void attention_kernel(const AttnArgs a) {
       q0 = seg.q0;
       if (i) __syncthreads();                       // the tile buffers in LDS are free again
     }
-    attention_tile<NQ, NW, SHIFT>(a, s_k, s_v, h, q0, dev_tile, q_base_dev, mq_dev, seg);
+    attention_tile<NQ, NW, KS, SHIFT>(a, lds, h, q0, dev_tile, q_base_dev, mq_dev, seg);
   }
 }
 
@@ -750,7 +846,7 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
   const int e = blockIdx.x >> 2, part = blockIdx.x & 3, tid = threadIdx.x;
   const SplitTile t = split_tile(a.sp, e);
   const int64_t q_base = a.q_off[t.head];
-  const int left = (int)(a.q_off[t.head + 1] - q_base) - t.q0;
+  const int left = a.q_rows[t.head] - t.q0;
   const int rows = left < BQ ? left : BQ;
   if (part * kReduceRows >= rows) return;
   const int np = t.last_share - t.first_share + 1;
@@ -835,31 +931,53 @@ constexpr int64_t kSmallTileRound = 768;
 
 // `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
 // `scratch` (fp32 words, or nullptr): room for the tiles that run in segments (attention_split.hpp).
-template <int NQ, int NW>
+template <int NQ, int NW, int KS = 1>
 void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t stream) {
   if (log2_keys)
-    hipLaunchKernelGGL((attention_kernel<NQ, NW, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
+    hipLaunchKernelGGL((attention_kernel<NQ, NW, KS, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
   else
-    hipLaunchKernelGGL((attention_kernel<NQ, NW, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
+    hipLaunchKernelGGL((attention_kernel<NQ, NW, KS, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
 }
 
-template <int NQ, int NW>
-hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, const int64_t* k_off_host, int H,
-                      hipStream_t stream, int extra_tiles = 0, float* scratch = nullptr, int64_t scratch_words = 0) {
-  constexpr int BQ = 16 * NQ * NW;
+// The query rows of a launch: `count` rows of every head from row `first` of the packed tensor.
+struct HeadRows {
+  int64_t first[kAttnMaxHeads];
+  int64_t count[kAttnMaxHeads];
+};
+HeadRows all_rows(const int64_t* q_off_host, int H) {
+  HeadRows r = {};
+  for (int h = 0; h < H; ++h) {
+    r.first[h] = q_off_host[h];
+    r.count[h] = q_off_host[h + 1] - q_off_host[h];
+  }
+  return r;
+}
+int64_t tiles_of(const HeadRows& r, int H, int rows) {
+  int64_t n = 0;
+  for (int h = 0; h < H; ++h) n += (r.count[h] + rows - 1) / rows;
+  return n;
+}
+
+template <int NQ, int NW, int KS = 1>
+hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles = 0, float* scratch = nullptr, int64_t scratch_words = 0) {
+  constexpr int BQ = 16 * NQ * (NW / KS);
   int64_t full = 0;
   int ragged = 0;
   for (int h = 0; h < H; ++h) {
-    const int64_t mq = q_off_host[h + 1] - q_off_host[h];
+    const int64_t mq = rows.count[h];
     a.tile_start[h] = (int32_t)full;
-    a.q_off[h] = q_off_host[h];
+    a.q_off[h] = rows.first[h];
+    a.q_rows[h] = (int32_t)mq;
     a.k_off[h] = k_off_host[h];
     full += mq / BQ;
     if (mq % BQ) a.ragged_head[ragged++] = h;
   }
   for (int h = H; h <= kAttnMaxHeads; ++h) {
     a.tile_start[h] = (int32_t)full;
-    a.q_off[h] = q_off_host[H];
+    if (h < kAttnMaxHeads) {
+      a.q_off[h] = 0;
+      a.q_rows[h] = 0;
+    }
     a.k_off[h] = k_off_host[H];
   }
   for (int i = ragged; i < kAttnMaxHeads; ++i) a.ragged_head[i] = 0;
@@ -875,10 +993,12 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, co
   a.split_m = nullptr;
   a.sp.n_tiles = 0;
   a.sp.slots = 0;
-  if (BQ == kAttnTileRows && scratch) {
+  if (KS == 1 && BQ == kAttnTileRows && scratch) {
     int64_t kept_full = full;
     int split_ragged = 0;
-    plan_attention_split(q_off_host, k_off_host, H, compute_units(), &a.sp, &kept_full, &split_ragged);
+    int64_t lengths[kAttnMaxHeads + 1] = {0};        // (the plan looks at the heads' lengths only)
+    for (int h = 0; h < H; ++h) lengths[h + 1] = lengths[h] + rows.count[h];
+    plan_attention_split(lengths, k_off_host, H, compute_units(), &a.sp, &kept_full, &split_ragged);
     const int64_t slots = split_slots(a.sp);
     if (a.sp.n_tiles > 0 && slots * kAttnSlotWords <= scratch_words) {
       // the first partial tiles (in head order) and the last full tiles run in segments; the others
@@ -898,7 +1018,7 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const int64_t* q_off_host, co
       a.sp.slots = 0;
     }
   }
-  launch_kernel<NQ, NW>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
+  launch_kernel<NQ, NW, KS>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
   if (a.sp.n_tiles > 0)
     hipLaunchKernelGGL(attention_split_reduce_kernel, dim3(4u * (unsigned)a.sp.n_tiles), dim3(256), 0, stream, a);
   return hipGetLastError();
@@ -955,7 +1075,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
   a.o2 = (bf16_t*)o2;
-  return launch_cfg<4, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
+  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
                           scratch_bytes / 4);
 }
 
@@ -972,18 +1092,47 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   a.H = H;
   // Tiles of 256 query rows (two workgroups per CU) are the efficient shape, and with scratch memory
   // the tiles in excess of a multiple of the CU count run in segments, so that any tile count fills
-  // the chip.  Without that split, a short problem that fits into one round of 128-row tiles (three
-  // workgroups per CU, 768 at a time) runs those instead: they fill the chip where the big tiles
-  // leave a third of it idle (measured: 0.132 against 0.144 ms at 16 x 5516 rows; with 800 small
-  // tiles, a second round, 0.19 against 0.17 ms).
-  int64_t tiles128 = 0;
-  for (int h = 0; h < H; ++h) tiles128 += (q_off_host[h + 1] - q_off_host[h] + 127) / 128;
-  if (tiles128 <= kSmallTileRound) {
-    const bool splits = scratch && attention_scratch_need(q_off_host, k_off_host, H) > 0 &&
-                        attention_scratch_need(q_off_host, k_off_host, H) <= scratch_bytes;
-    if (!splits) return launch_cfg<2, 4>(a, log2_keys, q_off_host, k_off_host, H, stream);
+  // the chip.
+  const HeadRows rows = all_rows(q_off_host, H);
+  const int64_t cus = compute_units(), tiles128 = tiles_of(rows, H, 128);
+  // A problem of at most one 64-row (128-row) tile per CU runs those, the keys cut in four (two) inside the
+  // workgroup, unless the walk is so short that the meeting costs more (2 us).  Kernel times of 16 heads against
+  // the 128-row tiles of one key group: four groups 266 rows x 266 keys 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5,
+  // 700 x 700 12.0 : 12.0, 1024 x 1024 14.0 : 15.4; two groups 1400 x 1400 17.3 : 17.2, 2048 x 2048 22.1 : 22.8,
+  // 2048 x 8192 68 : 91 (in segments 72).
+  int64_t keys = 0;
+  for (int h = 0; h < H; ++h) keys = std::max(keys, k_off_host[h + 1] - k_off_host[h]);
+  if (keys >= 768 && tiles_of(rows, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
+  if (keys >= 1536 && tiles128 <= cus) return launch_cfg<4, 4, 2>(a, log2_keys, rows, k_off_host, H, stream);
+  const int64_t need = scratch ? attention_scratch_need(q_off_host, k_off_host, H) : 0;
+  if (need == 0 || need > scratch_bytes) {
+    // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in tiles of
+    // 128 (64) rows whose keys are cut in two (four), if those are one round: a half (quarter) of a round instead
+    // of a whole one.  From two rounds on (a lone tile on a CU has 0.8 of the rate of a pair): 16 heads of 9000
+    // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 500, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
+    HeadRows whole = rows, rest = rows;
+    int64_t full = 0;
+    for (int h = 0; h < H; ++h) full += rows.count[h] / kAttnTileRows;
+    const bool rounds = full >= 2 * cus;
+    int64_t keep = full / cus * cus;
+    for (int h = 0; h < H; ++h) {
+      const int64_t nf = rows.count[h] / kAttnTileRows, n = (nf < keep ? nf : keep) * kAttnTileRows;
+      keep -= n / kAttnTileRows;
+      whole.count[h] = n;
+      rest.first[h] += n;
+      rest.count[h] -= n;
+    }
+    if (rounds && tiles_of(rest, H, 128) <= cus) {
+      const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
+      if (e != hipSuccess) return e;
+      if (tiles_of(rest, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rest, k_off_host, H, stream);
+      return launch_cfg<4, 4, 2>(a, log2_keys, rest, k_off_host, H, stream);
+    }
+    // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a
+    // time) runs those: they fill the chip where the big tiles leave a third of it idle.
+    if (tiles128 <= kSmallTileRound) return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
   }
-  return launch_cfg<4, 4>(a, log2_keys, q_off_host, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
+  return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------
