@@ -67,9 +67,10 @@
 // tiles, and attention_split_reduce_kernel adds the pieces of every tile up (attention_split.hpp).
 //
 // Few rows.  With less than a 256-row tile per CU a launch is as long as one workgroup's walk over the
-// keys.  Workgroups with KS key groups (KS = 2 or 4: 128 or 64 rows) walk a KS-th of them: a wave still owns 64
-// rows, so its products are as dense and read as little LDS as those of the big tile, and the groups
-// meet in LDS at the end - no scratch memory, no second kernel.  The limits are in launch_attention().
+// keys.  Workgroups with KS key groups walk a KS-th of them (64 rows: 4 waves, 4 groups; 128: 8 waves, 4; 256: 8
+// waves, 2): a wave still owns 64 rows, so its products are as dense and read as little LDS as those of the
+// big tile, and the groups meet in LDS at the end - no scratch memory, no second kernel.  The limits are in
+// launch_attention().
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -411,6 +412,14 @@ __device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ
   }
 }
 
+// 8 KB tiles of LDS of a workgroup: per key group two of K and two of V, and with several key groups room
+// for everybody's accumulators in their place.
+template <int NQ, int NW, int KS>
+constexpr int lds_tiles() {
+  const int acc = KS > 1 ? NQ * NW * 4 * 64 * 16 / (kKvTile * kDHead * 2) : 0;
+  return KS * 4 > acc ? KS * 4 : acc;
+}
+
 // One query tile (or one segment of it) of a workgroup: see attention_kernel.
 //   h, q0          : head and first query row of the tile
 //   dev_tile       : the tile comes from the device-side list (rows q_base_dev .. + mq_dev of q2 / o2)
@@ -689,7 +698,6 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     // The groups' sums, brought to the largest of their shifts of a row (all zero unless a group had
     // to take running maxima or the keys are plain), added in key order.  Every wave leaves its registers in
     // LDS as they are (the tile buffers: no group reads them any more) and adds up its share of the channels.
-    static_assert(NQ * NW * 4 * 64 * 16 <= KS * 4 * kKvTile * kDHead * 2, "the accumulators fit the tile buffers");
     f32x4* s_acc = (f32x4*)lds;                     // [wave][channel tile][query tile][lane]
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
@@ -782,7 +790,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2
 void attention_kernel(const AttnArgs a) {
   constexpr int BQ = 16 * NQ * (NW / KS);
   // per key group two tiles of K and two of V: [kv][d], 128-byte rows, chunk-swizzled
-  __shared__ __align__(16) bf16_t lds[KS * 4][kKvTile * kDHead];
+  __shared__ __align__(16) bf16_t lds[lds_tiles<NQ, NW, KS>()][kKvTile * kDHead];
 
   // blockIdx -> work.  Workgroups go round-robin to the 8 XCDs, and in blockIdx order to free
   // slots.  Every XCD walks its whole tiles first - the partial last tiles of the heads (they are
@@ -1095,21 +1103,28 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   // the chip.
   const HeadRows rows = all_rows(q_off_host, H);
   const int64_t cus = compute_units(), tiles128 = tiles_of(rows, H, 128);
-  // A problem of at most one 64-row (128-row) tile per CU runs those, the keys cut in four (two) inside the
-  // workgroup, unless the walk is so short that the meeting costs more (2 us).  Kernel times of 16 heads against
-  // the 128-row tiles of one key group: four groups 266 rows x 266 keys 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5,
-  // 700 x 700 12.0 : 12.0, 1024 x 1024 14.0 : 15.4; two groups 1400 x 1400 17.3 : 17.2, 2048 x 2048 22.1 : 22.8,
-  // 2048 x 8192 68 : 91 (in segments 72).
+  // A problem of at most one 64-row (128-row) tile per CU runs those, the keys cut in four among four (eight)
+  // waves, unless the walk is so short that the meeting costs more (2 us).  16 heads against the 128-row tiles
+  // of one key group: 64 rows 266 x 266 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5, 700 x 700 12.0 : 12.0, 1024 x 1024
+  // 14.0 : 15.4; 128 rows 1400 x 1400 18.1 : 17.2, 2048 x 2048 22.1 : 22.8, 2048 x 8192 63 : 91 (in segments 72; with
+  // four waves and two key groups, one wave a SIMD, 69).
   int64_t keys = 0;
   for (int h = 0; h < H; ++h) keys = std::max(keys, k_off_host[h + 1] - k_off_host[h]);
   if (keys >= 768 && tiles_of(rows, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
-  if (keys >= 1536 && tiles128 <= cus) return launch_cfg<4, 4, 2>(a, log2_keys, rows, k_off_host, H, stream);
+  if (keys >= 2048 && tiles128 <= cus) return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
   const int64_t need = scratch ? attention_scratch_need(q_off_host, k_off_host, H) : 0;
-  if (need == 0 || need > scratch_bytes) {
+  const bool whole_tiles = need == 0 || need > scratch_bytes;
+  // At most one round of 256-row tiles: eight waves and two key groups fill the CU that a lone tile of four
+  // waves does not (3000 x 3000 44 with 128-row tiles -> 41 us, 4096 x 4096 62 -> 59, 4096 x 10000 143 -> 134), and
+  // segments pay only where the round is far from full (192 tiles of 8192 keys: segments 110, so 96).
+  const int64_t tiles256 = tiles_of(rows, H, kAttnTileRows);
+  if (keys >= 2048 && tiles256 <= cus && (whole_tiles || 4 * tiles256 >= 3 * cus))
+    return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
+  if (whole_tiles) {
     // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in tiles of
-    // 128 (64) rows whose keys are cut in two (four), if those are one round: a half (quarter) of a round instead
+    // 128 (64) rows whose keys are cut in four, if those are one round: a half (quarter) of a round instead
     // of a whole one.  From two rounds on (a lone tile on a CU has 0.8 of the rate of a pair): 16 heads of 9000
-    // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 500, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
+    // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 495, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
     HeadRows whole = rows, rest = rows;
     int64_t full = 0;
     for (int h = 0; h < H; ++h) full += rows.count[h] / kAttnTileRows;
@@ -1126,7 +1141,7 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
       const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
       if (e != hipSuccess) return e;
       if (tiles_of(rest, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rest, k_off_host, H, stream);
-      return launch_cfg<4, 4, 2>(a, log2_keys, rest, k_off_host, H, stream);
+      return launch_cfg<4, 8, 4>(a, log2_keys, rest, k_off_host, H, stream);
     }
     // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a
     // time) runs those: they fill the chip where the big tiles leave a third of it idle.

@@ -1,5 +1,5 @@
-"""Stage 3 (Eq. 3-4) with the keys cut among the waves of a workgroup: heads of few rows (64-row tiles, four
-key groups; 128-row tiles, two), and what is left after whole rounds of 256-row tiles.  Both key
+"""Stage 3 (Eq. 3-4) with the keys cut among the waves of a workgroup: heads of few rows (64- and 128-row
+tiles, four key groups; 256-row tiles, two), and what is left after whole rounds of 256-row tiles.  Both key
 conventions, key counts around the dispatch's limits and where the groups' shares are unequal, one
 group with rows out of range, an empty head, against the oracle's attention."""
 import numpy as np
@@ -12,15 +12,17 @@ from gpu_util import require_gpu, f32, check_output
 
 pytestmark = pytest.mark.gpu
 
-# rows and keys per head.  On 256 CUs: four groups from 768 keys, two from 1536, the rounds from 512 full tiles.
+# rows and keys per head.  On 256 CUs: 64-row tiles from 768 keys, the others from 2048, the rounds from 512 full tiles.
 CASES = {
     "four_groups_limit": ([64, 65, 1, 256], [768, 767, 705, 768]),
     "four_groups_unequal": ([300, 17], [1089, 64]),           # 18 key tiles; a single one: three groups without keys
     "four_groups_empty_heads": ([100, 0, 40, 33], [900, 500, 0, 1]),
-    "two_groups_limit": ([8192, 8065, 1], [1536, 1535, 1473]),
-    "two_groups_one_tile": ([16384, 130], [1601, 31]),
+    "eight_waves_128_limit": ([8192, 8065, 1], [2048, 2047, 1985]),
+    "eight_waves_128_one_tile": ([16384, 130], [2113, 31]),
+    "eight_waves_256_limit": ([256 * 100, 256 * 100 + 1, 300, 200], [2048, 2047, 65, 1]),
+    "eight_waves_256_unequal": ([256 * 200, 257], [2113, 129]),
     "rounds_and_four_groups": ([256 * 256 + 100, 256 * 256 + 65, 77], [400, 333, 129]),
-    "rounds_and_two_groups": ([256 * 400, 256 * 200 + 3], [200, 321]),
+    "rounds_and_eight_waves": ([256 * 400, 256 * 200 + 3], [200, 321]),
 }
 
 
