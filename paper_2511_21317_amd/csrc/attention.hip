@@ -57,13 +57,14 @@
 // cores (row_sum_operand()), and a tile is checked once, at its end.  If a row's sum is outside
 // [2^-64, 2^64] (or inf / NaN), the workgroup takes the tile again with running maxima
 // (running_max_step(): the classic online softmax, not pipelined).  Measured against a guard inside the
-// loop for plain keys (a dot2 against ones and a compare per score pair) and a second launch that redid marked tiles for log2 keys:
+// loop for plain keys (a dot2 against ones and a compare per score pair) and a second launch that redid
+// marked tiles for log2 keys:
 // 16 ragged heads of 5500 x 9000 plain keys 219 -> 201 us, two 16 x 16 frames 27.3 -> 24.3 us a layer.
 //
-// End of a launch.  A CU runs its 256-row tiles two at a time, but one alone nearly twice as fast,
+// End of a launch.  A CU runs its 256-row tiles two at a time, but one alone at 0.8 of the rate of two,
 // so the launch time follows the largest number of whole tiles a CU gets.  When the caller has given
 // scratch memory, the tiles in excess of a multiple of the CU count are not run whole: their work
-// is cut into equal shares over the keys, one or two per CU, that are dispatched behind the whole
+// is cut into equal shares over the keys, one per CU, that are dispatched behind the whole
 // tiles, and attention_split_reduce_kernel adds the pieces of every tile up (attention_split.hpp).
 //
 // Few rows.  With less than a 256-row tile per CU a launch is as long as one workgroup's walk over the
@@ -114,7 +115,7 @@ struct AttnArgs {
   bf16_t* o2;
   // Every XCD (workgroup b goes to XCD b % 8) walks a sequence of full_per_xcd + ragged_per_xcd whole
   // tiles and then split_per_xcd shares of the tiles that run in segments over the keys
-  // (attention_split.hpp; none in a launch that only redoes marked tiles).  A segment writes
+  // (attention_split.hpp).  A segment writes
   // un-normalised fp32 results into its slot of the scratch memory and attention_split_reduce_kernel
   // adds them up.  The workgroups behind main_blocks = 8 * (sequence length) take the device-side tile
   // list.  n_ragged / ragged_head and n_full count only the tiles that stay whole.
@@ -122,7 +123,7 @@ struct AttnArgs {
   int32_t main_blocks;
   float* split_o;   // [slots * 256][64] sums of weight * v
   float* split_l;   // [slots * 256]     sums of weights
-  float* split_m;   // [slots * 256]     the rows' shifts (kernel with per-row shifts only)
+  float* split_m;   // [slots * 256]     the rows' shifts
   SplitPlan sp;
 };
 static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KB");

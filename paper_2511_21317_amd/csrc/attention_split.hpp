@@ -1,7 +1,7 @@
 // Work decomposition of stage 3 (paper Sec. 3.2 Eq. 3-4) for launches whose query tiles do not fill
 // the compute units evenly.
 //
-// A compute unit runs whole 256-row query tiles, two at a time, and one alone nearly twice as fast, so
+// A compute unit runs whole 256-row query tiles, two at a time, and one alone at 0.8 of the rate of two, so
 // a launch of T tiles on C units takes ceil(T / C) tile times: 400 tiles on 256 units cost as much as
 // 512.  The R = T mod C tiles in excess of a multiple of C (the partial last tiles of the heads first,
 // then full tiles from the end) are therefore not run whole.  Their work - R tiles x the key tiles of
