@@ -375,11 +375,16 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
 constexpr float kFastSumMin = 5.421010862427522e-20f;    // 2^-64
 constexpr float kFastSumMax = 1.8446744073709552e19f;    // 2^64
 
+// A maximum no finite score is below: where the running maxima start, and the shift of sums without a key.
+constexpr float kLowestScore = -3.402823466e38f;
+
 // One step of 32 keys with a running maximum per row (the classic online softmax), for tiles whose
-// rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.
+// rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.  The maxima are kept in
+// units of the raw scores: near the ends of the fp32 range the rounding of max * c alone is more than
+// the exponents can hold, s - max of neighbouring scores is exact.
 template <int NQ>
-__device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ], const bf16_t* sk, const bf16_t* sv,
-                                                 int kv_first, int Mk, int l16, int grp) {
+__device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ], float (&top)[NQ], const bf16_t* sk,
+                                                 const bf16_t* sv, int kv_first, int Mk, int l16, int grp) {
   const bf16x2 ones2 = {(bf16_t)1.0f, (bf16_t)1.0f};
   StepOperands op;
   load_k_operands(op, sk, l16, grp);
@@ -396,11 +401,16 @@ __device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ
       for (int r = 0; r < 4; ++r)
         if (kv_first + 16 * kt + 4 * grp + r >= Mk) s[kt][r] = -INFINITY;
     }
-    const float m = fmaxf(w.mc[qt], step_max(s[0], s[1]) * w.c);
-    const float sc = __builtin_amdgcn_exp2f(w.mc[qt] - m);
-    w.mc[qt] = m;
+    const float m = fmaxf(top[qt], step_max(s[0], s[1]));
+    const float sc = __builtin_amdgcn_exp2f((top[qt] - m) * w.c);
+    top[qt] = m;
     u32x8 p = {};
-    exp_pack<true>(s[0], s[1], w.c, m, p, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x4& x = s[e >> 1];
+      const int i = 2 * (e & 1);
+      p[e] = pack_bf16x2(__builtin_amdgcn_exp2f((x[i] - m) * w.c), __builtin_amdgcn_exp2f((x[i + 1] - m) * w.c));
+    }
     l[qt] *= sc;
 #pragma unroll
     for (int e = 0; e < 4; ++e) l[qt] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)p[e]), ones2, l[qt], false);
@@ -657,16 +667,17 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   for (int qt = 0; qt < NQ; ++qt) {
     const f32x4& l = w.l_acc[qt >> 1];
     l_tot[qt] = __shfl(qt & 1 ? l[2] + l[3] : l[0] + l[1], l16);
-    if (KS > 1 && n_tiles == 0) w.mc[qt] = -1e30f;      // (no keys, no say in the common shift)
+    if (KS > 1 && n_tiles == 0) w.mc[qt] = kLowestScore;      // (no keys, no say in the common shift)
     bad = bad || (n_tiles > 0 && !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax));
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
   // stages its tiles together) takes the tile again with running maxima.
   if (__syncthreads_or(active && bad)) {
+    float top[NQ];
     if (active) {
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) {
-        w.mc[qt] = -1e30f;
+        top[qt] = kLowestScore;
         l_tot[qt] = 0.f;
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -684,7 +695,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       if (active) {
 #pragma unroll 1
         for (int st = 0; st < kKvTile && kv0 + st < Mk; st += kStep)
-          running_max_step<NQ>(w, l_tot, &s_k[0][st * kDHead], &s_v[0][st * kDHead], kv0 + st, Mk, l16, grp);
+          running_max_step<NQ>(w, l_tot, top, &s_k[0][st * kDHead], &s_v[0][st * kDHead], kv0 + st, Mk, l16, grp);
       }
       __syncthreads();
     }
@@ -692,6 +703,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     for (int qt = 0; qt < NQ; ++qt) {
       l_tot[qt] += __shfl_xor(l_tot[qt], 16);
       l_tot[qt] += __shfl_xor(l_tot[qt], 32);
+      if (active) w.mc[qt] = fmaxf(top[qt] * w.c, kLowestScore);
     }
   }
 
@@ -712,7 +724,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     __syncthreads();
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      float wgt[KS], m = -1e30f, l = 0.f;
+      float wgt[KS], m = kLowestScore, l = 0.f;
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
         wgt[k] = s_shift[k * RG + rwave][qt * 16 + l16];
@@ -869,7 +881,7 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[i][q] = 0.f;
-  float m_row = -1e30f, l_row = 0.f;
+  float m_row = kLowestScore, l_row = 0.f;
   for (int p0 = 0; p0 < np; p0 += kReduceBatch) {
     f32x4 v[kReduceBatch][2][2];
     float m[kReduceBatch], l[kReduceBatch];
