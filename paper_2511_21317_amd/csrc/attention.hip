@@ -71,7 +71,7 @@
 // keys.  Workgroups with KS key groups walk a KS-th of them (64 rows: 4 waves, 4 groups; 128: 8 waves, 4; 256: 8
 // waves, 2): a wave still owns 64 rows, so its products are as dense and read as little LDS as those of the
 // big tile, and the groups meet in LDS at the end - no scratch memory, no second kernel.  The limits are in
-// launch_attention().
+// choose_attention_route().
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -947,11 +947,7 @@ int64_t compute_units() {
   return n;
 }
 
-// 128-row tiles that run at once (three workgroups per CU): a problem with no more of them runs those
-constexpr int64_t kSmallTileRound = 768;
-
 // `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
-// `scratch` (fp32 words, or nullptr): room for the tiles that run in segments (attention_split.hpp).
 template <int NQ, int NW, int KS = 1>
 void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t stream) {
   if (log2_keys)
@@ -973,14 +969,10 @@ HeadRows all_rows(const int64_t* q_off_host, int H) {
   }
   return r;
 }
-int64_t tiles_of(const HeadRows& r, int H, int rows) {
-  int64_t n = 0;
-  for (int h = 0; h < H; ++h) n += (r.count[h] + rows - 1) / rows;
-  return n;
-}
 
+// `route`: the split of a launch of 256-row tiles, if it has one; its partial results go to `scratch`.
 template <int NQ, int NW, int KS = 1>
-hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles = 0, float* scratch = nullptr, int64_t scratch_words = 0) {
+hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles = 0, const AttnRoute* route = nullptr, float* scratch = nullptr) {
   constexpr int BQ = 16 * NQ * (NW / KS);
   int64_t full = 0;
   int ragged = 0;
@@ -1014,30 +1006,21 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
   a.split_m = nullptr;
   a.sp.n_tiles = 0;
   a.sp.slots = 0;
-  if (KS == 1 && BQ == kAttnTileRows && scratch) {
-    int64_t kept_full = full;
-    int split_ragged = 0;
-    int64_t lengths[kAttnMaxHeads + 1] = {0};        // (the plan looks at the heads' lengths only)
-    for (int h = 0; h < H; ++h) lengths[h + 1] = lengths[h] + rows.count[h];
-    plan_attention_split(lengths, k_off_host, H, compute_units(), &a.sp, &kept_full, &split_ragged);
+  if (KS == 1 && BQ == kAttnTileRows && route && route->split.n_tiles > 0) {
+    // the first partial tiles (in head order) and the last full tiles run in segments; the others
+    // keep their order: partial tiles in front of the full tiles
+    a.sp = route->split;
     const int64_t slots = split_slots(a.sp);
-    if (a.sp.n_tiles > 0 && slots * kAttnSlotWords <= scratch_words) {
-      // the first partial tiles (in head order) and the last full tiles run in segments; the others
-      // keep their order: partial tiles in front of the full tiles
-      a.n_full = (int32_t)kept_full;
-      a.full_per_xcd = (int32_t)((kept_full + 7) / 8);
-      a.n_ragged = ragged - split_ragged;
-      a.ragged_per_xcd = (a.n_ragged + 7) / 8;
-      for (int i = 0; i < a.n_ragged; ++i) a.ragged_head[i] = a.ragged_head[split_ragged + i];
-      a.split_per_xcd = (a.sp.shares + 7) / 8;
-      a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd + a.split_per_xcd);
-      a.split_o = scratch;
-      a.split_l = scratch + slots * kAttnTileRows * kDHead;
-      a.split_m = a.split_l + slots * kAttnTileRows;
-    } else {
-      a.sp.n_tiles = 0;
-      a.sp.slots = 0;
-    }
+    a.n_full = (int32_t)route->kept_full;
+    a.full_per_xcd = (a.n_full + 7) / 8;
+    a.n_ragged = ragged - route->split_ragged;
+    a.ragged_per_xcd = (a.n_ragged + 7) / 8;
+    for (int i = 0; i < a.n_ragged; ++i) a.ragged_head[i] = a.ragged_head[route->split_ragged + i];
+    a.split_per_xcd = (a.sp.shares + 7) / 8;
+    a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd + a.split_per_xcd);
+    a.split_o = scratch;
+    a.split_l = scratch + slots * kAttnTileRows * kDHead;
+    a.split_m = a.split_l + slots * kAttnTileRows;
   }
   launch_kernel<NQ, NW, KS>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
   if (a.sp.n_tiles > 0)
@@ -1096,8 +1079,11 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
   a.o2 = (bf16_t*)o2;
-  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0, (float*)scratch,
-                          scratch_bytes / 4);
+  AttnRoute route;
+  plan_attention_split(q_off_host, k_off_host, H, compute_units(), &route.split, &route.kept_full, &route.split_ragged);
+  const bool fits = scratch && split_slots(route.split) * kAttnSlotWords <= scratch_bytes / 4;
+  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0,
+                          fits ? &route : nullptr, (float*)scratch);
 }
 
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,
@@ -1111,56 +1097,35 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
   a.H = H;
-  // Tiles of 256 query rows (two workgroups per CU) are the efficient shape, and with scratch memory
-  // the tiles in excess of a multiple of the CU count run in segments, so that any tile count fills
-  // the chip.
   const HeadRows rows = all_rows(q_off_host, H);
-  const int64_t cus = compute_units(), tiles128 = tiles_of(rows, H, 128);
-  // A problem of at most one 64-row (128-row) tile per CU runs those, the keys cut in four among four (eight)
-  // waves, unless the walk is so short that the meeting costs more (2 us).  16 heads against the 128-row tiles
-  // of one key group: 64 rows 266 x 266 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5, 700 x 700 12.0 : 12.0, 1024 x 1024
-  // 14.0 : 15.4; 128 rows 1400 x 1400 18.1 : 17.2, 2048 x 2048 22.1 : 22.8, 2048 x 8192 63 : 91 (in segments 72; with
-  // four waves and two key groups, one wave a SIMD, 69).
-  int64_t keys = 0;
-  for (int h = 0; h < H; ++h) keys = std::max(keys, k_off_host[h + 1] - k_off_host[h]);
-  if (keys >= 768 && tiles_of(rows, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
-  if (keys >= 2048 && tiles128 <= cus) return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
-  const int64_t need = scratch ? attention_scratch_need(q_off_host, k_off_host, H) : 0;
-  const bool whole_tiles = need == 0 || need > scratch_bytes;
-  // At most one round of 256-row tiles: eight waves and two key groups fill the CU that a lone tile of four
-  // waves does not (3000 x 3000 44 with 128-row tiles -> 41 us, 4096 x 4096 62 -> 59, 4096 x 10000 143 -> 134), and
-  // segments pay only where the round is far from full (192 tiles of 8192 keys: segments 110, so 96).
-  const int64_t tiles256 = tiles_of(rows, H, kAttnTileRows);
-  if (keys >= 2048 && tiles256 <= cus && (whole_tiles || 4 * tiles256 >= 3 * cus))
-    return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
-  if (whole_tiles) {
-    // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in tiles of
-    // 128 (64) rows whose keys are cut in four, if those are one round: a half (quarter) of a round instead
-    // of a whole one.  From two rounds on (a lone tile on a CU has 0.8 of the rate of a pair): 16 heads of 9000
-    // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 495, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
-    HeadRows whole = rows, rest = rows;
-    int64_t full = 0;
-    for (int h = 0; h < H; ++h) full += rows.count[h] / kAttnTileRows;
-    const bool rounds = full >= 2 * cus;
-    int64_t keep = full / cus * cus;
-    for (int h = 0; h < H; ++h) {
-      const int64_t nf = rows.count[h] / kAttnTileRows, n = (nf < keep ? nf : keep) * kAttnTileRows;
-      keep -= n / kAttnTileRows;
-      whole.count[h] = n;
-      rest.first[h] += n;
-      rest.count[h] -= n;
-    }
-    if (rounds && tiles_of(rest, H, 128) <= cus) {
+  const int64_t cus = compute_units();
+  AttnRoute route;
+  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
+  switch (route.tiles) {
+    case AttnTiles::kGroups64: return launch_cfg<4, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups128: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kRounds: {
+      HeadRows whole = rows, rest = rows;
+      int64_t keep = 0;
+      for (int h = 0; h < H; ++h) keep += rows.count[h] / kAttnTileRows;
+      keep = keep / cus * cus;
+      for (int h = 0; h < H; ++h) {
+        const int64_t n = std::min(rows.count[h] / kAttnTileRows, keep);
+        keep -= n;
+        whole.count[h] = n * kAttnTileRows;
+        rest.first[h] += n * kAttnTileRows;
+        rest.count[h] -= n * kAttnTileRows;
+      }
       const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
       if (e != hipSuccess) return e;
-      if (tiles_of(rest, H, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rest, k_off_host, H, stream);
+      if (count_rest_tiles(q_off_host, H, cus, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rest, k_off_host, H, stream);
       return launch_cfg<4, 8, 4>(a, log2_keys, rest, k_off_host, H, stream);
     }
-    // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a
-    // time) runs those: they fill the chip where the big tiles leave a third of it idle.
-    if (tiles128 <= kSmallTileRound) return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kTiles256: break;
   }
-  return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, (float*)scratch, scratch_bytes / 4);
+  return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, &route, (float*)scratch);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------

@@ -209,4 +209,105 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
 // Slots of scratch a plan uses (kAttnSlotWords fp32 words each).
 inline int64_t split_slots(const SplitPlan& p) { return p.n_tiles ? p.slots : 0; }
 
+// What the workgroups of a launch are: see choose_attention_route().
+enum class AttnTiles {
+  kTiles256,    // 256-row tiles; with a split those in excess run in segments
+  kTiles128,
+  kGroups64,    // 64- / 128- / 256-row tiles whose waves share the keys in four / four / two groups
+  kGroups128,
+  kGroups256,
+  kRounds,      // whole rounds of 256-row tiles, then the rest in kGroups64 or kGroups128: two launches
+};
+
+struct AttnRoute {
+  AttnTiles tiles;
+  SplitPlan split;          // kTiles256 only; n_tiles == 0: every tile runs whole
+  int64_t kept_full;        // full tiles that stay whole, and partial tiles that run in segments
+  int32_t split_ragged;
+};
+
+// 128-row tiles that run at once (three workgroups per CU): a problem with no more of them runs those
+constexpr int64_t kSmallTileRound = 768;
+
+inline int64_t count_tiles(const int64_t* q_off, int H, int rows) {
+  int64_t n = 0;
+  for (int h = 0; h < H; ++h) n += (q_off[h + 1] - q_off[h] + rows - 1) / rows;
+  return n;
+}
+
+// Tiles of `rows` (128 or 64) rows that are left of the heads when whole rounds of 256-row tiles, the heads' full
+// ones in head order, have run.
+inline int64_t count_rest_tiles(const int64_t* q_off, int H, int64_t cus, int rows) {
+  int64_t full = 0, n = 0;
+  for (int h = 0; h < H; ++h) full += (q_off[h + 1] - q_off[h]) / kAttnTileRows;
+  int64_t keep = full / cus * cus;
+  for (int h = 0; h < H; ++h) {
+    const int64_t mq = q_off[h + 1] - q_off[h], nf = mq / kAttnTileRows, whole = nf < keep ? nf : keep;
+    keep -= whole;
+    n += (mq - whole * kAttnTileRows + rows - 1) / rows;
+  }
+  return n;
+}
+
+// The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).
+inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words,
+                                   AttnRoute* out) {
+  AttnRoute& r = *out;
+  r.tiles = AttnTiles::kTiles256;
+  plan_attention_split(q_off, k_off, H, cus, &r.split, &r.kept_full, &r.split_ragged);
+  int64_t full = 0, keys = 0;
+  for (int h = 0; h < H; ++h) {
+    full += (q_off[h + 1] - q_off[h]) / kAttnTileRows;
+    if (k_off[h + 1] - k_off[h] > keys) keys = k_off[h + 1] - k_off[h];
+  }
+  auto no_split = [&]() {
+    r.split.n_tiles = r.split.slots = 0;
+    r.kept_full = full;
+    r.split_ragged = 0;
+  };
+  if (split_slots(r.split) * kAttnSlotWords > scratch_words) no_split();
+  // At most one 64-, 128- or 256-row tile per CU: workgroups whose waves share the keys, unless the walk is so short
+  // that the groups' meeting costs more (2 us).  16 heads against the 128-row tiles of one key group: 64 rows
+  // 266 x 266 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5, 700 x 700 12.0 : 12.0, 1024 x 1024 14.0 : 15.4; 128 rows
+  // 1400 x 1400 18.1 : 17.2, 2048 x 2048 22.1 : 22.8, 2048 x 8192 63 : 91; 256 rows 3000 x 3000 41 : 44, 4096 x 4096
+  // 59 : 62, 4096 x 10000 134 : 143.
+  // Such a workgroup walks a quarter (half) of the keys however many CUs are idle; segments cut the walk over
+  // all CUs and cost a second kernel and the traffic of the partial results.  The shorter of the two, in tenths
+  // of a us from both sides' times at 1 to 16 heads of 64 to 4000 rows and 1600 to 28000 keys, groups : segments:
+  // 16 heads 64 x 2500 20.3 : 20.8, x 4000 27.5 : 25.3, 250 x 12000 74 : 38, 500 x 4000 28 : 36, x 6000 41 : 40, 1000 x 6000
+  // 41 : 48, x 9000 59 : 58, x 28000 165 : 123, 2000 x 14000 101 : 124, 3000 x 9000 106 : 120, x 28000 333 : 292; one head
+  // of 1000 x 28000 158 : 39.
+  const int64_t kt = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
+  AttnTiles groups = AttnTiles::kTiles256;
+  int64_t groups_time = 0;
+  if (keys >= 768 && count_tiles(q_off, H, 64) <= cus) {
+    groups = AttnTiles::kGroups64;
+    groups_time = 70 + 14 * ((kt + 3) / 4);
+  } else if (keys >= 2048 && count_tiles(q_off, H, 128) <= cus) {
+    groups = AttnTiles::kGroups128;
+    groups_time = 80 + 16 * ((kt + 3) / 4);
+  } else if (keys >= 2048 && count_tiles(q_off, H, kAttnTileRows) <= cus) {
+    groups = AttnTiles::kGroups256;
+    groups_time = 60 + 15 * ((kt + 1) / 2);
+  }
+  const int64_t split_time = 120 + split_slots(r.split) / 2 + (r.split.shares > cus ? 15 : 9) * (int64_t)r.split.share_units;
+  if (groups != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups_time <= split_time)) {
+    no_split();
+    r.tiles = groups;
+    return;
+  }
+  if (r.split.n_tiles > 0) return;
+  // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in tiles of
+  // 128 (64) rows whose keys are cut in four, if those are one round: a half (quarter) of a round instead
+  // of a whole one.  From two rounds on (a lone tile on a CU has 0.8 of the rate of a pair): 16 heads of 9000
+  // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 495, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
+  if (full >= 2 * cus && count_rest_tiles(q_off, H, cus, 128) <= cus) {
+    r.tiles = AttnTiles::kRounds;
+    return;
+  }
+  // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a
+  // time) runs those: they fill the chip where the big tiles leave a third of it idle.
+  if (count_tiles(q_off, H, 128) <= kSmallTileRound) r.tiles = AttnTiles::kTiles128;
+}
+
 }  // namespace httm
