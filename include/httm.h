@@ -266,10 +266,11 @@ HTTM_API int httm_attention_log2(const void* q_m, const void* k_log2, const void
  * launch ends when its last workgroup ends, and a compute unit runs whole 256-row query tiles: T
  * tiles on C compute units take ceil(T / C) tile times.  With scratch, the T mod C tiles in excess
  * of a multiple of C - the partial last tiles of the heads first, then full tiles from the end - are
- * not run whole: their work is cut into equal shares over the keys, one or two per compute unit,
- * that run behind the whole tiles, and a second kernel adds the pieces of every tile up (in key
- * order: run-to-run identical), so that any tile count fills the chip.  Launches too short for the
- * split to pay (it costs about 15 us) run as without scratch.  The results agree with
+ * not run whole: their work is cut into equal shares over the keys, one per compute unit (two where
+ * a share would have more than 15360 keys), that run behind the whole tiles, and a second kernel adds the
+ * pieces of every tile up (in key order: run-to-run identical), so that any tile count fills the chip.
+ * Launches for which that does not pay run as without scratch: short ones, and ones of at most one tile per
+ * compute unit whose workgroups are done sooner with the keys shared among their own waves.  The results agree with
  * httm_attention_log2 to fp32 rounding of the sums.  httm_layer_forward does the same with the
  * attn_split region of its workspace.
  * httm_attention_scratch is httm_attention with the same scratch and the same rule; there every
@@ -284,8 +285,8 @@ HTTM_API int httm_attention_scratch(const void* q_m, const void* k_m, const void
                                     float scale, void* scratch, int64_t scratch_bytes, void* stream);
 
 /* Host only (no GPU needed): how stage 3 with scratch cuts a launch with these head lengths on a
- * device of `compute_units` compute units - the very functions the kernels evaluate; for tests and
- * diagnostics.  HOST arrays:
+ * device of `compute_units` compute units - the very functions the launch and the kernels evaluate; for tests
+ * and diagnostics.  A launch that would not be cut has no tiles in pieces.  HOST arrays:
  *   summary[8]  : tiles that run in pieces (0: none), shares, key tiles (of 64 keys) per share,
  *                 most tiles a share touches, slots of scratch (256 rows x 66 fp32 each), key tiles of
  *                 all split tiles together, full tiles that stay whole, partial tiles that are split

@@ -466,10 +466,9 @@ int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets
   if (H > HTTM_MAX_HEADS) return HTTM_E_UNSUPPORTED;
   for (int h = 0; h < H; ++h)
     if (q_offsets[h + 1] < q_offsets[h] || k_offsets[h + 1] < k_offsets[h]) return HTTM_E_INVALID_ARG;
-  SplitPlan sp;
-  int64_t kept_full = 0;
-  int split_ragged = 0;
-  plan_attention_split(q_offsets, k_offsets, H, compute_units, &sp, &kept_full, &split_ragged);
+  AttnRoute route;
+  choose_attention_route(q_offsets, k_offsets, H, compute_units, INT64_MAX, &route);
+  const SplitPlan& sp = route.split;
   const int64_t n_slots = split_slots(sp);
   summary[0] = sp.n_tiles;
   summary[1] = sp.shares;
@@ -477,8 +476,8 @@ int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets
   summary[3] = sp.span;
   summary[4] = (int32_t)n_slots;
   summary[5] = sp.units;
-  summary[6] = (int32_t)kept_full;
-  summary[7] = split_ragged;
+  summary[6] = (int32_t)route.kept_full;
+  summary[7] = route.split_ragged;
   if (segments) {
     if (max_segments < n_slots) return HTTM_E_WORKSPACE_TOO_SMALL;
     for (int64_t b = 0; b < n_slots; ++b) {

@@ -1031,11 +1031,9 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
 }  // namespace
 
 int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_host, int H) {
-  SplitPlan sp;
-  int64_t kept_full = 0;
-  int split_ragged = 0;
-  plan_attention_split(q_off_host, k_off_host, H, compute_units(), &sp, &kept_full, &split_ragged);
-  return split_slots(sp) * kAttnSlotWords * 4;
+  AttnRoute route;
+  choose_attention_route(q_off_host, k_off_host, H, compute_units(), INT64_MAX, &route);
+  return split_slots(route.split) * kAttnSlotWords * 4;
 }
 
 hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o,

@@ -261,7 +261,7 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
     if (k_off[h + 1] - k_off[h] > keys) keys = k_off[h + 1] - k_off[h];
   }
   auto no_split = [&]() {
-    r.split.n_tiles = r.split.slots = 0;
+    r.split.n_tiles = r.split.n_groups = r.split.units = r.split.share_units = r.split.shares = r.split.span = r.split.slots = 0;
     r.kept_full = full;
     r.split_ragged = 0;
   };

@@ -122,3 +122,15 @@ def test_split_is_taken_where_it_pays_and_only_there():
     assert _check_plan([256 * 31] * 16, [32768] * 16, 256)["n_tiles"] == 240   # 496 tiles: 240 in excess, long keys
     assert _check_plan([256 * 31] * 16, [8192] * 16, 256)["n_tiles"] == 0      # the same with shorter keys: no gain
     assert _check_plan([300] * 4, [100] * 4, 256)["n_tiles"] == 0              # fewer than 512 keys
+
+
+# heads, rows, keys of launches of at most one 64-, 128- or 256-row tile per CU, and whether they run in segments
+# (against many keys) or in key groups, which have no pieces to report
+@pytest.mark.parametrize("H,mq,mk,segments", [(16, 64, 2500, False), (16, 64, 6000, True), (8, 250, 12000, True), (1, 1000, 100000, True),
+                                              (16, 2000, 8192, False), (16, 2000, 28000, False), (16, 3000, 12000, False),
+                                              (16, 3000, 28000, True), (1, 128 * 256, 40000, False)])
+def test_plans_of_few_rows_say_what_the_launch_does(H, mq, mk, segments):
+    p = _check_plan([mq] * H, [mk] * H, 256)
+    assert (p["n_tiles"] > 0) == segments
+    if not segments:
+        assert p["shares"] == p["share_units"] == p["span"] == p["units"] == 0

@@ -45,3 +45,22 @@ def test_few_rows_take_segments_against_many_keys_only(H, mq, mk, segments, log2
         rows = np.unique(np.concatenate([np.arange(0, lens_q[h], max(1, lens_q[h] // 60)), np.arange(max(0, lens_q[h] - 20), lens_q[h])]))
         want = orc.attention(qf[qo[h]:qo[h + 1]], kf[ko[h]:ko[h + 1]], vf[ko[h]:ko[h + 1]], rows=rows)
         check_output(got[qo[h]:qo[h + 1]][rows], want, f"head {h}")
+
+
+def test_the_static_entry_point_takes_a_launch_in_key_groups_whatever_its_segments_would_need():
+    """128 tiles of 256 rows against 40000 keys: segments would need 41 MiB of partial results, more than the library's
+    array holds, but the launch runs in key groups and needs none."""
+    require_gpu()
+    mq, mk = 128 * 256, 40000
+    gen = torch.Generator().manual_seed(8800)
+    q, k, v = (torch.randn((n, 64), generator=gen) for n in (mq, mk, mk))
+    scale = np.float32(httm.LOG2_KEY_SCALE)
+    qm, km, vm = (t.to(torch.bfloat16).cuda() for t in (q, k * float(scale), v))
+    got, want = torch.full_like(qm, float("nan")), torch.full_like(qm, float("nan"))
+    httm.attention_log2_static(qm, km, vm, got, [0, mq], [0, mk])
+    scratch = torch.full((httm.attention_scratch_bytes(1),), 0xFF, dtype=torch.uint8, device="cuda")
+    httm.attention_log2(qm, km, vm, want, [0, mq], [0, mk], scratch=scratch)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and bool((scratch == 0xFF).all())
+    rows = np.arange(0, mq, 613)
+    check_output(f32(got)[rows], orc.attention(f32(qm), f32(km) / scale, f32(vm), rows=rows), "static, key groups")
