@@ -52,14 +52,14 @@
 // merged keys multiplied by scale * log2(e) ("log2 keys": the factor goes into the fp32 mean before its
 // one rounding to bf16, so nothing is rounded twice), the raw MFMA scores are the base-2 logits and the
 // kernel (SHIFT = false) uses the weights exp2(s) as they are.  With any other keys (SHIFT = true) it
-// takes one fma per score, scale and shift, with m the row's exact maximum over the first 32 keys, left
-// alone from there on.  Neither looks at the sums inside the loop: the row sums come from the matrix
-// cores (row_sum_operand()), and a tile is checked once, at its end.  If a row's sum is outside
-// [2^-64, 2^64] (or inf / NaN), the workgroup takes the tile again with running maxima
-// (running_max_step(): the classic online softmax, not pipelined).  Measured against a guard inside the
-// loop for plain keys (a dot2 against ones and a compare per score pair) and a second launch that redid
-// marked tiles for log2 keys:
-// 16 ragged heads of 5500 x 9000 plain keys 219 -> 201 us, two 16 x 16 frames 27.3 -> 24.3 us a layer.
+// takes one fma per score, scale and shift, with m the row's exact maximum over the first 32 keys until a step's
+// weights outgrow it (guard_step()).  The row sums come from the matrix cores (row_sum_operand()).  A tile without
+// shifts is checked once, at its end: if a row's sum is outside [2^-64, 2^64] (or inf / NaN), the workgroup takes
+// the tile again with running maxima (running_max_step(): the classic online softmax, not pipelined).  The same
+// check behind the shifts finds what they cannot hold (logits beyond 2^30, NaN next to a number).
+// Measured against a guard that sums on the vector ALU (a dot2 against ones and a compare per score pair) and, for
+// log2 keys, a second launch that redid marked tiles: 16 ragged heads of 5500 x 9000 plain keys 219 -> 205 us, two
+// 16 x 16 frames 27.3 -> 24.3 us a layer.
 //
 // End of a launch.  A CU runs its 256-row tiles two at a time, but one alone at 0.8 of the rate of two,
 // so the launch time follows the largest number of whole tiles a CU gets.  When the caller has given
@@ -147,7 +147,7 @@ struct WaveState {
   f32x4 o_acc[4][NQ];    // O^T accumulators, [16 channels][query tile]
   f32x4 s_cur[2][NQ];    // raw scores of the current step, [16 keys][query tile]
   u32x8 p_old[NQ / 2];   // bf16 P^T of the previous step, two query tiles each: two 16x16x32 B operands, one 16x16x64 one
-  float mc[NQ];          // shift m in log2 units
+  float nm[NQ];          // minus the shift m, in log2 units
   float c;               // factor from raw scores to log2 units (kernel with per-row shifts only)
   f32x4 l_acc[NQ / 2];   // row sums, from the matrix cores: see row_sum_operand()
   bf16x8 ones_a;         // A operand and index operand of the row sums
@@ -159,29 +159,52 @@ struct WaveState {
 // 16x16x32 takes 32 (18 against 16 cycles in a register-only loop), and the two k of every four that a row
 // of A drops are taken by another row.  Its B operand are the eight P^T registers of two query tiles
 // (query l%16 of both): the first tile's values are the k below 32 and the second one's the others,
-// which are multiplied by lanes 0..31 and lanes 32..63 of A.  So rows 0 and 1 of A hold ones in lanes below
-// 32 and rows 2 and 3 in the others; rows 0 and 2 keep the k 0, 1 of every four (index 0x4), rows 1 and 3
-// the k 2, 3 (0xE).  D[0][n] + D[1][n] is the sum of query n of the first tile, D[2][n] + D[3][n] that of
-// the second: registers 0..3 of lanes 0..15.  A step's 32 products take 512 matrix-core cycles; its
+// which are multiplied by lanes 0..31 and lanes 32..63 of A.  So rows 0 and 4 of A hold ones in lanes below
+// 32 and rows 8 and 12 in the others; rows 0 and 8 keep the k 0, 1 of every four (index 0x4), rows 4 and 12
+// the k 2, 3 (0xE).  D[0][n] + D[4][n] is the sum of query n of the first tile, D[8][n] + D[12][n] that of
+// the second: register 0 of the four lane groups (row_sums()), so that one comparison per pair looks at
+// every row.  A step's 32 products take 512 matrix-core cycles; its
 // row sums take 36 instead of the 64 of four dense 16x16x32.  Stage 3 is bound by those cycles and the
 // power they draw: 16 heads x 16384 x 16384 878 -> 860 us.
 __device__ __forceinline__ bf16x8 row_sum_operand(int lane) {
   const int m = lane & 15;
-  const uint32_t w = m < 4 && (m >> 1) == (lane >> 5) ? 0x3F803F80u : 0u;
+  const uint32_t w = (m & 3) == 0 && (m >> 3) == (lane >> 5) ? 0x3F803F80u : 0u;
   return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
 }
-__device__ __forceinline__ int row_sum_index(int lane) { return (lane & 1) ? (int)0xEEEEEEEEu : 0x44444444; }
+__device__ __forceinline__ int row_sum_index(int lane) { return (lane & 4) ? (int)0xEEEEEEEEu : 0x44444444; }
+// Exchange between neighbouring lane groups of 16 (halves of the wave): both lanes of a pair receive {x of the lower
+// one, x of the upper one}.
+struct LanePair {
+  float a, b;
+};
+__device__ __forceinline__ LanePair swap16(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return {__uint_as_float(lo), __uint_as_float(hi)};
+}
+__device__ __forceinline__ LanePair swap32(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return {__uint_as_float(lo), __uint_as_float(hi)};
+}
+// The sums of query column l16 of a pair's two query tiles from its register 0, in all lanes.
+__device__ __forceinline__ LanePair row_sums(float l0) {
+  const LanePair h = swap16(l0);
+  return swap32(h.a + h.b);
+}
 
 // exp2(s*c - m) (SHIFT) or exp2(s) of a step's 8 scores of one query column, packed to bf16: one half of
 // a pair's P^T operand.
 template <bool SHIFT>
-__device__ __forceinline__ void exp_pack(const f32x4& s0, const f32x4& s1, float c, float m, u32x8& p, int half) {
+__device__ __forceinline__ void exp_pack(const f32x4& s0, const f32x4& s1, float c, float nm, u32x8& p, int half) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const f32x4& s = e < 2 ? s0 : s1;
     const float x0 = s[2 * (e & 1)], x1 = s[2 * (e & 1) + 1];
-    const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x0, c, -m) : x0);
-    const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x1, c, -m) : x1);
+    const float p0 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x0, c, nm) : x0);
+    const float p1 = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x1, c, nm) : x1);
     p[4 * half + e] = pack_bf16x2(p0, p1);
   }
 }
@@ -189,8 +212,20 @@ __device__ __forceinline__ void exp_pack(const f32x4& s0, const f32x4& s1, float
 // The largest score of a query column among the 32 keys of a step (all four lane groups).
 __device__ __forceinline__ float step_max(const f32x4& s0, const f32x4& s1) {
   float t = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
-  t = fmaxf(t, __shfl_xor(t, 16));
-  return fmaxf(t, __shfl_xor(t, 32));
+  LanePair o = swap16(t);
+  o = swap32(fmaxf(o.a, o.b));
+  return fmaxf(o.a, o.b);
+}
+
+// Sums of weights a step may leave behind (of the keys one lane group adds up); beyond it the shift is raised, in
+// rows with a score 55 above it or with a sum before the step beyond kGuardGrown (one of which holds then).
+constexpr float kGuardSum = 1.152921504606846976e18f;    // 2^60
+constexpr float kGuardGrown = 2.88230376151711744e17f;   // 2^58
+constexpr float kLowestScore = -3.402823466e38f;         // no finite score is below: the shift of sums without a key
+
+template <int NQ>
+__device__ __forceinline__ void add_row_sums(WaveState<NQ>& w, const u32x8& p, int i) {
+  w.l_acc[i] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(w.ones_a, __builtin_bit_cast(bf16x16, p), w.l_acc[i], w.ones_idx, 0, 0);
 }
 
 // MFMA A operands of one step: 4 K fragments (16 key rows x 32 channels, [key tile * 2 + channel half]) and
@@ -238,15 +273,73 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Per-row shifts: the weights of a step are added to the row sums before they are multiplied with V, and a step that
+// brings a sum beyond kGuardSum (or to inf or NaN) is taken back here; `before` are the sums without it.  A row
+// with a score far above its shift takes that score for the shift, one whose sum has grown over many keys moves
+// it by 58; sums and accumulators follow, and the weights are taken again, from scores computed again with
+// the 32 rows of K at `kv_first` in memory: held to the end of the step they need 32 registers too many (100 to
+// 400 spilled).  One comparison per pair of query tiles and step.  16 ragged heads of 5500 x 9000 keys: 201 us without
+// the guard, where a row that leaves the range costs its tile another 1.8 passes (last key 60 above the
+// rest 777 us), 205 with it (300), 219 with sums and guard on the vector ALU (319; the latter at 9000 x 9000).
+template <int NQ>
+__device__ __forceinline__ void guard_step(WaveState<NQ>& w, u32x8 (&p)[NQ / 2], const float (&before)[NQ / 2], const char* kg,
+                                           int kv_first, int Mk, int lane) {
+  bool out = false;
+#pragma unroll
+  for (int i = 0; i < NQ / 2; ++i) out = out || !(w.l_acc[i][0] <= kGuardSum);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(out) == 0, 1)) return;
+  asm volatile("" : "+v"(lane));      // (nothing of the addresses below is to live in registers outside)
+  const int l16 = lane & 15, grp = lane >> 4;
+  bf16x8 ak[4];
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int row = kv_first + kt * 16 + l16;
+      ak[kt * 2 + ks] = *(const bf16x8*)(kg + (uint32_t)((row < Mk ? row : Mk - 1) * kRowBytes + (ks * 4 + grp) * 16));
+    }
+#pragma unroll
+  for (int i = 0; i < NQ / 2; ++i) {
+    float sc[2];
+    const LanePair sum = row_sums(before[i]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int qt = 2 * i + j;
+      f32x4 s[2];
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        s[kt] = mfma16(ak[kt * 2], w.qf[qt][0], f32x4{0.f, 0.f, 0.f, 0.f});
+        s[kt] = mfma16(ak[kt * 2 + 1], w.qf[qt][1], s[kt]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kv_first + 16 * kt + 4 * grp + r >= Mk) s[kt][r] = -INFINITY;
+      }
+      const float top = step_max(s[0], s[1]);
+      const float grown = (j ? sum.b : sum.a) > kGuardGrown ? 58.f : 0.f;
+      const float nm = fmaf(top, w.c, w.nm[qt]) > 55.f ? -(top * w.c) : w.nm[qt] - grown;
+      sc[j] = __builtin_amdgcn_exp2f(nm - w.nm[qt]);
+      w.nm[qt] = nm;
+      // (as a vector: from single elements the compiler builds the accumulators anew, in other registers)
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = w.o_acc[ct][qt] * f32x4{sc[j], sc[j], sc[j], sc[j]};
+      exp_pack<true>(s[0], s[1], w.c, w.nm[qt], p[i], j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    w.l_acc[i] = f32x4{before[i] * (grp >= 2 ? sc[1] : sc[0]), 0.f, 0.f, 0.f};
+    add_row_sums(w, p[i], i);
+  }
+}
+
 // One pipeline step of a wave outside the steady state (first tile, last tile, drain); the order of
 // issue is the compiler's.
 //   DO_QK : scores of the NEXT step from the 32 K rows at `sk`           -> becomes s_cur
 //   DO_PV : O^T += V^T P^T of the PREVIOUS step, V rows at `svt`
-//   DO_SM : softmax of the CURRENT step (s_cur -> p_old); its first key is `kv_first`
+//   DO_SM : softmax of the CURRENT step (s_cur -> p_old); its first key is `kv_first` (row of `kg`, K in memory)
 //   MASK  : keys >= Mk get weight 0;  FIRST : this is step 0 and fixes m
 template <int NQ, bool SHIFT, bool DO_QK, bool DO_PV, bool DO_SM, bool MASK, bool FIRST>
-__device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk, const bf16_t* svt,
-                                              int kv_first, int Mk, int l16, int grp) {
+__device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk, const bf16_t* svt, const char* kg,
+                                              int kv_first, int Mk, int lane) {
+  const int l16 = lane & 15, grp = lane >> 4;
   StepOperands op;
   f32x4 s_next[2][NQ];
   if (DO_QK) {
@@ -266,10 +359,10 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt)
         w.o_acc[ct][qt] = mfma16(op.av[ct], p_half(w.p_old[qt >> 1], qt & 1), w.o_acc[ct][qt]);
+    if (!SHIFT) {
 #pragma unroll
-    for (int i = 0; i < NQ / 2; ++i)
-      w.l_acc[i] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[i]), w.l_acc[i], w.ones_idx, 0, 0);
+      for (int i = 0; i < NQ / 2; ++i) add_row_sums(w, w.p_old[i], i);
+    }
   }
   if (DO_SM) {
     // s_cur[kt][qt][r]: key kv_first + 16*kt + 4*grp + r, query column l16 of tile qt
@@ -287,8 +380,17 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
     }
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      if (SHIFT && FIRST) w.mc[qt] = step_max(w.s_cur[0][qt], w.s_cur[1][qt]) * w.c;
-      exp_pack<SHIFT>(w.s_cur[0][qt], w.s_cur[1][qt], w.c, w.mc[qt], w.p_old[qt >> 1], qt & 1);
+      if (SHIFT && FIRST) w.nm[qt] = -fmaxf(step_max(w.s_cur[0][qt], w.s_cur[1][qt]) * w.c, kLowestScore);
+      exp_pack<SHIFT>(w.s_cur[0][qt], w.s_cur[1][qt], w.c, w.nm[qt], w.p_old[qt >> 1], qt & 1);
+    }
+    if (SHIFT) {
+      float before[NQ / 2];
+#pragma unroll
+      for (int i = 0; i < NQ / 2; ++i) {
+        before[i] = w.l_acc[i][0];
+        add_row_sums(w, w.p_old[i], i);
+      }
+      guard_step(w, w.p_old, before, kg, kv_first, Mk, lane);
     }
   }
   if (DO_QK) {
@@ -309,7 +411,9 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
 // every LDS read wait for all requests issued before it in program order.
 template <int NQ, bool SHIFT, bool PREFETCH, typename Between>
 __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, const bf16_t* sk_next,
-                                            const bf16_t* sv_next, int l16, int grp, Between between) {
+                                            const bf16_t* sv_next, const char* kg, int kv_first, int Mk, int lane,
+                                            Between between) {
+  const int l16 = lane & 15, grp = lane >> 4;
   // 8 * NQ groups: 4 * NQ products of each kind, every group with one of the 8 * NQ scores of the lane
   constexpr int NG = 8 * NQ;
   f32x4 s_next[2][NQ];
@@ -319,7 +423,7 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
     // (the empty asm after a result only pins where the instruction is issued)
     const int qt = g >> 3;
     const float x = w.s_cur[(g >> 2) & 1][qt][g & 3];
-    ex[g] = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x, w.c, -w.mc[qt]) : x);
+    ex[g] = __builtin_amdgcn_exp2f(SHIFT ? fmaf(x, w.c, w.nm[qt]) : x);
     asm volatile("" : "+v"(ex[g]));
   };
   auto pack = [&](int p) {   // values 2p, 2p + 1
@@ -327,14 +431,16 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
     asm volatile("" : "+v"(r));
     p_new[p >> 3][p & 7] = r;
   };
+  float before[NQ / 2];
+  auto sums = [&](int i) {   // per-row shifts: the new weights of a pair, complete now
+    before[i] = w.l_acc[i][0];
+    add_row_sums(w, p_new[i], i);
+  };
   auto group_end = [&](int g) {
     soft(g);
     if (g >= 2 && (g & 1) == 0) pack((g >> 1) - 1);
-    if ((g & 15) == 7) {
-      const int i = g >> 4;
-      w.l_acc[i] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-          w.ones_a, __builtin_bit_cast(bf16x16, w.p_old[i]), w.l_acc[i], w.ones_idx, 0, 0);
-    }
+    if (!SHIFT && (g & 15) == 7) add_row_sums(w, w.p_old[g >> 4], g >> 4);
+    if (SHIFT && g >= 16 && (g & 15) == 0) sums(g / 16 - 1);
     __builtin_amdgcn_sched_barrier(0);
   };
   // PV of step t-1 first: the V operands retire and their successors are requested ...
@@ -356,6 +462,10 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
     group_end(g);
   }
   pack(NG / 2 - 1);
+  if (SHIFT) {
+    sums(NQ / 2 - 1);
+    guard_step(w, p_new, before, kg, kv_first, Mk, lane);
+  }
   if (PREFETCH) load_k_operands(op, sk_next, l16, grp);
   __builtin_amdgcn_sched_barrier(0);
   between();        // requests that must follow the step's last LDS read in program order
@@ -374,9 +484,6 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
 // unnormalised products with V stay finite for |v| below 1e19.
 constexpr float kFastSumMin = 5.421010862427522e-20f;    // 2^-64
 constexpr float kFastSumMax = 1.8446744073709552e19f;    // 2^64
-
-// A maximum no finite score is below: where the running maxima start, and the shift of sums without a key.
-constexpr float kLowestScore = -3.402823466e38f;
 
 // One step of 32 keys with a running maximum per row (the classic online softmax), for tiles whose
 // rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.  The maxima are kept in
@@ -502,7 +609,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     const bf16_t* p = q_rows + (q_base + row) * kDHead + grp * 8;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) w.qf[qt][ks] = *(const bf16x8*)(p + ks * 32);
-    w.mc[qt] = 0.f;
+    w.nm[qt] = 0.f;
     w.l_acc[qt >> 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -562,31 +669,13 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
   __syncthreads();
   if (active) {
-    pipeline_step<NQ, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, 0, Mk, l16, grp);
-  }
-  if constexpr (SHIFT && KS > 1) {
-    // the shifts of a row are those of the kernel without key groups: from the first 32 keys of the head
-    if (key_group == 0 && active) {
-#pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-          if (16 * (r >> 2) + 4 * grp + (r & 3) >= Mk) w.s_cur[r >> 2][qt][r & 3] = -INFINITY;
-        const float m = step_max(w.s_cur[0][qt], w.s_cur[1][qt]) * w.c;
-        if (grp == 0) s_shift[rwave][qt * 16 + l16] = m;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) w.mc[qt] = active ? s_shift[rwave][qt * 16 + l16] : 0.f;
+    pipeline_step<NQ, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, kg, 0, Mk, lane);
   }
   if (active) {
     if (n_tiles > 1)
-      pipeline_step<NQ, SHIFT, true, false, true, false, KS == 1>(w, &s_k[0][kStep * kDHead], nullptr, 0,
-                                                        Mk, l16, grp);
+      pipeline_step<NQ, SHIFT, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
     else
-      pipeline_step<NQ, SHIFT, true, false, true, true, KS == 1>(w, &s_k[0][kStep * kDHead], nullptr, 0,
-                                                       Mk, l16, grp);
+      pipeline_step<NQ, SHIFT, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
   }
   __syncthreads();
 
@@ -610,8 +699,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     // an LDS read on the path of an active wave, the compiler would wait for it before the read)
     load_k_operands(op, kb, l16, grp);
     load_v_operands(op, vb, l16, grp);
-    steady_step<NQ, SHIFT, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, l16, grp, request);
-    steady_step<NQ, SHIFT, false>(w, op, nullptr, nullptr, l16, grp, [] {});
+    steady_step<NQ, SHIFT, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, kg, (2 * jt - 1) * kStep, Mk, lane, request);
+    steady_step<NQ, SHIFT, false>(w, op, nullptr, nullptr, kg, 2 * jt * kStep, Mk, lane, [] {});
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): K tile jt+1 and V tile jt are in LDS
     __syncthreads();
   };
@@ -640,9 +729,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     const bf16_t* kb = &s_k[j & 1][0];
     const bf16_t* vb = &s_v[(j - 1) & 1][0];
     if (active) {
-      pipeline_step<NQ, SHIFT, true, true, true, false, false>(w, kb, vb, 0, Mk, l16, grp);
-      pipeline_step<NQ, SHIFT, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead,
-                                                       2 * j * kStep, Mk, l16, grp);
+      pipeline_step<NQ, SHIFT, true, true, true, false, false>(w, kb, vb, kg, (2 * j - 1) * kStep, Mk, lane);
+      pipeline_step<NQ, SHIFT, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead, kg, 2 * j * kStep, Mk, lane);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the last V tile is in LDS
     __syncthreads();
@@ -651,23 +739,21 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   // ---- j = n_tiles: drain ---------------------------------------------------------------------------
   if (active) {
     const bf16_t* vb = &s_v[(n_tiles - 1) & 1][0];
-    pipeline_step<NQ, SHIFT, false, true, true, true, false>(w, nullptr, vb, (2 * n_tiles - 1) * kStep, Mk,
-                                                      l16, grp);
-    pipeline_step<NQ, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, 0, Mk, l16, grp);
+    pipeline_step<NQ, SHIFT, false, true, true, true, false>(w, nullptr, vb, kg, (2 * n_tiles - 1) * kStep, Mk, lane);
+    pipeline_step<NQ, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, kg, 0, Mk, lane);
   }
   }
-  // a group of n tiles has met n + 1 barriers, one more for shifts (none if it has no tile): the others of
-  // its workgroup wait
+  // a group of n tiles has met n + 1 barriers (none if it has no tile): the others of its workgroup wait
   if constexpr (KS > 1)
-    for (int b = n_tiles ? n_tiles : -1 - SHIFT; b < max_tiles; ++b) __syncthreads();
+    for (int b = n_tiles ? n_tiles : -1; b < max_tiles; ++b) __syncthreads();
 
   float l_tot[NQ];
   bool bad = false;
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
-    const f32x4& l = w.l_acc[qt >> 1];
-    l_tot[qt] = __shfl(qt & 1 ? l[2] + l[3] : l[0] + l[1], l16);
-    if (KS > 1 && n_tiles == 0) w.mc[qt] = kLowestScore;      // (no keys, no say in the common shift)
+    const LanePair sums = row_sums(w.l_acc[qt >> 1][0]);
+    l_tot[qt] = qt & 1 ? sums.b : sums.a;
+    if (KS > 1 && n_tiles == 0) w.nm[qt] = -kLowestScore;      // (no keys, no say in the common shift)
     bad = bad || (n_tiles > 0 && !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax));
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
@@ -701,9 +787,9 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     }
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      l_tot[qt] += __shfl_xor(l_tot[qt], 16);
-      l_tot[qt] += __shfl_xor(l_tot[qt], 32);
-      if (active) w.mc[qt] = fmaxf(top[qt] * w.c, kLowestScore);
+      const LanePair l1 = swap16(l_tot[qt]), l2 = swap32(l1.a + l1.b);
+      l_tot[qt] = l2.a + l2.b;
+      if (active) w.nm[qt] = -fmaxf(top[qt] * w.c, kLowestScore);
     }
   }
 
@@ -718,7 +804,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       for (int ct = 0; ct < 4; ++ct) s_acc[((wave * 4 + ct) * NQ + qt) * 64 + lane] = w.o_acc[ct][qt];
       if (grp == 0) {
         s_sum[wave][qt * 16 + l16] = l_tot[qt];
-        s_shift[wave][qt * 16 + l16] = w.mc[qt];
+        s_shift[wave][qt * 16 + l16] = -w.nm[qt];
       }
     }
     __syncthreads();
@@ -771,7 +857,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
           for (int ct = 0; ct < 4; ++ct) *(f32x4*)(po + (4 * ct + grp) * (BQ * 4)) = w.o_acc[ct][qt];
           if (grp == 0) {
             a.split_l[piece_row0 + (row - q0)] = l_tot[qt];
-            a.split_m[piece_row0 + (row - q0)] = w.mc[qt];
+            a.split_m[piece_row0 + (row - q0)] = -w.nm[qt];
           }
         }
       }
