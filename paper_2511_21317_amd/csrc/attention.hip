@@ -434,6 +434,7 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
   float before[NQ / 2];
   auto sums = [&](int i) {   // per-row shifts: the new weights of a pair, complete now
     before[i] = w.l_acc[i][0];
+    asm volatile("" : "+v"(before[i]));      // (this register, not a copy of all four)
     add_row_sums(w, p_new[i], i);
   };
   auto group_end = [&](int g) {
