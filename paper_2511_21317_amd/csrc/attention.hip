@@ -592,6 +592,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   }
 
   int max_tiles = 0;                              // of any key group (KS > 1)
+  __shared__ int s_again;                         // a wave has rows out of range
   __shared__ float s_sum[KS == 1 ? 1 : NW][NQ * 16], s_shift[KS == 1 ? 1 : NW][NQ * 16];
   if constexpr (KS > 1) {
     const int all = (Mk + kKvTile - 1) / kKvTile;
@@ -667,6 +668,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   load_k(0, 0);
   load_v(0, 0);
   if (n_tiles > 1) load_k(kKvTile, 1);
+  if (tid == 0) s_again = 0;            // (the first key group always has a tile)
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
   __syncthreads();
   if (active) {
@@ -758,8 +760,11 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     bad = bad || (n_tiles > 0 && !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax));
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
-  // stages its tiles together) takes the tile again with running maxima.
-  if (__syncthreads_or(active && bad)) {
+  // stages its tiles together) takes the tile again with running maxima.  (One flag and one barrier:
+  // __syncthreads_or() takes three, 0.3 us of an 8 us launch.)
+  if (active && bad) s_again = 1;
+  __syncthreads();
+  if (s_again) {
     float top[NQ];
     if (active) {
 #pragma unroll
