@@ -55,7 +55,9 @@
 // takes one fma per score, scale and shift, with m the row's exact maximum over the first 32 keys until a step's
 // weights outgrow it (guard_step()).  The row sums come from the matrix cores (row_sum_operand()).  A tile without
 // shifts is checked once, at its end: if a row's sum is outside [2^-64, 2^64] (or inf / NaN), the workgroup takes
-// the tile again with running maxima (running_max_step(): the classic online softmax, not pipelined).  The same
+// the tile again with running maxima (running_max_step(): the classic online softmax, not pipelined).  A key group's
+// or piece's own sum may be smaller (half of the keys masked: 16 x 2048 x 8192 179 -> 62 us) if the row's is not: the
+// groups are checked together, a piece looks at a few key tiles of the others (rest_holds).  The same
 // check behind the shifts finds what they cannot hold (logits beyond 2^30, NaN next to a number).
 // Measured against a guard that sums on the vector ALU (a dot2 against ones and a compare per score pair) and, for
 // log2 keys, a second launch that redid marked tiles: 16 ragged heads of 5500 x 9000 plain keys 219 -> 205 us, two
@@ -592,11 +594,12 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   }
 
   int max_tiles = 0;                              // of any key group (KS > 1)
-  __shared__ int s_again;                         // a wave has rows out of range
+  __shared__ int s_again, s_high;                 // a wave has rows out of range, above it
   __shared__ float s_sum[KS == 1 ? 1 : NW][NQ * 16], s_shift[KS == 1 ? 1 : NW][NQ * 16];
+  const int all = (Mk + kKvTile - 1) / kKvTile;
+  auto key_tiles = [&](int g) { return (g * all + KS - 1) / KS; };      // of the groups before group g
   if constexpr (KS > 1) {
-    const int all = (Mk + kKvTile - 1) / kKvTile;
-    const int t0 = (key_group * all + KS - 1) / KS, t1 = ((key_group + 1) * all + KS - 1) / KS;   // (never none for the first)
+    const int t0 = key_tiles(key_group), t1 = key_tiles(key_group + 1);   // (never none for the first)
     max_tiles = (all + KS - 1) / KS;
     k_base += (int64_t)t0 * kKvTile;
     Mk = (t1 * kKvTile < Mk ? t1 * kKvTile : Mk) - t0 * kKvTile;   // 0 for a group without a key tile
@@ -623,20 +626,20 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   // K: straight from global memory into LDS, no registers.  Lane l of a wave instruction fills
   // bytes [16 l, 16 l + 16) of a 1 KB block = rows 8*blk .. 8*blk+7; it fetches the chunk that
   // belongs at its position under the swizzle.
-  auto load_k = [&](int kv0, int buf, bool inside = false) {   // inside: the whole tile lies below Mk
+  auto load_rows = [&](const char* rows, int kv0, int n, bf16_t* buf, bool inside = false) {   // inside: the whole tile lies below n
 #pragma unroll
     for (int i = 0; i < LDK; ++i) {
       const int blk = rwave * LDK + i;
       const int r = blk * 8 + (lane >> 3);
       const int c = (lane & 7) ^ k_swizzle(r);
       int row = kv0 + r;
-      if (!inside) row = row < Mk ? row : Mk - 1;
-      const char* src = kg + (uint32_t)(row * kRowBytes + c * 16);
-      bf16_t* dst = &s_k[buf][blk * 512];
+      if (!inside) row = row < n ? row : n - 1;
+      const char* src = rows + (uint32_t)(row * kRowBytes + c * 16);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(buf + blk * 512), 16, 0, 0);
     }
   };
+  auto load_k = [&](int kv0, int buf, bool inside = false) { load_rows(kg, kv0, Mk, s_k[buf], inside); };
   // V the same way, under its own swizzle
   auto load_v = [&](int kv0, int buf, bool inside = false) {
 #pragma unroll
@@ -658,6 +661,49 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   w.ones_idx = row_sum_index(lane);
   const int n_tiles = (Mk + kKvTile - 1) / kKvTile;
 
+  // Whether the keys outside this piece alone bring the sums of all rows into the range (no shifts): then this
+  // piece's own sum may be as small as it is.  Looks at the head's first, middle and last key tile.
+  auto rest_holds = [&]() -> bool {
+    const int64_t k0 = a.k_off[h];
+    const int keys = (int)(a.k_off[h + 1] - k0), last = (keys - 1) / kKvTile;
+    float rest[NQ];
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) rest[qt] = 0.f;
+#pragma unroll 1
+    for (int i = 0; i < 3; ++i) {
+      const int kv0 = (i * last / 2) * kKvTile;
+      load_rows((const char*)(a.k + k0 * kDHead), kv0, keys, s_k[0]);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      if (active) {
+#pragma unroll 1
+        for (int st = 0; st < kKvTile; st += kStep) {
+          StepOperands op;
+          load_k_operands(op, &s_k[0][st * kDHead], l16, grp);
+#pragma unroll
+          for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+              const f32x4 sc = mfma16(op.ak[kt * 2 + 1], w.qf[qt][1], mfma16(op.ak[kt * 2], w.qf[qt][0], f32x4{0.f, 0.f, 0.f, 0.f}));
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                rest[qt] += kv0 + st + 16 * kt + 4 * grp + r < keys ? __builtin_amdgcn_exp2f(sc[r]) : 0.f;
+            }
+        }
+      }
+      __syncthreads();
+    }
+    bool low = false;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      const LanePair r1 = swap16(rest[qt]), r2 = swap32(r1.a + r1.b);
+      low = low || !(r2.a + r2.b >= kFastSumMin);
+    }
+    if (active && low) s_high = 1;       // (everybody has read it: two barriers a tile)
+    __syncthreads();
+    return !s_high;
+  };
+
   // Steps are numbered t = 0 .. 2*n_tiles-1 (32 keys each).  Outer iteration j runs the pipeline
   // slots t = 2j-1 and t = 2j, which read K tile j (scores of steps 2j, 2j+1) and V tile j-1
   // (products of steps 2j-2, 2j-1), while K tile j+1 and V tile j are on their way into the
@@ -668,7 +714,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   load_k(0, 0);
   load_v(0, 0);
   if (n_tiles > 1) load_k(kKvTile, 1);
-  if (tid == 0) s_again = 0;            // (the first key group always has a tile)
+  if (KS == 1 && tid == 0) s_again = s_high = 0;
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
   __syncthreads();
   if (active) {
@@ -751,20 +797,54 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     for (int b = n_tiles ? n_tiles : -1; b < max_tiles; ++b) __syncthreads();
 
   float l_tot[NQ];
-  bool bad = false;
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     const LanePair sums = row_sums(w.l_acc[qt >> 1][0]);
     l_tot[qt] = qt & 1 ? sums.b : sums.a;
     if (KS > 1 && n_tiles == 0) w.nm[qt] = -kLowestScore;      // (no keys, no say in the common shift)
-    bad = bad || (n_tiles > 0 && !(l_tot[qt] >= kFastSumMin && l_tot[qt] <= kFastSumMax));
   }
   // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
-  // stages its tiles together) takes the tile again with running maxima.  (One flag and one barrier:
-  // __syncthreads_or() takes three, 0.3 us of an 8 us launch.)
-  if (active && bad) s_again = 1;
-  __syncthreads();
-  if (s_again) {
+  // stages its tiles together) takes the tile again with running maxima.  The range is the row's, not that of
+  // a part of its keys: without shifts only the sum of all parts may not be small.
+  bool again = false;
+  if constexpr (KS == 1) {
+    // (one flag and one barrier: __syncthreads_or() takes three, 0.3 us of an 8 us launch)
+    bool high = false, low = false;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      high = high || !(l_tot[qt] <= kFastSumMax);
+      low = low || l_tot[qt] < kFastSumMin;
+    }
+    if (active && (high || low)) s_again = 1;
+    if (active && high) s_high = 1;
+    __syncthreads();
+    again = s_again;
+    if (!SHIFT && again && piece && !s_high) again = !rest_holds();
+  } else {
+    // every wave looks at the sums of all rows, so that no second barrier is needed to agree
+    static_assert(NQ * 16 == 64, "a lane per row of a wave");
+    if (grp == 0) {
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) s_sum[wave][qt * 16 + l16] = l_tot[qt];
+    }
+    __syncthreads();
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+      if (q0 + r * 16 * NQ >= Mq) continue;
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const float part = s_sum[k * RG + r][lane];
+        sum += part;
+        // (groups with shifts of their own: each part; one without a key tile has none)
+        if (SHIFT && key_tiles(k) < key_tiles(k + 1)) bad = bad || !(part >= kFastSumMin && part <= kFastSumMax);
+      }
+      if (!SHIFT) bad = bad || !(sum >= kFastSumMin && sum <= kFastSumMax);
+    }
+    again = __any(bad);
+  }
+  if (again) {
     float top[NQ];
     if (active) {
 #pragma unroll
@@ -809,7 +889,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) s_acc[((wave * 4 + ct) * NQ + qt) * 64 + lane] = w.o_acc[ct][qt];
       if (grp == 0) {
-        s_sum[wave][qt * 16 + l16] = l_tot[qt];
+        if (again) s_sum[wave][qt * 16 + l16] = l_tot[qt];
         s_shift[wave][qt * 16 + l16] = -w.nm[qt];
       }
     }

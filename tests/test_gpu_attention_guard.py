@@ -69,20 +69,53 @@ def test_rows_whose_scores_rise_match_the_oracle(shape, rise, log2):
     check_output(got[rows], orc.attention(qf, kf, vf, rows=rows), f"{shape}, {rise}", relative_to_magnitude=True)
 
 
+@pytest.mark.parametrize("rise,again", [("last_half_low", False), ("first_half_low", False), ("one_key_mid", True), ("all_low", True)])
+def test_pieces_without_shifts_are_judged_by_the_sums_of_their_rows(rise, again):
+    """Unshifted weights of a piece may be small if those of the rest of the row are not: such a piece keeps its shift
+    of zero.  It takes shifts of its own where its weights are too large, or all of the row's are small."""
+    require_gpu()
+    mq, mk, _ = SHAPES["pieces"]
+    gen = torch.Generator().manual_seed(8960)
+    q, k, v = (torch.randn((n, 64), generator=gen) for n in (mq, mk, mk))
+    q[:, 0] = (torch.arange(mq) % 3 == 1).float()
+    k[:, 0] = 0
+    k[:, 1:] *= float(httm.LOG2_KEY_SCALE)
+    for a, b, units in [(0, mk, -1500)] if rise == "all_low" else RISES[rise](mk):
+        k[a:b, 0] = units
+    qm, km, vm = (t.to(torch.bfloat16).cuda() for t in (q, k, v))
+    got = torch.full_like(qm, float("nan"))
+    scratch = torch.full((httm.attention_scratch_bytes(1),), 0xFF, dtype=torch.uint8, device="cuda")
+    httm.attention_log2(qm, km, vm, got, [0, mq], [0, mk], scratch=scratch)
+    torch.cuda.synchronize()
+    # the scratch holds, for every slot, 256 x 64 sums, then 256 row sums a slot, then 256 shifts a slot
+    slots = httm.attention_split_plan([0, mq], [0, mk], torch.cuda.get_device_properties(0).multi_processor_count)["slots"]
+    assert slots > 0
+    shifts = scratch.view(torch.float32)[slots * 256 * 65:slots * 256 * 66]
+    shifts = shifts[~torch.isnan(shifts)]                # (slots and rows that stay unused keep their NaN)
+    assert shifts.numel() > 0 and bool((shifts != 0).any()) == again
+    rows = np.arange(mq - 300, mq, 7)
+    want = orc.attention(f32(qm), f32(km) / np.float32(httm.LOG2_KEY_SCALE), f32(vm), rows=rows)
+    check_output(f32(got)[rows], want, rise, relative_to_magnitude=True)
+
+
 def test_a_row_with_nan_leaves_its_neighbours_alone():
     """Row sums of two query tiles come out of one instruction, where NaN times zero is NaN: the rows beside one with
     NaN are taken again on their own."""
     require_gpu()
     gen = torch.Generator().manual_seed(8950)
-    for mq, mk in ((301, 700), (300, 1089), (8192, 2113)):
+    for mq, mk, log2 in ((301, 700, False), (300, 1089, False), (8192, 2113, False), (301, 700, True), (300, 1089, True)):
         q, k, v = (torch.randn((n, 64), generator=gen) for n in (mq, mk, mk))
         q[5] = float("nan")
         q[100, 3] = float("inf")
-        qm, km, vm = (t.to(torch.bfloat16).cuda() for t in (q, k, v))
+        scale = np.float32(httm.LOG2_KEY_SCALE) if log2 else np.float32(1.0)
+        qm, km, vm = (t.to(torch.bfloat16).cuda() for t in (q, k * float(scale), v))
         got = torch.full_like(qm, 7.0)
-        httm.attention(qm, km, vm, got, [0, mq], [0, mk], 0.125)
+        if log2:
+            httm.attention_log2(qm, km, vm, got, [0, mq], [0, mk])
+        else:
+            httm.attention(qm, km, vm, got, [0, mq], [0, mk], 0.125)
         torch.cuda.synchronize()
         got = f32(got)
         assert np.isnan(got[[5, 100]]).all()
         rows = np.setdiff1d(np.arange(min(mq, 400)), [5, 100])
-        check_output(got[rows], orc.attention(f32(qm), f32(km), f32(vm), rows=rows), f"{mq} x {mk}")
+        check_output(got[rows], orc.attention(f32(qm), f32(km) / scale, f32(vm), rows=rows), f"{mq} x {mk}")
