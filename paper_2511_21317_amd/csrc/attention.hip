@@ -55,10 +55,12 @@
 // takes one fma per score, scale and shift, with m the row's exact maximum over the first 32 keys until a step's
 // weights outgrow it (guard_step()).  The row sums come from the matrix cores (row_sum_operand()).  A tile without
 // shifts is checked once, at its end: if a row's sum is outside [2^-64, 2^64] (or inf / NaN), the workgroup takes
-// the tile again with running maxima (running_max_step(): the classic online softmax, not pipelined).  A key group's
-// or piece's own sum may be smaller (half of the keys masked: 16 x 2048 x 8192 179 -> 62 us) if the row's is not: the
-// groups are checked together, a piece looks at a few key tiles of the others (rest_holds).  The same
-// check behind the shifts finds what they cannot hold (logits beyond 2^30, NaN next to a number).
+// the tile again with per-row shifts (16 x 9000 x 9000, one key 60 nats above the rest: 514 us against 266; with
+// running maxima 747, with a second launch for marked tiles 645).  A key group's or piece's own sum may be smaller
+// (half of the keys masked: 16 x 2048 x 8192 179 -> 57 us) if the row's is not: the groups are checked together, a
+// piece looks at a few key tiles of the others (rest_holds).  The same check behind the shifts finds what they cannot
+// hold (logits beyond 2^30, NaN next to a number): running maxima, not pipelined (running_max_step(): the classic
+// online softmax).
 // Measured against a guard that sums on the vector ALU (a dot2 against ones and a compare per score pair) and, for
 // log2 keys, a second launch that redid marked tiles: 16 ragged heads of 5500 x 9000 plain keys 219 -> 205 us, two
 // 16 x 16 frames 27.3 -> 24.3 us a layer.
@@ -156,6 +158,13 @@ struct WaveState {
   int ones_idx;
 };
 
+// A constant in a register of its own, here and now: the compiler moves constants that an instruction cannot hold
+// in front of the loop over a share's segments, where they take registers through the whole tile.
+__device__ __forceinline__ uint32_t local(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // Row sums on the matrix cores.  A sum does not need the zeros of a structured-sparse A
 // operand: v_smfmac_f32_16x16x64_bf16 takes 64 dense k per instruction in the time the dense
 // 16x16x32 takes 32 (18 against 16 cycles in a register-only loop), and the two k of every four that a row
@@ -170,10 +179,10 @@ struct WaveState {
 // power they draw: 16 heads x 16384 x 16384 878 -> 860 us.
 __device__ __forceinline__ bf16x8 row_sum_operand(int lane) {
   const int m = lane & 15;
-  const uint32_t w = (m & 3) == 0 && (m >> 3) == (lane >> 5) ? 0x3F803F80u : 0u;
+  const uint32_t w = (m & 3) == 0 && (m >> 3) == (lane >> 5) ? local(0x3F803F80u) : 0u;
   return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
 }
-__device__ __forceinline__ int row_sum_index(int lane) { return (lane & 4) ? (int)0xEEEEEEEEu : 0x44444444; }
+__device__ __forceinline__ int row_sum_index(int lane) { return (int)((lane & 4) ? local(0xEEEEEEEEu) : local(0x44444444u)); }
 // Exchange between neighbouring lane groups of 16 (halves of the wave): both lanes of a pair receive {x of the lower
 // one, x of the upper one}.
 struct LanePair {
@@ -291,6 +300,7 @@ __device__ __forceinline__ void guard_step(WaveState<NQ>& w, u32x8 (&p)[NQ / 2],
   for (int i = 0; i < NQ / 2; ++i) out = out || !(w.l_acc[i][0] <= kGuardSum);
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(out) == 0, 1)) return;
   asm volatile("" : "+v"(lane));      // (nothing of the addresses below is to live in registers outside)
+  const float masked = __uint_as_float(local(0xFF800000u));   // -inf
   const int l16 = lane & 15, grp = lane >> 4;
   bf16x8 ak[4];
 #pragma unroll
@@ -314,7 +324,7 @@ __device__ __forceinline__ void guard_step(WaveState<NQ>& w, u32x8 (&p)[NQ / 2],
         s[kt] = mfma16(ak[kt * 2 + 1], w.qf[qt][1], s[kt]);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (kv_first + 16 * kt + 4 * grp + r >= Mk) s[kt][r] = -INFINITY;
+          if (kv_first + 16 * kt + 4 * grp + r >= Mk) s[kt][r] = masked;
       }
       const float top = step_max(s[0], s[1]);
       const float grown = (j ? sum.b : sum.a) > kGuardGrown ? 58.f : 0.f;
@@ -366,9 +376,12 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
       for (int i = 0; i < NQ / 2; ++i) add_row_sums(w, w.p_old[i], i);
     }
   }
+  // (per-row shifts: products and softmax side by side need 4 to 6 registers too many)
+  if (SHIFT && DO_QK && DO_PV) __builtin_amdgcn_sched_barrier(0);
   if (DO_SM) {
     // s_cur[kt][qt][r]: key kv_first + 16*kt + 4*grp + r, query column l16 of tile qt
     if (MASK) {
+      const float masked = __uint_as_float(local(0xFF800000u));   // -inf
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -376,7 +389,7 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
           const int kv = kv_first + 16 * kt + 4 * grp + r;
           if (kv >= Mk) {
 #pragma unroll
-            for (int qt = 0; qt < NQ; ++qt) w.s_cur[kt][qt][r] = -INFINITY;
+            for (int qt = 0; qt < NQ; ++qt) w.s_cur[kt][qt][r] = masked;
           }
         }
     }
@@ -488,8 +501,8 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
 constexpr float kFastSumMin = 5.421010862427522e-20f;    // 2^-64
 constexpr float kFastSumMax = 1.8446744073709552e19f;    // 2^64
 
-// One step of 32 keys with a running maximum per row (the classic online softmax), for tiles whose
-// rows leave the range of the pipelined pass: any finite scores.  Not pipelined: rare.  The maxima are kept in
+// One step of 32 keys with a running maximum per row (the classic online softmax), for tiles with
+// rows that no pipelined pass holds: any finite scores.  Not pipelined: rare.  The maxima are kept in
 // units of the raw scores: near the ends of the fp32 range the rounding of max * c alone is more than
 // the exponents can hold, s - max of neighbouring scores is exact.
 template <int NQ>
@@ -586,9 +599,10 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 
   if (Mk == 0) {
     // softmax over an empty key set: defined as zero output
+    const uint32_t zero = local(0);
     for (int e = tid; e < BQ * kRowChunks; e += NT) {
       const int row = q0 + (e >> 3);
-      if (row < Mq) ((u32x4*)o_rows)[(q_base + row) * kRowChunks + (e & 7)] = u32x4{0, 0, 0, 0};
+      if (row < Mq) ((u32x4*)o_rows)[(q_base + row) * kRowChunks + (e & 7)] = u32x4{zero, zero, zero, zero};
     }
     return;
   }
@@ -699,150 +713,168 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       const LanePair r1 = swap16(rest[qt]), r2 = swap32(r1.a + r1.b);
       low = low || !(r2.a + r2.b >= kFastSumMin);
     }
-    if (active && low) s_high = 1;       // (everybody has read it: two barriers a tile)
+    if (active && low) s_high = (int)local(1);       // (everybody has read it: two barriers a tile)
     __syncthreads();
     return !s_high;
   };
 
+  // One pass over the keys; true if some row of the tile has left the range of its weights.
   // Steps are numbered t = 0 .. 2*n_tiles-1 (32 keys each).  Outer iteration j runs the pipeline
   // slots t = 2j-1 and t = 2j, which read K tile j (scores of steps 2j, 2j+1) and V tile j-1
   // (products of steps 2j-2, 2j-1), while K tile j+1 and V tile j are on their way into the
   // other LDS buffers.
-
-  if (KS == 1 || n_tiles > 0) {
-  // ---- j = 0 ---------------------------------------------------------------------------------------
-  load_k(0, 0);
-  load_v(0, 0);
-  if (n_tiles > 1) load_k(kKvTile, 1);
-  if (KS == 1 && tid == 0) s_again = s_high = 0;
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
-  __syncthreads();
-  if (active) {
-    pipeline_step<NQ, SHIFT, true, false, false, false, false>(w, &s_k[0][0], nullptr, kg, 0, Mk, lane);
-  }
-  if (active) {
-    if (n_tiles > 1)
-      pipeline_step<NQ, SHIFT, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
-    else
-      pipeline_step<NQ, SHIFT, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
-  }
-  __syncthreads();
-
-  // ---- j = 1 .. n_tiles-2: steady state, no masking ------------------------------------------------
-  int j = 1;
-  StepOperands op;
-  // Two tiles per trip with the buffer indices as constants (j is odd at the top): the LDS
-  // addresses become instruction offsets instead of a dozen vector adds per tile.
-  auto steady_tile = [&](auto parity, int jt) {
-    constexpr int P = decltype(parity)::value;        // jt & 1
-    const bf16_t* kb = &s_k[P][0];
-    const bf16_t* vb = &s_v[P ^ 1][0];
-    auto request = [&]() {
-      if ((jt + 2) * kKvTile <= Mk)
-        load_k((jt + 1) * kKvTile, P ^ 1, true);
-      else
-        load_k((jt + 1) * kKvTile, P ^ 1);
-      load_v(jt * kKvTile, P, true);                     // jt < n_tiles - 1: a full tile
-    };
-    // (a wave without valid rows runs the loop below instead: no global->LDS request may precede
-    // an LDS read on the path of an active wave, the compiler would wait for it before the read)
-    load_k_operands(op, kb, l16, grp);
-    load_v_operands(op, vb, l16, grp);
-    steady_step<NQ, SHIFT, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, kg, (2 * jt - 1) * kStep, Mk, lane, request);
-    steady_step<NQ, SHIFT, false>(w, op, nullptr, nullptr, kg, 2 * jt * kStep, Mk, lane, [] {});
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): K tile jt+1 and V tile jt are in LDS
+  float l_tot[NQ];
+  auto pass = [&](auto shifts) -> bool {
+    constexpr bool S = decltype(shifts)::value;
+    if (KS == 1 || n_tiles > 0) {
+    // ---- j = 0 ---------------------------------------------------------------------------------------
+    load_k(0, 0);
+    load_v(0, 0);
+    if (n_tiles > 1) load_k(kKvTile, 1);
+    if (KS == 1 && tid == 0) s_again = s_high = 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the global->LDS loads have landed
     __syncthreads();
-  };
-  if (!active) {
-    // a wave of a partial tile without valid rows: it only stages its share of K / V
-    for (; j < n_tiles - 1; ++j) {
-      load_k((j + 1) * kKvTile, (j + 1) & 1);
+    if (active) {
+      pipeline_step<NQ, S, true, false, false, false, false>(w, &s_k[0][0], nullptr, kg, 0, Mk, lane);
+    }
+    if (active) {
+      if (n_tiles > 1)
+        pipeline_step<NQ, S, true, false, true, false, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
+      else
+        pipeline_step<NQ, S, true, false, true, true, true>(w, &s_k[0][kStep * kDHead], nullptr, kg, 0, Mk, lane);
+    }
+    __syncthreads();
+
+    // ---- j = 1 .. n_tiles-2: steady state, no masking ------------------------------------------------
+    int j = 1;
+    StepOperands op;
+    // Two tiles per trip with the buffer indices as constants (j is odd at the top): the LDS
+    // addresses become instruction offsets instead of a dozen vector adds per tile.
+    auto steady_tile = [&](auto parity, int jt) {
+      constexpr int P = decltype(parity)::value;        // jt & 1
+      const bf16_t* kb = &s_k[P][0];
+      const bf16_t* vb = &s_v[P ^ 1][0];
+      auto request = [&]() {
+        if ((jt + 2) * kKvTile <= Mk)
+          load_k((jt + 1) * kKvTile, P ^ 1, true);
+        else
+          load_k((jt + 1) * kKvTile, P ^ 1);
+        load_v(jt * kKvTile, P, true);                     // jt < n_tiles - 1: a full tile
+      };
+      // (a wave without valid rows runs the loop below instead: no global->LDS request may precede
+      // an LDS read on the path of an active wave, the compiler would wait for it before the read)
+      load_k_operands(op, kb, l16, grp);
+      load_v_operands(op, vb, l16, grp);
+      steady_step<NQ, S, true>(w, op, kb + kStep * kDHead, vb + kStep * kDHead, kg, (2 * jt - 1) * kStep, Mk, lane, request);
+      steady_step<NQ, S, false>(w, op, nullptr, nullptr, kg, 2 * jt * kStep, Mk, lane, [] {});
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): K tile jt+1 and V tile jt are in LDS
+      __syncthreads();
+    };
+    if (!active) {
+      // a wave of a partial tile without valid rows: it only stages its share of K / V
+      for (; j < n_tiles - 1; ++j) {
+        load_k((j + 1) * kKvTile, (j + 1) & 1);
+        load_v(j * kKvTile, j & 1);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+      }
+    } else {
+      for (; j + 1 < n_tiles - 1; j += 2) {
+        steady_tile(std::integral_constant<int, 1>{}, j);
+        steady_tile(std::integral_constant<int, 0>{}, j + 1);
+      }
+      if (j < n_tiles - 1) {
+        steady_tile(std::integral_constant<int, 1>{}, j);
+        ++j;
+      }
+    }
+
+    // ---- j = n_tiles-1 (if it is not j = 0): the last K tile, its first step may be ragged ---------
+    if (j == n_tiles - 1) {
       load_v(j * kKvTile, j & 1);
-      __builtin_amdgcn_s_waitcnt(0x0F70);
+      const bf16_t* kb = &s_k[j & 1][0];
+      const bf16_t* vb = &s_v[(j - 1) & 1][0];
+      if (active) {
+        pipeline_step<NQ, S, true, true, true, false, false>(w, kb, vb, kg, (2 * j - 1) * kStep, Mk, lane);
+        pipeline_step<NQ, S, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead, kg, 2 * j * kStep, Mk, lane);
+      }
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the last V tile is in LDS
       __syncthreads();
     }
-  } else {
-    for (; j + 1 < n_tiles - 1; j += 2) {
-      steady_tile(std::integral_constant<int, 1>{}, j);
-      steady_tile(std::integral_constant<int, 0>{}, j + 1);
-    }
-    if (j < n_tiles - 1) {
-      steady_tile(std::integral_constant<int, 1>{}, j);
-      ++j;
-    }
-  }
 
-  // ---- j = n_tiles-1 (if it is not j = 0): the last K tile, its first step may be ragged ---------
-  if (j == n_tiles - 1) {
-    load_v(j * kKvTile, j & 1);
-    const bf16_t* kb = &s_k[j & 1][0];
-    const bf16_t* vb = &s_v[(j - 1) & 1][0];
+    // ---- j = n_tiles: drain ---------------------------------------------------------------------------
     if (active) {
-      pipeline_step<NQ, SHIFT, true, true, true, false, false>(w, kb, vb, kg, (2 * j - 1) * kStep, Mk, lane);
-      pipeline_step<NQ, SHIFT, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead, kg, 2 * j * kStep, Mk, lane);
+      const bf16_t* vb = &s_v[(n_tiles - 1) & 1][0];
+      pipeline_step<NQ, S, false, true, true, true, false>(w, nullptr, vb, kg, (2 * n_tiles - 1) * kStep, Mk, lane);
+      pipeline_step<NQ, S, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, kg, 0, Mk, lane);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the last V tile is in LDS
-    __syncthreads();
-  }
+    }
+    // a group of n tiles has met n + 1 barriers (none if it has no tile): the others of its workgroup wait
+    if constexpr (KS > 1)
+      for (int b = n_tiles ? n_tiles : -1; b < max_tiles; ++b) __syncthreads();
 
-  // ---- j = n_tiles: drain ---------------------------------------------------------------------------
-  if (active) {
-    const bf16_t* vb = &s_v[(n_tiles - 1) & 1][0];
-    pipeline_step<NQ, SHIFT, false, true, true, true, false>(w, nullptr, vb, kg, (2 * n_tiles - 1) * kStep, Mk, lane);
-    pipeline_step<NQ, SHIFT, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, kg, 0, Mk, lane);
-  }
-  }
-  // a group of n tiles has met n + 1 barriers (none if it has no tile): the others of its workgroup wait
-  if constexpr (KS > 1)
-    for (int b = n_tiles ? n_tiles : -1; b < max_tiles; ++b) __syncthreads();
-
-  float l_tot[NQ];
-#pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) {
-    const LanePair sums = row_sums(w.l_acc[qt >> 1][0]);
-    l_tot[qt] = qt & 1 ? sums.b : sums.a;
-    if (KS > 1 && n_tiles == 0) w.nm[qt] = -kLowestScore;      // (no keys, no say in the common shift)
-  }
-  // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
-  // stages its tiles together) takes the tile again with running maxima.  The range is the row's, not that of
-  // a part of its keys: without shifts only the sum of all parts may not be small.
-  bool again = false;
-  if constexpr (KS == 1) {
-    // (one flag and one barrier: __syncthreads_or() takes three, 0.3 us of an 8 us launch)
-    bool high = false, low = false;
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      high = high || !(l_tot[qt] <= kFastSumMax);
-      low = low || l_tot[qt] < kFastSumMin;
+      const LanePair sums = row_sums(w.l_acc[qt >> 1][0]);
+      l_tot[qt] = qt & 1 ? sums.b : sums.a;
+      if (KS > 1 && n_tiles == 0) w.nm[qt] = -kLowestScore;      // (no keys, no say in the common shift)
     }
-    if (active && (high || low)) s_again = 1;
-    if (active && high) s_high = 1;
-    __syncthreads();
-    again = s_again;
-    if (!SHIFT && again && piece && !s_high) again = !rest_holds();
-  } else {
-    // every wave looks at the sums of all rows, so that no second barrier is needed to agree
-    static_assert(NQ * 16 == 64, "a lane per row of a wave");
-    if (grp == 0) {
+    // Rare: a row of this tile left the range in which its weights are safe; the whole workgroup (it
+    // stages its tiles together) takes the tile again.  The range is the row's, not that of
+    // a part of its keys: without shifts only the sum of all parts may not be small.
+    bool again = false;
+    if constexpr (KS == 1) {
+      // (one flag and one barrier: __syncthreads_or() takes three, 0.3 us of an 8 us launch)
+      bool high = false, low = false;
 #pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) s_sum[wave][qt * 16 + l16] = l_tot[qt];
-    }
-    __syncthreads();
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < RG; ++r) {
-      if (q0 + r * 16 * NQ >= Mq) continue;
-      float sum = 0.f;
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const float part = s_sum[k * RG + r][lane];
-        sum += part;
-        // (groups with shifts of their own: each part; one without a key tile has none)
-        if (SHIFT && key_tiles(k) < key_tiles(k + 1)) bad = bad || !(part >= kFastSumMin && part <= kFastSumMax);
+      for (int qt = 0; qt < NQ; ++qt) {
+        high = high || !(l_tot[qt] <= kFastSumMax);
+        low = low || l_tot[qt] < kFastSumMin;
       }
-      if (!SHIFT) bad = bad || !(sum >= kFastSumMin && sum <= kFastSumMax);
+      if (active && (high || low)) s_again = (int)local(1);
+      if (active && high) s_high = (int)local(1);
+      __syncthreads();
+      again = s_again;
+      if (!S && again && piece && !s_high) again = !rest_holds();
+    } else {
+      // every wave looks at the sums of all rows, so that no second barrier is needed to agree
+      static_assert(NQ * 16 == 64, "a lane per row of a wave");
+      if (grp == 0) {
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) s_sum[wave][qt * 16 + l16] = l_tot[qt];
+      }
+      __syncthreads();
+      bool bad = false;
+#pragma unroll
+      for (int r = 0; r < RG; ++r) {
+        if (q0 + r * 16 * NQ >= Mq) continue;
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          const float part = s_sum[k * RG + r][lane];
+          sum += part;
+          // (groups with shifts of their own: each part; one without a key tile has none)
+          if (S && key_tiles(k) < key_tiles(k + 1)) bad = bad || !(part >= kFastSumMin && part <= kFastSumMax);
+        }
+        if (!S) bad = bad || !(sum >= kFastSumMin && sum <= kFastSumMax);
+      }
+      again = __any(bad);
     }
-    again = __any(bad);
+    return again;
+  };
+  bool again = pass(std::integral_constant<bool, SHIFT>{});
+  // Log2 keys, rare: once more with per-row shifts.  (The barrier: everybody has read the flags of the first pass.)
+  if constexpr (!SHIFT) {
+    if (again) {
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) {
+        w.l_acc[qt >> 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      __syncthreads();
+      again = pass(std::integral_constant<bool, true>{});
+    }
   }
   if (again) {
     float top[NQ];
@@ -881,7 +913,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 
   if constexpr (KS > 1) {
     // The groups' sums, brought to the largest of their shifts of a row (all zero unless a group had
-    // to take running maxima or the keys are plain), added in key order.  Every wave leaves its registers in
+    // to take shifts or the keys are plain), added in key order.  Every wave leaves its registers in
     // LDS as they are (the tile buffers: no group reads them any more) and adds up its share of the channels.
     f32x4* s_acc = (f32x4*)lds;                     // [wave][channel tile][query tile][lane]
 #pragma unroll
@@ -1027,7 +1059,7 @@ void attention_kernel(const AttnArgs a) {
 
 // The split tiles after attention_kernel ran them in segments: four workgroups per split tile (64 rows
 // each) bring its segments to the largest of their shifts of a row (all zero unless a segment had
-// to take running maxima or the keys are plain), add them in ascending key order (run-to-run
+// to take shifts or the keys are plain), add them in ascending key order (run-to-run
 // identical) and store the normalised rows.  Bound by the latency of one chain of loads - 16 to 30 MB
 // over the chip - so every thread fetches the sums and the shifts of its own row next to its
 // values instead of taking them from LDS behind a barrier, kReduceBatch segments at a time.
