@@ -176,8 +176,8 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   // One share per CU.  With any other number some CUs get one more than the others, and twice as many
   // (every CU two) double the partial results: 16 heads of 7000 rows and keys in 330 / 512 / 256 shares 210 /
   // 181 / 172 us, of 10000 in 314 / 512 / 256 364 / 344 / 328, of 15000 in 512 / 256 745 / 708.  Only very long
-  // shares are halved, which costs 2 % there (27000 rows and keys 2.27 : 2.21 ms): the launches whose partial
-  // results have never fitted the library's own array (httm_attention_log2_static) keep being refused.
+  // shares are halved, which costs 2 % there (27000 rows and keys 2.27 : 2.21 ms): those launches need more than
+  // the library's own array holds, and httm_attention_log2_static refuses them, as it always has.
   int64_t shares = units / kAttnLongShareUnits > cus ? 2 * cus : cus;
   if (shares > units / kAttnMinShareUnits) shares = units / kAttnMinShareUnits;
   if (shares > kAttnMaxShares) shares = kAttnMaxShares;
@@ -254,7 +254,8 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
                                    AttnRoute* out) {
   AttnRoute& r = *out;
   r.tiles = AttnTiles::kTiles256;
-  plan_attention_split(q_off, k_off, H, cus, &r.split, &r.kept_full, &r.split_ragged);
+  r.split.n_tiles = 0;
+  if (scratch_words > 0) plan_attention_split(q_off, k_off, H, cus, &r.split, &r.kept_full, &r.split_ragged);
   int64_t full = 0, keys = 0;
   for (int h = 0; h < H; ++h) {
     full += (q_off[h + 1] - q_off[h]) / kAttnTileRows;
@@ -265,7 +266,7 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
     r.kept_full = full;
     r.split_ragged = 0;
   };
-  if (split_slots(r.split) * kAttnSlotWords > scratch_words) no_split();
+  if (r.split.n_tiles == 0 || split_slots(r.split) * kAttnSlotWords > scratch_words) no_split();
   // At most one 64-, 128- or 256-row tile per CU: workgroups whose waves share the keys, unless the walk is so short
   // that the groups' meeting costs more (2 us).  16 heads against the 128-row tiles of one key group: 64 rows
   // 266 x 266 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5, 700 x 700 12.0 : 12.0, 1024 x 1024 14.0 : 15.4; 128 rows
