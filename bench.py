@@ -95,7 +95,7 @@ def shader_clock_mhz():
 
 def mfma_sustained_tflops():
     """What the chip sustains on the attention kernel's MFMA instruction alone: a register-only loop of
-    v_mfma_f32_32x32x16_bf16 with pseudo-random operands (paper_2511_21317_amd/csrc/mfma_probe.hip, its
+    v_mfma_f32_16x16x32_bf16 with pseudo-random operands (paper_2511_21317_amd/csrc/mfma_probe.hip, its
     own small library), two workgroups of four waves per compute unit, about 25 ms per launch so that
     the clock has settled under the power limit.  Median of 5 launches; None if the probe is not built."""
     import ctypes
@@ -110,13 +110,13 @@ def mfma_sustained_tflops():
     flop = [0.0]
 
     def run():
-        flop[0] = lib.httm_probe_mfma_bf16(out.data_ptr(), 40000, 2, torch.cuda.current_stream().cuda_stream)
+        flop[0] = lib.httm_probe_mfma_bf16(out.data_ptr(), 20000, 2, torch.cuda.current_stream().cuda_stream)
     ts = event_times_ms(run, 5, warmup=2)
     if flop[0] <= 0.0:
         return None
     ms = statistics.median(ts)
     return {"TFLOP/s": flop[0] / (ms * 1e-3) / 1e12, "ms": ms, "flop": flop[0],
-            "what": "register-only loop of v_mfma_f32_32x32x16_bf16, pseudo-random operands, 512 workgroups of 4 waves"}
+            "what": "register-only loop of v_mfma_f32_16x16x32_bf16, pseudo-random operands, 512 workgroups of 4 waves"}
 
 
 def pmc_traffic_bytes(kernel: str, workload_index: int):
@@ -290,7 +290,7 @@ def main():
     clocks["after_headline"] = shader_clock_mhz()
 
     a = headline["stages"]["attention"]
-    traffic, traffic_file = pmc_traffic_bytes("attention_kernel<2, 4, false>" if LK else "attention_kernel<2, 4, true>", w.index)
+    traffic, traffic_file = pmc_traffic_bytes("attention_kernel<4, 4, 1, false>" if LK else "attention_kernel<4, 4, 1, true>", w.index)
     roofline = {"kernel": "attention_kernel", "bound": "mfma", "achieved": a["TFLOP/s"],
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": a["TFLOP/s"] / PEAK_BF16_TFLOPS,
                 "traffic": None if special else traffic,
