@@ -616,7 +616,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     const int t0 = key_tiles(key_group), t1 = key_tiles(key_group + 1);   // (never none for the first)
     max_tiles = (all + KS - 1) / KS;
     k_base += (int64_t)t0 * kKvTile;
-    Mk = (t1 * kKvTile < Mk ? t1 * kKvTile : Mk) - t0 * kKvTile;   // 0 for a group without a key tile
+    Mk = (t1 * kKvTile < Mk ? t1 * kKvTile : Mk) - t0 * kKvTile;   // at most 0 for a group without a key tile
   }
 
   WaveState<NQ> w;

@@ -307,9 +307,9 @@ void match_merge_kernel(const MatchMergeArgs a) {
     if (TOPR) __syncthreads();
   } else {
     // ---- 3. similarities and arg-max -----------------------------------------------------------
-    // Wave w owns the tokens 64w .. 64w+63, i.e. the two 32-token tiles 2w and 2w+1.
-    // The two tiles go through the dst tiles side by side: they share the dst operand and the dst
-    // norms, and their dependent chains of LDS reads overlap.
+    // Wave w owns the tokens 64w .. 64w+63, i.e. the two 32-token tiles 2w and 2w+1 (one tile in the
+    // instance of 32 tokens).  The two tiles go through the dst tiles side by side: they share the dst operand
+    // and the dst norms, and their dependent chains of LDS reads overlap.
     const int ndt = (kd + 31) >> 5;
     float my_sc = 1.0f;                // similarity of token `tid` to the dst it would join
     if (wave * 64 < n) {

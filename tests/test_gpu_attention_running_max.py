@@ -1,6 +1,6 @@
-"""Stage 3 (Eq. 3-4) where rows leave the range of the pipelined pass: tiles and pieces of split tiles
-are taken again with running maxima, inside the same launch.  Both key conventions, key counts around
-the step (32) and tile (64) sizes, against the oracle's attention."""
+"""Stage 3 (Eq. 3-4) where rows leave the range of their weights: per-row shifts are raised in the step that needs
+it (plain keys), tiles and pieces without shifts are taken again with shifts, inside the same launch (log2 keys).
+Both key conventions, key counts around the step (32) and tile (64) sizes, against the oracle's attention."""
 import numpy as np
 import pytest
 import torch
@@ -42,7 +42,7 @@ def test_key_counts_around_steps_and_tiles_with_and_without_running_maxima(mk, l
     k[mk // 2:] *= 30
     got, qf, kf, vf = _run(q, k, v, mq, mk, log2)
     assert np.isfinite(got).all()
-    check_output(got, orc.attention(qf, kf, vf), f"{mk} keys, running maxima", relative_to_magnitude=True)
+    check_output(got, orc.attention(qf, kf, vf), f"{mk} keys, out of range", relative_to_magnitude=True)
 
 
 @pytest.mark.parametrize("log2", [True, False], ids=["log2_keys", "plain_keys"])

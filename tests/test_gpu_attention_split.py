@@ -88,8 +88,8 @@ def test_tiles_in_pieces_match_the_oracle_and_the_whole_tiles(mq, mk):
 
 
 def test_a_partial_tile_that_leaves_the_unshifted_range_is_redone_with_shifts():
-    """Keys of one piece of one head give weights far above 2^64: the sum of the pieces fails the
-    window test, the tile gets the mark and the kernel with per-row shifts redoes it (whole)."""
+    """Keys of one piece of one head give weights far above 2^64: the workgroup of that piece takes it again with
+    per-row shifts, and the sum of the pieces brings them to the largest shift of a row."""
     require_gpu()
     mq, mk = [16384 + 37] * 8, [8229] * 8
 
@@ -108,7 +108,8 @@ def test_a_partial_tile_that_leaves_the_unshifted_range_is_redone_with_shifts():
         want = orc.attention(f32(qm[r0:r1]), kk, f32(vm[ko[h]:ko[h + 1]]))
         check_output(split[r0:r1], want, f"split, head {h}")
     r0, r1 = _partial_rows(qo, 3)
-    assert np.array_equal(split[r0:r1], plain[r0:r1])     # both came from the kernel with shifts
+    # rows of head 3 are decided by one key each: the same bits from pieces and from the whole tile
+    assert np.array_equal(split[r0:r1], plain[r0:r1])
 
 
 def _split_rows(mq, mk):

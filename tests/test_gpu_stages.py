@@ -366,9 +366,8 @@ def test_log2_key_attention_on_ragged_heads(mq, mk):
 @pytest.mark.parametrize("case", ["huge_positive", "huge_negative", "growing", "one_head_of_three", "nan_free_zero_keys",
                                   "large_values"])
 def test_log2_key_attention_leaves_the_unshifted_range(case):
-    """Rows whose sum of 2^(q.k') is not inside [2^-64, 2^64] cannot use unshifted weights: their
-    tiles are marked by the fast kernel and redone with per-row shifts.  The result must match the
-    oracle whichever kernel computed a tile."""
+    """Rows whose sum of 2^(q.k') is not inside [2^-64, 2^64] cannot use unshifted weights: their workgroup takes
+    the tile again with per-row shifts.  The result must match the oracle whichever pass computed a tile."""
     require_gpu()
     gen = torch.Generator().manual_seed(4100)
     mq, mk = 600, 900
@@ -411,7 +410,8 @@ def test_log2_key_attention_leaves_the_unshifted_range(case):
 
 
 def test_log2_key_attention_rewrites_a_buffer_that_holds_old_marks():
-    """The output buffer of an earlier call, marks included, must not influence the next call."""
+    """What the output buffer holds before the call (an earlier call's result, any bit pattern) must not influence it:
+    what a launch has to take again it decides in its own workgroups, and nothing is left in the output."""
     require_gpu()
     gen = torch.Generator().manual_seed(4200)
     mq, mk = 512, 300
@@ -419,7 +419,7 @@ def test_log2_key_attention_rewrites_a_buffer_that_holds_old_marks():
     k2 = _log2_keys(torch.randn((mk, 64), generator=gen)).cuda()
     vm = torch.randn((mk, 64), generator=gen).to(torch.bfloat16).cuda()
     om = torch.empty_like(qm)
-    om.view(torch.int16).fill_(0x7FA5)               # every element looks like the redo mark
+    om.view(torch.int16).fill_(0x7FA5)               # NaN with a payload in every element
     httm.attention_log2(qm, k2, vm, om, [0, mq], [0, mk])
     torch.cuda.synchronize()
     kk = f32(k2) / np.float32(httm.LOG2_KEY_SCALE)
