@@ -289,9 +289,9 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 // with a score far above its shift takes that score for the shift, one whose sum has grown over many keys moves
 // it by 58; sums and accumulators follow, and the weights are taken again, from scores computed again with
 // the 32 rows of K at `kv_first` in memory: held to the end of the step they need 32 registers too many (100 to
-// 400 spilled).  One comparison per pair of query tiles and step.  16 ragged heads of 5500 x 9000 keys: 201 us without
-// the guard, where a row that leaves the range costs its tile another 1.8 passes (last key 60 above the
-// rest 777 us), 205 with it (300), 219 with sums and guard on the vector ALU (319; the latter at 9000 x 9000).
+// 400 spilled).  One comparison per pair of query tiles and step.  Sums and guard on the vector ALU / no guard, where a
+// row that leaves the range costs its tile 1.8 more passes / this: 16 ragged heads of 5500 x 9000 keys 217 / 198 / 206 us;
+// 9000 x 9000 with the last key 60 nats above the rest 308 / 771 / 288.
 template <int NQ>
 __device__ __forceinline__ void guard_step(WaveState<NQ>& w, u32x8 (&p)[NQ / 2], const float (&before)[NQ / 2], const char* kg,
                                            int kv_first, int Mk, int lane) {
