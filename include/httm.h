@@ -336,8 +336,8 @@ HTTM_API int httm_unmerge(const httm_plan_t* plan, const void* o_m, const int32_
  * holds, in this order (each 256-byte aligned): q_m, k_m, v_m, o_m ([H, M, d_head] bf16),
  * assign_q, assign_k ([H, N] int32) and, with outlier filtering, eps_q, q_out, o_out - see
  * httm_workspace_layout.
- * The reorder is fused into the matching kernel's loads and the inverse reorder into the
- * unmerge kernel's stores; results are identical to calling the four stages one by one. */
+ * The reorder is fused into the matching kernel's loads, stage 4 with the inverse reorder into the end
+ * of stage 3's tiles; results are identical to calling the four stages one by one. */
 HTTM_API int httm_layer_forward(const httm_plan_t* plan, const void* q, const void* k, const void* v,
                        void* out, void* workspace, size_t workspace_bytes, void* stream);
 

@@ -29,6 +29,7 @@ struct httm_plan {
   // general rule (dst_frac > 0) on blocks of more than 512 tokens: the similarities the selection of
   // the merging src tokens needs, when the caller asks for none
   float* d_score = nullptr;   // [2][H][N]
+  int32_t* d_spans = nullptr;   // UnmergeTarget::spans
   // outlier filtering only
   int64_t outlier_cap = 0;
   OutlierBuffers ob = {};
@@ -277,6 +278,7 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
   rc = upload(t.pi, &p->d_pi);
   if (rc == HTTM_OK) rc = upload(t.items_q, &p->d_items_q);
   if (rc == HTTM_OK) rc = upload(t.items_k, &p->d_items_k);
+  if (rc == HTTM_OK) rc = upload(t.spans_q, &p->d_spans);
   if (rc == HTTM_OK && g->variant == HTTM_VARIANT_UNIFORM) {
     e = hipMalloc((void**)&p->d_mean, (size_t)2 * t.N * 64 * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_slot, (size_t)2 * t.N * sizeof(int32_t));
@@ -293,7 +295,7 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
     b.max_tiles = (int32_t)(p->outlier_cap / kAttnDevTileRows + g->H);
     const size_t words = sizeof(SelectState) / 4 + 3 * 2048 + (size_t)g->H * 2 + 1 +
                          2 * (size_t)g->H * p->n_items + (size_t)g->H * (p->n_items / kOutlierCountItemsMin + 1) + 1 +
-                         2 * (size_t)b.max_tiles;
+                         2 * (size_t)b.max_tiles + (size_t)p->outlier_cap;
     uint32_t* base = nullptr;
     e = hipMalloc((void**)&base, words * 4);
     if (e == hipSuccess) e = hipMemset(base, 0, words * 4);
@@ -308,6 +310,7 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
       b.item_base = b.item_cnt + (size_t)g->H * p->n_items;
       b.wg_cnt = b.item_base + (size_t)g->H * p->n_items;
       b.tiles = b.wg_cnt + (size_t)g->H * (p->n_items / kOutlierCountItemsMin + 1);
+      b.token = b.tiles + 1 + 2 * (size_t)b.max_tiles;
     }
   }
   // "Synchronous": the copies and the memset above are complete before a kernel on any stream
@@ -331,7 +334,7 @@ int httm_plan_clone(const httm_plan_t* p, httm_plan_t** out) {
 
 int httm_plan_destroy(httm_plan_t* p) {
   if (!p) return HTTM_OK;
-  void* ptrs[] = {p->d_pi, p->d_items_q, p->d_items_k, p->d_mean, p->d_slot, p->d_uscore, p->d_score, p->ob.state};
+  void* ptrs[] = {p->d_pi, p->d_items_q, p->d_items_k, p->d_spans, p->d_mean, p->d_slot, p->d_uscore, p->d_score, p->ob.state};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete p;
@@ -544,25 +547,24 @@ int httm_layer_forward(const httm_plan_t* p, const void* q, const void* k, const
                     : run_match_merge(p, p->d_pi, q, k, v, q_m, k_m, v_m, assign_q, assign_k, nullptr,
                                       nullptr, st);
   if (rc != HTTM_OK) return rc;
-  // Stage 3.
+  // Stages 3 and 4.
   const int H = p->geom.H;
   int64_t q_off[HTTM_MAX_HEADS + 1], k_off[HTTM_MAX_HEADS + 1];
   for (int h = 0; h <= H; ++h) {
     q_off[h] = (int64_t)h * p->sizes.M_q;
     k_off[h] = (int64_t)h * p->sizes.M_k;
   }
+  // (with stage 4 and the inverse reorder at the end of its tiles)
+  const UnmergeTarget um = {out, assign_q, p->d_pi, p->d_spans, p->ob.token, p->sizes.N, H};
   if (filtered) {
     // Alg. 1: the outlier queries attend on their own - same launch, workgroups appended to the grid
     HTTM_HIP(launch_attention_both(q_m, k_m, v_m, o_m, q_off, k_off, H, 0.125f, q_out, o_out, p->ob.offsets,
                                    p->ob.tiles, p->ob.max_tiles, log2_keys(p), st, ws + p->ws.attn_split,
-                                   attention_scratch_bytes(H)));
+                                   attention_scratch_bytes(H), &um));
   } else {
     HTTM_HIP(launch_attention(q_m, k_m, v_m, o_m, q_off, k_off, H, 0.125f, log2_keys(p), st, ws + p->ws.attn_split,
-                              attention_scratch_bytes(H)));
+                              attention_scratch_bytes(H), &um));
   }
-  // Stage 4 with the inverse reorder fused.
-  HTTM_HIP(launch_unmerge(o_m, assign_q, p->d_pi, out, H, p->sizes.N, p->sizes.M_q, 1, st,
-                          filtered ? o_out : nullptr));
   return HTTM_OK;
 }
 

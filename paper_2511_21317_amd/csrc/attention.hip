@@ -129,6 +129,7 @@ struct AttnArgs {
   float* split_l;   // [slots * 256]     sums of weights
   float* split_m;   // [slots * 256]     the rows' shifts
   SplitPlan sp;
+  UnmergeTarget um;
 };
 static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
@@ -546,6 +547,105 @@ __device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ
   }
 }
 
+// ---- stage 4 at the end of a query tile ------------------------------------------------------------
+// (paper Sec. 3.2 Eq. 5-7 and the inverse reorder of Sec. 3.3, with the heads concatenated.)  The tile's
+// normalised rows lie in LDS; its tokens are found by looking at the clusters of the tokens of its merging blocks,
+// 64 per wave instruction, the ones that belong here moved to the front of the wave so that 8 lanes then copy
+// a row each to out[pi(j)][h].  A kernel of its own for this is bound by writing `out`; here the writes go out
+// under the products of the other workgroups, the rows are not read back and a launch is saved.  What is left
+// of it at the end of a launch is one tile's chain of round trips (clusters, exchange, stores: 2 to 4 us; 10 us in
+// attention_split_reduce_kernel where a block keeps a thousand clusters, of which its workgroups look for 64).
+// A layer with the stage-4 kernel behind it / with this: 2 frames of 16 x 16 22.8 / 17.4 us, 8 of 37 x 37 140.6 /
+// 135.9, 200 of 37 x 37 2973 / 2918, with outliers 5753 / 5675; every random geometry of 12 was faster.
+
+// 16-byte chunk c of row r of the tile, swizzled: the rows are 128 bytes apart.
+__device__ __forceinline__ int out_chunk(int r, int c) { return r * kRowChunks + (c ^ (r & 7)); }
+
+// The target out of the kernel's arguments, read here and now: the compiler would read it in front of the tile and
+// hold it in scalar registers that the tile has none left of.
+__device__ __forceinline__ UnmergeTarget unmerge_target() {
+  typedef const __attribute__((address_space(4))) char* args_t;
+  args_t p = (args_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnArgs, um);
+  asm volatile("" : "+s"(p));
+  return *(const UnmergeTarget*)p;
+}
+
+// A tile's search: kUnmergeBatch tokens per lane are requested together.
+constexpr int kUnmergeBatch = 4;
+struct UnmergeBatch {
+  int32_t row[kUnmergeBatch], token[kUnmergeBatch];   // row < 0: not of this tile
+};
+struct UnmergeSpan {
+  int first, end;
+};
+__device__ __forceinline__ UnmergeSpan unmerge_span(const UnmergeTarget& um, int q0, int n) {
+  return {um.spans[2 * (q0 / kUnmergeGroup)], um.spans[2 * ((q0 + n - 1) / kUnmergeGroup) + 1]};
+}
+template <int NT>
+__device__ __forceinline__ void unmerge_load(UnmergeBatch& b, const UnmergeTarget& um, int h, int q0, int n, int first, int end, int tid) {
+#pragma unroll
+  for (int u = 0; u < kUnmergeBatch; ++u) {
+    const int j = first + u * NT + tid, jc = j < end ? j : end - 1;
+    const int r = um.assign[h * um.N + jc] - q0;
+    b.token[u] = um.pi[jc];
+    b.row[u] = j < end && r >= 0 && r < n ? r : -1;
+  }
+}
+// Rows [q0, q0 + n) of head h, in LDS at `rows`, to their tokens; `b` holds the first batch.  NT threads.
+template <int NT>
+__device__ __forceinline__ void unmerge_store(UnmergeBatch& b, const UnmergeTarget& um, const u32x4* rows, int h, int q0, int n,
+                                              UnmergeSpan sp, int tid) {
+  const int lane = tid & 63, sub = lane >> 3, c = lane & 7;
+  u32x4* __restrict__ out = (u32x4*)um.out;
+  for (int first = sp.first; first < sp.end; first += NT * kUnmergeBatch) {
+    UnmergeBatch cur = b;
+    if (first + NT * kUnmergeBatch < sp.end) unmerge_load<NT>(b, um, h, q0, n, first + NT * kUnmergeBatch, sp.end, tid);
+#pragma unroll
+    for (int u = 0; u < kUnmergeBatch; ++u) {
+      const unsigned long long hit = __builtin_amdgcn_ballot_w64(cur.row[u] >= 0);
+      if (!hit) continue;
+      const int cnt = __popcll(hit);
+      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
+      const int to = 4 * (cur.row[u] >= 0 ? before : cnt + lane - before);      // (every lane has a place of its own)
+      const int r = __builtin_amdgcn_ds_permute(to, cur.row[u] >= 0 ? cur.row[u] : 0), t = __builtin_amdgcn_ds_permute(to, cur.token[u]);
+      // (four rows a lane at a time: one after the other, each waits for two exchanges and an LDS read)
+      for (int i = sub; i - sub < cnt; i += 32) {
+        int ri[4], ti[4];
+        u32x4 x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          ri[k] = __builtin_amdgcn_ds_bpermute(4 * (i + 8 * k), r);
+          ti[k] = __builtin_amdgcn_ds_bpermute(4 * (i + 8 * k), t);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = rows[out_chunk(ri[k], c)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (i + 8 * k < cnt) __builtin_nontemporal_store(x[k], &out[((int64_t)ti[k] * um.H + h) * kRowChunks + c]);
+      }
+    }
+  }
+}
+
+// What is left of a whole tile whose rows lie in LDS: they go to `o_rows`, and to their tokens.
+template <int NT, int BQ>
+__device__ __forceinline__ void unmerge_tile(const UnmergeTarget& um, UnmergeBatch& batch, const u32x4* rows,
+                                             u32x4* __restrict__ o_rows, int h, int q0, int n, int64_t q_base, bool dev_tile, UnmergeSpan span, int tid) {
+#pragma unroll
+  for (int i = 0; i < BQ * kRowChunks / NT; ++i) {
+    const int r = (tid >> 3) + i * (NT / 8), c = tid & 7;
+    if (r >= n) continue;
+    const u32x4 x = rows[out_chunk(r, c)];
+    o_rows[(q_base + q0 + r) * kRowChunks + c] = x;
+    if (dev_tile) {
+      // an outlier query: the one token it belongs to
+      const int64_t token = um.q2_token[q_base + q0 + r];
+      __builtin_nontemporal_store(x, (u32x4*)um.out + (token * um.H + h) * kRowChunks + c);
+    }
+  }
+  if (!dev_tile) unmerge_store<NT>(batch, um, rows, h, q0, n, span, tid);
+}
+
 // 8 KB tiles of LDS of a workgroup: per key group two of K and two of V, and with several key groups room
 // for everybody's accumulators in their place.
 template <int NQ, int NW, int KS>
@@ -926,6 +1026,8 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       }
     }
     __syncthreads();
+    const UnmergeTarget um = unmerge_target();
+    u32x2 o_part[NQ][4 / KS];
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
       float wgt[KS], m = kLowestScore, l = 0.f;
@@ -952,10 +1054,26 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[r] = fmaf(x[r], wgt[k], o[r]);
         }
-        if (row < Mq)
-          *(u32x2*)(o_rows + (q_base + row) * kDHead + 16 * ct + 4 * grp) =
-              u32x2{pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+        o_part[qt][c] = u32x2{pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+        if (row < Mq && !um.out) *(u32x2*)(o_rows + (q_base + row) * kDHead + 16 * ct + 4 * grp) = o_part[qt][c];
       }
+    }
+    if (um.out) {
+      const int n = Mq - q0 < BQ ? Mq - q0 : BQ;
+      const UnmergeSpan span = unmerge_span(um, q0, n);
+      UnmergeBatch batch;
+      unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+      u32x4* s_rows = (u32x4*)lds;
+      __syncthreads();                              // everybody has read the groups' sums
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) {
+        const int r = (rwave * NQ + qt) * 16 + l16;
+#pragma unroll
+        for (int c = 0; c < 4 / KS; ++c)
+          *((u32x2*)&s_rows[out_chunk(r, 2 * (key_group * (4 / KS) + c) + (grp >> 1))] + (grp & 1)) = o_part[qt][c];
+      }
+      __syncthreads();
+      unmerge_tile<NT, BQ>(um, batch, s_rows, (u32x4*)o_rows, h, q0, n, q_base, false, span, tid);
     }
     return;
   }
@@ -984,6 +1102,31 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   }
 
   // ---- normalise and store ---------------------------------------------------------------------
+  const UnmergeTarget um = unmerge_target();
+  if (um.out) {
+    // stage 4 as well.  (Every wave is through with the tile buffers: the barrier behind the last product.)
+    const int n = Mq - q0 < BQ ? Mq - q0 : BQ;
+    UnmergeSpan span = {0, 0};
+    UnmergeBatch batch;
+    if (!dev_tile) {
+      span = unmerge_span(um, q0, n);
+      unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+    }
+    u32x4* s_rows = (u32x4*)lds;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      const float inv = 1.0f / l_tot[qt];
+      const int r = (rwave * NQ + qt) * 16 + l16;
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct)
+        *((u32x2*)&s_rows[out_chunk(r, 2 * ct + (grp >> 1))] + (grp & 1)) =
+            u32x2{pack_bf16x2(w.o_acc[ct][qt][0] * inv, w.o_acc[ct][qt][1] * inv),
+                  pack_bf16x2(w.o_acc[ct][qt][2] * inv, w.o_acc[ct][qt][3] * inv)};
+    }
+    __syncthreads();
+    unmerge_tile<NT, BQ>(um, batch, s_rows, (u32x4*)o_rows, h, q0, n, q_base, dev_tile, span, tid);
+    return;
+  }
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     const float inv = 1.0f / l_tot[qt];
@@ -1067,7 +1210,7 @@ constexpr int kReduceRows = 64;
 constexpr int kReduceBatch = 3;
 __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnArgs a) {
   constexpr int BQ = kAttnTileRows;
-  __shared__ __align__(16) uint32_t s_out[kReduceRows * 32];   // the normalised bf16 rows, for whole-line stores
+  __shared__ u32x4 s_out[kReduceRows * kRowChunks];   // the normalised bf16 rows, for whole-line stores
   const int e = blockIdx.x >> 2, part = blockIdx.x & 3, tid = threadIdx.x;
   const SplitTile t = split_tile(a.sp, e);
   const int64_t q_base = a.q_off[t.head];
@@ -1077,6 +1220,13 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
   const int np = t.last_share - t.first_share + 1;
   // consecutive shares of one tile have consecutive slots
   const int64_t row0 = (int64_t)split_slot(t.first_share, e) * BQ;     // segment p: rows from row0 + p * BQ
+  const int q_part = t.q0 + part * kReduceRows, n_part = rows - part * kReduceRows < kReduceRows ? rows - part * kReduceRows : kReduceRows;
+  UnmergeSpan span = {0, 0};
+  UnmergeBatch batch;
+  if (a.um.out) {
+    span = unmerge_span(a.um, q_part, n_part);
+    unmerge_load<256>(batch, a.um, t.head, q_part, n_part, span.first, span.end, tid);
+  }
   // thread -> row r = tid % 64 of the part and the 16-byte output chunks c0, c0 + 4
   const int r = part * kReduceRows + (tid & 63), c0 = tid >> 6;
   const int rr = r < rows ? r : rows - 1;          // a row past the end reads a valid row and stores nothing
@@ -1128,16 +1278,16 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
     u32x4 o;
 #pragma unroll
     for (int q = 0; q < 4; ++q) o[q] = pack_bf16x2(acc[i][2 * q] * inv, acc[i][2 * q + 1] * inv);
-    *(u32x4*)&s_out[(tid & 63) * 32 + (c0 + 4 * i) * 4] = o;
+    s_out[out_chunk(tid & 63, c0 + 4 * i)] = o;
   }
   __syncthreads();
   // whole 128-byte rows: 8 threads per row
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int lr = (tid >> 3) + 32 * i, ch = tid & 7;
-    if (part * kReduceRows + lr < rows)
-      ((u32x4*)a.o)[(q_base + t.q0 + part * kReduceRows + lr) * kRowChunks + ch] = *(const u32x4*)&s_out[lr * 32 + ch * 4];
+    if (lr < n_part) ((u32x4*)a.o)[(q_base + q_part + lr) * kRowChunks + ch] = s_out[out_chunk(lr, ch)];
   }
+  if (a.um.out) unmerge_store<256>(batch, a.um, s_out, t.head, q_part, n_part, span, tid);
 }
 
 // compute units of the current device (asked once per device)
@@ -1268,7 +1418,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
                                  const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
                                  const void* q2, void* o2, const int32_t* q2_off_dev, const int32_t* tiles,
                                  int max_tiles, bool log2_keys, hipStream_t stream, void* scratch,
-                                 int64_t scratch_bytes) {
+                                 int64_t scratch_bytes, const UnmergeTarget* unmerge) {
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
   a.q = (const bf16_t*)q;
@@ -1277,6 +1427,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
   a.H = H;
+  if (unmerge) a.um = *unmerge;
   a.dev_q_off = q2_off_dev;
   a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
@@ -1290,7 +1441,8 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
 
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,
                             const int64_t* q_off_host, const int64_t* k_off_host, int H,
-                            float scale, bool log2_keys, hipStream_t stream, void* scratch, int64_t scratch_bytes) {
+                            float scale, bool log2_keys, hipStream_t stream, void* scratch, int64_t scratch_bytes,
+                            const UnmergeTarget* unmerge) {
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
   a.q = (const bf16_t*)q;
@@ -1299,6 +1451,7 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   a.o = (bf16_t*)o;
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
   a.H = H;
+  if (unmerge) a.um = *unmerge;
   const HeadRows rows = all_rows(q_off_host, H);
   const int64_t cus = compute_units();
   AttnRoute route;

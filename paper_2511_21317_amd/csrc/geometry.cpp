@@ -166,7 +166,28 @@ int build_tables(const httm_geom_t& g, bool with_pi, HostTables* out) {
   }
   t.M_q = mq;
   t.M_k = mk;
+  if (with_pi) t.spans_q = unmerge_spans(t.items_q, mq);
   return HTTM_OK;
+}
+
+std::vector<int32_t> unmerge_spans(const std::vector<WorkItem>& items, int64_t M) {
+  const int64_t groups = (M + kUnmergeGroup - 1) / kUnmergeGroup;
+  std::vector<int32_t> spans((size_t)(2 * groups));
+  size_t i = 0;   // work item of the row at hand
+  auto item_of = [&](int64_t row) -> const WorkItem& {
+    while (row >= (int64_t)items[i].moff + items[i].k) ++i;
+    return items[i];
+  };
+  for (int64_t g = 0; g < groups; ++g) {
+    const int64_t first = g * kUnmergeGroup, last = (first + kUnmergeGroup < M ? first + kUnmergeGroup : M) - 1;
+    const WorkItem& a = item_of(first);
+    const bool own_a = a.kd == a.n;         // every token a cluster, in order
+    spans[(size_t)(2 * g)] = a.start + (own_a ? (int32_t)(first - a.moff) : 0);
+    const WorkItem& b = item_of(last);
+    const bool own_b = b.kd == b.n;
+    spans[(size_t)(2 * g + 1)] = b.start + (own_b ? (int32_t)(last - b.moff) + 1 : b.n);
+  }
+  return spans;
 }
 
 int workspace_layout(const httm_geom_t& g, const HostTables& t, httm_workspace_layout_t* out) {

@@ -44,7 +44,14 @@ struct HostTables {
   std::vector<int32_t> block_kq, block_kk, block_offq, block_offk;
   std::vector<int32_t> block_src0, block_dims;  // WorkItem.src0 / dims of every real block (with pi only)
   std::vector<WorkItem> items_q, items_k;  // prefix pseudo-blocks followed by the real blocks
+  std::vector<int32_t> spans_q;            // unmerge_spans(items_q, M_q) (with pi only)
 };
+
+// For every group of kUnmergeGroup consecutive merged rows: the reordered positions [first, end) of the tokens
+// that may be members of one of them - the work items of the group's first and last row and what lies between;
+// exactly the group's own where an item keeps every token.
+constexpr int32_t kUnmergeGroup = 32;
+std::vector<int32_t> unmerge_spans(const std::vector<WorkItem>& items, int64_t M);
 
 // tokens per pseudo-block of the special prefix, in a plan whose merging blocks have at most
 // `block` tokens

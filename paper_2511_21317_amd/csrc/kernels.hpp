@@ -93,6 +93,7 @@ struct OutlierBuffers {      // all device memory, owned by the plan
   int32_t* wg_cnt;           // [H][n_items / kOutlierCountItemsMin + 1] the same summed per workgroup of the count kernel
   int32_t* item_base;        // [H][n_items] first outlier row of a work item, relative to its head
   int32_t* tiles;            // [1 + 2 * max_tiles]: n, then (head, first row) per attention tile
+  int32_t* token;            // [budget] input position of the token behind every row of q_out
   int32_t max_tiles;
 };
 // tau = the largest of the H*N deviations that is not among the `budget` largest; then the
@@ -133,6 +134,18 @@ hipError_t launch_match_f32(const float* xbar, const int32_t* pi, const WorkItem
 
 // ---- stage 3 -------------------------------------------------------------------------------
 constexpr int kAttnMaxHeads = HTTM_MAX_HEADS;
+// Where the rows of a launch go besides `o`: stage 4 at the end of every query tile, for the layer.  The
+// tokens that read a merged row sit in the row's merging block, and the blocks are contiguous in reordered
+// order, so a tile looks for its tokens in the positions that `spans` gives and no list of members is kept.
+struct UnmergeTarget {
+  void* out;                // [N, H * 64] bf16 in input order, or nullptr: `o` only
+  const int32_t* assign;    // [H][N] cluster of every reordered token (negative: an outlier query)
+  const int32_t* pi;        // [N]
+  const int32_t* spans;     // [2 * ceil(M / kUnmergeGroup)], see unmerge_spans()
+  const int32_t* q2_token;  // input position of every row of the device-described queries
+  int64_t N;
+  int32_t H;
+};
 // log2_keys: the keys carry the factor scale * log2(e) already (stage 2 with
 // MatchMergeStream.xm_scale), `scale` is ignored and the weights are exp2 of the raw scores.
 constexpr float kLog2KeyScale = 0.125f * 1.4426950408889634f;   // log2(e) / sqrt(d_head)
@@ -142,7 +155,7 @@ constexpr float kLog2KeyScale = 0.125f * 1.4426950408889634f;   // log2(e) / sqr
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,
                             const int64_t* q_off_host, const int64_t* k_off_host, int H,
                             float scale, bool log2_keys, hipStream_t stream, void* scratch = nullptr,
-                            int64_t scratch_bytes = 0);
+                            int64_t scratch_bytes = 0, const UnmergeTarget* unmerge = nullptr);
 // Bytes of scratch launch_attention would use for these head lengths if it had them (0: every tile
 // runs whole), and the library's own scratch for callers that cannot allocate: a static device
 // array of kAttnStaticScratchBytes, whose address on the current device *ptr receives.
@@ -159,7 +172,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
                                  const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
                                  const void* q2, void* o2, const int32_t* q2_off_dev, const int32_t* tiles,
                                  int max_tiles, bool log2_keys, hipStream_t stream, void* scratch = nullptr,
-                                 int64_t scratch_bytes = 0);
+                                 int64_t scratch_bytes = 0, const UnmergeTarget* unmerge = nullptr);
 hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o,
                                       const int32_t* q_off_dev, const int32_t* tiles, int max_tiles,
                                       const int64_t* k_off_host, int H, float scale, bool log2_keys,

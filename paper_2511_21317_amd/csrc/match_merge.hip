@@ -718,6 +718,7 @@ void outlier_refine_kernel(const RefineArgs a) {
     for (int w = 0; w < wave; ++w) r += s_wout[w];
     const int row = a.b.offsets[h] + a.b.item_base[h * a.n_items + blockIdx.x] + r;
     assign[tid] = -1 - row;
+    a.b.token[row] = a.pi[it.start + tid];
     u32x4* __restrict__ dst = (u32x4*)a.q_out + (int64_t)row * kRowChunks;
 #pragma unroll
     for (int c = 0; c < kRowChunks; ++c) dst[c] = *(const u32x4*)(tile + tid * kLdsRowBytes + c * 16);

@@ -398,6 +398,7 @@ struct RefineExtra {
   const int32_t* offsets;     // [H + 1] first outlier row of a head
   const int32_t* item_base;   // [H][n_items] first outlier row of a work item inside its head
   void* q_out;                // [budget, 64] bf16
+  int32_t* token;             // [budget] input position of the token behind every row of q_out
 };
 
 // Dynamic LDS: s_src[nmax] int32 | s_off[kmax + 1] int32 | s_cur[kmax] int32 | s_any[nmax] u16 |
@@ -503,6 +504,7 @@ __global__ __launch_bounds__(kBaThreads) void big_aggregate_kernel(const MatchMe
         const int row = base + before +
                         __builtin_amdgcn_mbcnt_hi((uint32_t)(ob >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ob, 0u));
         assign[t] = -1 - row;
+        rx.token[row] = s_src[t];
         const u32x4* __restrict__ srcrow = (const u32x4*)(x + (uint32_t)s_src[t] * kRowBytes);
         u32x4* __restrict__ dst = (u32x4*)rx.q_out + (int64_t)row * kRowChunks;
         u32x4 r8[kRowChunks];
@@ -780,7 +782,7 @@ hipError_t launch_outlier_refine_big(const RefineArgs& r, int max_k, hipStream_t
   a.s[0].n_items = r.n_items;
   a.s[0].M = r.M;
   a.s[0].eps = const_cast<float*>(r.eps);
-  const RefineExtra rx = {r.b.state, r.b.offsets, r.b.item_base, r.q_out};
+  const RefineExtra rx = {r.b.state, r.b.offsets, r.b.item_base, r.q_out, r.b.token};
   const int nmax = r.max_block, kmax = max_k > 0 ? max_k : r.max_block;
   hipError_t e = allow_big_lds<true>();
   if (e != hipSuccess) return e;

@@ -1,6 +1,8 @@
 // Stage 1 (temporal reordering, paper Sec. 3.3) and stage 4 (unmerge, Sec. 3.2 Eq. 5-7, with the
 // inverse reordering of Sec. 3.3 fused into the store addresses).
 //
+// (httm_layer_forward runs stage 4 inside stage 3's kernels instead, see attention.hip.)
+//
 // Both are pure data movement of 128-byte token rows and are bound by HBM bandwidth.  A row is
 // moved by 8 adjacent lanes, 16 bytes each, so every wavefront load/store instruction touches
 // whole 128-byte lines; each thread keeps four independent rows in flight.

@@ -1,0 +1,57 @@
+"""Stage 4 at the end of stage 3's tiles (httm_layer_forward) against the stage-4 kernel on the same merged
+outputs and assignments: the copies must agree bit for bit, whatever the tile size, the blocks and the row counts."""
+import pytest
+import torch
+
+import paper_2511_21317_amd as httm
+from gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+# name, S, Hp, Wp, b, T, rho_q, rho_kv, H, options
+CASES = [
+    ("one_token", 1, 1, 1, 1, 1, 0.0, 0.0, 1, {}),                                   # a tile with a single row
+    ("tiles128", 3, 19, 23, 4, 2, 0.5, 0.5, 16, {}),
+    ("tiles128_span_of_one_block", 2, 16, 16, 16, 2, 0.6, 0.2, 3, {}),               # 512-token blocks: a tile inside one
+    ("groups64", 7, 20, 21, 4, 2, 0.5, 0.4, 4, {}),                                  # keys shared in four groups
+    ("groups128", 20, 21, 21, 4, 2, 0.5, 0.5, 5, {}),
+    ("groups256", 9, 29, 31, 4, 2, 0.55, 0.5, 15, {}),
+    ("segments", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {}),
+    ("segments_plain_keys", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {"log2_keys": False}),
+    ("unmerged", 8, 21, 19, 4, 2, 0.0, 0.0, 16, {"variant": "none"}),                # exact spans, no search
+    ("top_r", 6, 25, 27, 8, 4, 0.4, 0.4, 8, {"dst_frac": 0.25}),
+    ("top_r_nothing_merges", 4, 17, 16, 8, 2, 0.0, 0.0, 6, {"dst_frac": 0.25}),      # all clusters, not in order
+    ("uniform", 5, 22, 20, 5, 3, 0.6, 0.5, 12, {"variant": "uniform"}),
+    ("big_blocks", 31, 9, 37, 128, 30, 0.9, 0.7, 4, {"chunked_blocks": True}),
+    ("big_blocks_little_merged", 30, 8, 17, 128, 30, 0.1, 0.5, 3, {"chunked_blocks": True}),
+    ("outliers", 9, 21, 22, 5, 3, 0.7, 0.6, 8, {"outlier_frac": 0.1}),
+    ("outliers_few", 9, 21, 22, 5, 3, 0.7, 0.6, 8, {"outlier_frac": 0.0003}),
+    ("outliers_segments", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {"outlier_frac": 0.05}),
+    ("outliers_big_blocks", 20, 9, 31, 128, 20, 0.8, 0.7, 4, {"chunked_blocks": True, "outlier_frac": 0.1}),
+    ("anchored", 6, 18, 17, 4, 3, 0.8, 0.8, 7, {"anchor_first_frame": True}),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_layer_outputs_are_the_stage_kernels_copies(case):
+    require_gpu()
+    name, S, Hp, Wp, b, T, rho_q, rho_kv, H, opts = case
+    print(f"[case] {name}", flush=True)
+    plan = httm.Plan(httm.make_geom(S, Hp, Wp, b, T, rho_q, rho_kv, H=H, **{"log2_keys": True, **opts}))
+    gen = torch.Generator(device="cuda").manual_seed(len(name))
+    q, k, v = (torch.randn((H, plan.N, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out = torch.full((plan.N, H * 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = httm.alloc_workspace(plan)
+    for _ in range(2):                                   # (the second call finds the first one's workspace)
+        out.fill_(float("nan"))
+        httm.layer_forward(plan, q, k, v, out, ws)
+    views = httm.workspace_views(plan, ws)
+    want = torch.empty_like(out)
+    if plan.outlier_cap:
+        httm.unmerge_filtered(plan, views["o_m"], views["o_out"], views["assign_q"], want)
+    else:
+        httm.unmerge(plan, views["o_m"], views["assign_q"], want)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    assert bool(torch.isfinite(out.float()).all())
+    plan.close()
