@@ -72,10 +72,14 @@
 // tiles, and attention_split_reduce_kernel adds the pieces of every tile up (attention_split.hpp).
 //
 // Few rows.  With less than a 256-row tile per CU a launch is as long as one workgroup's walk over the
-// keys.  Workgroups with KS key groups walk a KS-th of them (64 rows: 4 waves, 4 groups; 128: 8 waves, 4; 256: 8
-// waves, 2): a wave still owns 64 rows, so its products are as dense and read as little LDS as those of the
-// big tile, and the groups meet in LDS at the end - no scratch memory, no second kernel.  The limits are in
-// choose_attention_route().
+// keys.  Workgroups with KS key groups walk a KS-th of them and the groups meet in LDS at the end - no scratch
+// memory, no second kernel.  Tiles of 32 rows (4 waves, 4 groups), 64 (8 waves, 4), 128 (8 waves, 2) have waves of 32
+// rows: a short walk is a chain of waits (LDS reads at the head of a tile, the tile's arrival, the barrier), which two
+// waves per SIMD or fewer rows per wave shorten more than their reading twice the LDS per product costs.  Long
+// walks are bound by the LDS reads and the products: waves of 64 rows, tiles of 128 (8 waves, 4 groups) and 256 rows
+// (8 waves, 2).  16 heads x 500 x 500 9.2 (128-row tiles of one group) -> 6.7 us, 1000 x 1000 12.1 -> 10.3, 1384 x 1384
+// 16.9 -> 15.3, 1000 x 6000 40.5 (64-row tiles, 4 waves of 64 rows) -> 34.8; a layer of 2 frames of 16 x 16 17.4 ->
+// 14.8.  All times and the choice: choose_key_groups().
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -938,7 +942,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       if (!S && again && piece && !s_high) again = !rest_holds();
     } else {
       // every wave looks at the sums of all rows, so that no second barrier is needed to agree
-      static_assert(NQ * 16 == 64, "a lane per row of a wave");
+      static_assert(NQ * 16 == 64 || NQ * 16 == 32, "a lane (two) per row of a wave");
       if (grp == 0) {
 #pragma unroll
         for (int qt = 0; qt < NQ; ++qt) s_sum[wave][qt * 16 + l16] = l_tot[qt];
@@ -951,7 +955,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
         float sum = 0.f;
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
-          const float part = s_sum[k * RG + r][lane];
+          const float part = s_sum[k * RG + r][lane & (NQ * 16 - 1)];
           sum += part;
           // (groups with shifts of their own: each part; one without a key tile has none)
           if (S && key_tiles(k) < key_tiles(k + 1)) bad = bad || !(part >= kFastSumMin && part <= kFastSumMax);
@@ -1146,7 +1150,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 
 // SHIFT = false: the keys carry the logit scale, weights exp2(s).  SHIFT = true: any keys and scale.
 template <int NQ, int NW, int KS, bool SHIFT>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2 ? 3 : 2, NQ == 2 ? 3 : 2)))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2 && KS == 1 ? 3 : 2, NQ == 2 && KS == 1 ? 3 : 2)))
 void attention_kernel(const AttnArgs a) {
   constexpr int BQ = 16 * NQ * (NW / KS);
   // per key group two tiles of K and two of V: [kv][d], 128-byte rows, chunk-swizzled
@@ -1382,6 +1386,19 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
   return hipGetLastError();
 }
 
+// A launch without a split.
+hipError_t launch_tiles(AttnTiles tiles, AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream) {
+  switch (tiles) {
+    case AttnTiles::kGroups32: return launch_cfg<2, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups64: return launch_cfg<2, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups128: return launch_cfg<2, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups128Wide: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    default: return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream);
+  }
+}
+
 }  // namespace
 
 int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_host, int H) {
@@ -1456,31 +1473,23 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   const int64_t cus = compute_units();
   AttnRoute route;
   choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
-  switch (route.tiles) {
-    case AttnTiles::kGroups64: return launch_cfg<4, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups128: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kRounds: {
-      HeadRows whole = rows, rest = rows;
-      int64_t keep = 0;
-      for (int h = 0; h < H; ++h) keep += rows.count[h] / kAttnTileRows;
-      keep = keep / cus * cus;
-      for (int h = 0; h < H; ++h) {
-        const int64_t n = std::min(rows.count[h] / kAttnTileRows, keep);
-        keep -= n;
-        whole.count[h] = n * kAttnTileRows;
-        rest.first[h] += n * kAttnTileRows;
-        rest.count[h] -= n * kAttnTileRows;
-      }
-      const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
-      if (e != hipSuccess) return e;
-      if (count_rest_tiles(q_off_host, H, cus, 64) <= cus) return launch_cfg<4, 4, 4>(a, log2_keys, rest, k_off_host, H, stream);
-      return launch_cfg<4, 8, 4>(a, log2_keys, rest, k_off_host, H, stream);
-    }
-    case AttnTiles::kTiles256: break;
+  if (route.tiles == AttnTiles::kTiles256)
+    return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, &route, (float*)scratch);
+  if (route.tiles != AttnTiles::kRounds) return launch_tiles(route.tiles, a, log2_keys, rows, k_off_host, H, stream);
+  HeadRows whole = rows, rest = rows;
+  int64_t keep = 0;
+  for (int h = 0; h < H; ++h) keep += rows.count[h] / kAttnTileRows;
+  keep = keep / cus * cus;
+  for (int h = 0; h < H; ++h) {
+    const int64_t n = std::min(rows.count[h] / kAttnTileRows, keep);
+    keep -= n;
+    whole.count[h] = n * kAttnTileRows;
+    rest.first[h] += n * kAttnTileRows;
+    rest.count[h] -= n * kAttnTileRows;
   }
-  return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, &route, (float*)scratch);
+  const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
+  if (e != hipSuccess) return e;
+  return launch_tiles(route.rest, a, log2_keys, rest, k_off_host, H, stream);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------

@@ -213,10 +213,12 @@ inline int64_t split_slots(const SplitPlan& p) { return p.n_tiles ? p.slots : 0;
 enum class AttnTiles {
   kTiles256,    // 256-row tiles; with a split those in excess run in segments
   kTiles128,
-  kGroups64,    // 64- / 128- / 256-row tiles whose waves share the keys in four / four / two groups
+  kGroups32,    // tiles of so many rows whose waves share the keys in four / four / two / four / two groups; waves of 32
+  kGroups64,    // rows but for the last two, whose 64-row waves read less LDS a product and start and end later
   kGroups128,
+  kGroups128Wide,
   kGroups256,
-  kRounds,      // whole rounds of 256-row tiles, then the rest in kGroups64 or kGroups128: two launches
+  kRounds,      // whole rounds of 256-row tiles, then the rest in key groups: two launches
 };
 
 struct AttnRoute {
@@ -224,6 +226,7 @@ struct AttnRoute {
   SplitPlan split;          // kTiles256 only; n_tiles == 0: every tile runs whole
   int64_t kept_full;        // full tiles that stay whole, and partial tiles that run in segments
   int32_t split_ragged;
+  AttnTiles rest;           // kRounds: what the rest runs in
 };
 
 // 128-row tiles that run at once (three workgroups per CU): a problem with no more of them runs those
@@ -235,7 +238,7 @@ inline int64_t count_tiles(const int64_t* q_off, int H, int rows) {
   return n;
 }
 
-// Tiles of `rows` (128 or 64) rows that are left of the heads when whole rounds of 256-row tiles, the heads' full
+// Tiles of `rows` rows that are left of the heads when whole rounds of 256-row tiles, the heads' full
 // ones in head order, have run.
 inline int64_t count_rest_tiles(const int64_t* q_off, int H, int64_t cus, int rows) {
   int64_t full = 0, n = 0;
@@ -247,6 +250,36 @@ inline int64_t count_rest_tiles(const int64_t* q_off, int H, int64_t cus, int ro
     n += (mq - whole * kAttnTileRows + rows - 1) / rows;
   }
   return n;
+}
+
+// At most one tile of 32, 64, 128 or 256 rows per CU (`count(rows)` of them): the tiles whose waves share the keys, or
+// 128-row tiles of one key group, that take the least time, in tenths of a us, for heads of at most kt key tiles.  A wave
+// walks a quarter (half) of the keys of its tile; the groups' meeting is in the constant.  us at 16 heads (log2 keys), tiles
+// of 32 / 64 / 128 / 128 wide / 256 rows / 128 rows of one group, x where there is more than one a CU:
+//   250 x 250 5.5 / 6.7 / 7.8 / 9.5 / 11.4 / 7.1, 500 x 500 6.7 / 8.0 / 9.6 / 11.4 / 14.6 / 9.2, 500 x 4000 22.5 / 23.7 / 34.7 /
+//   32.1 / 51 / 45.6, 1000 x 1000 x / 10.3 / 12.7 / 14.5 / 19.8 / 13.6, 1000 x 6000 x / 34.8 / 50 / 45 / 73 / 70, 1384 x 1384
+//   x / x / 15.3 / 17.8 / 23.7 / 17.0, 2000 x 500 x / x / 10.2 / 12.0 / 15.1 / 9.8, 2000 x 4500 x / x / 40.1 / 39.2 / 57 / 53, 2000
+//   x 14000 x / x / 108 / 99 / 156 / 150, 4000 x 500 x / x / x / x / 15.8 / 13.6, 4000 x 1500 x / x / x / x / 27.4 / 28.1.
+// Plain keys take 5 to 15 % more everywhere.
+struct AttnGroups {
+  AttnTiles tiles;
+  int64_t time;
+};
+template <typename Count>
+inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt) {
+  AttnGroups best = {AttnTiles::kTiles256, INT64_MAX};
+  auto offer = [&](AttnTiles tiles, int rows, int64_t waves_of_tiles, int64_t time) {
+    if (time < best.time && count(rows) <= waves_of_tiles * cus) best = {tiles, time};
+  };
+  const int64_t half = (kt + 1) / 2, quarter = (kt + 3) / 4;
+  offer(AttnTiles::kGroups32, 32, 1, 45 + 11 * quarter);
+  offer(AttnTiles::kGroups64, 64, 1, 58 + 11 * quarter);
+  offer(AttnTiles::kGroups128, 128, 1, 60 + 19 * half / 2);
+  offer(AttnTiles::kGroups128Wide, 128, 1, 86 + 17 * quarter);
+  offer(AttnTiles::kGroups256, kAttnTileRows, 1, 95 + 15 * half);
+  offer(AttnTiles::kTiles128, 128, 1, 49 + 11 * kt / 2);
+  offer(AttnTiles::kTiles128, 128, 2, 66 + 9 * kt);
+  return best;
 }
 
 // The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).
@@ -267,43 +300,27 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
     r.split_ragged = 0;
   };
   if (r.split.n_tiles == 0 || split_slots(r.split) * kAttnSlotWords > scratch_words) no_split();
-  // At most one 64-, 128- or 256-row tile per CU: workgroups whose waves share the keys, unless the walk is so short
-  // that the groups' meeting costs more (2 us).  16 heads against the 128-row tiles of one key group: 64 rows
-  // 266 x 266 10.8 : 8.9 us, 266 x 1000 12.9 : 14.5, 700 x 700 12.0 : 12.0, 1024 x 1024 14.0 : 15.4; 128 rows
-  // 1400 x 1400 18.1 : 17.2, 2048 x 2048 22.1 : 22.8, 2048 x 8192 63 : 91; 256 rows 3000 x 3000 41 : 44, 4096 x 4096
-  // 59 : 62, 4096 x 10000 134 : 143.
-  // Such a workgroup walks a quarter (half) of the keys however many CUs are idle; segments cut the walk over
-  // all CUs and cost a second kernel and the traffic of the partial results.  The shorter of the two, in tenths
-  // of a us from both sides' times at 1 to 16 heads of 64 to 4000 rows and 1600 to 28000 keys, groups : segments:
-  // 16 heads 64 x 2500 20.3 : 20.8, x 4000 27.5 : 25.3, 250 x 12000 74 : 38, 500 x 4000 28 : 36, x 6000 41 : 40, 1000 x 6000
-  // 41 : 48, x 9000 59 : 58, x 28000 165 : 123, 2000 x 14000 101 : 124, 3000 x 9000 106 : 120, x 28000 333 : 292; one head
-  // of 1000 x 28000 158 : 39.
+  // Workgroups that share the keys among their waves walk a quarter (half) of them however many CUs are idle; segments
+  // cut the walk over all CUs and cost a second kernel and the traffic of the partial results.  The shorter of the
+  // two, in tenths of a us from segments' times at 1 to 16 heads of 64 to 4000 rows and 1600 to 28000 keys: 16 heads 64 x
+  // 4000 25.3, 250 x 12000 38, 500 x 4000 36, x 6000 40, 1000 x 6000 48, x 9000 58, x 28000 123, 2000 x 14000 124, 3000 x 9000 120,
+  // x 28000 292; one head of 1000 x 28000 39.
   const int64_t kt = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
-  AttnTiles groups = AttnTiles::kTiles256;
-  int64_t groups_time = 0;
-  if (keys >= 768 && count_tiles(q_off, H, 64) <= cus) {
-    groups = AttnTiles::kGroups64;
-    groups_time = 70 + 14 * ((kt + 3) / 4);
-  } else if (keys >= 2048 && count_tiles(q_off, H, 128) <= cus) {
-    groups = AttnTiles::kGroups128;
-    groups_time = 80 + 16 * ((kt + 3) / 4);
-  } else if (keys >= 2048 && count_tiles(q_off, H, kAttnTileRows) <= cus) {
-    groups = AttnTiles::kGroups256;
-    groups_time = 60 + 15 * ((kt + 1) / 2);
-  }
+  const AttnGroups groups = choose_key_groups([&](int rows) { return count_tiles(q_off, H, rows); }, cus, kt);
   const int64_t split_time = 120 + split_slots(r.split) / 2 + (r.split.shares > cus ? 15 : 9) * (int64_t)r.split.share_units;
-  if (groups != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups_time <= split_time)) {
+  if (groups.tiles != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups.time <= split_time)) {
     no_split();
-    r.tiles = groups;
+    r.tiles = groups.tiles;
     return;
   }
   if (r.split.n_tiles > 0) return;
-  // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in tiles of
-  // 128 (64) rows whose keys are cut in four, if those are one round: a half (quarter) of a round instead
+  // No split.  Whole rounds of 256-row tiles first; what is left - the last rows of the heads - in smaller tiles whose
+  // keys are cut in four or two, if those are one round: a half (quarter) of a round instead
   // of a whole one.  From two rounds on (a lone tile on a CU has 0.8 of the rate of a pair): 16 heads of 9000
   // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 495, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
   if (full >= 2 * cus && count_rest_tiles(q_off, H, cus, 128) <= cus) {
     r.tiles = AttnTiles::kRounds;
+    r.rest = choose_key_groups([&](int rows) { return count_rest_tiles(q_off, H, cus, rows); }, cus, kt).tiles;
     return;
   }
   // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a

@@ -11,10 +11,12 @@ pytestmark = pytest.mark.gpu
 # name, S, Hp, Wp, b, T, rho_q, rho_kv, H, options
 CASES = [
     ("one_token", 1, 1, 1, 1, 1, 0.0, 0.0, 1, {}),                                   # a tile with a single row
-    ("tiles128", 3, 19, 23, 4, 2, 0.5, 0.5, 16, {}),
-    ("tiles128_span_of_one_block", 2, 16, 16, 16, 2, 0.6, 0.2, 3, {}),               # 512-token blocks: a tile inside one
-    ("groups64", 7, 20, 21, 4, 2, 0.5, 0.4, 4, {}),                                  # keys shared in four groups
-    ("groups128", 20, 21, 21, 4, 2, 0.5, 0.5, 5, {}),
+    ("groups32", 2, 16, 16, 4, 2, 0.5, 0.5, 16, {}),                                 # keys shared in four groups
+    ("groups32_span_of_one_block", 2, 16, 16, 16, 2, 0.6, 0.2, 3, {}),               # 512-token blocks: a tile inside one
+    ("groups64", 3, 19, 23, 4, 2, 0.5, 0.5, 16, {}),
+    ("groups128", 7, 20, 21, 4, 2, 0.5, 0.4, 16, {}),
+    ("groups128_wide", 20, 21, 21, 4, 2, 0.5, 0.5, 5, {}),
+    ("tiles128", 9, 25, 24, 4, 2, 0.5, 0.9, 16, {}),
     ("groups256", 9, 29, 31, 4, 2, 0.55, 0.5, 15, {}),
     ("segments", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {}),
     ("segments_plain_keys", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {"log2_keys": False}),
