@@ -61,16 +61,29 @@ struct SplitSegment {
   int32_t slot;         // where its partial results go
 };
 
+// (Device code asks for all groups at once, a lane each: one after the other they are 20 dependent reads of cold
+// argument memory.  The plan has at least one group there.)
 __host__ __device__ inline int split_group_of_tile(const SplitPlan& p, int e) {
+#ifdef __HIP_DEVICE_COMPILE__
+  static_assert(kAttnSplitGroups <= 64, "a lane per group");
+  const int g = threadIdx.x & 63;
+  return __popcll(__builtin_amdgcn_ballot_w64(g < p.n_groups && p.grp[g].tile0 <= e)) - 1;
+#else
   int g = 0;
   while (g + 1 < p.n_groups && p.grp[g + 1].tile0 <= e) ++g;
   return g;
+#endif
 }
 
 // The tile of the excess set that unit `unit` (0 <= unit < p.units) belongs to.
 __host__ __device__ inline int split_tile_of_unit(const SplitPlan& p, int unit) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const int l = threadIdx.x & 63;
+  const int g = __popcll(__builtin_amdgcn_ballot_w64(l < p.n_groups && p.grp[l].cum <= unit)) - 1;
+#else
   int g = 0;
   while (g + 1 < p.n_groups && p.grp[g + 1].cum <= unit) ++g;
+#endif
   return p.grp[g].tile0 + (unit - p.grp[g].cum) / p.grp[g].kt;
 }
 
