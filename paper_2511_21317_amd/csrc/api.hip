@@ -154,7 +154,7 @@ int run_match_merge_filtered(const httm_plan_t* p, const void* q, const void* k,
                            st, eps_q);
   if (rc != HTTM_OK) return rc;
   HTTM_HIP(launch_outlier_select(eps_q, p->geom.H, p->sizes.N, p->outlier_cap, p->d_items_q,
-                                 p->n_items, (int)p->sizes.max_block, p->ob, kAttnDevTileRows, st));
+                                 p->n_items, (int)p->sizes.max_block, p->ob, p->ob.tile_rows, st));
   RefineArgs r;
   std::memset(&r, 0, sizeof(r));
   r.x = q;
@@ -184,8 +184,8 @@ int run_attention_outliers(const httm_plan_t* p, const void* q_out, const void* 
                            void* o_out, hipStream_t st) {
   int64_t k_off[HTTM_MAX_HEADS + 1];
   for (int h = 0; h <= p->geom.H; ++h) k_off[h] = (int64_t)h * p->sizes.M_k;
-  HTTM_HIP(launch_attention_dev_tiles(q_out, k_m, v_m, o_out, p->ob.offsets, p->ob.tiles,
-                                      p->ob.max_tiles, k_off, p->geom.H, 0.125f, log2_keys(p), st));
+  const DevTiles dev = {p->ob.offsets, p->ob.tiles, p->ob.max_tiles, p->ob.tile_kind};
+  HTTM_HIP(launch_attention_dev_tiles(q_out, k_m, v_m, o_out, dev, k_off, p->geom.H, 0.125f, log2_keys(p), st));
   return HTTM_OK;
 }
 
@@ -292,7 +292,8 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
   p->outlier_cap = p->sizes.outlier_cap;
   if (rc == HTTM_OK && p->outlier_cap > 0) {
     OutlierBuffers& b = p->ob;
-    b.max_tiles = (int32_t)(p->outlier_cap / kAttnDevTileRows + g->H);
+    choose_dev_tiles(p->outlier_cap, p->sizes.M_q, p->sizes.M_k, g->H, &b.tile_kind, &b.tile_rows);
+    b.max_tiles = (int32_t)(p->outlier_cap / b.tile_rows + g->H);
     const size_t words = sizeof(SelectState) / 4 + 3 * 2048 + (size_t)g->H * 2 + 1 +
                          2 * (size_t)g->H * p->n_items + (size_t)g->H * (p->n_items / kOutlierCountItemsMin + 1) + 1 +
                          2 * (size_t)b.max_tiles + (size_t)p->outlier_cap;
@@ -557,10 +558,10 @@ int httm_layer_forward(const httm_plan_t* p, const void* q, const void* k, const
   // (with stage 4 and the inverse reorder at the end of its tiles)
   const UnmergeTarget um = {out, assign_q, p->d_pi, p->d_spans, p->ob.token, p->sizes.N, H};
   if (filtered) {
-    // Alg. 1: the outlier queries attend on their own - same launch, workgroups appended to the grid
-    HTTM_HIP(launch_attention_both(q_m, k_m, v_m, o_m, q_off, k_off, H, 0.125f, q_out, o_out, p->ob.offsets,
-                                   p->ob.tiles, p->ob.max_tiles, log2_keys(p), st, ws + p->ws.attn_split,
-                                   attention_scratch_bytes(H), &um));
+    // Alg. 1: the outlier queries attend on their own
+    const DevTiles dev = {p->ob.offsets, p->ob.tiles, p->ob.max_tiles, p->ob.tile_kind};
+    HTTM_HIP(launch_attention_both(q_m, k_m, v_m, o_m, q_off, k_off, H, 0.125f, q_out, o_out, dev, log2_keys(p), st,
+                                   ws + p->ws.attn_split, attention_scratch_bytes(H), &um));
   } else {
     HTTM_HIP(launch_attention(q_m, k_m, v_m, o_m, q_off, k_off, H, 0.125f, log2_keys(p), st, ws + p->ws.attn_split,
                               attention_scratch_bytes(H), &um));

@@ -1064,9 +1064,12 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     }
     if (um.out) {
       const int n = Mq - q0 < BQ ? Mq - q0 : BQ;
-      const UnmergeSpan span = unmerge_span(um, q0, n);
+      UnmergeSpan span = {0, 0};
       UnmergeBatch batch;
-      unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+      if (!dev_tile) {
+        span = unmerge_span(um, q0, n);
+        unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+      }
       u32x4* s_rows = (u32x4*)lds;
       __syncthreads();                              // everybody has read the groups' sums
 #pragma unroll
@@ -1077,7 +1080,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
           *((u32x2*)&s_rows[out_chunk(r, 2 * (key_group * (4 / KS) + c) + (grp >> 1))] + (grp & 1)) = o_part[qt][c];
       }
       __syncthreads();
-      unmerge_tile<NT, BQ>(um, batch, s_rows, (u32x4*)o_rows, h, q0, n, q_base, false, span, tid);
+      unmerge_tile<NT, BQ>(um, batch, s_rows, (u32x4*)o_rows, h, q0, n, q_base, dev_tile, span, tid);
     }
     return;
   }
@@ -1305,7 +1308,6 @@ int64_t compute_units() {
   return n;
 }
 
-// `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
 template <int NQ, int NW, int KS = 1>
 void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t stream) {
   if (log2_keys)
@@ -1386,16 +1388,17 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
   return hipGetLastError();
 }
 
-// A launch without a split.
-hipError_t launch_tiles(AttnTiles tiles, AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream) {
+// A launch without a split.  `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
+hipError_t launch_tiles(AttnTiles tiles, AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream,
+                        int extra_tiles = 0) {
   switch (tiles) {
-    case AttnTiles::kGroups32: return launch_cfg<2, 4, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups64: return launch_cfg<2, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups128: return launch_cfg<2, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups128Wide: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream);
-    case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream);
-    default: return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream);
+    case AttnTiles::kGroups32: return launch_cfg<2, 4, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kGroups64: return launch_cfg<2, 8, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kGroups128: return launch_cfg<2, 8, 2>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kGroups128Wide: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    default: return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
   }
 }
 
@@ -1407,35 +1410,30 @@ int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_h
   return split_slots(route.split) * kAttnSlotWords * 4;
 }
 
-hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o,
-                                      const int32_t* q_off_dev, const int32_t* tiles, int max_tiles,
-                                      const int64_t* k_off_host, int H, float scale, bool log2_keys,
-                                      hipStream_t stream) {
-  static_assert(kAttnDevTileRows == 16 * 4 * 4, "the device tile list is cut for attention_kernel<4, 4>");
-  if (max_tiles <= 0) return hipSuccess;
-  AttnArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.q = (const bf16_t*)q;
-  a.k = (const bf16_t*)k;
-  a.v = (const bf16_t*)v;
-  a.o = (bf16_t*)o;
-  a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.H = H;
-  for (int h = 0; h <= kAttnMaxHeads; ++h) a.k_off[h] = k_off_host[h < H ? h : H];
-  a.dev_q_off = q_off_dev;
-  a.dev_tiles = tiles;
-  a.q2 = a.q;
-  a.o2 = a.o;
-  a.main_blocks = 0;        // no whole tiles, no segments: every workgroup takes the device-side list
-  launch_kernel<4, 4>(a, log2_keys, (unsigned)max_tiles, stream);
-  return hipGetLastError();
+void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows) {
+  // Next to merged rows in 256-row tiles the others are more of the same in one launch.  Otherwise both are short
+  // launches of their own, in the tiles that are quickest.  Layers with the outlier filter, all in one
+  // launch of 256-row tiles / so: 16 heads x 923 rows and 4961 others 76.1 / 73.2 us, 12 x 450 and 1207 59.2 / 55.6.
+  int64_t q_off[kAttnMaxHeads + 1], k_off[kAttnMaxHeads + 1];
+  for (int h = 0; h <= H; ++h) {
+    q_off[h] = h * M_q;
+    k_off[h] = h * M_k;
+  }
+  const int64_t cus = compute_units();
+  AttnRoute route;
+  choose_attention_route(q_off, k_off, H, cus, attention_scratch_bytes(H) / 4, &route);
+  AttnTiles t = AttnTiles::kTiles256;
+  if (route.tiles != AttnTiles::kTiles256)
+    t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile).tiles;
+  *kind = (int32_t)t;
+  *tile_rows = t == AttnTiles::kGroups32 ? 32 : t == AttnTiles::kGroups64 ? 64
+             : t == AttnTiles::kTiles256 || t == AttnTiles::kGroups256 ? kAttnTileRows : 128;
 }
 
-hipError_t launch_attention_both(const void* q, const void* k, const void* v, void* o,
-                                 const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
-                                 const void* q2, void* o2, const int32_t* q2_off_dev, const int32_t* tiles,
-                                 int max_tiles, bool log2_keys, hipStream_t stream, void* scratch,
-                                 int64_t scratch_bytes, const UnmergeTarget* unmerge) {
+hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o, const DevTiles& dev,
+                                      const int64_t* k_off_host, int H, float scale, bool log2_keys,
+                                      hipStream_t stream, const UnmergeTarget* unmerge) {
+  if (dev.max_tiles <= 0) return hipSuccess;
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
   a.q = (const bf16_t*)q;
@@ -1445,15 +1443,40 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
   a.H = H;
   if (unmerge) a.um = *unmerge;
-  a.dev_q_off = q2_off_dev;
-  a.dev_tiles = max_tiles > 0 ? tiles : nullptr;
+  a.dev_q_off = dev.q_off;
+  a.dev_tiles = dev.tiles;
+  a.q2 = a.q;
+  a.o2 = a.o;
+  HeadRows none = {};       // no whole tiles, no segments: every workgroup takes the device-side list
+  return launch_tiles((AttnTiles)dev.kind, a, log2_keys, none, k_off_host, H, stream, dev.max_tiles);
+}
+
+hipError_t launch_attention_both(const void* q, const void* k, const void* v, void* o,
+                                 const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
+                                 const void* q2, void* o2, const DevTiles& dev, bool log2_keys, hipStream_t stream,
+                                 void* scratch, int64_t scratch_bytes, const UnmergeTarget* unmerge) {
+  AttnRoute route;
+  choose_attention_route(q_off_host, k_off_host, H, compute_units(), scratch ? scratch_bytes / 4 : 0, &route);
+  if (route.tiles != AttnTiles::kTiles256 || dev.kind != (int32_t)AttnTiles::kTiles256) {
+    const hipError_t e = launch_attention(q, k, v, o, q_off_host, k_off_host, H, scale, log2_keys, stream, scratch, scratch_bytes, unmerge);
+    if (e != hipSuccess) return e;
+    return launch_attention_dev_tiles(q2, k, v, o2, dev, k_off_host, H, scale, log2_keys, stream, unmerge);
+  }
+  AttnArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.q = (const bf16_t*)q;
+  a.k = (const bf16_t*)k;
+  a.v = (const bf16_t*)v;
+  a.o = (bf16_t*)o;
+  a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
+  a.H = H;
+  if (unmerge) a.um = *unmerge;
+  a.dev_q_off = dev.q_off;
+  a.dev_tiles = dev.max_tiles > 0 ? dev.tiles : nullptr;
   a.q2 = (const bf16_t*)q2;
   a.o2 = (bf16_t*)o2;
-  AttnRoute route;
-  plan_attention_split(q_off_host, k_off_host, H, compute_units(), &route.split, &route.kept_full, &route.split_ragged);
-  const bool fits = scratch && split_slots(route.split) * kAttnSlotWords <= scratch_bytes / 4;
-  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, max_tiles > 0 ? max_tiles : 0,
-                          fits ? &route : nullptr, (float*)scratch);
+  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, dev.max_tiles > 0 ? dev.max_tiles : 0,
+                          &route, (float*)scratch);
 }
 
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,

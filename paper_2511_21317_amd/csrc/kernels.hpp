@@ -95,6 +95,8 @@ struct OutlierBuffers {      // all device memory, owned by the plan
   int32_t* tiles;            // [1 + 2 * max_tiles]: n, then (head, first row) per attention tile
   int32_t* token;            // [budget] input position of the token behind every row of q_out
   int32_t max_tiles;
+  int32_t tile_kind;         // the kernel that takes the tiles (an AttnTiles), see choose_dev_tiles()
+  int32_t tile_rows;
 };
 // tau = the largest of the H*N deviations that is not among the `budget` largest; then the
 // outlier counts per (work item, head), their prefix offsets and the tile list of the second
@@ -165,18 +167,23 @@ hipError_t attention_static_scratch(void** ptr);
 // Query rows and tiles are described by device memory (the outlier queries of Sec. 3.4, whose
 // number per head is only known on the device): q / o rows of head h are
 // [q_off_dev[h], q_off_dev[h+1]); tiles[0] tiles follow in `tiles` as (head, first row) pairs.
-constexpr int kAttnDevTileRows = 256;
-// Both in one launch: the host-described sequences (q, o) and, appended to the grid, the
-// device-described query rows (q2, o2) against the same keys / values.
+struct DevTiles {
+  const int32_t* q_off;
+  const int32_t* tiles;
+  int32_t max_tiles;
+  int32_t kind;
+};
+// The tiles of at most `rows` such queries behind H heads of M_q merged rows and M_k keys in a layer: which kernel
+// takes them and how many rows a tile has.
+void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows);
+// Both: the host-described sequences (q, o) and the device-described query rows (q2, o2) against the same keys / values.
 hipError_t launch_attention_both(const void* q, const void* k, const void* v, void* o,
                                  const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
-                                 const void* q2, void* o2, const int32_t* q2_off_dev, const int32_t* tiles,
-                                 int max_tiles, bool log2_keys, hipStream_t stream, void* scratch = nullptr,
-                                 int64_t scratch_bytes = 0, const UnmergeTarget* unmerge = nullptr);
-hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o,
-                                      const int32_t* q_off_dev, const int32_t* tiles, int max_tiles,
+                                 const void* q2, void* o2, const DevTiles& dev, bool log2_keys, hipStream_t stream,
+                                 void* scratch = nullptr, int64_t scratch_bytes = 0, const UnmergeTarget* unmerge = nullptr);
+hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o, const DevTiles& dev,
                                       const int64_t* k_off_host, int H, float scale, bool log2_keys,
-                                      hipStream_t stream);
+                                      hipStream_t stream, const UnmergeTarget* unmerge = nullptr);
 
 // ---- stage 4 -------------------------------------------------------------------------------
 // fused != 0: out[pi[j]][h*64 + c] = o_m[h][assign[h][j]][c]  (out is [N, H*64])
