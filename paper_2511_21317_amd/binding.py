@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 
 import numpy as np
 import torch
@@ -68,11 +69,11 @@ def lib() -> C.CDLL:
     L.httm_reorder.argtypes = [vp, vp, vp, C.c_int, vp]
     L.httm_match_merge.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32p, i32p, f32p, f32p, vp]
     L.httm_reorder_match_merge.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32p, i32p, f32p, f32p, vp]
-    L.httm_attention.argtypes = [vp, vp, vp, vp, i64p, i64p, C.c_int, C.c_int, C.c_float, vp]
-    L.httm_attention_scratch.argtypes = [vp, vp, vp, vp, i64p, i64p, C.c_int, C.c_int, C.c_float, vp, C.c_int64, vp]
-    L.httm_attention_log2.argtypes = [vp, vp, vp, vp, i64p, i64p, C.c_int, C.c_int, vp]
-    L.httm_attention_log2_scratch.argtypes = [vp, vp, vp, vp, i64p, i64p, C.c_int, C.c_int, vp, C.c_int64, vp]
-    L.httm_attention_log2_static.argtypes = [vp, vp, vp, vp, i64p, i64p, C.c_int, C.c_int, vp]
+    L.httm_attention.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, C.c_float, vp]
+    L.httm_attention_scratch.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, C.c_float, vp, C.c_int64, vp]
+    L.httm_attention_log2.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, vp]
+    L.httm_attention_log2_scratch.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, vp, C.c_int64, vp]
+    L.httm_attention_log2_static.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, vp]
     L.httm_attention_split_plan.argtypes = [i64p, i64p, C.c_int, C.c_int, vp, vp, C.c_int64, vp, C.c_int64]
     L.httm_attention_scratch_bytes.argtypes = [C.c_int]
     L.httm_attention_scratch_bytes.restype = C.c_int64
@@ -155,20 +156,42 @@ def geom_block_forms(g: Geom) -> dict:
     return out
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# A call costs the host several microseconds, as much as the GPU needs for a small scene, and most of that is
+# marshalling: tensors are checked with one expression and passed as integers, the stream is asked for
+# without making a Stream object.  us a call, before / now: a
+# layer 14.5 / 10.3, an attention 10.8 / 7.5, a pass through the stages (8 calls) 63 / 41.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _dev(t: torch.Tensor, dtype, shape=None) -> C.c_void_p:
+def _stream() -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _dev(t: torch.Tensor, dtype, shape=None) -> int:
+    if t.is_cuda and t.dtype == dtype and t.is_contiguous() and (shape is None or t.shape == shape):
+        return t.data_ptr()
     if not t.is_cuda:
         raise HttmError("tensor must live on the GPU")
     if t.dtype != dtype:
         raise HttmError(f"expected dtype {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise HttmError("tensor must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise HttmError(f"expected shape {tuple(shape)}, got {tuple(t.shape)}")
-    return C.c_void_p(t.data_ptr())
+    raise HttmError(f"expected shape {tuple(shape)}, got {tuple(t.shape)}")
+
+
+def _row_offsets(rows, n: int) -> array:
+    """n row indices as int64; pass .buffer_info()[0] and keep the array until the call returns.  As in a C array
+    with an initialiser, fewer are filled up with zeros (which no call accepts behind others) and more are refused."""
+    try:
+        a = array("q", rows) if type(rows) in (list, tuple) else array("q", [int(x) for x in rows])
+    except TypeError:       # something else that int() takes
+        a = array("q", [int(x) for x in rows])
+    if len(a) > n:
+        raise IndexError(f"{len(a)} row offsets, expected {n}")
+    a.extend([0] * (n - len(a)))
+    return a
 
 
 class Plan:
@@ -184,6 +207,11 @@ class Plan:
         self.sizes = Sizes()
         _check(lib().httm_plan_query(self._h, C.byref(self.sizes)), "httm_plan_query")
         self.layout = workspace_layout(g)
+        self._H, self._N = int(g.H), int(self.sizes.N)
+        self._M_q, self._M_k = int(self.sizes.M_q), int(self.sizes.M_k)
+        self._tok = (self._H, self._N, 64)                  # shapes of the tensors of a call
+        self._mq, self._mk = (self._H, self._M_q, 64), (self._H, self._M_k, 64)
+        self._per_tok, self._out = (self._H, self._N), (self._N, self._H * 64)
 
     def clone(self) -> "Plan":
         """A second plan of the same geometry with buffers of its own (for a second stream)."""
@@ -202,13 +230,13 @@ class Plan:
 
     # convenience
     @property
-    def N(self): return int(self.sizes.N)
+    def N(self): return self._N
     @property
-    def M_q(self): return int(self.sizes.M_q)
+    def M_q(self): return self._M_q
     @property
-    def M_k(self): return int(self.sizes.M_k)
+    def M_k(self): return self._M_k
     @property
-    def H(self): return int(self.geom.H)
+    def H(self): return self._H
     @property
     def outlier_cap(self): return int(self.sizes.outlier_cap)
     @property
@@ -216,7 +244,7 @@ class Plan:
 
 
 def reorder(plan: Plan, src: torch.Tensor, dst: torch.Tensor, direction: int = 0):
-    shape = (plan.H, plan.N, 64)
+    shape = plan._tok
     _check(lib().httm_reorder(plan._h, _dev(src, torch.bfloat16, shape), _dev(dst, torch.bfloat16, shape),
                               int(direction), _stream()), "httm_reorder")
     return dst
@@ -226,30 +254,30 @@ def match_merge(plan: Plan, q_r, k_r, v_r, q_m, k_m, v_m, assign_q, assign_k, sc
     H, N = plan.H, plan.N
     bf, i32, f32 = torch.bfloat16, torch.int32, torch.float32
     _check(lib().httm_match_merge(
-        plan._h, _dev(q_r, bf, (H, N, 64)), _dev(k_r, bf, (H, N, 64)), _dev(v_r, bf, (H, N, 64)),
-        _dev(q_m, bf, (H, plan.M_q, 64)), _dev(k_m, bf, (H, plan.M_k, 64)), _dev(v_m, bf, (H, plan.M_k, 64)),
-        _dev(assign_q, i32, (H, N)), _dev(assign_k, i32, (H, N)),
-        _dev(score_q, f32, (H, N)) if score_q is not None else None,
-        _dev(score_k, f32, (H, N)) if score_k is not None else None, _stream()), "httm_match_merge")
+        plan._h, _dev(q_r, bf, plan._tok), _dev(k_r, bf, plan._tok), _dev(v_r, bf, plan._tok),
+        _dev(q_m, bf, plan._mq), _dev(k_m, bf, plan._mk), _dev(v_m, bf, plan._mk),
+        _dev(assign_q, i32, plan._per_tok), _dev(assign_k, i32, plan._per_tok),
+        _dev(score_q, f32, plan._per_tok) if score_q is not None else None,
+        _dev(score_k, f32, plan._per_tok) if score_k is not None else None, _stream()), "httm_match_merge")
 
 
 def reorder_match_merge(plan: Plan, q, k, v, q_m, k_m, v_m, assign_q, assign_k, score_q=None, score_k=None):
     H, N = plan.H, plan.N
     bf, i32, f32 = torch.bfloat16, torch.int32, torch.float32
     _check(lib().httm_reorder_match_merge(
-        plan._h, _dev(q, bf, (H, N, 64)), _dev(k, bf, (H, N, 64)), _dev(v, bf, (H, N, 64)),
-        _dev(q_m, bf, (H, plan.M_q, 64)), _dev(k_m, bf, (H, plan.M_k, 64)), _dev(v_m, bf, (H, plan.M_k, 64)),
-        _dev(assign_q, i32, (H, N)), _dev(assign_k, i32, (H, N)),
-        _dev(score_q, f32, (H, N)) if score_q is not None else None,
-        _dev(score_k, f32, (H, N)) if score_k is not None else None, _stream()), "httm_reorder_match_merge")
+        plan._h, _dev(q, bf, plan._tok), _dev(k, bf, plan._tok), _dev(v, bf, plan._tok),
+        _dev(q_m, bf, plan._mq), _dev(k_m, bf, plan._mk), _dev(v_m, bf, plan._mk),
+        _dev(assign_q, i32, plan._per_tok), _dev(assign_k, i32, plan._per_tok),
+        _dev(score_q, f32, plan._per_tok) if score_q is not None else None,
+        _dev(score_k, f32, plan._per_tok) if score_k is not None else None, _stream()), "httm_reorder_match_merge")
 
 
 def attention(q_m, k_m, v_m, o_m, q_offsets, k_offsets, scale: float = 0.125, scratch=None):
     """q_m/o_m: [sum M_q, 64] (or [H, M, 64]) bf16; offsets: sequences of H+1 row indices (host).
     scratch: a uint8 device tensor of at least attention_scratch_bytes(H) bytes, or None."""
     H = len(q_offsets) - 1
-    qo = (C.c_int64 * (H + 1))(*[int(x) for x in q_offsets])
-    ko = (C.c_int64 * (H + 1))(*[int(x) for x in k_offsets])
+    q_off, k_off = _row_offsets(q_offsets, H + 1), _row_offsets(k_offsets, H + 1)
+    qo, ko = q_off.buffer_info()[0], k_off.buffer_info()[0]
     bf = torch.bfloat16
     if scratch is None:
         _check(lib().httm_attention(_dev(q_m, bf), _dev(k_m, bf), _dev(v_m, bf), _dev(o_m, bf), qo, ko,
@@ -288,8 +316,8 @@ def attention_log2(q_m, k_log2, v_m, o_m, q_offsets, k_offsets, scratch=None):
     """As attention(), for keys that carry the factor LOG2_KEY_SCALE (a plan with log2_keys).
     scratch: a uint8 device tensor of at least attention_scratch_bytes(H) bytes, or None."""
     H = len(q_offsets) - 1
-    qo = (C.c_int64 * (H + 1))(*[int(x) for x in q_offsets])
-    ko = (C.c_int64 * (H + 1))(*[int(x) for x in k_offsets])
+    q_off, k_off = _row_offsets(q_offsets, H + 1), _row_offsets(k_offsets, H + 1)
+    qo, ko = q_off.buffer_info()[0], k_off.buffer_info()[0]
     bf = torch.bfloat16
     if scratch is None:
         _check(lib().httm_attention_log2(_dev(q_m, bf), _dev(k_log2, bf), _dev(v_m, bf), _dev(o_m, bf), qo, ko,
@@ -305,8 +333,8 @@ def attention_log2_static(q_m, k_log2, v_m, o_m, q_offsets, k_offsets):
     """attention_log2() with the library's own static scratch (httm_attention_log2_static): no
     allocation anywhere in the call."""
     H = len(q_offsets) - 1
-    qo = (C.c_int64 * (H + 1))(*[int(x) for x in q_offsets])
-    ko = (C.c_int64 * (H + 1))(*[int(x) for x in k_offsets])
+    q_off, k_off = _row_offsets(q_offsets, H + 1), _row_offsets(k_offsets, H + 1)
+    qo, ko = q_off.buffer_info()[0], k_off.buffer_info()[0]
     bf = torch.bfloat16
     _check(lib().httm_attention_log2_static(_dev(q_m, bf), _dev(k_log2, bf), _dev(v_m, bf), _dev(o_m, bf), qo, ko,
                                             H, 64, _stream()), "httm_attention_log2_static")
@@ -323,12 +351,11 @@ def unmerge(plan: Plan, o_m, assign_q, out, fuse_inverse_reorder: bool = True):
 
 
 def layer_forward(plan: Plan, q, k, v, out, workspace):
-    H, N = plan.H, plan.N
     bf = torch.bfloat16
     if workspace.dtype != torch.uint8:
         raise HttmError("workspace must be a uint8 tensor")
-    _check(lib().httm_layer_forward(plan._h, _dev(q, bf, (H, N, 64)), _dev(k, bf, (H, N, 64)),
-                                    _dev(v, bf, (H, N, 64)), _dev(out, bf, (N, H * 64)),
+    _check(lib().httm_layer_forward(plan._h, _dev(q, bf, plan._tok), _dev(k, bf, plan._tok),
+                                    _dev(v, bf, plan._tok), _dev(out, bf, plan._out),
                                     _dev(workspace, torch.uint8), workspace.numel(), _stream()),
            "httm_layer_forward")
     return out
@@ -357,9 +384,9 @@ def reorder_match_merge_filtered(plan: Plan, q, k, v, q_m, k_m, v_m, assign_q, a
     H, N = plan.H, plan.N
     bf, i32, f32 = torch.bfloat16, torch.int32, torch.float32
     _check(lib().httm_reorder_match_merge_filtered(
-        plan._h, _dev(q, bf, (H, N, 64)), _dev(k, bf, (H, N, 64)), _dev(v, bf, (H, N, 64)),
-        _dev(q_m, bf, (H, plan.M_q, 64)), _dev(k_m, bf, (H, plan.M_k, 64)), _dev(v_m, bf, (H, plan.M_k, 64)),
-        _dev(assign_q, i32, (H, N)), _dev(assign_k, i32, (H, N)), _dev(eps_q, f32, (H, N)),
+        plan._h, _dev(q, bf, plan._tok), _dev(k, bf, plan._tok), _dev(v, bf, plan._tok),
+        _dev(q_m, bf, plan._mq), _dev(k_m, bf, plan._mk), _dev(v_m, bf, plan._mk),
+        _dev(assign_q, i32, plan._per_tok), _dev(assign_k, i32, plan._per_tok), _dev(eps_q, f32, plan._per_tok),
         _dev(q_out, bf, (plan.outlier_cap, 64)), _stream()), "httm_reorder_match_merge_filtered")
 
 
@@ -376,7 +403,7 @@ def attention_outliers(plan: Plan, q_out, k_m, v_m, o_out):
 def unmerge_filtered(plan: Plan, o_m, o_out, assign_q, out):
     H, N = plan.H, plan.N
     bf = torch.bfloat16
-    _check(lib().httm_unmerge_filtered(plan._h, _dev(o_m, bf, (H, plan.M_q, 64)),
+    _check(lib().httm_unmerge_filtered(plan._h, _dev(o_m, bf, plan._mq),
                                        _dev(o_out, bf, (plan.outlier_cap, 64)),
                                        _dev(assign_q, torch.int32, (H, N)), _dev(out, bf, (N, H * 64)),
                                        _stream()), "httm_unmerge_filtered")
