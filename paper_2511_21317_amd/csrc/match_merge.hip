@@ -169,13 +169,19 @@ __device__ __forceinline__ void request_rows(const void* head_base, uint32_t hea
 // tokens, us with the instances of 64, 256 and 512 tokens alone -> with these: blocks of 16 tokens 158 ->
 // 108, 32: 98 -> 76, 75: 153 -> 108, 100: 102 -> 73, 128: 113 -> 79, 150: 96 -> 87, 192: 89 -> 79, 294:
 // 147 -> 107, 320: 177 -> 118, 384: 155 -> 137; 64 and 256 tokens unchanged.
+// From 257 tokens on always 8 waves: five to seven leave the SIMDs of a CU unevenly filled (one workgroup of six a CU), and
+// the matching's tiles and the clusters go round all eight.  Against a wave per 64 tokens, 16 heads, us: 48 frames of
+// 32 x 32 in blocks of 384 tokens 159 -> 117, with 40 % merged 117 -> 80 (20 frames), general rule 60 -> 43 (10), 320: 54 ->
+// 49, 294: 51 -> 45, 448: 44 -> 43; 192 tokens by four waves 52 -> 57, so those stay.
 template <int NW, int MAXN, bool TOPR>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MAXN == 32 ? 6 : 4, 8)))
 void match_merge_kernel(const MatchMergeArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int ITER = MAXN * kRowChunks / NT;
-  constexpr int SUB = ITER / 4;                       // 32-token tiles of a wave
-  static_assert(MAXN <= NT && (ITER == 4 || ITER == 8), "a thread per token, one or two 32-token tiles per wave");
+  constexpr int SUB = (MAXN + 32 * NW - 1) / (32 * NW);   // 32-token tiles of a wave
+  // SPREAD: fewer tokens than threads; the tiles go round the waves and thread t takes token t's cluster from LDS
+  constexpr bool SPREAD = MAXN < NT && MAXN > 32;
+  static_assert(MAXN <= NT && MAXN % 32 == 0 && SUB <= 2 && (SPREAD || ITER == 4 || ITER == 8), "a thread per token, one or two 32-token tiles per wave");
 
   // phase A (matching): inverse norms of all tokens / of the dst tokens
   // phase B (aggregation): member lists - the same storage, the phases are separated by barriers
@@ -189,6 +195,8 @@ void match_merge_kernel(const MatchMergeArgs a) {
   __shared__ __align__(16) unsigned char tile[(MAXN + 1) * kLdsRowBytes];
   __shared__ __align__(16) unsigned char s_union[kUnionBytes];
   __shared__ uint16_t s_dpos[MAXN];
+  __shared__ uint16_t s_res[SPREAD ? MAXN : 1];          // cluster of every token, and its similarity
+  __shared__ float s_sim[SPREAD && TOPR ? MAXN : 1];
   int16_t* s_cl = (int16_t*)(s_union + ((kUnionT0 + 15) & ~15));
   float* s_invn = (float*)s_union;                    // [MAXN]
   float* s_dinv = s_invn + MAXN;                      // [MAXN]
@@ -312,12 +320,12 @@ void match_merge_kernel(const MatchMergeArgs a) {
     // and the dst norms, and their dependent chains of LDS reads overlap.
     const int ndt = (kd + 31) >> 5;
     float my_sc = 1.0f;                // similarity of token `tid` to the dst it would join
-    if (wave * 64 < n) {
+    if (wave * (SPREAD ? 32 : 64) < n) {
       int tok[SUB];
       const unsigned char* xrow[SUB];
 #pragma unroll
       for (int sub = 0; sub < SUB; ++sub) {
-        tok[sub] = (wave * SUB + sub) * 32 + l32;
+        tok[sub] = (SPREAD ? sub * NW + wave : wave * SUB + sub) * 32 + l32;
         xrow[sub] = tile + (tok[sub] < n ? tok[sub] : n - 1) * kLdsRowBytes + half * 16;
       }
       float best[SUB];
@@ -382,6 +390,8 @@ void match_merge_kernel(const MatchMergeArgs a) {
         }
         my_cl = c;
         my_sc = sc;
+        if (SPREAD) s_res[t] = (uint16_t)c;
+        if (SPREAD && TOPR) s_sim[t] = sc;
         if (!TOPR) {
           assign[t] = it.moff + c;
           if (score) score[t] = sc;
@@ -389,6 +399,10 @@ void match_merge_kernel(const MatchMergeArgs a) {
       }
     }
     __syncthreads();   // everybody is done with s_invn / s_dinv
+    if (SPREAD) {
+      my_cl = tid < n ? (int)s_res[tid] : -1;
+      if (TOPR && tid < n) my_sc = s_sim[tid];
+    }
 
     if (TOPR) {
       // ---- 3b. top-r selection (Sec. 3.2): of the n - kd src tokens only the r = n - k with the
@@ -923,9 +937,9 @@ static void launch_match_merge_sized(const MatchMergeArgs& a, int n_items, hipSt
     case 2: return launch_match_merge_as<2, 128, TOPR>(a, n_items, stream);
     case 3: return launch_match_merge_as<3, 192, TOPR>(a, n_items, stream);
     case 4: return launch_match_merge_as<4, 256, TOPR>(a, n_items, stream);
-    case 5: return launch_match_merge_as<5, 320, TOPR>(a, n_items, stream);
-    case 6: return launch_match_merge_as<6, 384, TOPR>(a, n_items, stream);
-    case 7: return launch_match_merge_as<7, 448, TOPR>(a, n_items, stream);
+    case 5: return launch_match_merge_as<8, 320, TOPR>(a, n_items, stream);
+    case 6: return launch_match_merge_as<8, 384, TOPR>(a, n_items, stream);
+    case 7: return launch_match_merge_as<8, 448, TOPR>(a, n_items, stream);
     default: return launch_match_merge_as<8, 512, TOPR>(a, n_items, stream);
   }
 }
