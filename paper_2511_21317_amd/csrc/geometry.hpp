@@ -55,7 +55,7 @@ std::vector<int32_t> unmerge_spans(const std::vector<WorkItem>& items, int64_t M
 
 // tokens per pseudo-block of the special prefix, in a plan whose merging blocks have at most
 // `block` tokens
-inline int32_t prefix_chunk(int64_t block) { return block <= 32 ? 32 : 64; }
+inline int32_t prefix_chunk(int64_t block) { return block <= 16 ? 16 : block <= 32 ? 32 : 64; }
 
 // Validate a geometry (returns an HTTM_E_* code).
 int check_geom(const httm_geom_t& g);

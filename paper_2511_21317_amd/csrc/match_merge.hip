@@ -169,19 +169,21 @@ __device__ __forceinline__ void request_rows(const void* head_base, uint32_t hea
 // tokens, us with the instances of 64, 256 and 512 tokens alone -> with these: blocks of 16 tokens 158 ->
 // 108, 32: 98 -> 76, 75: 153 -> 108, 100: 102 -> 73, 128: 113 -> 79, 150: 96 -> 87, 192: 89 -> 79, 294:
 // 147 -> 107, 320: 177 -> 118, 384: 155 -> 137; 64 and 256 tokens unchanged.
+// At most 16 tokens: half the rows and scores of the instance of 32; 16 heads x 20580 tokens 53.6 -> 47.5 us, 24165 64.5 ->
+// 55.5, 8 heads x 3910 9.5 -> 8.6.
 // From 257 tokens on always 8 waves: five to seven leave the SIMDs of a CU unevenly filled (one workgroup of six a CU), and
 // the matching's tiles and the clusters go round all eight.  Against a wave per 64 tokens, 16 heads, us: 48 frames of
 // 32 x 32 in blocks of 384 tokens 159 -> 117, with 40 % merged 117 -> 80 (20 frames), general rule 60 -> 43 (10), 320: 54 ->
 // 49, 294: 51 -> 45, 448: 44 -> 43; 192 tokens by four waves 52 -> 57, so those stay.
 template <int NW, int MAXN, bool TOPR>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MAXN == 32 ? 6 : 4, 8)))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MAXN <= 32 ? 6 : 4, 8)))
 void match_merge_kernel(const MatchMergeArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int ITER = MAXN * kRowChunks / NT;
   constexpr int SUB = (MAXN + 32 * NW - 1) / (32 * NW);   // 32-token tiles of a wave
   // SPREAD: fewer tokens than threads; the tiles go round the waves and thread t takes token t's cluster from LDS
   constexpr bool SPREAD = MAXN < NT && MAXN > 32;
-  static_assert(MAXN <= NT && MAXN % 32 == 0 && SUB <= 2 && (SPREAD || ITER == 4 || ITER == 8), "a thread per token, one or two 32-token tiles per wave");
+  static_assert(MAXN <= NT && MAXN % 16 == 0 && SUB <= 2 && (SPREAD || ITER == 2 || ITER == 4 || ITER == 8), "a thread per token, one or two 32-token tiles per wave");
 
   // phase A (matching): inverse norms of all tokens / of the dst tokens
   // phase B (aggregation): member lists - the same storage, the phases are separated by barriers
@@ -260,10 +262,11 @@ void match_merge_kernel(const MatchMergeArgs a) {
     s_dpos[m] = (uint16_t)p;
     s_cl[p] = (int16_t)m;
   }
-  // pad the last 32-wide dst tile with NaN: a NaN score never compares greater, so the arg-max
-  // below needs no bounds test
+  // pad the last 32-wide dst tile (the 16 dst tokens there can be) with NaN: a NaN score never compares
+  // greater, so the arg-max below needs no bounds test
+  constexpr int kDstPad = MAXN < 32 ? 16 : 32;
   if (!s.preset)
-    for (int m = kd + tid; m < ((kd + 31) & ~31); m += NT) s_dinv[m] = __builtin_nanf("");
+    for (int m = kd + tid; m < ((kd + kDstPad - 1) & ~(kDstPad - 1)); m += NT) s_dinv[m] = __builtin_nanf("");
   __syncthreads();
 
   // ---- 2. rows to LDS, and their inverse norms ---------------------------------------------------
@@ -353,7 +356,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
         }
         // acc[sub][r] = <dst row, token>, dst row = dt*32 + 8*(r/4) + 4*half + r%4, token = l32 of the tile.
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < kDstPad / 8; ++g) {
           const int mb = dt * 32 + 8 * g + 4 * half;
           const f32x4 dv = *(const f32x4*)(s_dinv + mb);   // mb is a multiple of 4: aligned
 #pragma unroll
@@ -945,6 +948,7 @@ static void launch_match_merge_as(const MatchMergeArgs& a, int n_items, hipStrea
 }
 template <bool TOPR>
 static void launch_match_merge_sized(const MatchMergeArgs& a, int n_items, hipStream_t stream) {
+  if (a.max_block <= 16) return launch_match_merge_as<1, 16, TOPR>(a, n_items, stream);
   if (a.max_block <= 32) return launch_match_merge_as<1, 32, TOPR>(a, n_items, stream);
   switch ((a.max_block + 63) / 64) {
     case 1: return launch_match_merge_as<1, 64, TOPR>(a, n_items, stream);
