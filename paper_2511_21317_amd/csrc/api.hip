@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <memory>
 #include <new>
 
 #include "../../include/httm.h"
@@ -17,6 +18,7 @@ struct httm_plan {
   httm_sizes_t sizes;
   httm_workspace_layout_t ws;
   int device = -1;
+  char* d_tables = nullptr;   // the allocation behind d_pi, d_items_q, d_items_k and d_spans
   int32_t* d_pi = nullptr;
   WorkItem* d_items_q = nullptr;
   WorkItem* d_items_k = nullptr;
@@ -84,12 +86,34 @@ void fill_sizes(const httm_geom_t& g, const HostTables& t, httm_sizes_t* s,
   if (ws) *ws = l;
 }
 
-template <typename T>
-int upload(const std::vector<T>& host, T** dev) {
-  *dev = nullptr;
-  if (host.empty()) return HTTM_OK;
-  HTTM_HIP(hipMalloc((void**)dev, host.size() * sizeof(T)));
-  HTTM_HIP(hipMemcpy(*dev, host.data(), host.size() * sizeof(T), hipMemcpyHostToDevice));
+// The plan's index tables in one allocation, each 256-byte aligned.  A copy from pageable memory takes 11 us whatever its
+// size, so the small tables go over as one: a plan of 2 frames of 16x16 60 -> 38 us, 8 frames of 37x37 108 -> 73.
+int upload_tables(const HostTables& t, httm_plan_t* p) {
+  const struct { const void* host; size_t bytes; void** dev; } tables[] = {
+      {t.pi.data(), t.pi.size() * sizeof(t.pi[0]), (void**)&p->d_pi},
+      {t.items_q.data(), t.items_q.size() * sizeof(WorkItem), (void**)&p->d_items_q},
+      {t.items_k.data(), t.items_k.size() * sizeof(WorkItem), (void**)&p->d_items_k},
+      {t.spans_q.data(), t.spans_q.size() * sizeof(t.spans_q[0]), (void**)&p->d_spans}};
+  auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+  const size_t first = padded(tables[0].bytes);
+  size_t rest = 0;
+  for (int i = 1; i < 4; ++i) rest += padded(tables[i].bytes);
+  if (first + rest == 0) return HTTM_OK;
+  std::unique_ptr<char[]> staged(new (std::nothrow) char[rest + 1]);
+  if (!staged) return HTTM_E_OUT_OF_MEMORY;
+  HTTM_HIP(hipMalloc((void**)&p->d_tables, first + rest));
+  size_t at = 0;
+  for (int i = 1; i < 4; ++i) {
+    if (tables[i].bytes == 0) continue;
+    std::memcpy(staged.get() + at, tables[i].host, tables[i].bytes);
+    *tables[i].dev = p->d_tables + first + at;
+    at += padded(tables[i].bytes);
+  }
+  if (tables[0].bytes) {
+    *tables[0].dev = p->d_tables;
+    HTTM_HIP(hipMemcpy(p->d_tables, tables[0].host, tables[0].bytes, hipMemcpyHostToDevice));
+  }
+  if (rest) HTTM_HIP(hipMemcpy(p->d_tables + first, staged.get(), rest, hipMemcpyHostToDevice));
   return HTTM_OK;
 }
 
@@ -275,10 +299,7 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
     delete p;
     return hip_fail(e);
   }
-  rc = upload(t.pi, &p->d_pi);
-  if (rc == HTTM_OK) rc = upload(t.items_q, &p->d_items_q);
-  if (rc == HTTM_OK) rc = upload(t.items_k, &p->d_items_k);
-  if (rc == HTTM_OK) rc = upload(t.spans_q, &p->d_spans);
+  rc = upload_tables(t, p);
   if (rc == HTTM_OK && g->variant == HTTM_VARIANT_UNIFORM) {
     e = hipMalloc((void**)&p->d_mean, (size_t)2 * t.N * 64 * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_slot, (size_t)2 * t.N * sizeof(int32_t));
@@ -335,7 +356,7 @@ int httm_plan_clone(const httm_plan_t* p, httm_plan_t** out) {
 
 int httm_plan_destroy(httm_plan_t* p) {
   if (!p) return HTTM_OK;
-  void* ptrs[] = {p->d_pi, p->d_items_q, p->d_items_k, p->d_spans, p->d_mean, p->d_slot, p->d_uscore, p->d_score, p->ob.state};
+  void* ptrs[] = {p->d_tables, p->d_mean, p->d_slot, p->d_uscore, p->d_score, p->ob.state};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete p;
