@@ -299,6 +299,16 @@ HTTM_API int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* 
                                        int32_t* summary, int32_t* segments, int64_t max_segments,
                                        int32_t* tiles, int64_t max_tiles);
 
+/* Host only: which tiles stage 3 runs a launch with these head lengths in, on a device of `compute_units` compute
+ * units and with `scratch_bytes` of scratch (0: none) - the decision the launch evaluates; for tests and diagnostics.
+ *   tiles[2] : of the launch's workgroups, and of those of a second launch behind it (-1: there is none):
+ *              0 256 rows (the ones httm_attention_split_plan reports run in pieces), 1 128 rows, 2 32, 3 64, 4 128
+ *              with 32-row waves, 5 128 with 64-row waves, 6 256 - 2 to 6 share the keys among their waves
+ *   rows     : or NULL; [2][H][2] int64: first query row inside the head and number of rows of every
+ *              head, for both launches */
+HTTM_API int httm_attention_route(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units,
+                                  int64_t scratch_bytes, int32_t* tiles, int64_t* rows);
+
 /* httm_attention_log2_scratch for callers that cannot allocate device memory and have no buffer to
  * pass: code that runs under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  The scratch is an array of HTTM_STATIC_SCRATCH_BYTES inside the library's device code

@@ -531,6 +531,29 @@ int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets
   return HTTM_OK;
 }
 
+int httm_attention_route(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units, int64_t scratch_bytes,
+                         int32_t* tiles, int64_t* rows) {
+  if (!q_offsets || !k_offsets || !tiles || H <= 0 || compute_units <= 0 || scratch_bytes < 0) return HTTM_E_INVALID_ARG;
+  if (H > HTTM_MAX_HEADS) return HTTM_E_UNSUPPORTED;
+  for (int h = 0; h < H; ++h)
+    if (q_offsets[h + 1] < q_offsets[h] || k_offsets[h + 1] < k_offsets[h]) return HTTM_E_INVALID_ARG;
+  AttnRoute route;
+  choose_attention_route(q_offsets, k_offsets, H, compute_units, scratch_bytes / 4, &route);
+  const bool rounds = route.tiles == AttnTiles::kRounds;
+  tiles[0] = (int32_t)(rounds ? AttnTiles::kTiles256 : route.tiles);
+  tiles[1] = rounds ? (int32_t)route.rest : -1;
+  if (rows) {
+    HeadRows part[2] = {all_rows(q_offsets, H), {}};
+    if (rounds) split_rounds(q_offsets, H, compute_units, &part[0], &part[1]);
+    for (int i = 0; i < 2; ++i)
+      for (int h = 0; h < H; ++h) {
+        rows[2 * (i * H + h)] = part[i].count[h] ? part[i].first[h] - q_offsets[h] : 0;
+        rows[2 * (i * H + h) + 1] = part[i].count[h];
+      }
+  }
+  return HTTM_OK;
+}
+
 int64_t httm_attention_scratch_bytes(int H) { return H > 0 && H <= HTTM_MAX_HEADS ? attention_scratch_bytes(H) : 0; }
 
 int httm_unmerge(const httm_plan_t* p, const void* o_m, const int32_t* assign_q, void* out,
@@ -577,7 +600,7 @@ int httm_layer_forward(const httm_plan_t* p, const void* q, const void* k, const
     k_off[h] = (int64_t)h * p->sizes.M_k;
   }
   // (with stage 4 and the inverse reorder at the end of its tiles)
-  const UnmergeTarget um = {out, assign_q, p->d_pi, p->d_spans, p->ob.token, p->sizes.N, H};
+  const UnmergeTarget um = {out, assign_q, p->d_pi, p->d_spans, p->ob.token, p->sizes.N, p->sizes.M_q, H};
   if (filtered) {
     // Alg. 1: the outlier queries attend on their own
     const DevTiles dev = {p->ob.offsets, p->ob.tiles, p->ob.max_tiles, p->ob.tile_kind};

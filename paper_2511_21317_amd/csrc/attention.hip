@@ -573,6 +573,13 @@ __device__ __forceinline__ UnmergeTarget unmerge_target() {
   asm volatile("" : "+s"(p));
   return *(const UnmergeTarget*)p;
 }
+// First row of a tile inside its head (where its clusters count from), likewise read late.
+__device__ __forceinline__ int unmerge_row0(const UnmergeTarget& um, int h, int q0) {
+  typedef const __attribute__((address_space(4))) char* args_t;
+  args_t p = (args_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnArgs, q_off) + h * sizeof(int64_t);
+  asm volatile("" : "+s"(p));
+  return row_in_head(*(const __attribute__((address_space(4))) int64_t*)p, h, um.M, q0);
+}
 
 // A tile's search: kUnmergeBatch tokens per lane are requested together.
 constexpr int kUnmergeBatch = 4;
@@ -582,28 +589,28 @@ struct UnmergeBatch {
 struct UnmergeSpan {
   int first, end;
 };
-__device__ __forceinline__ UnmergeSpan unmerge_span(const UnmergeTarget& um, int q0, int n) {
-  return {um.spans[2 * (q0 / kUnmergeGroup)], um.spans[2 * ((q0 + n - 1) / kUnmergeGroup) + 1]};
+__device__ __forceinline__ UnmergeSpan unmerge_span(const UnmergeTarget& um, int row0, int n) {
+  return {um.spans[2 * (row0 / kUnmergeGroup)], um.spans[2 * ((row0 + n - 1) / kUnmergeGroup) + 1]};
 }
 template <int NT>
-__device__ __forceinline__ void unmerge_load(UnmergeBatch& b, const UnmergeTarget& um, int h, int q0, int n, int first, int end, int tid) {
+__device__ __forceinline__ void unmerge_load(UnmergeBatch& b, const UnmergeTarget& um, int h, int row0, int n, int first, int end, int tid) {
 #pragma unroll
   for (int u = 0; u < kUnmergeBatch; ++u) {
     const int j = first + u * NT + tid, jc = j < end ? j : end - 1;
-    const int r = um.assign[h * um.N + jc] - q0;
+    const int r = um.assign[h * um.N + jc] - row0;
     b.token[u] = um.pi[jc];
     b.row[u] = j < end && r >= 0 && r < n ? r : -1;
   }
 }
-// Rows [q0, q0 + n) of head h, in LDS at `rows`, to their tokens; `b` holds the first batch.  NT threads.
+// Rows [row0, row0 + n) of head h, in LDS at `rows`, to their tokens; `b` holds the first batch.  NT threads.
 template <int NT>
-__device__ __forceinline__ void unmerge_store(UnmergeBatch& b, const UnmergeTarget& um, const u32x4* rows, int h, int q0, int n,
+__device__ __forceinline__ void unmerge_store(UnmergeBatch& b, const UnmergeTarget& um, const u32x4* rows, int h, int row0, int n,
                                               UnmergeSpan sp, int tid) {
   const int lane = tid & 63, sub = lane >> 3, c = lane & 7;
   u32x4* __restrict__ out = (u32x4*)um.out;
   for (int first = sp.first; first < sp.end; first += NT * kUnmergeBatch) {
     UnmergeBatch cur = b;
-    if (first + NT * kUnmergeBatch < sp.end) unmerge_load<NT>(b, um, h, q0, n, first + NT * kUnmergeBatch, sp.end, tid);
+    if (first + NT * kUnmergeBatch < sp.end) unmerge_load<NT>(b, um, h, row0, n, first + NT * kUnmergeBatch, sp.end, tid);
 #pragma unroll
     for (int u = 0; u < kUnmergeBatch; ++u) {
       const unsigned long long hit = __builtin_amdgcn_ballot_w64(cur.row[u] >= 0);
@@ -647,7 +654,7 @@ __device__ __forceinline__ void unmerge_tile(const UnmergeTarget& um, UnmergeBat
       __builtin_nontemporal_store(x, (u32x4*)um.out + (token * um.H + h) * kRowChunks + c);
     }
   }
-  if (!dev_tile) unmerge_store<NT>(batch, um, rows, h, q0, n, span, tid);
+  if (!dev_tile) unmerge_store<NT>(batch, um, rows, h, unmerge_row0(um, h, q0), n, span, tid);
 }
 
 // 8 KB tiles of LDS of a workgroup: per key group two of K and two of V, and with several key groups room
@@ -1067,8 +1074,9 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
       UnmergeSpan span = {0, 0};
       UnmergeBatch batch;
       if (!dev_tile) {
-        span = unmerge_span(um, q0, n);
-        unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+        const int row0 = unmerge_row0(um, h, q0);
+        span = unmerge_span(um, row0, n);
+        unmerge_load<NT>(batch, um, h, row0, n, span.first, span.end, tid);
       }
       u32x4* s_rows = (u32x4*)lds;
       __syncthreads();                              // everybody has read the groups' sums
@@ -1116,8 +1124,9 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
     UnmergeSpan span = {0, 0};
     UnmergeBatch batch;
     if (!dev_tile) {
-      span = unmerge_span(um, q0, n);
-      unmerge_load<NT>(batch, um, h, q0, n, span.first, span.end, tid);
+      const int row0 = unmerge_row0(um, h, q0);
+      span = unmerge_span(um, row0, n);
+      unmerge_load<NT>(batch, um, h, row0, n, span.first, span.end, tid);
     }
     u32x4* s_rows = (u32x4*)lds;
 #pragma unroll
@@ -1228,11 +1237,12 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
   // consecutive shares of one tile have consecutive slots
   const int64_t row0 = (int64_t)split_slot(t.first_share, e) * BQ;     // segment p: rows from row0 + p * BQ
   const int q_part = t.q0 + part * kReduceRows, n_part = rows - part * kReduceRows < kReduceRows ? rows - part * kReduceRows : kReduceRows;
+  const int row0_part = row_in_head(q_base, t.head, a.um.M, q_part);
   UnmergeSpan span = {0, 0};
   UnmergeBatch batch;
   if (a.um.out) {
-    span = unmerge_span(a.um, q_part, n_part);
-    unmerge_load<256>(batch, a.um, t.head, q_part, n_part, span.first, span.end, tid);
+    span = unmerge_span(a.um, row0_part, n_part);
+    unmerge_load<256>(batch, a.um, t.head, row0_part, n_part, span.first, span.end, tid);
   }
   // thread -> row r = tid % 64 of the part and the 16-byte output chunks c0, c0 + 4
   const int r = part * kReduceRows + (tid & 63), c0 = tid >> 6;
@@ -1294,7 +1304,7 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
     const int lr = (tid >> 3) + 32 * i, ch = tid & 7;
     if (lr < n_part) ((u32x4*)a.o)[(q_base + q_part + lr) * kRowChunks + ch] = s_out[out_chunk(lr, ch)];
   }
-  if (a.um.out) unmerge_store<256>(batch, a.um, s_out, t.head, q_part, n_part, span, tid);
+  if (a.um.out) unmerge_store<256>(batch, a.um, s_out, t.head, row0_part, n_part, span, tid);
 }
 
 // compute units of the current device (asked once per device)
@@ -1314,20 +1324,6 @@ void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t
     hipLaunchKernelGGL((attention_kernel<NQ, NW, KS, false>), dim3(grid), dim3(64 * NW), 0, stream, a);
   else
     hipLaunchKernelGGL((attention_kernel<NQ, NW, KS, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
-}
-
-// The query rows of a launch: `count` rows of every head from row `first` of the packed tensor.
-struct HeadRows {
-  int64_t first[kAttnMaxHeads];
-  int64_t count[kAttnMaxHeads];
-};
-HeadRows all_rows(const int64_t* q_off_host, int H) {
-  HeadRows r = {};
-  for (int h = 0; h < H; ++h) {
-    r.first[h] = q_off_host[h];
-    r.count[h] = q_off_host[h + 1] - q_off_host[h];
-  }
-  return r;
 }
 
 // `route`: the split of a launch of 256-row tiles, if it has one; its partial results go to `scratch`.
@@ -1499,17 +1495,8 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   if (route.tiles == AttnTiles::kTiles256)
     return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, &route, (float*)scratch);
   if (route.tiles != AttnTiles::kRounds) return launch_tiles(route.tiles, a, log2_keys, rows, k_off_host, H, stream);
-  HeadRows whole = rows, rest = rows;
-  int64_t keep = 0;
-  for (int h = 0; h < H; ++h) keep += rows.count[h] / kAttnTileRows;
-  keep = keep / cus * cus;
-  for (int h = 0; h < H; ++h) {
-    const int64_t n = std::min(rows.count[h] / kAttnTileRows, keep);
-    keep -= n;
-    whole.count[h] = n * kAttnTileRows;
-    rest.first[h] += n * kAttnTileRows;
-    rest.count[h] -= n * kAttnTileRows;
-  }
+  HeadRows whole, rest;
+  split_rounds(q_off_host, H, cus, &whole, &rest);
   const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
   if (e != hipSuccess) return e;
   return launch_tiles(route.rest, a, log2_keys, rest, k_off_host, H, stream);

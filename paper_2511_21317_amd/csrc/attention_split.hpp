@@ -22,6 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "../../include/httm.h"
+
 namespace httm {
 
 constexpr int kAttnTileRows = 256;        // query rows of a tile of the kernel instance that splits
@@ -294,6 +296,39 @@ inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt) {
   offer(AttnTiles::kTiles128, 128, 2, 66 + 9 * kt);
   return best;
 }
+
+// The query rows of a launch: `count` rows of every head from row `first` of the packed tensor.
+struct HeadRows {
+  int64_t first[HTTM_MAX_HEADS];
+  int64_t count[HTTM_MAX_HEADS];
+};
+inline HeadRows all_rows(const int64_t* q_off, int H) {
+  HeadRows r = {};
+  for (int h = 0; h < H; ++h) {
+    r.first[h] = q_off[h];
+    r.count[h] = q_off[h + 1] - q_off[h];
+  }
+  return r;
+}
+
+// kRounds: the rows of the two launches.
+inline void split_rounds(const int64_t* q_off, int H, int64_t cus, HeadRows* whole, HeadRows* rest) {
+  *whole = *rest = all_rows(q_off, H);
+  int64_t keep = 0;
+  for (int h = 0; h < H; ++h) keep += whole->count[h] / kAttnTileRows;
+  keep = keep / cus * cus;
+  for (int h = 0; h < H; ++h) {
+    const int64_t nf = whole->count[h] / kAttnTileRows, n = nf < keep ? nf : keep;
+    keep -= n;
+    whole->count[h] = n * kAttnTileRows;
+    rest->first[h] += n * kAttnTileRows;
+    rest->count[h] -= n * kAttnTileRows;
+  }
+}
+
+// First row, inside head h of M rows, of the tile at `q0` of a launch whose rows of that head begin at row `first` of the
+// packed tensor: a launch may have the last rows of a head only.
+__host__ __device__ inline int row_in_head(int64_t first, int h, int64_t M, int q0) { return (int)(first - h * M) + q0; }
 
 // The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).
 inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words,

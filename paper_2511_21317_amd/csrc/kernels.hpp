@@ -145,7 +145,7 @@ struct UnmergeTarget {
   const int32_t* pi;        // [N]
   const int32_t* spans;     // [2 * ceil(M / kUnmergeGroup)], see unmerge_spans()
   const int32_t* q2_token;  // input position of every row of the device-described queries
-  int64_t N;
+  int64_t N, M;             // tokens and merged rows of a head: head h owns the rows [h * M, (h + 1) * M) of q and o
   int32_t H;
 };
 // log2_keys: the keys carry the factor scale * log2(e) already (stage 2 with

@@ -1,0 +1,75 @@
+"""Host-side check of the tiles stage 3 (Eq. 3-4) runs a launch in (httm_attention_route evaluates the launch's own
+decision): the launches take every row of every head exactly once, in tiles whose edges stage 4 at their end can look
+up, and many rows against few keys run in two launches.  No GPU needed."""
+import numpy as np
+import pytest
+
+import paper_2511_21317_amd as httm
+from test_gpu_layer_unmerge import CASES
+
+
+def _check_rows(mq, mk, scratch_bytes=None):
+    qo, ko = ([int(x) for x in np.concatenate([[0], np.cumsum(n)])] for n in (mq, mk))
+    r = httm.attention_route(qo, ko, 256, scratch_bytes)
+    for h, m in enumerate(mq):
+        end = 0
+        for launch in range(len(r["tiles"])):
+            first, count = (int(x) for x in r["rows"][launch, h])
+            if count == 0:
+                continue
+            assert first == end and first % 32 == 0, (h, launch, first, end)
+            end = first + count
+        assert end == m
+    return r
+
+
+def _layer_rows(case):
+    name, S, Hp, Wp, b, T, rho_q, rho_kv, H, opts = case
+    s = httm.geom_sizes(httm.make_geom(S, Hp, Wp, b, T, rho_q, rho_kv, H=H, **opts))
+    return [int(s.M_q)] * H, [int(s.M_k)] * H
+
+
+# the cases of test_gpu_layer_unmerge.py that are there for the tiles their names begin with
+KINDS = ("groups128_wide", "groups128", "groups32", "groups64", "groups256", "tiles128", "segments", "rounds")
+BY_KIND = [(c, kind) for c in CASES for kind in KINDS[:1] if c[0].startswith(kind)] + \
+          [(c, kind) for c in CASES for kind in KINDS[1:] if c[0].startswith(kind) and not c[0].startswith(KINDS[0])]
+
+
+def test_every_kind_of_tile_has_a_layer():
+    assert {kind for _, kind in BY_KIND} == set(KINDS)
+
+
+@pytest.mark.parametrize("case,kind", BY_KIND, ids=[c[0] for c, _ in BY_KIND])
+def test_layers_run_in_the_tiles_their_names_say(case, kind):
+    mq, mk = _layer_rows(case)
+    r = _check_rows(mq, mk)
+    off = lambda n: [h * n[0] for h in range(len(n) + 1)]  # noqa: E731
+    if kind == "rounds":
+        # the second launch begins inside heads: their first rows ran in the first one
+        assert len(r["tiles"]) == 2 and r["tiles"][0] == "tiles256"
+        assert ((r["rows"][1, :, 0] > 0) & (r["rows"][1, :, 1] > 0)).any()
+        if "head_in_both" in case[0]:
+            assert ((r["rows"][0, :, 1] > 0) & (r["rows"][1, :, 1] > 256)).any()
+    elif kind == "segments":
+        assert r["tiles"] == ["tiles256"] and httm.attention_split_plan(off(mq), off(mk))["n_tiles"] > 0
+    else:
+        assert r["tiles"] == [kind]
+
+
+# many queries against few keys, in layers: frames, grid, block, frames a block, merged shares, heads
+@pytest.mark.parametrize("geom", [(32, 21, 37, 8, 4, 0.6, 0.9, 16), (32, 28, 18, 4, 2, 0.38, 0.89, 16), (19, 28, 37, 4, 2, 0.5, 0.9, 16)])
+def test_layers_of_many_rows_and_few_keys_take_every_row_once(geom):
+    mq, mk = _layer_rows(("", *geom, {}))
+    assert len(_check_rows(mq, mk)["tiles"]) == 2
+
+
+@pytest.mark.parametrize("seed", range(100))
+def test_random_launches_take_every_row_once(seed):
+    rng = np.random.default_rng(4700 + seed)
+    H = int(rng.integers(1, 25))
+    if seed % 2:
+        mq, mk = [int(rng.integers(1, 16000))] * H, [int(rng.integers(1, 4000))] * H
+    else:
+        mq, mk = ([int(x) for x in rng.integers(0, n, H)] for n in (16000, 4000))
+    _check_rows(mq, mk)
+    _check_rows(mq, mk, 0)

@@ -31,6 +31,14 @@ CASES = [
     ("outliers_segments", 8, 37, 35, 4, 2, 0.5, 0.5, 16, {"outlier_frac": 0.05}),
     ("outliers_big_blocks", 20, 9, 31, 128, 20, 0.8, 0.7, 4, {"chunked_blocks": True, "outlier_frac": 0.1}),
     ("anchored", 6, 18, 17, 4, 3, 0.8, 0.8, 7, {"anchor_first_frame": True}),
+    # many queries against few keys: whole rounds of tiles, then the heads' last rows in a launch of their own
+    ("rounds", 13, 37, 37, 8, 4, 0.5, 0.9, 16, {}),
+    ("rounds_plain_keys", 13, 37, 37, 8, 4, 0.5, 0.9, 16, {"log2_keys": False}),
+    ("rounds_head_in_both", 19, 28, 37, 4, 2, 0.5, 0.9, 16, {}),
+    ("rounds_queries_unmerged", 9, 37, 37, 4, 2, 0.0, 0.9, 12, {}),
+    ("rounds_24_heads", 9, 37, 37, 4, 2, 0.5, 0.85, 24, {}),
+    ("rounds_outliers", 13, 37, 37, 8, 4, 0.5, 0.9, 16, {"outlier_frac": 0.05}),
+    ("rounds_outliers_plain_keys", 19, 28, 37, 4, 2, 0.5, 0.9, 16, {"outlier_frac": 0.002, "log2_keys": False}),
 ]
 
 
