@@ -356,7 +356,16 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
   const int64_t kt = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
   const AttnGroups groups = choose_key_groups([&](int rows) { return count_tiles(q_off, H, rows); }, cus, kt);
   const int64_t split_time = 120 + split_slots(r.split) / 2 + (r.split.shares > cus ? 15 : 9) * (int64_t)r.split.share_units;
-  if (groups.tiles != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups.time <= split_time)) {
+  // Long keys, whose segments need more than the library's own array: there the fitted times put segments too low against
+  // tiles of 64-row waves (us, segments / groups: one head of 29824 x 35072 277 / 250, 24 of 2346 x 56082 761 / 680, 12 of
+  // 2618 x 172602 1332 / 1176, 24 of 1064 x 45280 319 / 316, 8 of 3935 x 91614 583 / 601), so the line has terms of its own.
+  // httm_attention_log2_static accepts by it, too: what runs in key groups needs nothing of the array.
+  const int64_t half = (kt + 1) / 2, quarter = (kt + 3) / 4;
+  int64_t groups_time = groups.time;
+  if (split_slots(r.split) * kAttnSlotWords * 4 > HTTM_STATIC_SCRATCH_BYTES)
+    groups_time = count_tiles(q_off, H, 64) <= cus ? 70 + 14 * quarter : count_tiles(q_off, H, 128) <= cus ? 80 + 16 * quarter
+                : count_tiles(q_off, H, kAttnTileRows) <= cus ? 60 + 15 * half : INT64_MAX;
+  if (groups.tiles != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups_time <= split_time)) {
     no_split();
     r.tiles = groups.tiles;
     return;

@@ -73,3 +73,18 @@ def test_random_launches_take_every_row_once(seed):
         mq, mk = ([int(x) for x in rng.integers(0, n, H)] for n in (16000, 4000))
     _check_rows(mq, mk)
     _check_rows(mq, mk, 0)
+
+
+# heads, rows, keys of launches whose segments would need more than the 32 MiB of httm_attention_log2_static: in key
+# groups where those are no slower, which need nothing of it (None: segments, refused there)
+@pytest.mark.parametrize("H,mq,mk,tiles", [(1, 29824, 35072, "groups128_wide"), (2, 15376, 33474, "groups128_wide"),
+                                           (32, 950, 86828, "groups128_wide"), (8, 3935, 91614, "groups128_wide"),
+                                           (1, 55294, 21770, "groups256"), (24, 2346, 56082, "groups256"),
+                                           (1, 456 * 256, 20000, None), (1, 10418, 105994, None), (27, 557, 48900, None)])
+def test_launches_with_long_segments_run_in_key_groups_where_they_are_no_slower(H, mq, mk, tiles):
+    off = lambda n: [h * n for h in range(H + 1)]  # noqa: E731
+    r, p = _check_rows([mq] * H, [mk] * H), httm.attention_split_plan(off(mq), off(mk))
+    if tiles:
+        assert r["tiles"] == [tiles] and p["slots"] == 0
+    else:
+        assert r["tiles"] == ["tiles256"] and p["slots"] * 256 * 66 * 4 > 32 << 20

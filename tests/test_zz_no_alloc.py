@@ -70,3 +70,18 @@ def test_static_scratch_entry_point_refuses_what_does_not_fit():
         httm.attention_log2_static(qm, k2, vm, out, qo, ko)
     torch.cuda.synchronize()
     assert torch.isnan(out.float()).all(), "a refused call launches nothing"
+
+
+def test_static_scratch_entry_point_takes_launches_whose_keys_are_shared_inside_workgroups():
+    require_gpu()
+    # 233 tiles of 128 rows: their 512 shares would need 42 MB, their key groups need no scratch memory
+    mq, mk = [29824], [35072]
+    assert httm.attention_split_plan([0, mq[0]], [0, mk[0]])["slots"] == 0
+    qm, k2, vm, qo, ko = _case(mq, mk, 7005)
+    got, want = torch.full_like(qm, float("nan")), torch.full_like(qm, float("nan"))
+    httm.attention_log2_static(qm, k2, vm, got, qo, ko)
+    scratch = torch.empty(httm.attention_scratch_bytes(1), dtype=torch.uint8, device="cuda")
+    httm.attention_log2(qm, k2, vm, want, qo, ko, scratch=scratch)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and bool(torch.isfinite(got.float()).all())
+    _check_against_oracle(qm, k2, vm, qo, ko, got, 0, mq[0] - 64, mq[0], "last rows")
