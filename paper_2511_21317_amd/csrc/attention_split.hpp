@@ -20,6 +20,7 @@
 // tests) and the kernels (which segment am I, which slots belong to my tile) both call them.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 #include "../../include/httm.h"
@@ -253,6 +254,17 @@ inline int64_t count_tiles(const int64_t* q_off, int H, int rows) {
   return n;
 }
 
+// The same as the launch's grid deals them to the 8 XCDs, full tiles and the heads' partial ones each by themselves: 8 times
+// those of the first XCD, which is what has to fit its share of the CUs.
+inline int64_t count_dealt_tiles(const int64_t* q_off, int H, int rows) {
+  int64_t full = 0, ragged = 0;
+  for (int h = 0; h < H; ++h) {
+    full += (q_off[h + 1] - q_off[h]) / rows;
+    ragged += (q_off[h + 1] - q_off[h]) % rows != 0;
+  }
+  return 8 * ((full + 7) / 8 + (ragged + 7) / 8);
+}
+
 // Tiles of `rows` rows that are left of the heads when whole rounds of 256-row tiles, the heads' full
 // ones in head order, have run.
 inline int64_t count_rest_tiles(const int64_t* q_off, int H, int64_t cus, int rows) {
@@ -267,8 +279,8 @@ inline int64_t count_rest_tiles(const int64_t* q_off, int H, int64_t cus, int ro
   return n;
 }
 
-// At most one tile of 32, 64, 128 or 256 rows per CU (`count(rows)` of them): the tiles whose waves share the keys, or
-// 128-row tiles of one key group, that take the least time, in tenths of a us, for heads of at most kt key tiles.  A wave
+// At most one tile of 32, 64, 128 or 256 rows per CU whose waves share the keys, or at most two 128-row tiles of one key
+// group per CU (`count(rows)` tiles): those that take the least time, in tenths of a us, for heads of at most kt key tiles.  A wave
 // walks a quarter (half) of the keys of its tile; the groups' meeting is in the constant.  us at 16 heads (log2 keys), tiles
 // of 32 / 64 / 128 / 128 wide / 256 rows / 128 rows of one group, x where there is more than one a CU:
 //   250 x 250 5.5 / 6.7 / 7.8 / 9.5 / 11.4 / 7.1, 500 x 500 6.7 / 8.0 / 9.6 / 11.4 / 14.6 / 9.2, 500 x 4000 22.5 / 23.7 / 34.7 /
@@ -293,7 +305,7 @@ inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt) {
   offer(AttnTiles::kGroups128Wide, 128, 1, 86 + 17 * quarter);
   offer(AttnTiles::kGroups256, kAttnTileRows, 1, 95 + 15 * half);
   offer(AttnTiles::kTiles128, 128, 1, 49 + 11 * kt / 2);
-  offer(AttnTiles::kTiles128, 128, 2, 66 + 9 * kt);
+  offer(AttnTiles::kTiles128, 128, 2, 60 + 9 * kt);
   return best;
 }
 
@@ -349,22 +361,41 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
   };
   if (r.split.n_tiles == 0 || split_slots(r.split) * kAttnSlotWords > scratch_words) no_split();
   // Workgroups that share the keys among their waves walk a quarter (half) of them however many CUs are idle; segments
-  // cut the walk over all CUs and cost a second kernel and the traffic of the partial results.  The shorter of the
-  // two, in tenths of a us from segments' times at 1 to 16 heads of 64 to 4000 rows and 1600 to 28000 keys: 16 heads 64 x
-  // 4000 25.3, 250 x 12000 38, 500 x 4000 36, x 6000 40, 1000 x 6000 48, x 9000 58, x 28000 123, 2000 x 14000 124, 3000 x 9000 120,
-  // x 28000 292; one head of 1000 x 28000 39.
-  const int64_t kt = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
-  const AttnGroups groups = choose_key_groups([&](int rows) { return count_tiles(q_off, H, rows); }, cus, kt);
-  const int64_t split_time = 120 + split_slots(r.split) / 2 + (r.split.shares > cus ? 15 : 9) * (int64_t)r.split.share_units;
-  // Long keys, whose segments need more than the library's own array: there the fitted times put segments too low against
-  // tiles of 64-row waves (us, segments / groups: one head of 29824 x 35072 277 / 250, 24 of 2346 x 56082 761 / 680, 12 of
-  // 2618 x 172602 1332 / 1176, 24 of 1064 x 45280 319 / 316, 8 of 3935 x 91614 583 / 601), so the line has terms of its own.
-  // httm_attention_log2_static accepts by it, too: what runs in key groups needs nothing of the array.
-  const int64_t half = (kt + 1) / 2, quarter = (kt + 3) / 4;
-  int64_t groups_time = groups.time;
-  if (split_slots(r.split) * kAttnSlotWords * 4 > HTTM_STATIC_SCRATCH_BYTES)
-    groups_time = count_tiles(q_off, H, 64) <= cus ? 70 + 14 * quarter : count_tiles(q_off, H, 128) <= cus ? 80 + 16 * quarter
+  // cut the walk over all CUs and cost a second kernel and the traffic of the partial results.  The shorter of the two, in
+  // tenths of a us, fitted to 1700 shapes of 1 to 64 heads, 16 to 12000 rows and 200 to 40000 keys, each in every kind of
+  // tiles (what this takes is 0.4 % above the best on average and for one in fifty more than 6 %):
+  //  * segments: a step is the shorter the fewer of the tile's 256 rows there are, and the pieces of a tile are added up one
+  //    after the other (24 heads of 68 x 6785 27 us, key groups 38; one head of 5646 x 5999 33, key groups 29).
+  //  * groups in tiles of 32 and 64 rows read every key once a tile: 0.023 us for every key tile of every head, and long
+  //    walks at full occupancy an eighth more (64 heads of 90 x 19556 148 us, segments 105; 8 of 1831 x 27212 139 : 126).
+  //  * a tile too many on the first XCD is as long as all the others again (3 heads of 5423 x 23452, 252 full tiles of 64 rows
+  //    and 3 partial ones: 226 us, segments 114).
+  //  * segments that need more than the library's own array are those of keys so long that the estimate is too low for them:
+  //    there by the lines 70 + 14, 80 + 16 a quarter, 60 + 15 a half (one head of 29824 x 35072 segments 277, groups 250, 24 of
+  //    2346 x 56082 761 : 680, 12 of 2618 x 172602 1332 : 1176, 24 of 1064 x 45280 319 : 316, 8 of 3935 x 91614 583 : 601).
+  //    httm_attention_log2_static accepts by them, too: what runs in key groups needs nothing of the array.
+  const int64_t kt = (keys + kAttnKeyTile - 1) / kAttnKeyTile, half = (kt + 1) / 2, quarter = (kt + 3) / 4;
+  const bool few = count_tiles(q_off, H, 64) <= cus;
+  const bool lines = split_slots(r.split) * kAttnSlotWords * 4 > HTTM_STATIC_SCRATCH_BYTES;
+  const AttnGroups groups = choose_key_groups(
+      [&](int rows) { return lines ? count_tiles(q_off, H, rows) : count_dealt_tiles(q_off, H, rows); }, cus, kt);
+  const int64_t u = r.split.share_units;
+  int64_t groups_time = groups.time, split_time = 0;
+  if (lines) {
+    groups_time = few ? 70 + 14 * quarter : count_tiles(q_off, H, 128) <= cus ? 80 + 16 * quarter
                 : count_tiles(q_off, H, kAttnTileRows) <= cus ? 60 + 15 * half : INT64_MAX;
+    split_time = 120 + split_slots(r.split) / 2 + (r.split.shares > cus ? 15 : 9) * u;
+  } else if (r.split.n_tiles > 0) {
+    int64_t rows = 0, all_kt = 0;
+    for (int h = 0; h < H; ++h) {
+      const int64_t mq = q_off[h + 1] - q_off[h];
+      rows += mq;
+      if (mq > 0) all_kt += (k_off[h + 1] - k_off[h] + kAttnKeyTile - 1) / kAttnKeyTile;
+    }
+    const int64_t tile_rows = kAttnTileRows * count_tiles(q_off, H, kAttnTileRows);
+    split_time = 112 + 28 * split_slots(r.split) / 100 + (73 * u + (29 * u + 42 * kt / u) * rows / tile_rows) / 10;
+    if (few && groups.tiles != AttnTiles::kTiles256) groups_time += std::max<int64_t>(groups.time - 300, 0) / 8 + 3 * all_kt / 128 - 8;
+  }
   if (groups.tiles != AttnTiles::kTiles256 && (r.split.n_tiles == 0 || groups_time <= split_time)) {
     no_split();
     r.tiles = groups.tiles;

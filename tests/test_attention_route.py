@@ -88,3 +88,13 @@ def test_launches_with_long_segments_run_in_key_groups_where_they_are_no_slower(
         assert r["tiles"] == [tiles] and p["slots"] == 0
     else:
         assert r["tiles"] == ["tiles256"] and p["slots"] * 256 * 66 * 4 > 32 << 20
+
+
+# few rows a head against many keys, where key groups would read every head's keys once per tile: in segments; and a
+# launch whose 64-row tiles fit the CUs but not, as they are dealt out, the first XCD's
+@pytest.mark.parametrize("H,mq,mk,segments", [(24, 68, 6785, True), (64, 90, 19556, True), (32, 141, 8058, True), (16, 41, 4702, True),
+                                              (3, 5423, 23452, True), (16, 250, 3000, False), (12, 929, 4000, False)])
+def test_few_rows_a_head(H, mq, mk, segments):
+    off = lambda n: [h * n for h in range(H + 1)]  # noqa: E731
+    assert (httm.attention_split_plan(off(mq), off(mk))["n_tiles"] > 0) == segments
+    assert (_check_rows([mq] * H, [mk] * H)["tiles"] == ["tiles256"]) == segments
