@@ -1398,38 +1398,7 @@ hipError_t launch_tiles(AttnTiles tiles, AttnArgs& a, bool log2_keys, const Head
   }
 }
 
-}  // namespace
-
-int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_host, int H) {
-  AttnRoute route;
-  choose_attention_route(q_off_host, k_off_host, H, compute_units(), INT64_MAX, &route);
-  return split_slots(route.split) * kAttnSlotWords * 4;
-}
-
-void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows) {
-  // Next to merged rows in 256-row tiles the others are more of the same in one launch.  Otherwise both are short
-  // launches of their own, in the tiles that are quickest.  Layers with the outlier filter, all in one
-  // launch of 256-row tiles / so: 16 heads x 923 rows and 4961 others 76.1 / 73.2 us, 12 x 450 and 1207 59.2 / 55.6.
-  int64_t q_off[kAttnMaxHeads + 1], k_off[kAttnMaxHeads + 1];
-  for (int h = 0; h <= H; ++h) {
-    q_off[h] = h * M_q;
-    k_off[h] = h * M_k;
-  }
-  const int64_t cus = compute_units();
-  AttnRoute route;
-  choose_attention_route(q_off, k_off, H, cus, attention_scratch_bytes(H) / 4, &route);
-  AttnTiles t = AttnTiles::kTiles256;
-  if (route.tiles != AttnTiles::kTiles256)
-    t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile).tiles;
-  *kind = (int32_t)t;
-  *tile_rows = t == AttnTiles::kGroups32 ? 32 : t == AttnTiles::kGroups64 ? 64
-             : t == AttnTiles::kTiles256 || t == AttnTiles::kGroups256 ? kAttnTileRows : 128;
-}
-
-hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o, const DevTiles& dev,
-                                      const int64_t* k_off_host, int H, float scale, bool log2_keys,
-                                      hipStream_t stream, const UnmergeTarget* unmerge) {
-  if (dev.max_tiles <= 0) return hipSuccess;
+AttnArgs attention_args(const void* q, const void* k, const void* v, void* o, int H, float scale, bool log2_keys, const UnmergeTarget* unmerge) {
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
   a.q = (const bf16_t*)q;
@@ -1439,6 +1408,62 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
   a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
   a.H = H;
   if (unmerge) a.um = *unmerge;
+  return a;
+}
+
+// `extra_tiles` of the device-side list go to the end of the (last) launch.
+hipError_t launch_route(const AttnRoute& route, AttnArgs& a, bool log2_keys, const int64_t* q_off_host, const int64_t* k_off_host, int H,
+                        int64_t cus, hipStream_t stream, void* scratch, int extra_tiles) {
+  if (route.tiles == AttnTiles::kTiles256)
+    return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, extra_tiles, &route, (float*)scratch);
+  if (route.tiles != AttnTiles::kRounds)
+    return launch_tiles(route.tiles, a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, extra_tiles);
+  HeadRows whole, rest;
+  split_rounds(q_off_host, H, cus, &whole, &rest);
+  const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
+  if (e != hipSuccess) return e;
+  return launch_tiles(route.rest, a, log2_keys, rest, k_off_host, H, stream, extra_tiles);
+}
+
+}  // namespace
+
+int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_host, int H) {
+  AttnRoute route;
+  choose_attention_route(q_off_host, k_off_host, H, compute_units(), INT64_MAX, &route);
+  return split_slots(route.split) * kAttnSlotWords * 4;
+}
+
+void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows) {
+  // In the merged rows' tiles, behind them in the same launch, if all of them are still one round, and in 256-row tiles of one
+  // key group always.  Otherwise in a launch of their own, in the tiles that are quickest: a launch of 256-row tiles of one key
+  // group for both would be quicker behind whole rounds (3 to 7 %), but the merged rows' sums would not be those of the
+  // separate stage call.  Layers with the outlier filter, us, all in 256-row tiles of one key group / always two launches /
+  // so: 12 heads x 360 rows x 360 keys and 698 others 57 / 55 / 49, 16 x 1140 x 1140 and 441 69 / 67 / 56, 16 x 2676 x 2676 and 6790
+  // 102 / 111 / 91, 24 x 2028 x 2028 and 10872 105 / 114 / 94, 8 x 6294 x 8726 and 3530 252 / 218 / 174, 24 x 1578 x 1578 and
+  // 5736 86 / 93 / 78; two launches: 12 x 4962 x 4962 and 10522 184 / 169 / 169, 16 x 9914 x 1471 and 3988 163 / 172 / 172.
+  int64_t q_off[kAttnMaxHeads + 1], k_off[kAttnMaxHeads + 1];
+  for (int h = 0; h <= H; ++h) {
+    q_off[h] = h * M_q;
+    k_off[h] = h * M_k;
+  }
+  const int64_t cus = compute_units();
+  AttnRoute route;
+  choose_attention_route(q_off, k_off, H, cus, attention_scratch_bytes(H) / 4, &route);
+  AttnTiles t = last_tiles(route);
+  if (t != AttnTiles::kTiles256) {
+    const int64_t extra = rows / attention_tile_rows(t) + (H + 1) / 2;     // (a partial tile per head at most: half of them, say)
+    if (count_last_tiles(route, q_off, H, cus) + (extra + 7) / 8 * 8 > (t == AttnTiles::kTiles128 ? kSmallTileRound : cus))
+      t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile).tiles;
+  }
+  *kind = (int32_t)t;
+  *tile_rows = attention_tile_rows(t);
+}
+
+hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o, const DevTiles& dev,
+                                      const int64_t* k_off_host, int H, float scale, bool log2_keys,
+                                      hipStream_t stream, const UnmergeTarget* unmerge) {
+  if (dev.max_tiles <= 0) return hipSuccess;
+  AttnArgs a = attention_args(q, k, v, o, H, scale, log2_keys, unmerge);
   a.dev_q_off = dev.q_off;
   a.dev_tiles = dev.tiles;
   a.q2 = a.q;
@@ -1451,55 +1476,31 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
                                  const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,
                                  const void* q2, void* o2, const DevTiles& dev, bool log2_keys, hipStream_t stream,
                                  void* scratch, int64_t scratch_bytes, const UnmergeTarget* unmerge) {
+  AttnArgs a = attention_args(q, k, v, o, H, scale, log2_keys, unmerge);
+  const int64_t cus = compute_units();
   AttnRoute route;
-  choose_attention_route(q_off_host, k_off_host, H, compute_units(), scratch ? scratch_bytes / 4 : 0, &route);
-  if (route.tiles != AttnTiles::kTiles256 || dev.kind != (int32_t)AttnTiles::kTiles256) {
-    const hipError_t e = launch_attention(q, k, v, o, q_off_host, k_off_host, H, scale, log2_keys, stream, scratch, scratch_bytes, unmerge);
-    if (e != hipSuccess) return e;
-    return launch_attention_dev_tiles(q2, k, v, o2, dev, k_off_host, H, scale, log2_keys, stream, unmerge);
+  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
+  const bool together = dev.max_tiles > 0 && dev.kind == (int32_t)last_tiles(route);
+  if (together) {
+    a.dev_q_off = dev.q_off;
+    a.dev_tiles = dev.tiles;
+    a.q2 = (const bf16_t*)q2;
+    a.o2 = (bf16_t*)o2;
   }
-  AttnArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.q = (const bf16_t*)q;
-  a.k = (const bf16_t*)k;
-  a.v = (const bf16_t*)v;
-  a.o = (bf16_t*)o;
-  a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.H = H;
-  if (unmerge) a.um = *unmerge;
-  a.dev_q_off = dev.q_off;
-  a.dev_tiles = dev.max_tiles > 0 ? dev.tiles : nullptr;
-  a.q2 = (const bf16_t*)q2;
-  a.o2 = (bf16_t*)o2;
-  return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, dev.max_tiles > 0 ? dev.max_tiles : 0,
-                          &route, (float*)scratch);
+  const hipError_t e = launch_route(route, a, log2_keys, q_off_host, k_off_host, H, cus, stream, scratch, together ? dev.max_tiles : 0);
+  if (e != hipSuccess || together) return e;
+  return launch_attention_dev_tiles(q2, k, v, o2, dev, k_off_host, H, scale, log2_keys, stream, unmerge);
 }
 
 hipError_t launch_attention(const void* q, const void* k, const void* v, void* o,
                             const int64_t* q_off_host, const int64_t* k_off_host, int H,
                             float scale, bool log2_keys, hipStream_t stream, void* scratch, int64_t scratch_bytes,
                             const UnmergeTarget* unmerge) {
-  AttnArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.q = (const bf16_t*)q;
-  a.k = (const bf16_t*)k;
-  a.v = (const bf16_t*)v;
-  a.o = (bf16_t*)o;
-  a.scale_log2 = log2_keys ? 1.0f : scale * 1.4426950408889634f;
-  a.H = H;
-  if (unmerge) a.um = *unmerge;
-  const HeadRows rows = all_rows(q_off_host, H);
+  AttnArgs a = attention_args(q, k, v, o, H, scale, log2_keys, unmerge);
   const int64_t cus = compute_units();
   AttnRoute route;
   choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
-  if (route.tiles == AttnTiles::kTiles256)
-    return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, 0, &route, (float*)scratch);
-  if (route.tiles != AttnTiles::kRounds) return launch_tiles(route.tiles, a, log2_keys, rows, k_off_host, H, stream);
-  HeadRows whole, rest;
-  split_rounds(q_off_host, H, cus, &whole, &rest);
-  const hipError_t e = launch_cfg<4, 4>(a, log2_keys, whole, k_off_host, H, stream);
-  if (e != hipSuccess) return e;
-  return launch_tiles(route.rest, a, log2_keys, rest, k_off_host, H, stream);
+  return launch_route(route, a, log2_keys, q_off_host, k_off_host, H, cus, stream, scratch, 0);
 }
 
 // ---- scratch that belongs to the library -------------------------------------------------------

@@ -245,6 +245,18 @@ struct AttnRoute {
   AttnTiles rest;           // kRounds: what the rest runs in
 };
 
+inline int attention_tile_rows(AttnTiles t) {
+  switch (t) {
+    case AttnTiles::kGroups32: return 32;
+    case AttnTiles::kGroups64: return 64;
+    case AttnTiles::kTiles128: case AttnTiles::kGroups128: case AttnTiles::kGroups128Wide: return 128;
+    default: return kAttnTileRows;
+  }
+}
+
+// The tiles of the only or the last launch of a route.
+inline AttnTiles last_tiles(const AttnRoute& r) { return r.tiles == AttnTiles::kRounds ? r.rest : r.tiles; }
+
 // 128-row tiles that run at once (three workgroups per CU): a problem with no more of them runs those
 constexpr int64_t kSmallTileRound = 768;
 
@@ -341,6 +353,17 @@ inline void split_rounds(const int64_t* q_off, int H, int64_t cus, HeadRows* who
 // First row, inside head h of M rows, of the tile at `q0` of a launch whose rows of that head begin at row `first` of the
 // packed tensor: a launch may have the last rows of a head only.
 __host__ __device__ inline int row_in_head(int64_t first, int h, int64_t M, int q0) { return (int)(first - h * M) + q0; }
+
+// Tiles of the only or the last launch of a route, dealt out as in count_dealt_tiles.
+inline int64_t count_last_tiles(const AttnRoute& r, const int64_t* q_off, int H, int64_t cus) {
+  const int rows = attention_tile_rows(last_tiles(r));
+  if (r.tiles != AttnTiles::kRounds) return count_dealt_tiles(q_off, H, rows);
+  HeadRows whole, rest;
+  split_rounds(q_off, H, cus, &whole, &rest);
+  int64_t off[HTTM_MAX_HEADS + 1] = {0};
+  for (int h = 0; h < H; ++h) off[h + 1] = off[h] + rest.count[h];
+  return count_dealt_tiles(off, H, rows);
+}
 
 // The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).
 inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words,

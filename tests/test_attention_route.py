@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import paper_2511_21317_amd as httm
-from test_gpu_layer_unmerge import CASES
+from test_gpu_layer_unmerge import CASES, FILTERED
 
 
 def _check_rows(mq, mk, scratch_bytes=None):
@@ -31,15 +31,14 @@ def _layer_rows(case):
 
 # the cases of test_gpu_layer_unmerge.py that are there for the tiles their names begin with
 KINDS = ("groups128_wide", "groups128", "groups32", "groups64", "groups256", "tiles128", "segments", "rounds")
-BY_KIND = [(c, kind) for c in CASES for kind in KINDS[:1] if c[0].startswith(kind)] + \
-          [(c, kind) for c in CASES for kind in KINDS[1:] if c[0].startswith(kind) and not c[0].startswith(KINDS[0])]
+BY_KIND = [(c, next(kind for kind in KINDS if c[0].startswith(kind))) for c in CASES + FILTERED if c[0].startswith(KINDS)]
 
 
 def test_every_kind_of_tile_has_a_layer():
     assert {kind for _, kind in BY_KIND} == set(KINDS)
 
 
-@pytest.mark.parametrize("case,kind", BY_KIND, ids=[c[0] for c, _ in BY_KIND])
+@pytest.mark.parametrize("case,kind", BY_KIND, ids=["-".join(str(x) for x in c[:1] + c[9:]) for c, _ in BY_KIND])
 def test_layers_run_in_the_tiles_their_names_say(case, kind):
     mq, mk = _layer_rows(case)
     r = _check_rows(mq, mk)

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import paper_2511_21317_amd as httm
-from gpu_util import require_gpu
+from gpu_util import merged_attention, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -61,6 +61,44 @@ def test_layer_outputs_are_the_stage_kernels_copies(case):
         httm.unmerge_filtered(plan, views["o_m"], views["o_out"], views["assign_q"], want)
     else:
         httm.unmerge(plan, views["o_m"], views["assign_q"], want)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    assert bool(torch.isfinite(out.float()).all())
+    plan.close()
+
+
+# the outlier queries in the merged rows' tiles, behind them in one launch, or in tiles and a launch of their own
+FILTERED = [
+    ("groups32", 5, 19, 17, 4, 2, 0.86, 0.86, 8, {"outlier_frac": 0.05, "log2_keys": False}),
+    ("groups64", 3, 33, 19, 4, 4, 0.34, 0.73, 8, {"outlier_frac": 0.005}),
+    ("groups128", 4, 20, 17, 4, 1, 0.24, 0.24, 16, {"outlier_frac": 0.02}),
+    ("groups128_apart", 5, 28, 19, 4, 4, 0.38, 0.35, 16, {"outlier_frac": 0.1}),
+    ("groups128_wide", 25, 21, 17, 5, 3, 0.65, 0.49, 8, {"outlier_frac": 0.005}),
+    ("groups256", 4, 37, 31, 5, 3, 0.41, 0.41, 16, {"outlier_frac": 0.1}),
+    ("groups256_plain_keys", 33, 29, 15, 6, 6, 0.7, 0.7, 8, {"outlier_frac": 0.02, "log2_keys": False}),
+    ("groups256_apart", 19, 27, 34, 4, 4, 0.73, 0.73, 12, {"outlier_frac": 0.05}),
+    ("tiles128", 3, 32, 26, 8, 4, 0.47, 0.89, 16, {"outlier_frac": 0.1, "log2_keys": False}),
+    ("rounds", 11, 33, 30, 4, 2, 0.25, 0.91, 16, {"outlier_frac": 0.02}),
+    ("rounds_apart", 19, 31, 21, 6, 6, 0.21, 0.89, 16, {"outlier_frac": 0.02, "log2_keys": False}),
+]
+
+
+@pytest.mark.parametrize("case", FILTERED, ids=[c[0] for c in FILTERED])
+def test_filtered_layer_outputs_are_those_of_the_stage_calls(case):
+    require_gpu()
+    name, S, Hp, Wp, b, T, rho_q, rho_kv, H, opts = case
+    print(f"[case] filtered {name}", flush=True)
+    plan = httm.Plan(httm.make_geom(S, Hp, Wp, b, T, rho_q, rho_kv, H=H, **{"log2_keys": True, **opts}))
+    gen = torch.Generator(device="cuda").manual_seed(100 + len(name))
+    q, k, v = (torch.randn((H, plan.N, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out, want = (torch.full((plan.N, H * 64), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    httm.layer_forward(plan, q, k, v, out, httm.alloc_workspace(plan))
+    staged = httm.workspace_views(plan, httm.alloc_workspace(plan))
+    httm.reorder_match_merge_filtered(plan, q, k, v, staged["q_m"], staged["k_m"], staged["v_m"], staged["assign_q"],
+                                      staged["assign_k"], staged["eps_q"], staged["q_out"])
+    merged_attention(plan, staged["q_m"], staged["k_m"], staged["v_m"], staged["o_m"])
+    httm.attention_outliers(plan, staged["q_out"], staged["k_m"], staged["v_m"], staged["o_out"])
+    httm.unmerge_filtered(plan, staged["o_m"], staged["o_out"], staged["assign_q"], want)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), want.view(torch.int16))
     assert bool(torch.isfinite(out.float()).all())
