@@ -1453,7 +1453,7 @@ void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* ki
   if (t != AttnTiles::kTiles256) {
     const int64_t extra = rows / attention_tile_rows(t) + (H + 1) / 2;     // (a partial tile per head at most: half of them, say)
     if (count_last_tiles(route, q_off, H, cus) + (extra + 7) / 8 * 8 > (t == AttnTiles::kTiles128 ? kSmallTileRound : cus))
-      t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile).tiles;
+      t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile, 0, rows).tiles;
   }
   *kind = (int32_t)t;
   *tile_rows = attention_tile_rows(t);

@@ -304,10 +304,15 @@ struct AttnGroups {
   AttnTiles tiles;
   int64_t time;
 };
+// A workgroup with a full tile looks its head up, one after the other (from the ninth on a fortieth of a us each); one with
+// a partial tile has it from a list, and heads of at most 64 rows leave half of a 128-row tile's waves out of the way: us, 32-row
+// tiles / 128-row tiles of one group, 16 heads of 40 x 73 6.7 / 6.4, 32 of 33 x 66 7.1 / 6.3, 64 of 66 x 69 8.4 / 6.8, but 16 of
+// 132 x 67 6.8 / 7.4.  `longest`: rows of the longest head.
 template <typename Count>
-inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt) {
+inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt, int H, int64_t longest) {
   AttnGroups best = {AttnTiles::kTiles256, INT64_MAX};
   auto offer = [&](AttnTiles tiles, int rows, int64_t waves_of_tiles, int64_t time) {
+    if (longest >= rows && H > 8) time += (H - 8) / 4;
     if (time < best.time && count(rows) <= waves_of_tiles * cus) best = {tiles, time};
   };
   const int64_t half = (kt + 1) / 2, quarter = (kt + 3) / 4;
@@ -316,7 +321,7 @@ inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt) {
   offer(AttnTiles::kGroups128, 128, 1, 60 + 19 * half / 2);
   offer(AttnTiles::kGroups128Wide, 128, 1, 86 + 17 * quarter);
   offer(AttnTiles::kGroups256, kAttnTileRows, 1, 95 + 15 * half);
-  offer(AttnTiles::kTiles128, 128, 1, 49 + 11 * kt / 2);
+  offer(AttnTiles::kTiles128, 128, 1, (longest <= 64 ? 44 : 49) + 11 * kt / 2);
   offer(AttnTiles::kTiles128, 128, 2, 60 + 9 * kt);
   return best;
 }
@@ -372,8 +377,9 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
   r.tiles = AttnTiles::kTiles256;
   r.split.n_tiles = 0;
   if (scratch_words > 0) plan_attention_split(q_off, k_off, H, cus, &r.split, &r.kept_full, &r.split_ragged);
-  int64_t full = 0, keys = 0;
+  int64_t full = 0, keys = 0, longest = 0;
   for (int h = 0; h < H; ++h) {
+    longest = std::max(longest, q_off[h + 1] - q_off[h]);
     full += (q_off[h + 1] - q_off[h]) / kAttnTileRows;
     if (k_off[h + 1] - k_off[h] > keys) keys = k_off[h + 1] - k_off[h];
   }
@@ -401,7 +407,7 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
   const bool few = count_tiles(q_off, H, 64) <= cus;
   const bool lines = split_slots(r.split) * kAttnSlotWords * 4 > HTTM_STATIC_SCRATCH_BYTES;
   const AttnGroups groups = choose_key_groups(
-      [&](int rows) { return lines ? count_tiles(q_off, H, rows) : count_dealt_tiles(q_off, H, rows); }, cus, kt);
+      [&](int rows) { return lines ? count_tiles(q_off, H, rows) : count_dealt_tiles(q_off, H, rows); }, cus, kt, H, longest);
   const int64_t u = r.split.share_units;
   int64_t groups_time = groups.time, split_time = 0;
   if (lines) {
@@ -431,7 +437,7 @@ inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, i
   // rows and keys 321 -> 294 us, 10186 x 15158 523 -> 495, 12500 579 -> 554; 5516 120 with 128-row tiles, 133 so.
   if (full >= 2 * cus && count_rest_tiles(q_off, H, cus, 128) <= cus) {
     r.tiles = AttnTiles::kRounds;
-    r.rest = choose_key_groups([&](int rows) { return count_rest_tiles(q_off, H, cus, rows); }, cus, kt).tiles;
+    r.rest = choose_key_groups([&](int rows) { return count_rest_tiles(q_off, H, cus, rows); }, cus, kt, H, longest).tiles;
     return;
   }
   // Otherwise a short problem that fits into one round of 128-row tiles (three workgroups per CU, 768 at a

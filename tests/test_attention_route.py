@@ -97,3 +97,12 @@ def test_few_rows_a_head(H, mq, mk, segments):
     off = lambda n: [h * n for h in range(H + 1)]  # noqa: E731
     assert (httm.attention_split_plan(off(mq), off(mk))["n_tiles"] > 0) == segments
     assert (_check_rows([mq] * H, [mk] * H)["tiles"] == ["tiles256"]) == segments
+
+
+# against two key tiles: heads of at most 64 rows leave half of a 128-row tile's waves idle, longer ones do not; full tiles
+# of many heads look theirs up
+@pytest.mark.parametrize("H,mq,mk,tiles", [(16, 40, 73, "tiles128"), (32, 64, 128, "tiles128"), (48, 43, 65, "tiles128"), (16, 65, 128, "groups32"),
+                                           (64, 66, 69, "tiles128"), (3, 181, 80, "groups32"),
+                                           (16, 200, 100, "groups32"), (16, 40, 129, "groups32"), (16, 500, 64, "tiles128")])
+def test_few_rows_against_few_keys(H, mq, mk, tiles):
+    assert _check_rows([mq] * H, [mk] * H)["tiles"] == [tiles]
