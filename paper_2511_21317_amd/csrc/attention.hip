@@ -557,8 +557,9 @@ __device__ __forceinline__ void running_max_step(WaveState<NQ>& w, float (&l)[NQ
 // 64 per wave instruction, the ones that belong here moved to the front of the wave so that 8 lanes then copy
 // a row each to out[pi(j)][h].  A kernel of its own for this is bound by writing `out`; here the writes go out
 // under the products of the other workgroups, the rows are not read back and a launch is saved.  What is left
-// of it at the end of a launch is one tile's chain of round trips (clusters, exchange, stores: 2 to 4 us; 10 us in
-// attention_split_reduce_kernel where a block keeps a thousand clusters, of which its workgroups look for 64).
+// of it at the end of a launch is one tile's chain of round trips (clusters, exchange, stores: 2 to 4 us).  In
+// attention_split_reduce_kernel it is 1 to 2 us, 21 where a block keeps a thousand clusters (3840 tokens, which four
+// workgroups a tile walk for 64 rows each: 15 -> 36 us, against a stage-4 kernel of 181).
 // A layer with the stage-4 kernel behind it / with this: 2 frames of 16 x 16 22.8 / 17.4 us, 8 of 37 x 37 140.6 /
 // 135.9, 200 of 37 x 37 2973 / 2918, with outliers 5753 / 5675; every random geometry of 12 was faster.
 

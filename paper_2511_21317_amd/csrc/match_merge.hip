@@ -318,8 +318,9 @@ void match_merge_kernel(const MatchMergeArgs a) {
     if (TOPR) __syncthreads();
   } else {
     // ---- 3. similarities and arg-max -----------------------------------------------------------
-    // Wave w owns the tokens 64w .. 64w+63, i.e. the two 32-token tiles 2w and 2w+1 (one tile in the
-    // instance of 32 tokens).  The two tiles go through the dst tiles side by side: they share the dst operand
+    // Wave w owns the tokens 64w .. 64w+63, i.e. the two 32-token tiles 2w and 2w+1 (one tile, or half of one, in the
+    // instances of 32 and 16 tokens); in the eight-wave instances of fewer than 512 tokens (SPREAD) the tiles w and w+8, as
+    // far as there are any.  Two tiles go through the dst tiles side by side: they share the dst operand
     // and the dst norms, and their dependent chains of LDS reads overlap.
     const int ndt = (kd + 31) >> 5;
     float my_sc = 1.0f;                // similarity of token `tid` to the dst it would join
@@ -382,7 +383,7 @@ void match_merge_kernel(const MatchMergeArgs a) {
         }
       }
       // lanes 0..31 publish tile 0 and lanes 32..63 tile 1, so that afterwards thread `tid` holds
-      // the result of token `tid`
+      // the result of token `tid` (SPREAD: it gets it from s_res / s_sim behind the barrier)
       const int t = SUB == 2 && half ? tok[SUB - 1] : tok[0];
       if (t < n && (SUB == 2 || half == 0)) {
         int c = s_cl[t];
