@@ -286,7 +286,8 @@ HTTM_API int httm_attention_scratch(const void* q_m, const void* k_m, const void
 
 /* Host only (no GPU needed): how stage 3 with scratch cuts a launch with these head lengths on a
  * device of `compute_units` compute units - the very functions the launch and the kernels evaluate; for tests
- * and diagnostics.  A launch that would not be cut has no tiles in pieces.  HOST arrays:
+ * and diagnostics.  A launch that would not be cut has no tiles in pieces; one with log2 keys may run in larger tiles and be
+ * cut otherwise: httm_attention_wide_plan.  HOST arrays:
  *   summary[8]  : tiles that run in pieces (0: none), shares, key tiles (of 64 keys) per share,
  *                 most tiles a share touches, slots of scratch (256 rows x 66 fp32 each), key tiles of
  *                 all split tiles together, full tiles that stay whole, partial tiles that are split
@@ -301,6 +302,7 @@ HTTM_API int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* 
 
 /* Host only: which tiles stage 3 runs a launch with these head lengths in, on a device of `compute_units` compute
  * units and with `scratch_bytes` of scratch (0: none) - the decision the launch evaluates; for tests and diagnostics.
+ * (Log2 keys: unless httm_attention_wide_plan reports 512-row tiles.)
  *   tiles[2] : of the launch's workgroups, and of those of a second launch behind it (-1: there is none):
  *              0 256 rows (the ones httm_attention_split_plan reports run in pieces), 1 128 rows, 2 32, 3 64, 4 128
  *              with 32-row waves, 5 128 with 64-row waves, 6 256 - 2 to 6 share the keys among their waves
@@ -309,12 +311,24 @@ HTTM_API int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* 
 HTTM_API int httm_attention_route(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units,
                                   int64_t scratch_bytes, int32_t* tiles, int64_t* rows);
 
+/* Host only: whether a launch with log2 keys runs in 512-row tiles instead of what the two functions above report
+ * (long launches that leave few compute units idle in them), and how it is cut then; for tests and diagnostics.
+ *   summary[6] : 1 or 0 (then the rest is 0), tiles that run in pieces, shares, slots of scratch (256 rows x 66 fp32
+ *                each), full tiles that stay whole, partial tiles that are split
+ *   segments   : or NULL; 6 int32 per segment (at most max_segments, else HTTM_E_WORKSPACE_TOO_SMALL): share, head, first
+ *                query row, key tiles [t0, t1) of the head's sequence (t1 may be one more than there are), first slot (a
+ *                segment of more than 256 rows has two).  summary[1] + summary[2] bounds their number.
+ * Returns the number of segments, or a negative code. */
+HTTM_API int httm_attention_wide_plan(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units,
+                                      int64_t scratch_bytes, int32_t* summary, int32_t* segments, int64_t max_segments);
+
 /* httm_attention_log2_scratch for callers that cannot allocate device memory and have no buffer to
  * pass: code that runs under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  The scratch is an array of HTTM_STATIC_SCRATCH_BYTES inside the library's device code
+ * hipMalloc.  The scratch is an array inside the library's device code
  * (every GPU the library has run on holds its copy until the process ends); the call allocates and
  * frees nothing.  Arguments, layout and results as httm_attention_log2_scratch (bit-identical to
- * it).  A launch whose partial results need more than the array holds is refused with
+ * it).  A launch whose partial results (as httm_attention_split_plan reports them) need more than
+ * HTTM_STATIC_SCRATCH_BYTES is refused with
  * HTTM_E_WORKSPACE_TOO_SMALL and nothing is launched: use httm_attention_log2_scratch with a buffer
  * of the caller, or httm_attention_log2, which needs none.  All calls on one GPU share the array:
  * two of them that overlap in time (two streams) race - serialise them.  Its contents between

@@ -75,6 +75,7 @@ def lib() -> C.CDLL:
     L.httm_attention_log2_scratch.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, vp, C.c_int64, vp]
     L.httm_attention_log2_static.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int, C.c_int, vp]
     L.httm_attention_split_plan.argtypes = [i64p, i64p, C.c_int, C.c_int, vp, vp, C.c_int64, vp, C.c_int64]
+    L.httm_attention_wide_plan.argtypes = [i64p, i64p, C.c_int, C.c_int, C.c_int64, vp, vp, C.c_int64]
     L.httm_attention_route.argtypes = [i64p, i64p, C.c_int, C.c_int, C.c_int64, vp, vp]
     L.httm_attention_scratch_bytes.argtypes = [C.c_int]
     L.httm_attention_scratch_bytes.restype = C.c_int64
@@ -88,7 +89,7 @@ def lib() -> C.CDLL:
     for name in ("httm_geom_sizes", "httm_workspace_layout", "httm_geom_tables", "httm_geom_block_forms", "httm_plan_create", "httm_plan_clone",
                  "httm_plan_destroy", "httm_plan_query", "httm_reorder", "httm_match_merge",
                  "httm_reorder_match_merge",
-                 "httm_attention", "httm_attention_scratch", "httm_attention_log2", "httm_attention_log2_scratch", "httm_attention_log2_static", "httm_attention_split_plan", "httm_attention_route", "httm_unmerge", "httm_layer_forward",
+                 "httm_attention", "httm_attention_scratch", "httm_attention_log2", "httm_attention_log2_scratch", "httm_attention_log2_static", "httm_attention_split_plan", "httm_attention_route", "httm_attention_wide_plan", "httm_unmerge", "httm_layer_forward",
                  "httm_reorder_match_merge_filtered", "httm_attention_outliers", "httm_unmerge_filtered",
                  "httm_outlier_stats", "httm_global_match"):
         getattr(L, name).restype = C.c_int
@@ -324,6 +325,24 @@ def attention_route(q_offsets, k_offsets, compute_units: int = 256, scratch_byte
     _check(lib().httm_attention_route(qo, ko, H, int(compute_units), scratch, ptr(tiles), ptr(rows)), "httm_attention_route")
     names = [ATTENTION_TILES[t] for t in tiles if t >= 0]
     return {"tiles": names, "rows": rows[:len(names)]}
+
+
+def attention_wide_plan(q_offsets, k_offsets, compute_units: int = 256, scratch_bytes: int | None = None) -> dict | None:
+    """How a launch with log2 keys runs in 512-row tiles (host only), None if it does not: "segments" are rows of share,
+    head, first query row, first and last key tile, slot.  scratch_bytes: None = attention_scratch_bytes(H)."""
+    H = len(q_offsets) - 1
+    qo = (C.c_int64 * (H + 1))(*[int(x) for x in q_offsets])
+    ko = (C.c_int64 * (H + 1))(*[int(x) for x in k_offsets])
+    scratch = attention_scratch_bytes(H) if scratch_bytes is None else int(scratch_bytes)
+    summary, seg = np.zeros(6, np.int32), np.zeros((2048, 6), np.int32)
+    ptr = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    n = lib().httm_attention_wide_plan(qo, ko, H, int(compute_units), scratch, ptr(summary), ptr(seg), seg.shape[0])
+    if n < 0:
+        _check(n, "httm_attention_wide_plan")
+    if not summary[0]:
+        return None
+    names = ("n_tiles", "shares", "slots", "kept_full", "split_ragged")
+    return {**{k: int(v) for k, v in zip(names, summary[1:])}, "segments": seg[:n]}
 
 
 def attention_scratch_bytes(H: int) -> int:

@@ -18,6 +18,8 @@ SOURCES = ["api.hip", "geometry.cpp", "reorder_unmerge.hip", "match_merge.hip", 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU ops
+    # products of kernels with more than 256 registers a lane: results in the ordinary registers (attention.hip, mfma_o())
+    "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-fvisibility=hidden", "-Wall", "-Wno-unused-function",
 ]
 

@@ -313,7 +313,7 @@ int httm_plan_create(const httm_geom_t* g, httm_plan_t** out) {
   p->outlier_cap = p->sizes.outlier_cap;
   if (rc == HTTM_OK && p->outlier_cap > 0) {
     OutlierBuffers& b = p->ob;
-    choose_dev_tiles(p->outlier_cap, p->sizes.M_q, p->sizes.M_k, g->H, &b.tile_kind, &b.tile_rows);
+    choose_dev_tiles(p->outlier_cap, p->sizes.M_q, p->sizes.M_k, g->H, (g->flags & HTTM_FLAG_LOG2_KEYS) != 0, &b.tile_kind, &b.tile_rows);
     b.max_tiles = (int32_t)(p->outlier_cap / b.tile_rows + g->H);
     const size_t words = sizeof(SelectState) / 4 + 3 * 2048 + (size_t)g->H * 2 + 1 +
                          2 * (size_t)g->H * p->n_items + (size_t)g->H * (p->n_items / kOutlierCountItemsMin + 1) + 1 +
@@ -481,7 +481,7 @@ int httm_attention_log2_static(const void* q_m, const void* k_log2, const void* 
   void* lib_scratch = nullptr;
   HTTM_HIP(attention_static_scratch(&lib_scratch));
   return run_attention(q_m, k_log2, v_m, o_m, q_offsets, k_offsets, H, d_head, 1.0f, true, lib_scratch,
-                       kAttnStaticScratchBytes, stream);
+                       kAttnScratchBytes, stream);
 }
 
 int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units,
@@ -513,7 +513,7 @@ int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets
       int first = 0, count = 0;
       split_share_tiles(sp, s, &first, &count);
       for (int e = first; e < first + count; ++e) {
-        const SplitSegment g = split_segment(sp, s, e);
+        const SplitSegment g = split_segment<false>(sp, s, e);
         const int32_t row[5] = {g.head, g.q0, g.t0, g.t1, g.slot};
         if (g.slot < 0 || g.slot >= n_slots) return HTTM_E_INVALID_ARG;
         std::memcpy(segments + 5 * (int64_t)g.slot, row, sizeof(row));
@@ -523,7 +523,7 @@ int httm_attention_split_plan(const int64_t* q_offsets, const int64_t* k_offsets
   if (tiles) {
     if (max_tiles < sp.n_tiles) return HTTM_E_WORKSPACE_TOO_SMALL;
     for (int e = 0; e < sp.n_tiles; ++e) {
-      const SplitTile t = split_tile(sp, e);
+      const SplitTile t = split_tile<false>(sp, e);
       const int32_t row[4] = {t.head, t.q0, t.first_share, t.last_share};
       std::memcpy(tiles + 4 * e, row, sizeof(row));
     }
@@ -552,6 +552,39 @@ int httm_attention_route(const int64_t* q_offsets, const int64_t* k_offsets, int
       }
   }
   return HTTM_OK;
+}
+
+int httm_attention_wide_plan(const int64_t* q_offsets, const int64_t* k_offsets, int H, int compute_units, int64_t scratch_bytes,
+                             int32_t* summary, int32_t* segments, int64_t max_segments) {
+  if (!q_offsets || !k_offsets || !summary || H <= 0 || compute_units <= 0 || scratch_bytes < 0) return HTTM_E_INVALID_ARG;
+  if (H > HTTM_MAX_HEADS) return HTTM_E_UNSUPPORTED;
+  for (int h = 0; h < H; ++h)
+    if (q_offsets[h + 1] < q_offsets[h] || k_offsets[h + 1] < k_offsets[h]) return HTTM_E_INVALID_ARG;
+  AttnRoute route;
+  choose_attention_route(q_offsets, k_offsets, H, compute_units, scratch_bytes / 4, &route, true);
+  for (int i = 0; i < 6; ++i) summary[i] = 0;
+  if (route.tiles != AttnTiles::kTiles512) return 0;
+  const SplitPlan& sp = route.split;
+  summary[0] = 1;
+  if (sp.n_tiles == 0) return 0;
+  summary[1] = sp.n_tiles;
+  summary[2] = sp.shares;
+  summary[3] = sp.slots;
+  summary[4] = (int32_t)route.kept_full;
+  summary[5] = route.split_ragged;
+  int n = 0;
+  for (int s = 0; s < sp.shares; ++s) {
+    int first, count;
+    split_share_tiles(sp, s, &first, &count);
+    for (int i = 0; i < count; ++i, ++n) {
+      if (!segments) continue;
+      if (n >= max_segments) return HTTM_E_WORKSPACE_TOO_SMALL;
+      const SplitSegment g = split_segment<true>(sp, s, first + i);
+      const int32_t row[6] = {s, g.head, g.q0, g.t0, g.t1, g.slot};
+      std::memcpy(segments + 6 * n, row, sizeof(row));
+    }
+  }
+  return n;
 }
 
 int64_t httm_attention_scratch_bytes(int H) { return H > 0 && H <= HTTM_MAX_HEADS ? attention_scratch_bytes(H) : 0; }

@@ -129,6 +129,7 @@ struct AttnArgs {
   // list.  n_ragged / ragged_head and n_full count only the tiles that stay whole.
   int32_t split_per_xcd;
   int32_t main_blocks;
+  int32_t share_block0;   // 512-row tiles: the shares come last, from this workgroup on
   float* split_o;   // [slots * 256][64] sums of weight * v
   float* split_l;   // [slots * 256]     sums of weights
   float* split_m;   // [slots * 256]     the rows' shifts
@@ -141,6 +142,9 @@ static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KB");
 // chunk c of row r sits at chunk position c ^ (2 * ((r >> 1) & 3)), so that the eight rows which half a
 // transposing read touches (32 bytes each, same channels) fall into eight different 32-byte bank groups.
 __device__ __forceinline__ int v_swizzle(int row) { return ((row >> 1) & 3) << 1; }
+
+// One tile of K or V in LDS
+typedef bf16_t KvTile[kKvTile * kDHead];
 
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
@@ -289,6 +293,25 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Waves of 128 rows (NQ = 8) hold their accumulators in accumulation registers.  The compiler decides between the two
+// register files once for all products of a kernel, and the scores are read by vector instructions, so these products are
+// written out.  It does not know how long their results take: nothing else touches the accumulators between
+// accumulators_settled() before the first and after the last one (a product that adds to the register of an earlier one
+// needs no wait; the wave's loop has neither spills nor copies of them, in which that would not hold).
+template <int NQ>
+__device__ __forceinline__ void mfma_o(f32x4& o, const bf16x8& a, const bf16x8& b) {
+  if constexpr (NQ == 8)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(o) : "v"(a), "v"(b));
+  else
+    o = mfma16(a, b, o);
+}
+template <int NQ>
+__device__ __forceinline__ void accumulators_settled(WaveState<NQ>& w) {
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt)
+    asm volatile("s_nop 15\n\ts_nop 3" : "+a"(w.o_acc[0][qt]), "+a"(w.o_acc[1][qt]), "+a"(w.o_acc[2][qt]), "+a"(w.o_acc[3][qt]));
+}
+
 // Per-row shifts: the weights of a step are added to the row sums before they are multiplied with V, and a step that
 // brings a sum beyond kGuardSum (or to inf or NaN) is taken back here; `before` are the sums without it.  A row
 // with a score far above its shift takes that score for the shift, one whose sum has grown over many keys moves
@@ -369,20 +392,22 @@ __device__ __forceinline__ void pipeline_step(WaveState<NQ>& w, const bf16_t* sk
         for (int qt = 0; qt < NQ; ++qt)
           s_next[kt][qt] = mfma16(op.ak[kt * 2 + ks], w.qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s_next[kt][qt]);
   }
+  // (waves of 128 rows have no registers for two of a step's three parts side by side)
+  if (NQ == 8) __builtin_amdgcn_sched_barrier(0);
   if (DO_PV) {
     load_v_operands(op, svt, l16, grp);
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt)
-        w.o_acc[ct][qt] = mfma16(op.av[ct], p_half(w.p_old[qt >> 1], qt & 1), w.o_acc[ct][qt]);
+        mfma_o<NQ>(w.o_acc[ct][qt], op.av[ct], p_half(w.p_old[qt >> 1], qt & 1));
     if (!SHIFT) {
 #pragma unroll
       for (int i = 0; i < NQ / 2; ++i) add_row_sums(w, w.p_old[i], i);
     }
   }
   // (per-row shifts: products and softmax side by side need 4 to 6 registers too many)
-  if (SHIFT && DO_QK && DO_PV) __builtin_amdgcn_sched_barrier(0);
+  if ((SHIFT || NQ == 8) && DO_QK && DO_PV) __builtin_amdgcn_sched_barrier(0);
   if (DO_SM) {
     // s_cur[kt][qt][r]: key kv_first + 16*kt + 4*grp + r, query column l16 of tile qt
     if (MASK) {
@@ -490,6 +515,67 @@ __device__ __forceinline__ void steady_step(WaveState<NQ>& w, StepOperands& op, 
   if (PREFETCH) load_k_operands(op, sk_next, l16, grp);
   __builtin_amdgcn_sched_barrier(0);
   between();        // requests that must follow the step's last LDS read in program order
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+    w.s_cur[0][qt] = s_next[0][qt];
+    w.s_cur[1][qt] = s_next[1][qt];
+  }
+#pragma unroll
+  for (int i = 0; i < NQ / 2; ++i) w.p_old[i] = p_new[i];
+}
+
+// The steady-state step of a wave of 128 rows (log2 keys): steady_step()'s order of issue, with the LDS reads between the
+// products as well - its K operands among the products with V, the next step's V operands among its products with K.
+// One wave per SIMD has nothing to issue while a burst of reads waits for its turn at the LDS.  `middle` runs between the two
+// kinds of products, `fill(g)` in the groups of the first kind.
+template <typename Middle, typename Fill>
+__device__ __forceinline__ void wide_step(WaveState<8>& w, StepOperands& op, const bf16_t* sk, const bf16_t* sv_next, int lane, Middle middle, Fill fill) {
+  constexpr int NQ = 8, NG = 8 * NQ;
+  const int l16 = lane & 15, grp = lane >> 4;
+  f32x4 s_next[2][NQ];
+  float ex[NG];
+  u32x8 p_new[NQ / 2];
+  s16x4 v_part[2];
+  auto pack = [&](int p) {   // values 2p, 2p + 1
+    uint32_t r = pack_bf16x2(ex[2 * p], ex[2 * p + 1]);
+    asm volatile("" : "+v"(r));
+    p_new[p >> 3][p & 7] = r;
+  };
+  auto group_end = [&](int g) {
+    ex[g] = __builtin_amdgcn_exp2f(w.s_cur[(g >> 2) & 1][g >> 3][g & 3]);
+    asm volatile("" : "+v"(ex[g]));
+    if (g >= 2 && (g & 1) == 0) pack((g >> 1) - 1);
+    if ((g & 15) == 7) add_row_sums(w, w.p_old[g >> 4], g >> 4);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int ksw = k_swizzle(l16), krow = 4 * grp + (l16 >> 2), vsw = v_swizzle(krow);
+#pragma unroll
+  for (int g = 0; g < NG / 2; ++g) {
+    const int ct = g / NQ, qt = ct & 1 ? NQ - 1 - g % NQ : g % NQ;
+    mfma_o<NQ>(w.o_acc[ct][qt], op.av[ct], p_half(w.p_old[qt >> 1], qt & 1));
+    if (g % 4 == 1 && g / 4 < 4) {
+      const int i = g / 4;
+      op.ak[i] = *(const bf16x8*)(sk + ((i >> 1) * 16 + l16) * kDHead + (((i & 1) * 4 + grp) ^ ksw) * 8);
+    }
+    fill(g);
+    group_end(g);
+  }
+  middle();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int g = NG / 2; g < NG; ++g) {
+    const int i = g - NG / 2, ks = i / (2 * NQ), kt = (i / NQ) & 1, qt = kt ? NQ - 1 - i % NQ : i % NQ;
+    s_next[kt][qt] = mfma16(op.ak[kt * 2 + ks], w.qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s_next[kt][qt]);
+    if (i % 3 == 1 && i < 24) {
+      const int ct = i / 6, half = i / 3 & 1;
+      const bf16_t* p = sv_next + (krow + 16 * half) * kDHead + ((2 * ct + ((l16 & 3) >> 1)) ^ vsw) * 8 + 4 * (l16 & 1);
+      v_part[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+      if (half) op.av[ct] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v_part[0], v_part[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    group_end(g);
+  }
+  pack(NG / 2 - 1);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
@@ -1161,6 +1247,326 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
   }
 }
 
+// ---- tiles of 512 rows --------------------------------------------------------------------------------
+// Long launches with log2 keys: four waves of 128 rows, one workgroup per CU.  What bounds a long launch is power, and an
+// operand read from LDS that serves 8 products instead of 4 halves the LDS reads, the requests and the barriers of a
+// product.  The accumulators and Q lie in accumulation registers (mfma_o()), which is all 512 registers of a lane, so
+// there is one wave per SIMD and nothing hides its waits: every operand is read 10 to 30 products before its first use,
+// between other products (wide_step()), the next tile's behind a barrier in the middle of the tile's second step, and a
+// tile's requests have one and a half tiles until that barrier - three buffers each of K and V, LDS objects of their own, so
+// that reads of one do not wait for the requests to another.  Products, their order and the sums of a row are
+// those of the 256-row tiles, bit for bit.  16 heads of 24576 rows x 28700 keys: 1.855 GHz with the matrix cores busy 75 % of
+// the cycles in 256-row tiles; with bursts of reads 2.07 GHz and 69 % here.  us, 256-row tiles / two buffers and the reads in
+// bursts at the ends of a step's halves / two buffers / three: 16 x 16384 x 16384 780 / 775 / 754 / 749, 24576 x 28700 2040 / 2020 /
+// 1965 / 1950, 24 x 37477 x 9201 1517 / - / 1515 / 1473 (later rounds are not in step any more: K and V come from further away).
+// A tile with a row out of the range of its weights is taken again as two 256-row tiles with shifts, one after the other
+// (16 x 28700 x 12001, every tile 1258 / 1427: a lone workgroup); with half of the keys masked 958 / 946.
+
+// True if a row has left the range of its weights; then nothing is stored.
+__device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile& k1, KvTile& k2, KvTile& v0, KvTile& v1, KvTile& v2, u32x4* s_rows, int& s_again, int& s_low,
+                                          const int h, const int q0, const bool dev_tile, const int64_t q_base_dev, const int mq_dev,
+                                          const SplitSegment seg) {
+  constexpr int NQ = 8, NT = 256;
+  const bool piece = seg.slot >= 0;
+  const int64_t q_base = dev_tile ? q_base_dev : a.q_off[h];
+  int64_t k_base = a.k_off[h];
+  const int Mq = dev_tile ? mq_dev : a.q_rows[h];
+  int Mk = (int)(a.k_off[h + 1] - k_base);
+  if (piece) {
+    k_base += (int64_t)seg.t0 * kKvTile;
+    Mk = (seg.t1 * kKvTile < Mk ? seg.t1 * kKvTile : Mk) - seg.t0 * kKvTile;
+  }
+  const bf16_t* __restrict__ q_rows = dev_tile ? a.q2 : a.q;
+  u32x4* __restrict__ o_rows = (u32x4*)(dev_tile ? a.o2 : a.o);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));      // (as in attention_tile())
+  const int lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wq0 = q0 + wave * 16 * NQ;
+  const bool active = __builtin_amdgcn_readfirstlane((int)(wq0 < Mq)) != 0;
+  WaveState<NQ> w;
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+    int row = wq0 + qt * 16 + l16;
+    row = row < Mq ? row : Mq - 1;
+    const bf16_t* p = q_rows + (q_base + row) * kDHead + grp * 8;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) w.qf[qt][ks] = *(const bf16x8*)(p + ks * 32);
+    w.nm[qt] = 0.f;
+    w.l_acc[qt >> 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) w.o_acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  w.c = 1.f;
+  w.ones_a = row_sum_operand(lane);
+  w.ones_idx = row_sum_index(lane);
+  const char* kg = (const char*)(a.k + k_base * kDHead);
+  const char* vg = (const char*)(a.v + k_base * kDHead);
+  // (clamped without a branch: a loop of one block)
+  auto load = [&](const char* rows, int kv0, KvTile& buf, auto is_v) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int blk = wave * 2 + i, r = blk * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ (decltype(is_v)::value ? v_swizzle(r) : k_swizzle(r));
+      const int row = kv0 + r < Mk ? kv0 + r : Mk - 1;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rows + (uint32_t)(row * kRowBytes + c * 16)),
+                                       (__attribute__((address_space(3))) void*)(&buf[blk * 512]), 16, 0, 0);
+    }
+  };
+  auto load_k = [&](int tile, KvTile& buf) { load(kg, tile * kKvTile, buf, std::false_type{}); };
+  auto load_v = [&](int tile, KvTile& buf) { load(vg, tile * kKvTile, buf, std::true_type{}); };
+  auto landed = [] {
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    __syncthreads();
+  };
+  const int n_tiles = (Mk + kKvTile - 1) / kKvTile;
+  load_k(0, k0);
+  load_v(0, v0);
+  if (n_tiles > 1) load_k(1, k1);
+  if (tid == 0) s_again = s_low = 0;
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) asm volatile("" : "+a"(w.qf[qt][0]), "+a"(w.qf[qt][1]));
+  accumulators_settled(w);
+  landed();
+  // the steps, 0 .. 2 * n_tiles - 1, as in attention_tile()
+  if (active) {
+    pipeline_step<NQ, false, true, false, false, false, false>(w, k0, nullptr, kg, 0, Mk, lane);
+    if (n_tiles > 1)
+      pipeline_step<NQ, false, true, false, true, false, true>(w, k0 + kStep * kDHead, nullptr, kg, 0, Mk, lane);
+    else
+      pipeline_step<NQ, false, true, false, true, true, true>(w, k0 + kStep * kDHead, nullptr, kg, 0, Mk, lane);
+  }
+  __syncthreads();
+  int j = 1;
+  if (n_tiles > 1) {
+    // Tile jt asks for K tile jt + 2 and V tile jt + 1 (past the end: the last rows again, so that it is always four requests),
+    // and waits for those of the tile before.
+    auto arrived = [] {
+      __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4) lgkmcnt(0)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    load_k(2, k2);
+    load_v(1, v1);
+    if (!active) {
+      // a wave of a partial tile without valid rows: it only stages its share of K / V
+      for (; j < n_tiles - 1; ++j) {
+        const int m = j % 3;
+        load_k(j + 2, m == 0 ? k2 : m == 1 ? k0 : k1);
+        load_v(j + 1, m == 0 ? v1 : m == 1 ? v2 : v0);
+        arrived();
+      }
+    } else {
+      StepOperands op;
+      load_v_operands(op, v0, l16, grp);
+      __builtin_amdgcn_sched_barrier(0);
+      // K tile jt (kc, the next one kn) against V tile jt - 1 (vc, the next one vn), whose first operands are there; kr, vr:
+      // what everybody has read, K tile jt - 1 and V tile jt - 2, before the barrier of tile jt - 1.  (Behind a request the compiler
+      // waits for all LDS reads, the youngest as well: the requests lie where the next wait is for all that there are.)
+      auto tile = [&](int jt, KvTile& kc, KvTile& kn, KvTile& kr, KvTile& vc, KvTile& vn, KvTile& vr) {
+        wide_step(w, op, kc, vc + kStep * kDHead, lane, [] {}, [&](int g) {
+          if (g == 17) load_k(jt + 2, kr);
+          if (g == 21) load_v(jt + 1, vr);
+        });
+        wide_step(w, op, kc + kStep * kDHead, vn, lane, arrived, [](int) {});
+      };
+      for (; j + 2 < n_tiles - 1; j += 3) {
+        tile(j, k1, k2, k0, v0, v1, v2);
+        tile(j + 1, k2, k0, k1, v1, v2, v0);
+        tile(j + 2, k0, k1, k2, v2, v0, v1);
+      }
+      if (j < n_tiles - 1) {
+        tile(j, k1, k2, k0, v0, v1, v2);
+        ++j;
+        if (j < n_tiles - 1) {
+          tile(j, k2, k0, k1, v1, v2, v0);
+          ++j;
+        }
+      }
+    }
+    // the last K tile, its second step may be ragged
+    const int m = j % 3;
+    const bf16_t *kb = m == 0 ? k0 : m == 1 ? k1 : k2, *vb = m == 0 ? v2 : m == 1 ? v0 : v1;
+    if (active) {
+      pipeline_step<NQ, false, true, true, true, false, false>(w, kb, vb, kg, (2 * j - 1) * kStep, Mk, lane);
+      pipeline_step<NQ, false, true, true, true, true, false>(w, kb + kStep * kDHead, vb + kStep * kDHead, kg, 2 * j * kStep, Mk, lane);
+    }
+    landed();
+  }
+  if (active) {
+    const int m = n_tiles % 3;
+    const bf16_t* vb = m == 0 ? v2 : m == 1 ? v0 : v1;
+    pipeline_step<NQ, false, false, true, true, true, false>(w, nullptr, vb, kg, (2 * n_tiles - 1) * kStep, Mk, lane);
+    pipeline_step<NQ, false, false, true, false, false, false>(w, nullptr, vb + kStep * kDHead, kg, 0, Mk, lane);
+  }
+  accumulators_settled(w);
+  float l_tot[NQ];
+  bool high = false, low = false;
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+    const LanePair sums = row_sums(w.l_acc[qt >> 1][0]);
+    l_tot[qt] = qt & 1 ? sums.b : sums.a;
+    high = high || !(l_tot[qt] <= kFastSumMax);
+    low = low || l_tot[qt] < kFastSumMin;
+  }
+  if (active && high) s_again = 1;
+  if (active && low) s_low = 1;
+  if (piece) {
+    __syncthreads();
+    if (s_again) return true;
+    if (s_low) {
+      // its own sums may be small if those of the head's first, middle and last key tile alone are not (attention_tile())
+      const int64_t head0 = a.k_off[h];
+      const int keys = (int)(a.k_off[h + 1] - head0), last = (keys - 1) / kKvTile;
+      kg = (const char*)(a.k + head0 * kDHead);
+      Mk = keys;
+      float rest[NQ];
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) rest[qt] = 0.f;
+#pragma unroll 1
+      for (int i = 0; i < 3; ++i) {
+        load_k(i * last / 2, k0);
+        landed();
+        if (active) {
+#pragma unroll 1
+          for (int st = 0; st < kKvTile; st += kStep) {
+            StepOperands op;
+            load_k_operands(op, k0 + st * kDHead, l16, grp);
+#pragma unroll
+            for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+              for (int kt = 0; kt < 2; ++kt) {
+                const f32x4 sc = mfma16(op.ak[kt * 2 + 1], w.qf[qt][1], mfma16(op.ak[kt * 2], w.qf[qt][0], f32x4{0.f, 0.f, 0.f, 0.f}));
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                  rest[qt] += i * last / 2 * kKvTile + st + 16 * kt + 4 * grp + r < keys ? __builtin_amdgcn_exp2f(sc[r]) : 0.f;
+              }
+          }
+        }
+        __syncthreads();
+      }
+      low = false;
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) {
+        const LanePair r1 = swap16(rest[qt]), r2 = swap32(r1.a + r1.b);
+        low = low || !(r2.a + r2.b >= kFastSumMin);
+      }
+      if (active && low) s_again = 1;
+      __syncthreads();
+      if (s_again) return true;
+    }
+    if (active) {
+      // (slots as attention_tile() leaves them, two for a tile)
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) {
+        const int r = (wave * NQ + qt) * 16 + l16;
+        if (q0 + r >= Mq) continue;
+        const int64_t slot_row0 = (int64_t)(seg.slot + r / kAttnTileRows) * kAttnTileRows, sr = r % kAttnTileRows;
+        float* po = a.split_o + slot_row0 * kDHead + sr * 4;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) *(f32x4*)(po + (4 * ct + grp) * (kAttnTileRows * 4)) = w.o_acc[ct][qt];
+        if (grp == 0) {
+          a.split_l[slot_row0 + sr] = l_tot[qt];
+          a.split_m[slot_row0 + sr] = 0.f;
+        }
+      }
+    }
+    return false;
+  }
+  const UnmergeTarget um = unmerge_target();
+  const int n = Mq - q0 < kWideRows ? Mq - q0 : kWideRows;
+  UnmergeSpan span = {0, 0};
+  UnmergeBatch batch;
+  if (um.out && !dev_tile) {
+    const int row0 = unmerge_row0(um, h, q0);
+    span = unmerge_span(um, row0, n);
+    unmerge_load<NT>(batch, um, h, row0, n, span.first, span.end, tid);
+  }
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+    const float inv = 1.0f / l_tot[qt];
+    const int r = (wave * NQ + qt) * 16 + l16;
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+      *((u32x2*)&s_rows[out_chunk(r, 2 * ct + (grp >> 1))] + (grp & 1)) =
+          u32x2{pack_bf16x2(w.o_acc[ct][qt][0] * inv, w.o_acc[ct][qt][1] * inv),
+                pack_bf16x2(w.o_acc[ct][qt][2] * inv, w.o_acc[ct][qt][3] * inv)};
+  }
+  __syncthreads();
+  if (s_again || s_low) return true;
+  if (um.out) {
+    unmerge_tile<NT, kWideRows>(um, batch, s_rows, o_rows, h, q0, n, q_base, dev_tile, span, tid);
+    return false;
+  }
+#pragma unroll
+  for (int i = 0; i < kWideRows * kRowChunks / NT; ++i) {
+    const int r = (tid >> 3) + i * (NT / 8), c = tid & 7;
+    if (r < n) o_rows[(q_base + q0 + r) * kRowChunks + c] = s_rows[out_chunk(r, c)];
+  }
+  return false;
+}
+
+// Whole tiles as in attention_kernel, then the device-side list's, then the shares.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attention_wide_kernel(const AttnArgs a) {
+  __shared__ __align__(16) KvTile k0, k1, k2, v0, v1, v2;
+  __shared__ __align__(16) bf16_t rows[kWideRows / kKvTile][kKvTile * kDHead];   // the finished rows
+  __shared__ int s_again, s_low;
+  const int block = (int)blockIdx.x, xcd = block & 7, pos = block >> 3;
+  int h = 0, q0 = 0, mq_dev = 0;
+  int64_t q_base_dev = 0;
+  int share = -1, first = 0, count = 1;
+  const bool dev_tile = block >= a.main_blocks && block < a.share_block0;
+  if (dev_tile) {
+    if (!a.dev_tiles) return;
+    const int t = block - a.main_blocks;
+    if (t >= a.dev_tiles[0]) return;
+    h = a.dev_tiles[1 + 2 * t];
+    q0 = a.dev_tiles[2 + 2 * t];
+    q_base_dev = a.dev_q_off[h];
+    mq_dev = a.dev_q_off[h + 1] - a.dev_q_off[h];
+  } else if (block >= a.share_block0) {
+    const int item = (block - a.share_block0) >> 3;
+    share = xcd * a.split_per_xcd + item;
+    if (item >= a.split_per_xcd || share >= a.sp.shares) return;
+    split_share_tiles(a.sp, share, &first, &count);
+  } else if (pos < a.ragged_per_xcd) {
+    const int i = pos * 8 + xcd;
+    if (i >= a.n_ragged) return;
+    h = a.ragged_head[i];
+    q0 = (a.tile_start[h + 1] - a.tile_start[h]) * kWideRows;
+  } else {
+    const int tile = xcd * a.full_per_xcd + (pos - a.ragged_per_xcd);
+    if (tile >= a.n_full) return;
+    while (tile >= a.tile_start[h + 1]) ++h;
+    q0 = (tile - a.tile_start[h]) * kWideRows;
+  }
+#pragma unroll 1
+  for (int i = 0; i < count; ++i) {
+    SplitSegment seg = {0, 0, 0, 0, -1};
+    if (share >= 0) {
+      seg = split_segment<true>(a.sp, share, first + i);
+      h = seg.head;
+      q0 = seg.q0;
+      if (i) __syncthreads();                       // the tile buffers in LDS are free again
+    }
+    const int n = (dev_tile ? mq_dev : a.q_rows[h]) - q0;
+    if (n <= kAttnTileRows) {
+      // a partial tile with few rows: waves of 64 rows, which walk twice as fast
+      attention_tile<4, 4, 1, false>(a, rows, h, q0, dev_tile, q_base_dev, mq_dev, seg);
+      continue;
+    }
+    if (!wide_tile(a, k0, k1, k2, v0, v1, v2, (u32x4*)rows, s_again, s_low, h, q0, dev_tile, q_base_dev, mq_dev, seg)) continue;
+    // Rare: with per-row shifts, in 256-row tiles.
+#pragma unroll 1
+    for (int r = 0; r < n && r < kWideRows; r += kAttnTileRows) {
+      __syncthreads();
+      attention_tile<4, 4, 1, true>(a, rows, h, q0 + r, dev_tile, q_base_dev, mq_dev, seg);
+      if (share >= 0) ++seg.slot;
+    }
+  }
+}
+
 // SHIFT = false: the keys carry the logit scale, weights exp2(s).  SHIFT = true: any keys and scale.
 template <int NQ, int NW, int KS, bool SHIFT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NQ == 2 && KS == 1 ? 3 : 2, NQ == 2 && KS == 1 ? 3 : 2)))
@@ -1208,7 +1614,7 @@ void attention_kernel(const AttnArgs a) {
   for (int i = 0; i < count; ++i) {
     SplitSegment seg = {0, 0, 0, 0, -1};
     if (share >= 0) {
-      seg = split_segment(a.sp, share, first + i);
+      seg = split_segment<false>(a.sp, share, first + i);
       h = seg.head;
       q0 = seg.q0;
       if (i) __syncthreads();                       // the tile buffers in LDS are free again
@@ -1217,7 +1623,7 @@ void attention_kernel(const AttnArgs a) {
   }
 }
 
-// The split tiles after attention_kernel ran them in segments: four workgroups per split tile (64 rows
+// The split tiles after attention_kernel ran them in segments: four (eight) workgroups per split tile (64 rows
 // each) bring its segments to the largest of their shifts of a row (all zero unless a segment had
 // to take shifts or the keys are plain), add them in ascending key order (run-to-run
 // identical) and store the normalised rows.  Bound by the latency of one chain of loads - 16 to 30 MB
@@ -1225,18 +1631,21 @@ void attention_kernel(const AttnArgs a) {
 // values instead of taking them from LDS behind a barrier, kReduceBatch segments at a time.
 constexpr int kReduceRows = 64;
 constexpr int kReduceBatch = 3;
+template <bool WIDE>
 __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnArgs a) {
-  constexpr int BQ = kAttnTileRows;
+  constexpr int BQ = kAttnTileRows;                // rows of a slot
   __shared__ u32x4 s_out[kReduceRows * kRowChunks];   // the normalised bf16 rows, for whole-line stores
-  const int e = blockIdx.x >> 2, part = blockIdx.x & 3, tid = threadIdx.x;
-  const SplitTile t = split_tile(a.sp, e);
+  constexpr int TILE = WIDE ? kWideRows : BQ, PARTS = TILE / kReduceRows;
+  const int e = blockIdx.x / PARTS, part = blockIdx.x % PARTS, tid = threadIdx.x;
+  const SplitTile t = split_tile<WIDE>(a.sp, e);
   const int64_t q_base = a.q_off[t.head];
   const int left = a.q_rows[t.head] - t.q0;
-  const int rows = left < BQ ? left : BQ;
+  const int rows = left < TILE ? left : TILE;
   if (part * kReduceRows >= rows) return;
   const int np = t.last_share - t.first_share + 1;
-  // consecutive shares of one tile have consecutive slots
-  const int64_t row0 = (int64_t)split_slot(t.first_share, e) * BQ;     // segment p: rows from row0 + p * BQ
+  // consecutive shares of one tile have consecutive slots (pairs of slots, the second for the rows from 256 on)
+  const int64_t step = slots_per_segment<WIDE>(a.sp, e) * BQ;
+  const int64_t row0 = (int64_t)(split_slot<WIDE>(a.sp, t.first_share, e) + part * kReduceRows / BQ) * BQ;     // segment p: rows from row0 + p * step
   const int q_part = t.q0 + part * kReduceRows, n_part = rows - part * kReduceRows < kReduceRows ? rows - part * kReduceRows : kReduceRows;
   const int row0_part = row_in_head(q_base, t.head, a.um.M, q_part);
   UnmergeSpan span = {0, 0};
@@ -1247,7 +1656,7 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
   }
   // thread -> row r = tid % 64 of the part and the 16-byte output chunks c0, c0 + 4
   const int r = part * kReduceRows + (tid & 63), c0 = tid >> 6;
-  const int rr = r < rows ? r : rows - 1;          // a row past the end reads a valid row and stores nothing
+  const int rr = (r < rows ? r : rows - 1) % BQ;          // a row past the end reads a valid row and stores nothing
   float acc[2][8];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -1259,7 +1668,7 @@ __global__ __launch_bounds__(256) void attention_split_reduce_kernel(const AttnA
     float m[kReduceBatch], l[kReduceBatch];
 #pragma unroll
     for (int u = 0; u < kReduceBatch; ++u) {
-      const int64_t row = row0 + (int64_t)(p0 + u < np ? p0 + u : np - 1) * BQ + rr;   // past the last one: that one again
+      const int64_t row = row0 + (int64_t)(p0 + u < np ? p0 + u : np - 1) * step + rr;   // past the last one: that one again
       m[u] = a.split_m[row];
       l[u] = a.split_l[row];
       const float* ps = a.split_o + (row - rr) * kDHead + rr * 4;
@@ -1327,10 +1736,9 @@ void launch_kernel(const AttnArgs& a, bool log2_keys, unsigned grid, hipStream_t
     hipLaunchKernelGGL((attention_kernel<NQ, NW, KS, true>), dim3(grid), dim3(64 * NW), 0, stream, a);
 }
 
-// `route`: the split of a launch of 256-row tiles, if it has one; its partial results go to `scratch`.
-template <int NQ, int NW, int KS = 1>
-hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles = 0, const AttnRoute* route = nullptr, float* scratch = nullptr) {
-  constexpr int BQ = 16 * NQ * (NW / KS);
+// The tiles of `tile_rows` rows of a launch, into its arguments; with a split (`route`) those that stay whole, and the
+// segments, whose partial results go to `scratch`.
+void set_tiles(AttnArgs& a, int tile_rows, const HeadRows& rows, const int64_t* k_off_host, int H, const AttnRoute* route, float* scratch) {
   int64_t full = 0;
   int ragged = 0;
   for (int h = 0; h < H; ++h) {
@@ -1339,8 +1747,8 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
     a.q_off[h] = rows.first[h];
     a.q_rows[h] = (int32_t)mq;
     a.k_off[h] = k_off_host[h];
-    full += mq / BQ;
-    if (mq % BQ) a.ragged_head[ragged++] = h;
+    full += mq / tile_rows;
+    if (mq % tile_rows) a.ragged_head[ragged++] = h;
   }
   for (int h = H; h <= kAttnMaxHeads; ++h) {
     a.tile_start[h] = (int32_t)full;
@@ -1353,36 +1761,58 @@ hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const i
   for (int i = ragged; i < kAttnMaxHeads; ++i) a.ragged_head[i] = 0;
   a.n_full = (int32_t)full;
   a.n_ragged = ragged;
-  a.full_per_xcd = (int32_t)((full + 7) / 8);
-  a.ragged_per_xcd = (ragged + 7) / 8;
-  if (full + ragged + extra_tiles == 0) return hipSuccess;
-  a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd);
   a.split_per_xcd = 0;
   a.split_o = nullptr;
   a.split_l = nullptr;
   a.split_m = nullptr;
   a.sp.n_tiles = 0;
   a.sp.slots = 0;
-  if (KS == 1 && BQ == kAttnTileRows && route && route->split.n_tiles > 0) {
+  if (route && route->split.n_tiles > 0) {
     // the first partial tiles (in head order) and the last full tiles run in segments; the others
     // keep their order: partial tiles in front of the full tiles
     a.sp = route->split;
     const int64_t slots = split_slots(a.sp);
     a.n_full = (int32_t)route->kept_full;
-    a.full_per_xcd = (a.n_full + 7) / 8;
     a.n_ragged = ragged - route->split_ragged;
-    a.ragged_per_xcd = (a.n_ragged + 7) / 8;
     for (int i = 0; i < a.n_ragged; ++i) a.ragged_head[i] = a.ragged_head[route->split_ragged + i];
     a.split_per_xcd = (a.sp.shares + 7) / 8;
-    a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd + a.split_per_xcd);
     a.split_o = scratch;
     a.split_l = scratch + slots * kAttnTileRows * kDHead;
     a.split_m = a.split_l + slots * kAttnTileRows;
   }
-  launch_kernel<NQ, NW, KS>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
-  if (a.sp.n_tiles > 0)
-    hipLaunchKernelGGL(attention_split_reduce_kernel, dim3(4u * (unsigned)a.sp.n_tiles), dim3(256), 0, stream, a);
+  a.full_per_xcd = (a.n_full + 7) / 8;
+  a.ragged_per_xcd = (a.n_ragged + 7) / 8;
+}
+
+hipError_t launch_reduce(const AttnArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.sp.tile_rows / kReduceRows * a.sp.n_tiles));
+  if (a.sp.n_tiles > 0 && a.sp.tile_rows == kWideRows)
+    hipLaunchKernelGGL((attention_split_reduce_kernel<true>), grid, dim3(256), 0, stream, a);
+  else if (a.sp.n_tiles > 0)
+    hipLaunchKernelGGL((attention_split_reduce_kernel<false>), grid, dim3(256), 0, stream, a);
   return hipGetLastError();
+}
+
+// `route`: the split of a launch of 256-row tiles, if it has one.
+template <int NQ, int NW, int KS = 1>
+hipError_t launch_cfg(AttnArgs& a, bool log2_keys, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles = 0, const AttnRoute* route = nullptr, float* scratch = nullptr) {
+  set_tiles(a, 16 * NQ * (NW / KS), rows, k_off_host, H, route, scratch);
+  if (a.n_full + a.n_ragged + a.sp.n_tiles + extra_tiles == 0) return hipSuccess;
+  a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd + a.split_per_xcd);
+  launch_kernel<NQ, NW, KS>(a, log2_keys, (unsigned)a.main_blocks + (unsigned)extra_tiles, stream);
+  return launch_reduce(a, stream);
+}
+
+// 512-row tiles (log2 keys).  The shares come behind the device-side list's tiles: they are the shorter ones, and a launch
+// ends the more evenly the shorter its last workgroups are.
+hipError_t launch_wide(AttnArgs& a, const HeadRows& rows, const int64_t* k_off_host, int H, hipStream_t stream, int extra_tiles,
+                       const AttnRoute* route = nullptr, float* scratch = nullptr) {
+  set_tiles(a, kWideRows, rows, k_off_host, H, route, scratch);
+  if (a.n_full + a.n_ragged + a.sp.n_tiles + extra_tiles == 0) return hipSuccess;
+  a.main_blocks = 8 * (a.full_per_xcd + a.ragged_per_xcd);
+  a.share_block0 = a.main_blocks + (extra_tiles + 7) / 8 * 8;
+  hipLaunchKernelGGL(attention_wide_kernel, dim3((unsigned)(a.share_block0 + 8 * a.split_per_xcd)), dim3(256), 0, stream, a);
+  return launch_reduce(a, stream);
 }
 
 // A launch without a split.  `extra_tiles` workgroups are appended for the device-side tile list (a.dev_tiles), if any.
@@ -1395,6 +1825,7 @@ hipError_t launch_tiles(AttnTiles tiles, AttnArgs& a, bool log2_keys, const Head
     case AttnTiles::kGroups128Wide: return launch_cfg<4, 8, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
     case AttnTiles::kGroups256: return launch_cfg<4, 8, 2>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
     case AttnTiles::kTiles128: return launch_cfg<2, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
+    case AttnTiles::kTiles512: return launch_wide(a, rows, k_off_host, H, stream, extra_tiles);
     default: return launch_cfg<4, 4>(a, log2_keys, rows, k_off_host, H, stream, extra_tiles);
   }
 }
@@ -1417,6 +1848,8 @@ hipError_t launch_route(const AttnRoute& route, AttnArgs& a, bool log2_keys, con
                         int64_t cus, hipStream_t stream, void* scratch, int extra_tiles) {
   if (route.tiles == AttnTiles::kTiles256)
     return launch_cfg<4, 4>(a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, extra_tiles, &route, (float*)scratch);
+  if (route.tiles == AttnTiles::kTiles512)
+    return launch_wide(a, all_rows(q_off_host, H), k_off_host, H, stream, extra_tiles, &route, (float*)scratch);
   if (route.tiles != AttnTiles::kRounds)
     return launch_tiles(route.tiles, a, log2_keys, all_rows(q_off_host, H), k_off_host, H, stream, extra_tiles);
   HeadRows whole, rest;
@@ -1434,7 +1867,7 @@ int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_h
   return split_slots(route.split) * kAttnSlotWords * 4;
 }
 
-void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows) {
+void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, bool log2_keys, int32_t* kind, int32_t* tile_rows) {
   // In the merged rows' tiles, behind them in the same launch, if all of them are still one round, and in 256-row tiles of one
   // key group always.  Otherwise in a launch of their own, in the tiles that are quickest: a launch of 256-row tiles of one key
   // group for both would be quicker behind whole rounds (3 to 7 %), but the merged rows' sums would not be those of the
@@ -1449,9 +1882,24 @@ void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* ki
   }
   const int64_t cus = compute_units();
   AttnRoute route;
-  choose_attention_route(q_off, k_off, H, cus, attention_scratch_bytes(H) / 4, &route);
+  choose_attention_route(q_off, k_off, H, cus, attention_scratch_bytes(H) / 4, &route, log2_keys);
   AttnTiles t = last_tiles(route);
-  if (t != AttnTiles::kTiles256) {
+  if (t == AttnTiles::kTiles512) {
+    // Small tiles, which share the keys, if all of them are one round.  Else behind the merged rows in the same launch or in
+    // 256-row tiles of their own, by the time in rounds of 512-row tiles (thousandths): whole rounds, what is left over next to the
+    // merged rows' segments, and half a round of 256-row tiles takes 0.6 of one.  us a layer of 16 heads, all in 256-row tiles /
+    // together / two launches: 28650 x 28650 and 65952 others 3369 / 3310 / -, 28700 x 28700 and 439680 5481 / 5362 / -, 25980 x 25980 and
+    // 39571 2572 / 2565 / -, 2634 / - / 2543, and 131904 3145 / 3233 / -, 3108 / - / 3107, 17760 x 17760 and 42209 1347 / 1365 / -, 1410 / - / 1405;
+    // in small tiles: 28650 x 28650 and 6595 2989 / - / 2832.
+    const AttnTiles small = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile, 0, rows).tiles;
+    const int64_t dev = 1000 * (rows / kWideRows + H / 2) / cus, left = dev % 1000, segments = 1000 * route.split.n_tiles / cus;
+    const int64_t together = left == 0 ? segments : std::max<int64_t>(1000, left + segments);
+    const int64_t apart = segments + (left == 0 ? 0 : left <= 500 ? 600 : 1000);
+    if (attention_tile_rows(small) < kAttnTileRows)
+      t = small;
+    else if (apart < together)
+      t = AttnTiles::kTiles256;
+  } else if (t != AttnTiles::kTiles256) {
     const int64_t extra = rows / attention_tile_rows(t) + (H + 1) / 2;     // (a partial tile per head at most: half of them, say)
     if (count_last_tiles(route, q_off, H, cus) + (extra + 7) / 8 * 8 > (t == AttnTiles::kTiles128 ? kSmallTileRound : cus))
       t = choose_key_groups([&](int n) { return rows / n + H; }, cus, (M_k + kAttnKeyTile - 1) / kAttnKeyTile, 0, rows).tiles;
@@ -1480,7 +1928,7 @@ hipError_t launch_attention_both(const void* q, const void* k, const void* v, vo
   AttnArgs a = attention_args(q, k, v, o, H, scale, log2_keys, unmerge);
   const int64_t cus = compute_units();
   AttnRoute route;
-  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
+  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route, log2_keys);
   const bool together = dev.max_tiles > 0 && dev.kind == (int32_t)last_tiles(route);
   if (together) {
     a.dev_q_off = dev.q_off;
@@ -1500,7 +1948,7 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
   AttnArgs a = attention_args(q, k, v, o, H, scale, log2_keys, unmerge);
   const int64_t cus = compute_units();
   AttnRoute route;
-  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route);
+  choose_attention_route(q_off_host, k_off_host, H, cus, scratch ? scratch_bytes / 4 : 0, &route, log2_keys);
   return launch_route(route, a, log2_keys, q_off_host, k_off_host, H, cus, stream, scratch, 0);
 }
 
@@ -1510,7 +1958,8 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
 // device array of fixed size.  Every GPU the library runs on holds its own copy at its own address
 // until the process ends; the array's name is only a host-side handle, the address comes from
 // hipGetSymbolAddress, once per device, and only that pointer is ever handed to a kernel.
-static __device__ __align__(256) unsigned char g_static_scratch[kAttnStaticScratchBytes];
+// (More of it than kAttnStaticScratchBytes, by which launches are accepted: those of 512-row tiles take larger slots.)
+static __device__ __align__(256) unsigned char g_static_scratch[kAttnScratchBytes];
 
 hipError_t attention_static_scratch(void** ptr) {
   static std::mutex mu;

@@ -28,6 +28,7 @@
 namespace httm {
 
 constexpr int kAttnTileRows = 256;        // query rows of a tile of the kernel instance that splits
+constexpr int kWideRows = 512;            // the same of the kernel with 128 rows a wave
 constexpr int kAttnKeyTile = 64;          // keys per unit
 constexpr int kAttnSplitGroups = 64;      // runs of tiles of one head the excess set may consist of
 constexpr int kAttnMaxShares = 512;
@@ -41,8 +42,8 @@ constexpr int64_t kAttnSlotWords = (int64_t)kAttnTileRows * (64 + 2);   // 64 su
 constexpr int64_t kAttnScratchBytes = (int64_t)(kAttnMaxShares + kAttnMaxExcess) * kAttnSlotWords * 4;
 
 // `count` consecutive tiles of one head in the excess set: tile e of the set (tile0 <= e < tile0 +
-// count) covers the query rows from q0 + (e - tile0) * 256 and the units [cum + (e - tile0) * kt,
-// ... + kt), kt = key tiles of the head.
+// count) covers the query rows from q0 + (e - tile0) * tile_rows and the units [cum + (e - tile0) * kt,
+// ... + kt), kt = key tiles of the head (half of them where a unit is two: see narrow_tiles).
 struct SplitGroup {
   int32_t head, q0, tile0, cum, kt;
 };
@@ -54,7 +55,12 @@ struct SplitPlan {
   int32_t share_units;  // units per share (the last share may be shorter)
   int32_t shares;
   int32_t span;         // most tiles a share touches
-  int32_t slots;        // shares + n_tiles - 1 (a few slots stay unused: a share and a tile that end together)
+  int32_t slots;        // 256-row tiles: shares + n_tiles - 1 (a few slots stay unused: a share and a tile that end together)
+  int32_t tile_rows;    // 256 or 512
+  // 512-row tiles: the first narrow_tiles ones are partial ones of at most 256 rows, whose segments have one slot of scratch
+  // instead of two and whose units are two key tiles, because they walk twice as fast
+  int32_t narrow_tiles;
+  int32_t slot_shift;   // what makes the slots of the other ones follow those
   SplitGroup grp[kAttnSplitGroups];
 };
 
@@ -91,8 +97,14 @@ __host__ __device__ inline int split_tile_of_unit(const SplitPlan& p, int unit) 
 }
 
 // Slot of the partial results of share s in tile e: consecutive segments differ in s, in e or in
-// both, both never decrease, so s + e is unique; the largest is shares + n_tiles - 2.
-__host__ __device__ inline int split_slot(int share, int tile) { return share + tile; }
+// both, both never decrease, so s + e is unique; the largest is shares + n_tiles - 2.  512-row tiles (WIDE) have two slots, the
+// second one for their rows from 256 on, but for the partial tiles that need one only: those come first.
+template <bool WIDE>
+__host__ __device__ inline int slots_per_segment(const SplitPlan& p, int tile) { return WIDE && tile >= p.narrow_tiles ? 2 : 1; }
+template <bool WIDE>
+__host__ __device__ inline int split_slot(const SplitPlan& p, int share, int tile) {
+  return slots_per_segment<WIDE>(p, tile) == 1 ? share + tile : 2 * (share + tile) - p.slot_shift;
+}
 
 // Share s covers the units [s * share_units, (s + 1) * share_units) (the last one up to p.units): the
 // tiles first .. first + count - 1 of the excess set.
@@ -104,6 +116,7 @@ __host__ __device__ inline void split_share_tiles(const SplitPlan& p, int share,
 }
 
 // The part of share s that lies in tile e (one of split_share_tiles).
+template <bool WIDE>
 __host__ __device__ inline SplitSegment split_segment(const SplitPlan& p, int share, int e) {
   const SplitGroup& g = p.grp[split_group_of_tile(p, e)];
   const int tu0 = g.cum + (e - g.tile0) * g.kt;       // first unit of tile e
@@ -111,37 +124,41 @@ __host__ __device__ inline SplitSegment split_segment(const SplitPlan& p, int sh
   const int u1 = u0 + p.share_units < p.units ? u0 + p.share_units : p.units;
   SplitSegment s;
   s.head = g.head;
-  s.q0 = g.q0 + (e - g.tile0) * kAttnTileRows;
-  s.t0 = (u0 > tu0 ? u0 : tu0) - tu0;
-  s.t1 = (u1 < tu0 + g.kt ? u1 : tu0 + g.kt) - tu0;
-  s.slot = split_slot(share, e);
+  s.q0 = g.q0 + (e - g.tile0) * (WIDE ? kWideRows : kAttnTileRows);
+  const int per_unit = slots_per_segment<WIDE>(p, e) == 1 && WIDE ? 2 : 1;       // key tiles
+  s.t0 = per_unit * ((u0 > tu0 ? u0 : tu0) - tu0);
+  s.t1 = per_unit * ((u1 < tu0 + g.kt ? u1 : tu0 + g.kt) - tu0);      // (may be one more than there are)
+  s.slot = split_slot<WIDE>(p, share, e);
   return s;
 }
 
 // Tile e of the excess set for the kernel that adds its segments up: the shares first..last (in key
-// order) each left one segment, in slot split_slot(share, e).
+// order) each left one segment, in slot split_slot(p, share, e).
 struct SplitTile {
   int32_t head, q0, first_share, last_share;
 };
+template <bool WIDE>
 __host__ __device__ inline SplitTile split_tile(const SplitPlan& p, int e) {
   const SplitGroup& g = p.grp[split_group_of_tile(p, e)];
   const int tu0 = g.cum + (e - g.tile0) * g.kt;
-  return {g.head, g.q0 + (e - g.tile0) * kAttnTileRows, tu0 / p.share_units, (tu0 + g.kt - 1) / p.share_units};
+  return {g.head, g.q0 + (e - g.tile0) * (WIDE ? kWideRows : kAttnTileRows), tu0 / p.share_units, (tu0 + g.kt - 1) / p.share_units};
 }
 
-// What the host decides for a launch of 256-row tiles on `cus` compute units.  out->n_tiles == 0: no
+// What the host decides for a launch of 256-row (512-row) tiles on `cus` compute units.  out->n_tiles == 0: no
 // split.  *kept_full receives the number of full tiles that stay whole (the first ones, in head
 // order), *split_ragged the number of partial tiles (in head order, the first ones) that are split.
 // q_off / k_off: H + 1 row offsets each.
-inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, SplitPlan* out,
+inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int tile_rows, SplitPlan* out,
                                  int64_t* kept_full, int* split_ragged) {
   SplitPlan& p = *out;
-  p.n_tiles = p.n_groups = p.units = p.share_units = p.shares = p.span = p.slots = 0;
+  p.n_tiles = p.n_groups = p.units = p.share_units = p.shares = p.span = p.slots = p.slot_shift = 0;
+  p.tile_rows = tile_rows;
+  p.narrow_tiles = 0;
   int64_t full = 0, ragged = 0, min_mk = INT64_MAX;
   for (int h = 0; h < H; ++h) {
     const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h];
-    full += mq / kAttnTileRows;
-    ragged += (mq % kAttnTileRows) != 0;
+    full += mq / tile_rows;
+    ragged += (mq % tile_rows) != 0;
     if (mq > 0 && mk < min_mk) min_mk = mk;
   }
   *kept_full = full;
@@ -154,12 +171,15 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   int64_t left = R;
   int64_t units = 0;
   int n_groups = 0, n_tiles = 0;
+  const bool wide = tile_rows == kWideRows;
+  bool narrow = wide;                                // every partial tile
+  for (int h = 0; h < H; ++h) narrow = narrow && (q_off[h + 1] - q_off[h]) % tile_rows <= kAttnTileRows;
   for (int h = 0; h < H && left > 0; ++h) {
     const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h];
-    if (mq % kAttnTileRows == 0) continue;
+    if (mq % tile_rows == 0) continue;
     if (n_groups == kAttnSplitGroups) return;
-    const int32_t kt = (int32_t)((mk + kAttnKeyTile - 1) / kAttnKeyTile);
-    p.grp[n_groups++] = {h, (int32_t)(mq / kAttnTileRows) * kAttnTileRows, n_tiles, (int32_t)units, kt};
+    const int32_t tile = narrow ? 2 * kAttnKeyTile : kAttnKeyTile, kt = (int32_t)((mk + tile - 1) / tile);
+    p.grp[n_groups++] = {h, (int32_t)(mq / tile_rows) * tile_rows, n_tiles, (int32_t)units, kt};
     n_tiles += 1;
     units += kt;
     --left;
@@ -169,13 +189,13 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   int64_t tile_start = 0;
   for (int h = 0; h < H && left > 0; ++h) {
     const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h];
-    const int64_t nf = mq / kAttnTileRows;
+    const int64_t nf = mq / tile_rows;
     const int64_t lo = first_split_full > tile_start ? first_split_full : tile_start;   // first split tile of this head
     if (lo < tile_start + nf) {
       if (n_groups == kAttnSplitGroups) return;
       const int32_t cnt = (int32_t)(tile_start + nf - lo);
       const int32_t kt = (int32_t)((mk + kAttnKeyTile - 1) / kAttnKeyTile);
-      p.grp[n_groups++] = {h, (int32_t)(lo - tile_start) * kAttnTileRows, n_tiles, (int32_t)units, kt};
+      p.grp[n_groups++] = {h, (int32_t)(lo - tile_start) * tile_rows, n_tiles, (int32_t)units, kt};
       n_tiles += cnt;
       units += (int64_t)cnt * kt;
       left -= cnt;
@@ -188,13 +208,15 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   // (cus - R) * units / R >= 24 * cus.  16 heads, split against whole tiles, by the units saved per CU: 22
   // (7400 rows and keys) 191 : 184 us, 27 (7000) 172 : 172, 33 (6700) 161 : 162, 44 (6376) 146 : 153, 54 (11000)
   // 392 : 406, 78 (10000) 328 : 346.
-  if ((cus - R) * (units / R) < 24 * cus) return;
+  // 512-row tiles save twice as much per unit.
+  if ((cus - R) * (units / R) < (wide ? 12 : 24) * cus) return;
   // One share per CU.  With any other number some CUs get one more than the others, and twice as many
   // (every CU two) double the partial results: 16 heads of 7000 rows and keys in 330 / 512 / 256 shares 210 /
   // 181 / 172 us, of 10000 in 314 / 512 / 256 364 / 344 / 328, of 15000 in 512 / 256 745 / 708.  Only very long
   // shares are halved, which costs 2 % there (27000 rows and keys 2.27 : 2.21 ms): those launches need more than
   // the library's own array holds, and httm_attention_log2_static refuses them, as it always has.
-  int64_t shares = units / kAttnLongShareUnits > cus ? 2 * cus : cus;
+  // A CU holds one 512-row workgroup.
+  int64_t shares = units / kAttnLongShareUnits > cus && !wide ? 2 * cus : cus;
   if (shares > units / kAttnMinShareUnits) shares = units / kAttnMinShareUnits;
   if (shares > kAttnMaxShares) shares = kAttnMaxShares;
   if (shares < 1) return;
@@ -218,6 +240,11 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
   }
   p.span = span;
   p.slots = p.shares + p.n_tiles - 1;
+  if (wide) {
+    p.narrow_tiles = narrow ? n_split_ragged : 0;
+    if (p.narrow_tiles > 0 && p.narrow_tiles < n_tiles) p.slot_shift = split_tile<true>(p, p.narrow_tiles).first_share + p.narrow_tiles;
+    p.slots = split_slot<true>(p, p.shares - 1, n_tiles - 1) + slots_per_segment<true>(p, n_tiles - 1);
+  }
   *kept_full = first_split_full;
   *split_ragged = n_split_ragged;
 }
@@ -235,11 +262,12 @@ enum class AttnTiles {
   kGroups128Wide,
   kGroups256,
   kRounds,      // whole rounds of 256-row tiles, then the rest in key groups: two launches
+  kTiles512,    // log2 keys: 512-row tiles; with a split those in excess run in segments
 };
 
 struct AttnRoute {
   AttnTiles tiles;
-  SplitPlan split;          // kTiles256 only; n_tiles == 0: every tile runs whole
+  SplitPlan split;          // kTiles256 and kTiles512 only; n_tiles == 0: every tile runs whole
   int64_t kept_full;        // full tiles that stay whole, and partial tiles that run in segments
   int32_t split_ragged;
   AttnTiles rest;           // kRounds: what the rest runs in
@@ -250,6 +278,7 @@ inline int attention_tile_rows(AttnTiles t) {
     case AttnTiles::kGroups32: return 32;
     case AttnTiles::kGroups64: return 64;
     case AttnTiles::kTiles128: case AttnTiles::kGroups128: case AttnTiles::kGroups128Wide: return 128;
+    case AttnTiles::kTiles512: return kWideRows;
     default: return kAttnTileRows;
   }
 }
@@ -326,6 +355,9 @@ inline AttnGroups choose_key_groups(Count count, int64_t cus, int64_t kt, int H,
   return best;
 }
 
+// Keys of the shortest head from which on a launch may run in 512-row tiles.
+constexpr int64_t kWideKeys = 2048;
+
 // The query rows of a launch: `count` rows of every head from row `first` of the packed tensor.
 struct HeadRows {
   int64_t first[HTTM_MAX_HEADS];
@@ -370,13 +402,56 @@ inline int64_t count_last_tiles(const AttnRoute& r, const int64_t* q_off, int H,
   return count_dealt_tiles(off, H, rows);
 }
 
-// The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).
-inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words,
-                                   AttnRoute* out) {
+// Log2 keys: whether a launch runs in 512-row tiles, and how it is split.  Both sides' times in ns, fitted to launches of 16
+// heads: a pair of 256-row tiles takes 1517 a key tile and a 512-row tile 1462, with 5 and 7.5 us for their ends; segments
+// and their sum, which are twice as large, take 12 and 20 us.  A head's last tile of at most 256 rows is half a tile.  A
+// split launch has to gain 1.5 % by this, another one 0.5 %.  Every tile of a round has to be as long as the others: one workgroup
+// on a CU leaves it idle behind a short one (12 heads of 36 000 rows against 7000 to 17 000 keys 1126 us in 256-row tiles, 1237 in
+// these).  us, 256-row tiles / these: 16 heads of 16384 x 4096 206 / 203, 16384 x 16384 780 / 749, 17600 x 17600 900 / 888,
+// 28700 x 9000 767 / 758, 28650 x 28650 2362 / 2294, 28700 x 83140 6870 / 6693, 8112 x 21619 521 / 500, 24 of 61587 x 6566 1778 /
+// 1761; 57 random launches of 8 to 24 heads 0.975 of the time in the median, 1.007 at most.
+inline bool choose_wide_tiles(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words, AttnRoute* out) {
   AttnRoute& r = *out;
+  int64_t min_keys = INT64_MAX, max_keys = 0, halves = 0, halves256 = 0, work = 0, work256 = 0;    // half tiles, and times their key tiles
+  for (int h = 0; h < H; ++h) {
+    const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h], kt = (mk + kAttnKeyTile - 1) / kAttnKeyTile;
+    if (mq == 0) continue;
+    min_keys = std::min(min_keys, mk);
+    max_keys = std::max(max_keys, mk);
+    const int64_t n256 = (mq + kAttnTileRows - 1) / kAttnTileRows;
+    const int64_t n = mq / kWideRows * 2 + (mq % kWideRows == 0 ? 0 : mq % kWideRows <= kAttnTileRows ? 1 : 2);
+    halves += n;
+    halves256 += n256;
+    work += n * kt;
+    work256 += n256 * kt;
+  }
+  const int64_t tiles = count_tiles(q_off, H, kWideRows);
+  // (rounds of tiles, one a CU: all have to be of one length)
+  if (tiles < cus || min_keys < kWideKeys || max_keys - min_keys > min_keys / 32) return false;
+  r.tiles = AttnTiles::kTiles512;
+  r.split.n_tiles = 0;
+  if (scratch_words > 0) {
+    plan_attention_split(q_off, k_off, H, cus, kWideRows, &r.split, &r.kept_full, &r.split_ragged);
+    if (split_slots(r.split) * kAttnSlotWords > scratch_words) r.split.n_tiles = 0;
+    // (less than an eighth of a round in segments: many short pieces of a tile, 12 heads of 22575 x 22575 and 31752 outliers, 28
+    // tiles, 1582 : 1617)
+    if (r.split.n_tiles > 0 && r.split.n_tiles * 8 < cus) return false;
+  }
+  const int64_t rounds = (tiles + cus - 1) / cus * cus;
+  const int64_t time = r.split.n_tiles > 0 ? (work * 1462 + halves * 7500) / 2 / cus + 20000 : (work / halves * 1462 + 7500) * rounds / cus;
+  const int64_t time256 = (work256 * 1517 + halves256 * 5000) / 2 / cus + (halves256 % cus ? 12000 : 0);
+  return time * (r.split.n_tiles > 0 ? 203 : 201) <= time256 * 200;
+}
+
+// The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).  `log2_keys`: one
+// whose keys carry the logit scale, which may run in 512-row tiles.
+inline void choose_attention_route(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words,
+                                   AttnRoute* out, bool log2_keys = false) {
+  AttnRoute& r = *out;
+  if (log2_keys && choose_wide_tiles(q_off, k_off, H, cus, scratch_words, out)) return;
   r.tiles = AttnTiles::kTiles256;
   r.split.n_tiles = 0;
-  if (scratch_words > 0) plan_attention_split(q_off, k_off, H, cus, &r.split, &r.kept_full, &r.split_ragged);
+  if (scratch_words > 0) plan_attention_split(q_off, k_off, H, cus, kAttnTileRows, &r.split, &r.kept_full, &r.split_ragged);
   int64_t full = 0, keys = 0, longest = 0;
   for (int h = 0; h < H; ++h) {
     longest = std::max(longest, q_off[h + 1] - q_off[h]);

@@ -159,8 +159,9 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, void* o
                             float scale, bool log2_keys, hipStream_t stream, void* scratch = nullptr,
                             int64_t scratch_bytes = 0, const UnmergeTarget* unmerge = nullptr);
 // Bytes of scratch launch_attention would use for these head lengths if it had them (0: every tile
-// runs whole), and the library's own scratch for callers that cannot allocate: a static device
-// array of kAttnStaticScratchBytes, whose address on the current device *ptr receives.
+// runs whole) in 256-row tiles, and the library's own scratch for callers that cannot allocate: a static device
+// array, whose address on the current device *ptr receives.  It has kAttnScratchBytes; by kAttnStaticScratchBytes launches are
+// accepted.
 constexpr int64_t kAttnStaticScratchBytes = 32ll << 20;
 int64_t attention_scratch_need(const int64_t* q_off_host, const int64_t* k_off_host, int H);
 hipError_t attention_static_scratch(void** ptr);
@@ -175,7 +176,7 @@ struct DevTiles {
 };
 // The tiles of at most `rows` such queries behind H heads of M_q merged rows and M_k keys in a layer: which kernel
 // takes them and how many rows a tile has.
-void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, int32_t* kind, int32_t* tile_rows);
+void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, bool log2_keys, int32_t* kind, int32_t* tile_rows);
 // Both: the host-described sequences (q, o) and the device-described query rows (q2, o2) against the same keys / values.
 hipError_t launch_attention_both(const void* q, const void* k, const void* v, void* o,
                                  const int64_t* q_off_host, const int64_t* k_off_host, int H, float scale,

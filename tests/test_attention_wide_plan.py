@@ -1,0 +1,74 @@
+"""Host-side check of stage 3's (Eq. 3-4) launches in 512-row tiles: which launches with log2 keys run in them, and that the
+segments of the tiles in excess cover every (query row, key tile) pair once, in slots nobody else writes, inside the
+scratch the library asks for.  No GPU needed."""
+import numpy as np
+import pytest
+
+import paper_2511_21317_amd as httm
+
+ROWS, SLOT_ROWS = 512, 256
+
+
+def _offsets(n):
+    return [int(x) for x in np.concatenate([[0], np.cumsum(n)])]
+
+
+def check_wide_plan(mq, mk, scratch_bytes=None):
+    H = len(mq)
+    p = httm.attention_wide_plan(_offsets(mq), _offsets(mk), 256, scratch_bytes)
+    if p is None:
+        return None
+    full, ragged = [m // ROWS for m in mq], [h for h in range(H) if mq[h] % ROWS]
+    T = sum(full) + len(ragged)
+    assert T >= 256
+    if p["n_tiles"] == 0:
+        return p
+    assert p["n_tiles"] == T % 256 and p["slots"] * SLOT_ROWS * 66 * 4 <= httm.attention_scratch_bytes(H)
+    flat = [(h, t * ROWS) for h in range(H) for t in range(full[h])]
+    tiles = [(h, full[h] * ROWS) for h in ragged[:p["split_ragged"]]] + flat[p["kept_full"]:]
+    assert len(tiles) == p["n_tiles"]
+    seen, owner, shares = {t: 0 for t in tiles}, {}, set()
+    for share, h, q0, t0, t1, slot in p["segments"].tolist():
+        kt, rows = -(-mk[h] // 64), min(ROWS, mq[h] - q0)
+        assert t0 == seen[(h, q0)] and t0 < t1 <= kt + 1 and (t1 <= kt or rows <= SLOT_ROWS)     # in key order, without a gap
+        seen[(h, q0)] = min(t1, kt)
+        shares.add(share)
+        for s in range(slot, slot + -(-rows // SLOT_ROWS)):
+            assert s not in owner and s < p["slots"]
+            owner[s] = share
+    assert all(seen[(h, q0)] == -(-mk[h] // 64) for h, q0 in tiles)
+    assert shares == set(range(p["shares"])) and p["shares"] <= 256
+    return p
+
+
+@pytest.mark.parametrize("H,mq,mk,n_tiles", [
+    (16, 28650, 28650, 128), (16, 28700, 28700, 144), (16, 28700, 83140, 144), (16, 43968, 17600, 96), (16, 16384, 4096, 0),
+    (16, 16384, 2000, None), (16, 5516, 5516, None), (16, 10992, 10992, None), (16, 9000, 9000, None), (16, 28700, 2048, None)])
+def test_which_launches_run_in_512_row_tiles(H, mq, mk, n_tiles):
+    p = check_wide_plan([mq] * H, [mk] * H)
+    assert (p["n_tiles"] if p else None) == n_tiles
+
+
+def test_heads_of_different_key_lengths_do_not():
+    assert check_wide_plan([28700] * 16, [28700] * 15 + [30000]) is None
+    assert check_wide_plan([28700] * 15 + [0], [28700] * 15 + [512]) is not None      # (a head without rows has no say)
+
+
+def test_without_scratch_only_whole_rounds():
+    assert check_wide_plan([28700] * 16, [28700] * 16, 0) is None
+    assert check_wide_plan([16384] * 16, [16384] * 16, 0)["n_tiles"] == 0
+
+
+@pytest.mark.parametrize("seed", range(150))
+def test_random_launches_are_covered_exactly_once(seed):
+    rng = np.random.default_rng(51200 + seed)
+    H = int(rng.integers(1, 24))
+    if seed % 3 == 0:      # equal heads
+        mq, mk = [int(rng.integers(9000, 60000))] * H, [int(rng.integers(2048, 60000))] * H
+    elif seed % 3 == 1:    # ragged heads, some without rows
+        mq = [int(x) for x in rng.integers(0, 70000, H)]
+        mk = [30000 + int(x) for x in rng.integers(0, 900, H)]
+    else:                  # every head's last tile has at most 256 rows
+        mq = [int(ROWS * rng.integers(10, 120) + rng.integers(1, 257)) for _ in range(H)]
+        mk = [12000 + int(x) for x in rng.integers(0, 300, H)]
+    check_wide_plan(mq, mk)
