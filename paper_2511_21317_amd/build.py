@@ -2,9 +2,13 @@
 gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
+import glob
 import os
 import shutil
 import subprocess
+import tempfile
+
+from .isa_check import hazards
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -36,16 +40,31 @@ def _compile(sources, target, verbose, extra_flags):
     for s in sources:
         srcs += ["-x", "hip", os.path.join(CSRC, s)]
     tmp = target + ".tmp"
-    cmd = [hipcc_path(), *HIPCC_FLAGS, *extra_flags, *srcs, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+    with tempfile.TemporaryDirectory() as steps:          # the compiler's intermediate files, the assembly among them
+        cmd = [hipcc_path(), *HIPCC_FLAGS, *extra_flags, "-save-temps=cwd", *srcs, "-o", tmp]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, cwd=steps, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout)
+        _check_products(glob.glob(os.path.join(glob.escape(steps), "*gfx950*.s")))
     if verbose:
         noise = "is not a recognized feature for this target"
         print("\n".join(l for l in res.stdout.splitlines() if noise not in l), flush=True)
     os.replace(tmp, target)
+
+
+def _check_products(assembly_files):
+    """The products that attention.hip writes out (mfma_o()) are right only as far from other instructions as the compiler
+    happens to put them: a build in which they are not is refused."""
+    for path in assembly_files:
+        with open(path) as f:
+            asm = f.read()
+        count, found = hazards(asm)
+        if found:
+            raise RuntimeError(f"{os.path.basename(path)}: written-out products without their wait states:\n" + "\n".join(found[:20]))
+        if count == 0 and os.path.basename(path).startswith("attention-"):
+            raise RuntimeError(f"{os.path.basename(path)}: no written-out products found, so none were checked")
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:

@@ -295,9 +295,12 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 
 // Waves of 128 rows (NQ = 8) hold their accumulators in accumulation registers.  The compiler decides between the two
 // register files once for all products of a kernel, and the scores are read by vector instructions, so these products are
-// written out.  It does not know how long their results take: nothing else touches the accumulators between
-// accumulators_settled() before the first and after the last one (a product that adds to the register of an earlier one
-// needs no wait; the wave's loop has neither spills nor copies of them, in which that would not hold).
+// written out.  The compiler keeps no wait states around an asm statement: two between a vector instruction that writes an
+// operand and the product, and what the product takes before its result is touched.  accumulators_settled() in front of the
+// first product and behind the last one holds the latter where the accumulators are set and read; inside the loop only
+// products touch them (one that adds to the register of an earlier one needs no wait), and the operands are written long
+// before, by LDS reads, which are waited for, and by the step before.  That it came out so, without spills and copies in
+// between, is checked in the assembly by every build, which fails otherwise (isa_check.py).
 template <int NQ>
 __device__ __forceinline__ void mfma_o(f32x4& o, const bf16x8& a, const bf16x8& b) {
   if constexpr (NQ == 8)
