@@ -1262,11 +1262,15 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 // the cycles in 256-row tiles; with bursts of reads 2.07 GHz and 69 % here.  us, 256-row tiles / two buffers and the reads in
 // bursts at the ends of a step's halves / two buffers / three: 16 x 16384 x 16384 780 / 775 / 754 / 749, 24576 x 28700 2040 / 2020 /
 // 1965 / 1950, 24 x 37477 x 9201 1517 / - / 1515 / 1473 (later rounds are not in step any more: K and V come from further away).
-// A tile with a row out of the range of its weights is taken again as two 256-row tiles with shifts, one after the other
-// (16 x 28700 x 12001, every tile 1258 / 1427: a lone workgroup); with half of the keys masked 958 / 946.
+// A half with a row out of the range of its weights is taken again as a 256-row tile with shifts: a workgroup alone on its CU,
+// 0.6 of the time of a pair of them.  us, launches of 256-row tiles / every tile with such a row taken again whole / this,
+// 16 x 28700 x 12001: one row in the first tile of each head 1121 / 1213 / 1116, one row in 4096 1436 / 1759 / 1373, one in 512 1965 /
+// 2345 / 1686, all rows 2202 / 2342 / 2335, all scores low 2019 / 2244 / 2228, half of the keys masked 964 / 960 / 950; 16 x 16384 x 9000, one
+// row a head 537 / 690 / 556, all rows 951 / 1011 / 1005.
 
-// True if a row has left the range of its weights; then nothing is stored.
-__device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile& k1, KvTile& k2, KvTile& v0, KvTile& v1, KvTile& v2, u32x4* s_rows, int& s_again, int& s_low,
+// The halves of the tile (bit 0: rows 0 .. 255, bit 1: the others) with a row that has left the range of its weights; nothing is
+// stored of these.
+__device__ __forceinline__ int wide_tile(const AttnArgs& a, KvTile& k0, KvTile& k1, KvTile& k2, KvTile& v0, KvTile& v1, KvTile& v2, u32x4* s_rows, int (&s_again)[2], int (&s_low)[2],
                                           const int h, const int q0, const bool dev_tile, const int64_t q_base_dev, const int mq_dev,
                                           const SplitSegment seg) {
   constexpr int NQ = 8, NT = 256;
@@ -1285,7 +1289,7 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
   asm volatile("" : "+v"(tid));      // (as in attention_tile())
   const int lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wq0 = q0 + wave * 16 * NQ;
+  const int wq0 = q0 + wave * 16 * NQ, wave_half = wave >> 1;
   const bool active = __builtin_amdgcn_readfirstlane((int)(wq0 < Mq)) != 0;
   WaveState<NQ> w;
 #pragma unroll
@@ -1326,7 +1330,7 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
   load_k(0, k0);
   load_v(0, v0);
   if (n_tiles > 1) load_k(1, k1);
-  if (tid == 0) s_again = s_low = 0;
+  if (tid < 2) s_again[tid] = s_low[tid] = 0;
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) asm volatile("" : "+a"(w.qf[qt][0]), "+a"(w.qf[qt][1]));
   accumulators_settled(w);
@@ -1413,12 +1417,11 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
     high = high || !(l_tot[qt] <= kFastSumMax);
     low = low || l_tot[qt] < kFastSumMin;
   }
-  if (active && high) s_again = 1;
-  if (active && low) s_low = 1;
+  if (active && high) s_again[wave_half] = 1;
+  if (active && low) s_low[wave_half] = 1;
+  __syncthreads();
   if (piece) {
-    __syncthreads();
-    if (s_again) return true;
-    if (s_low) {
+    if (s_low[0] | s_low[1]) {
       // its own sums may be small if those of the head's first, middle and last key tile alone are not (attention_tile())
       const int64_t head0 = a.k_off[h];
       const int keys = (int)(a.k_off[h + 1] - head0), last = (keys - 1) / kKvTile;
@@ -1455,11 +1458,11 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
         const LanePair r1 = swap16(rest[qt]), r2 = swap32(r1.a + r1.b);
         low = low || !(r2.a + r2.b >= kFastSumMin);
       }
-      if (active && low) s_again = 1;
+      if (active && low) s_again[wave_half] = 1;
       __syncthreads();
-      if (s_again) return true;
     }
-    if (active) {
+    const int bad = __builtin_amdgcn_readfirstlane(s_again[0] | 2 * s_again[1]);
+    if (active && !(bad >> wave_half & 1)) {
       // (slots as attention_tile() leaves them, two for a tile)
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) {
@@ -1475,14 +1478,18 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
         }
       }
     }
-    return false;
+    return bad;
   }
+  const int bad = __builtin_amdgcn_readfirstlane((s_again[0] | s_low[0]) | 2 * (s_again[1] | s_low[1]));
+  if (bad == 3) return bad;
   const UnmergeTarget um = unmerge_target();
-  const int n = Mq - q0 < kWideRows ? Mq - q0 : kWideRows;
+  // the rows that are stored
+  const int n_tile = Mq - q0 < kWideRows ? Mq - q0 : kWideRows;
+  const int first = bad == 1 ? kAttnTileRows : 0, n = (bad == 2 ? kAttnTileRows : n_tile) - first;
   UnmergeSpan span = {0, 0};
   UnmergeBatch batch;
   if (um.out && !dev_tile) {
-    const int row0 = unmerge_row0(um, h, q0);
+    const int row0 = unmerge_row0(um, h, q0 + first);
     span = unmerge_span(um, row0, n);
     unmerge_load<NT>(batch, um, h, row0, n, span.first, span.end, tid);
   }
@@ -1497,24 +1504,24 @@ __device__ __forceinline__ bool wide_tile(const AttnArgs& a, KvTile& k0, KvTile&
                 pack_bf16x2(w.o_acc[ct][qt][2] * inv, w.o_acc[ct][qt][3] * inv)};
   }
   __syncthreads();
-  if (s_again || s_low) return true;
+  const u32x4* rows = s_rows + first * kRowChunks;
   if (um.out) {
-    unmerge_tile<NT, kWideRows>(um, batch, s_rows, o_rows, h, q0, n, q_base, dev_tile, span, tid);
-    return false;
+    unmerge_tile<NT, kWideRows>(um, batch, rows, o_rows, h, q0 + first, n, q_base, dev_tile, span, tid);
+    return bad;
   }
 #pragma unroll
   for (int i = 0; i < kWideRows * kRowChunks / NT; ++i) {
     const int r = (tid >> 3) + i * (NT / 8), c = tid & 7;
-    if (r < n) o_rows[(q_base + q0 + r) * kRowChunks + c] = s_rows[out_chunk(r, c)];
+    if (r < n) o_rows[(q_base + q0 + first + r) * kRowChunks + c] = rows[out_chunk(r, c)];
   }
-  return false;
+  return bad;
 }
 
 // Whole tiles as in attention_kernel, then the device-side list's, then the shares.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attention_wide_kernel(const AttnArgs a) {
   __shared__ __align__(16) KvTile k0, k1, k2, v0, v1, v2;
   __shared__ __align__(16) bf16_t rows[kWideRows / kKvTile][kKvTile * kDHead];   // the finished rows
-  __shared__ int s_again, s_low;
+  __shared__ int s_again[2], s_low[2];
   const int block = (int)blockIdx.x, xcd = block & 7, pos = block >> 3;
   int h = 0, q0 = 0, mq_dev = 0;
   int64_t q_base_dev = 0;
@@ -1559,13 +1566,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       attention_tile<4, 4, 1, false>(a, rows, h, q0, dev_tile, q_base_dev, mq_dev, seg);
       continue;
     }
-    if (!wide_tile(a, k0, k1, k2, v0, v1, v2, (u32x4*)rows, s_again, s_low, h, q0, dev_tile, q_base_dev, mq_dev, seg)) continue;
+    const int bad = wide_tile(a, k0, k1, k2, v0, v1, v2, (u32x4*)rows, s_again, s_low, h, q0, dev_tile, q_base_dev, mq_dev, seg);
     // Rare: with per-row shifts, in 256-row tiles.
 #pragma unroll 1
-    for (int r = 0; r < n && r < kWideRows; r += kAttnTileRows) {
+    for (int half = 0; bad >> half != 0; ++half) {
+      if (!(bad >> half & 1)) continue;
+      SplitSegment part = seg;
+      if (share >= 0) part.slot += half;
       __syncthreads();
-      attention_tile<4, 4, 1, true>(a, rows, h, q0 + r, dev_tile, q_base_dev, mq_dev, seg);
-      if (share >= 0) ++seg.slot;
+      attention_tile<4, 4, 1, true>(a, rows, h, q0 + half * kAttnTileRows, dev_tile, q_base_dev, mq_dev, part);
     }
   }
 }

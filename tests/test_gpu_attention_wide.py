@@ -91,6 +91,39 @@ def test_rows_out_of_the_unshifted_range():
     _check_rows(q, k2, v, qo, ko, out, [0, 3, 5, 7, 9, 14, 15])
 
 
+def test_only_the_half_with_a_row_out_of_range_is_taken_again():
+    """One key that only single rows see brings these out of the range: their 256-row halves of the tiles are taken again with
+    shifts; every other row keeps the bits it has without that key's channel."""
+    require_gpu()
+    mq, mk = 28650, 17001
+    # (head, row): whole tiles, first and last rows of either half; a partial tile in pieces; a full tile in pieces
+    bad = [(1, 512 * 10), (1, 512 * 13 + 255), (2, 512 * 20 + 256), (4, 512 * 9 + 511), (5, 512 * 3 + 7), (5, 512 * 3 + 300),
+           (0, mq - 1), (3, mq // 512 * 512 + 30), (15, 512 * 50 + 3), (14, 512 * 52 + 400)]
+
+    def change(key_value):
+        def set_channel(q, k, qo, ko):
+            q[:, 0] = 0
+            k[:, 0] = 0
+            for h, r in bad:
+                q[qo[h] + r, 0] = 1.0
+            k[torch.tensor(ko[:-1]) + 9000, 0] = key_value
+        return set_channel
+
+    plan, *_, calm, _ = _run([mq] * 16, [mk] * 16, 6250, change(0.0))
+    pieces = {(h, q0) for _, h, q0, *_ in plan["segments"].tolist()}
+    assert (0, mq // 512 * 512) in pieces and (15, 512 * 50) in pieces and (1, 512 * 10) not in pieces
+    _, q, k2, v, qo, ko, out, _ = _run([mq] * 16, [mk] * 16, 6250, change(1200.0))
+    again = torch.zeros(qo[-1], dtype=torch.bool, device="cuda")
+    for h, r in bad:
+        again[qo[h] + r // 256 * 256:min(qo[h] + r // 256 * 256 + 256, qo[h + 1])] = True
+        kk = f32(k2[ko[h]:ko[h + 1]]) / np.float32(httm.LOG2_KEY_SCALE)
+        rows = [x for x in (r - 1, r, r + 1, r // 256 * 256, r // 256 * 256 + 255) if 0 <= x < mq]
+        want = orc.attention(f32(q[qo[h]:qo[h + 1]][rows]), kk, f32(v[ko[h]:ko[h + 1]]))
+        check_output(f32(out[qo[h]:qo[h + 1]][rows]), want, f"head {h}, rows around {r}", relative_to_magnitude=True)
+    assert bool(torch.isfinite(out.float()).all())
+    assert torch.equal(out[~again], calm[~again])
+
+
 def test_the_library_s_own_scratch_gives_the_same_bits():
     require_gpu()
     plan, q, k2, v, qo, ko, out, _ = _run([28700] * 16, [14401] * 16, 6300)
