@@ -1,5 +1,5 @@
 """Stage 3 (Eq. 3-4) in 512-row tiles: long launches with log2 keys, against the oracle on rows either side of the edges of
-tiles, slots and waves, and against the same call without scratch, whose rows of whole tiles have the same sums."""
+tiles, slots and waves, and against launches of a few of the heads in 256-row tiles, whose sums are the same."""
 import numpy as np
 import pytest
 import torch
@@ -22,11 +22,34 @@ def _run(mq, mk, seed, change=None):
         change(q, k, qo, ko)
     q, v, k2 = q.bfloat16(), v.bfloat16(), (k * httm.LOG2_KEY_SCALE).bfloat16()
     scratch = torch.full((LIMIT,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN bit patterns
-    out, plain = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    out = torch.full_like(q, float("nan"))
     httm.attention_log2(q, k2, v, out, qo, ko, scratch=scratch)
-    httm.attention_log2(q, k2, v, plain, qo, ko)
     torch.cuda.synchronize()
-    return plan, q, k2, v, qo, ko, out, plain
+    return plan, q, k2, v, qo, ko, out
+
+
+def _in_256_row_tiles(q, k2, v, qo, ko):
+    """The same rows, a few heads a launch, so that none runs in 512-row tiles; which rows ran whole in 256-row tiles."""
+    H, cus = len(qo) - 1, torch.cuda.get_device_properties(0).multi_processor_count
+    out, whole = torch.full_like(q, float("nan")), torch.zeros(qo[-1], dtype=torch.bool, device="cuda")
+    h = 0
+    while h < H:
+        for n in (7, 6, 5, 4, 3, 2, 1):
+            a = max(0, min(h, H - n))
+            b = min(H, a + n)
+            qr, kr = [x - qo[a] for x in qo[a:b + 1]], [x - ko[a] for x in ko[a:b + 1]]
+            route = httm.attention_route(qr, kr, cus, 0)
+            if httm.attention_wide_plan(qr, kr, cus, 0) is None and route["tiles"][0] == "tiles256":
+                break
+        assert httm.attention_wide_plan(qr, kr, cus, 0) is None
+        httm.attention_log2(q[qo[a]:qo[b]], k2[ko[a]:ko[b]], v[ko[a]:ko[b]], out[qo[a]:qo[b]], qr, kr)
+        whole[qo[a]:qo[b]] = False
+        if route["tiles"][0] == "tiles256":
+            for i, (first, rows) in enumerate(route["rows"][0].tolist()):
+                whole[qo[a + i] + first:qo[a + i] + first + rows] = True
+        h = b
+    torch.cuda.synchronize()
+    return out, whole
 
 
 def _check_rows(q, k2, v, qo, ko, out, heads):
@@ -59,16 +82,18 @@ CASES = [
 def test_wide_tiles_match_the_oracle(mq, mk, n_tiles):
     require_gpu()
     print(f"[case] {mq} {mk}", flush=True)
-    plan, q, k2, v, qo, ko, out, plain = _run(mq, mk, 6100 + len(mq) + mq[0] % 100)
+    plan, q, k2, v, qo, ko, out = _run(mq, mk, 6100 + len(mq) + mq[0] % 100)
     assert plan is not None and (plan["n_tiles"] > 0 if n_tiles is None else plan["n_tiles"] == n_tiles)
     _check_rows(q, k2, v, qo, ko, out, [0, 1, len(mq) // 2, len(mq) - 1])
     pieces = torch.zeros(qo[-1], dtype=torch.bool, device="cuda")
     for _, h, q0, *_ in plan["segments"].tolist():
         pieces[qo[h] + q0:min(qo[h] + q0 + 512, qo[h + 1])] = True
-    d = (out.float() - plain.float()).abs()
-    assert bool((d <= 2.0 ** -7 * plain.float().abs() + 1e-5).all()), float(d.max())     # fp32 rounding of the pieces' sums
-    if len(httm.attention_route(qo, ko, 256, 0)["tiles"]) == 1:     # (else some of its rows run in key groups)
-        assert torch.equal(out[~pieces], plain[~pieces])
+    narrow, whole = _in_256_row_tiles(q, k2, v, qo, ko)
+    d = (out.float() - narrow.float()).abs()
+    assert bool((d <= 2.0 ** -7 * narrow.float().abs() + 1e-5).all()), float(d.max())     # fp32 rounding of the pieces' sums
+    same = whole & ~pieces
+    assert int(same.sum()) > qo[-1] // 2
+    assert torch.equal(out[same], narrow[same])
 
 
 def test_rows_out_of_the_unshifted_range():
@@ -85,10 +110,65 @@ def test_rows_out_of_the_unshifted_range():
             k[ko[h] + first:ko[h + 1], 0] = -100.0            # 7, 15: half of the keys masked; 9: all scores low
         k[ko[14] + 100, :] = 40.0 * torch.sign(q[qo[15] - 1, :])      # head 14: one key that some rows like
 
-    plan, q, k2, v, qo, ko, out, plain = _run([28700] * 16, [14401] * 16, 6200, change)
+    plan, q, k2, v, qo, ko, out = _run([28700] * 16, [14401] * 16, 6200, change)
     assert plan is not None and plan["n_tiles"] == 144
     assert bool(torch.isfinite(out.float()).all())
     _check_rows(q, k2, v, qo, ko, out, [0, 3, 5, 7, 9, 14, 15])
+
+
+def test_rows_with_nan_or_infinity_leave_their_neighbours_alone():
+    """In whole tiles, full tiles in pieces and a partial tile in pieces: those rows are NaN, the other halves of their tiles
+    and all other tiles keep their bits."""
+    require_gpu()
+    mq, mk = 28650, 17001
+    bad = [(1, 512 * 10 + 5), (2, 512 * 20 + 300), (0, mq - 1), (15, 512 * 50 + 3), (15, 512 * 51 + 511)]
+
+    def change(q, k, qo, ko):
+        for i, (h, r) in enumerate(bad):
+            if i % 2:
+                q[qo[h] + r, 3] = float("inf")
+            else:
+                q[qo[h] + r] = float("nan")
+
+    _, *_, calm = _run([mq] * 16, [mk] * 16, 6260)
+    plan, q, k2, v, qo, ko, out = _run([mq] * 16, [mk] * 16, 6260, change)
+    pieces = {(h, q0) for _, h, q0, *_ in plan["segments"].tolist()}
+    assert (0, mq // 512 * 512) in pieces and (15, 512 * 50) in pieces and (1, 512 * 10) not in pieces
+    again = torch.zeros(qo[-1], dtype=torch.bool, device="cuda")
+    for h, r in bad:
+        first = r // 256 * 256
+        again[qo[h] + first:min(qo[h] + first + 256, qo[h + 1])] = True
+        assert bool(torch.isnan(out[qo[h] + r].float()).all())
+        rows = [x for x in range(first, min(first + 256, mq)) if x != r and (abs(x - r) <= 16 or x % 16 == r % 16 or x % 37 == 0)]
+        kk = f32(k2[ko[h]:ko[h + 1]]) / np.float32(httm.LOG2_KEY_SCALE)
+        want = orc.attention(f32(q[qo[h]:qo[h + 1]][rows]), kk, f32(v[ko[h]:ko[h + 1]]))
+        check_output(f32(out[qo[h]:qo[h + 1]][rows]), want, f"head {h}, rows beside {r}")
+    assert torch.equal(out[~again], calm[~again])
+
+
+def test_rows_whose_every_score_is_the_lowest():
+    """No shift holds them (running maxima behind the pass with shifts): uniform weights, the mean of the values."""
+    require_gpu()
+    mq, mk = 28700, 14401
+    masked = torch.zeros(mq, dtype=torch.bool)
+    masked[[5, 300, 512 * 20 + 256, 512 * 54 + 100, 512 * 55 + 511, mq - 1]] = True      # whole tiles, pieces, the narrow tile
+
+    def change(q, k, qo, ko):
+        for h in (0, 7, 15):
+            q[qo[h]:qo[h + 1], 0] = masked.float().cuda()
+            k[ko[h]:ko[h + 1], 0] = float(torch.finfo(torch.bfloat16).min)         # (the key factor is below 1)
+
+    plan, q, k2, v, qo, ko, out = _run([mq] * 16, [mk] * 16, 6270, change)
+    assert plan is not None and plan["n_tiles"] == 144 and bool(torch.isfinite(k2.float()).all())
+    rows = np.unique(np.concatenate([np.flatnonzero(masked) + d for d in (-16, -1, 1, 16)]))
+    rows = rows[(rows < mq) & ~masked.numpy()[np.minimum(rows, mq - 1)]]
+    for h in (0, 7, 15):
+        got, vh = f32(out[qo[h]:qo[h + 1]]), f32(v[ko[h]:ko[h + 1]])
+        m = got[masked.numpy()]
+        check_output(m, np.broadcast_to(vh.astype(np.float64).mean(axis=0), m.shape), f"head {h}, masked rows")
+        qh, kh = f32(q[qo[h]:qo[h + 1]][rows.tolist()]), f32(k2[ko[h]:ko[h + 1]]) / np.float32(httm.LOG2_KEY_SCALE)
+        qh[:, 0] = kh[:, 0] = 0                 # what the other rows see of the channel: 0 * lowest
+        check_output(got[rows], orc.attention(qh, kh, vh), f"head {h}, rows beside them")
 
 
 def test_only_the_half_with_a_row_out_of_range_is_taken_again():
@@ -109,10 +189,10 @@ def test_only_the_half_with_a_row_out_of_range_is_taken_again():
             k[torch.tensor(ko[:-1]) + 9000, 0] = key_value
         return set_channel
 
-    plan, *_, calm, _ = _run([mq] * 16, [mk] * 16, 6250, change(0.0))
+    plan, *_, calm = _run([mq] * 16, [mk] * 16, 6250, change(0.0))
     pieces = {(h, q0) for _, h, q0, *_ in plan["segments"].tolist()}
     assert (0, mq // 512 * 512) in pieces and (15, 512 * 50) in pieces and (1, 512 * 10) not in pieces
-    _, q, k2, v, qo, ko, out, _ = _run([mq] * 16, [mk] * 16, 6250, change(1200.0))
+    _, q, k2, v, qo, ko, out = _run([mq] * 16, [mk] * 16, 6250, change(1200.0))
     again = torch.zeros(qo[-1], dtype=torch.bool, device="cuda")
     for h, r in bad:
         again[qo[h] + r // 256 * 256:min(qo[h] + r // 256 * 256 + 256, qo[h + 1])] = True
@@ -126,7 +206,7 @@ def test_only_the_half_with_a_row_out_of_range_is_taken_again():
 
 def test_the_library_s_own_scratch_gives_the_same_bits():
     require_gpu()
-    plan, q, k2, v, qo, ko, out, _ = _run([28700] * 16, [14401] * 16, 6300)
+    plan, q, k2, v, qo, ko, out = _run([28700] * 16, [14401] * 16, 6300)
     assert plan["slots"] * 256 * 66 * 4 > 32 << 20
     own = torch.full_like(q, float("nan"))
     httm.attention_log2_static(q, k2, v, own, qo, ko)
@@ -134,9 +214,11 @@ def test_the_library_s_own_scratch_gives_the_same_bits():
     assert torch.equal(own, out)
 
 
-def test_a_layer_s_outlier_queries_behind_wide_tiles():
+@pytest.mark.parametrize("out_of_range", [False, True], ids=["in_range", "out_of_range"])
+def test_a_layer_s_outlier_queries_behind_wide_tiles(out_of_range):
     """100 frames of 37 x 37, a tenth of the queries outliers: merged rows and outliers in one launch of 512-row tiles, the
-    pieces behind both.  The same bits as the separate calls (which are checked against the oracle elsewhere)."""
+    pieces behind both.  The same bits as the separate calls (which are checked against the oracle elsewhere), also where
+    merged rows and outliers leave the range of their weights."""
     require_gpu()
     S, H = 100, 16
     plan = httm.Plan(httm.make_geom(S, 37, 37, 4, 4, 0.8, 0.8, H=H, log2_keys=True, outlier_frac=0.1))
@@ -144,11 +226,15 @@ def test_a_layer_s_outlier_queries_behind_wide_tiles():
     assert httm.attention_wide_plan(off, [h * plan.M_k for h in range(H + 1)])["n_tiles"] > 0
     gen = torch.Generator(device="cuda").manual_seed(6400)
     q, k, v = (torch.randn((H, plan.N, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    if out_of_range:
+        q[:, :, 0] = (torch.arange(plan.N, device="cuda") % 3001 < 2).bfloat16()
+        k[:, :, 0] = 0
+        k[:, 1374 * 50 + 3, 0] = 3000.0                   # a special token: it stays a key of its own
     out = torch.full((plan.N, H * 64), float("nan"), dtype=torch.bfloat16, device="cuda")
     ws = httm.alloc_workspace(plan)
     httm.layer_forward(plan, q, k, v, out, ws)
     w = httm.workspace_views(plan, ws)
-    o_m, o_out = torch.empty_like(w["o_m"]), torch.empty_like(w["o_out"])
+    o_m, o_out = torch.empty_like(w["o_m"]), torch.full_like(w["o_out"], float("nan"))
     scratch = torch.empty(LIMIT, dtype=torch.uint8, device="cuda")
     httm.attention_log2(w["q_m"], w["k_m"], w["v_m"], o_m, off, [h * plan.M_k for h in range(H + 1)], scratch=scratch)
     httm.attention_outliers(plan, w["q_out"], w["k_m"], w["v_m"], o_out)
@@ -158,4 +244,52 @@ def test_a_layer_s_outlier_queries_behind_wide_tiles():
     httm.unmerge_filtered(plan, o_m, o_out, w["assign_q"], want)
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+    if out_of_range:
+        seen = w["k_m"][:, :, 0].float().amax(1)
+        assert bool((seen > 400).all())
+        counts = torch.bincount((w["assign_q"] < 0).nonzero()[:, 0], minlength=H).tolist()
+        first = [0] + [int(x) for x in np.cumsum(counts)]
+        for h in (0, 9, H - 1):
+            kk, vv = f32(w["k_m"][h]) / np.float32(httm.LOG2_KEY_SCALE), f32(w["v_m"][h])
+            for name, rows, res in (("merged", w["q_m"][h], o_m[h]), ("outliers", w["q_out"][first[h]:first[h + 1]], o_out[first[h]:first[h + 1]])):
+                far = (rows[:, 0].float() * seen[h] > 80).nonzero()[:, 0].tolist()
+                assert far, name
+                pick = sorted({x for r in far[:6] for x in (r - 1, r, r + 1, r // 256 * 256) if 0 <= x < len(rows)})
+                check_output(f32(res[pick]), orc.attention(f32(rows[pick]), kk, vv), f"head {h}, {name}", relative_to_magnitude=True)
+    plan.close()
+
+
+@pytest.mark.parametrize("frac", [0.0, 0.1], ids=["layer", "filtered"])
+def test_a_captured_layer_in_wide_tiles_replays_to_the_bits_of_the_eager_call(frac):
+    require_gpu()
+    S, H = 100, 16
+    plan = httm.Plan(httm.make_geom(S, 37, 37, 4, 4, 0.8, 0.8, H=H, log2_keys=True, outlier_frac=frac))
+    assert httm.attention_wide_plan([h * plan.M_q for h in range(H + 1)], [h * plan.M_k for h in range(H + 1)])["n_tiles"] > 0
+    gen = torch.Generator(device="cuda").manual_seed(6500)
+    q, k, v = (torch.empty((H, plan.N, 64), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    out, ws = torch.empty((plan.N, H * 64), dtype=torch.bfloat16, device="cuda"), httm.alloc_workspace(plan)
+    eager, eager_ws = torch.empty_like(out), httm.alloc_workspace(plan)
+
+    def new_inputs(spread):
+        for t in (q, k, v):
+            t.copy_((torch.randn(t.shape, generator=gen, device="cuda") * spread).bfloat16())
+        httm.layer_forward(plan, q, k, v, eager, eager_ws)
+        torch.cuda.synchronize()
+
+    new_inputs(1.0)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        httm.layer_forward(plan, q, k, v, out, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        httm.layer_forward(plan, q, k, v, out, ws)
+    for spread in (1.0, 4.0, 0.7, 1.0):                  # (the second time rows leave the range of their weights)
+        new_inputs(spread)
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
     plan.close()
