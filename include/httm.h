@@ -324,7 +324,7 @@ HTTM_API int httm_attention_wide_plan(const int64_t* q_offsets, const int64_t* k
 
 /* httm_attention_log2_scratch for callers that cannot allocate device memory and have no buffer to
  * pass: code that runs under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  The scratch is an array inside the library's device code
+ * hipMalloc.  The scratch is an array of 51.8 MB inside the library's device code
  * (every GPU the library has run on holds its copy until the process ends); the call allocates and
  * frees nothing.  Arguments, layout and results as httm_attention_log2_scratch (bit-identical to
  * it).  A launch whose partial results (as httm_attention_split_plan reports them) need more than

@@ -1253,7 +1253,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 // ---- tiles of 512 rows --------------------------------------------------------------------------------
 // Long launches with log2 keys: four waves of 128 rows, one workgroup per CU.  What bounds a long launch is power, and an
 // operand read from LDS that serves 8 products instead of 4 halves the LDS reads, the requests and the barriers of a
-// product.  The accumulators and Q lie in accumulation registers (mfma_o()), which is all 512 registers of a lane, so
+// product.  The accumulators and Q lie in accumulation registers (mfma_o()): 454 registers a lane, so
 // there is one wave per SIMD and nothing hides its waits: every operand is read 10 to 30 products before its first use,
 // between other products (wide_step()), the next tile's behind a barrier in the middle of the tile's second step, and a
 // tile's requests have one and a half tiles until that barrier - three buffers each of K and V, LDS objects of their own, so
@@ -1368,10 +1368,11 @@ __device__ __forceinline__ int wide_tile(const AttnArgs& a, KvTile& k0, KvTile& 
       StepOperands op;
       load_v_operands(op, v0, l16, grp);
       __builtin_amdgcn_sched_barrier(0);
-      // K tile jt (kc, the next one kn) against V tile jt - 1 (vc, the next one vn), whose first operands are there; kr, vr:
-      // what everybody has read, K tile jt - 1 and V tile jt - 2, before the barrier of tile jt - 1.  (Behind a request the compiler
+      // K tile jt (kc) against V tile jt - 1 (vc), whose first operands are there, and the first operands of V tile jt (vn), behind the
+      // barrier that says that it has arrived.  Requested are K tile jt + 2 into the buffer kr of K tile jt - 1 and V tile jt + 1 into
+      // the buffer vr of V tile jt - 2: everybody has read those before the barrier of tile jt - 1.  (Behind a request the compiler
       // waits for all LDS reads, the youngest as well: the requests lie where the next wait is for all that there are.)
-      auto tile = [&](int jt, KvTile& kc, KvTile& kn, KvTile& kr, KvTile& vc, KvTile& vn, KvTile& vr) {
+      auto tile = [&](int jt, KvTile& kc, KvTile& kr, KvTile& vc, KvTile& vn, KvTile& vr) {
         wide_step(w, op, kc, vc + kStep * kDHead, lane, [] {}, [&](int g) {
           if (g == 17) load_k(jt + 2, kr);
           if (g == 21) load_v(jt + 1, vr);
@@ -1379,15 +1380,15 @@ __device__ __forceinline__ int wide_tile(const AttnArgs& a, KvTile& k0, KvTile& 
         wide_step(w, op, kc + kStep * kDHead, vn, lane, arrived, [](int) {});
       };
       for (; j + 2 < n_tiles - 1; j += 3) {
-        tile(j, k1, k2, k0, v0, v1, v2);
-        tile(j + 1, k2, k0, k1, v1, v2, v0);
-        tile(j + 2, k0, k1, k2, v2, v0, v1);
+        tile(j, k1, k0, v0, v1, v2);
+        tile(j + 1, k2, k1, v1, v2, v0);
+        tile(j + 2, k0, k2, v2, v0, v1);
       }
       if (j < n_tiles - 1) {
-        tile(j, k1, k2, k0, v0, v1, v2);
+        tile(j, k1, k0, v0, v1, v2);
         ++j;
         if (j < n_tiles - 1) {
-          tile(j, k2, k0, k1, v1, v2, v0);
+          tile(j, k2, k1, v1, v2, v0);
           ++j;
         }
       }

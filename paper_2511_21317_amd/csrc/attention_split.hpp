@@ -38,7 +38,12 @@ constexpr int kAttnLongShareUnits = 240;  // shares of more than 15360 keys are 
 constexpr int kAttnMaxPiecesPerTile = 32; // bounds what one workgroup of the second kernel has to add up
 constexpr int64_t kAttnSlotWords = (int64_t)kAttnTileRows * (64 + 2);   // 64 sums of weight * v, sum of weights, shift
 
-// Scratch that covers any launch: a slot per (share, tile) pair that can occur.
+// Scratch that covers any launch in 256-row tiles: a slot per (share, tile) pair that can occur.  A segment of a 512-row tile
+// has two slots, so a plan of those may need 1020; one that needs more than these 767 is dropped (choose_wide_tiles()), mostly
+// for 256-row tiles: with 16 equal heads those of 20 500 to 23 500, 29 000 to 31 500 and 37 000 to 39 500 rows, about a third of
+// the long launches.  What that leaves, us, so / with room for 1020 slots (17 MB more in every workspace and on every GPU):
+// 16 heads of 21000 x 21000 1356 / 1317, 23500 x 23500 1697 / 1636, 29142 x 29142 2582 / 2497, 31190 x 31190 3018 / 2858, 39600 x 39600
+// 4826 / 4584, 22000 x 60000 3976 / 3861.
 constexpr int64_t kAttnScratchBytes = (int64_t)(kAttnMaxShares + kAttnMaxExcess) * kAttnSlotWords * 4;
 
 // `count` consecutive tiles of one head in the excess set: tile e of the set (tile0 <= e < tile0 +
@@ -407,7 +412,7 @@ inline int64_t count_last_tiles(const AttnRoute& r, const int64_t* q_off, int H,
 // and their sum, which are twice as large, take 12 and 20 us.  A head's last tile of at most 256 rows is half a tile.  A
 // split launch has to gain 1.5 % by this, another one 0.5 %.  Every tile of a round has to be as long as the others: one workgroup
 // on a CU leaves it idle behind a short one (12 heads of 36 000 rows against 7000 to 17 000 keys 1126 us in 256-row tiles, 1237 in
-// these).  us, 256-row tiles / these: 16 heads of 16384 x 4096 206 / 203, 16384 x 16384 780 / 749, 17600 x 17600 900 / 888,
+// these).  A plan that needs more slots than there are is dropped (kAttnScratchBytes).  us, 256-row tiles / these: 16 heads of 16384 x 4096 206 / 203, 16384 x 16384 780 / 749, 17600 x 17600 900 / 888,
 // 28700 x 9000 767 / 758, 28650 x 28650 2362 / 2294, 28700 x 83140 6870 / 6693, 8112 x 21619 521 / 500, 24 of 61587 x 6566 1778 /
 // 1761; 57 random launches of 8 to 24 heads 0.975 of the time in the median, 1.007 at most.
 inline bool choose_wide_tiles(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words, AttnRoute* out) {

@@ -31,8 +31,8 @@ struct WorkItem {
   int32_t dims;
 };
 
-// Scratch of stage 3 that covers any launch (attention_split.hpp: kAttnScratchBytes; a slot of
-// 256 rows x 66 fp32 for each of the at most 512 + 255 - 1 segments).
+// Scratch of stage 3 (attention_split.hpp: kAttnScratchBytes; a slot of 256 rows x 66 fp32 for each of the at most
+// 512 + 255 - 1 segments of a launch in 256-row tiles, and for as many plans of 512-row tiles as fit).
 inline int64_t attention_scratch_bytes(int) { return (int64_t)(512 + 255) * 256 * (64 + 2) * 4; }
 
 struct HostTables {
