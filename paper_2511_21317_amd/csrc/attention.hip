@@ -130,6 +130,7 @@ struct AttnArgs {
   int32_t split_per_xcd;
   int32_t main_blocks;
   int32_t share_block0;   // 512-row tiles: the shares come last, from this workgroup on
+  int32_t dev_halves;     // 256-row tiles: 1 if the device-side list's are 512-row tiles, which two workgroups take then
   float* split_o;   // [slots * 256][64] sums of weight * v
   float* split_l;   // [slots * 256]     sums of weights
   float* split_m;   // [slots * 256]     the rows' shifts
@@ -1601,12 +1602,13 @@ void attention_kernel(const AttnArgs a) {
   const int pos = block >> 3, whole_per_xcd = a.full_per_xcd + a.ragged_per_xcd;
   if (dev_tile) {
     if (!a.dev_tiles) return;
-    const int t = block - a.main_blocks;
+    const int half = (block - a.main_blocks) & a.dev_halves, t = (block - a.main_blocks) >> a.dev_halves;
     if (t >= a.dev_tiles[0]) return;
     h = a.dev_tiles[1 + 2 * t];
-    q0 = a.dev_tiles[2 + 2 * t];
+    q0 = a.dev_tiles[2 + 2 * t] + half * kAttnTileRows;
     q_base_dev = a.dev_q_off[h];
     mq_dev = a.dev_q_off[h + 1] - a.dev_q_off[h];
+    if (q0 >= mq_dev) return;
   } else if (KS == 1 && pos >= whole_per_xcd) {
     const int item = pos - whole_per_xcd;
     share = xcd * a.split_per_xcd + item;
@@ -1921,6 +1923,17 @@ void choose_dev_tiles(int64_t rows, int64_t M_q, int64_t M_k, int H, bool log2_k
   *tile_rows = attention_tile_rows(t);
 }
 
+// Whether the 512-row tiles of a device-side list of `rows` rows run quicker in a launch of their own as two 256-row tiles each,
+// which gives the same sums: in time per key tile, a round of 512-row tiles takes 1462, one of pairs of 256-row tiles 1517 and a
+// last one with no more than one a CU 0.6 of that.  us, 512-row tiles / two 256-row tiles, 16 heads against 28650 keys: 32976 rows
+// 557 / 393, 65952 562 / 593, 175872 1189 / 1016, 219840 1235 / 1293, 329760 1925 / 2003, 28700 keys: 131904 1188 / 958, 439680 2624 / 2458,
+// 17760 keys: 70348 350 / 371.
+bool dev_tiles_in_halves(int64_t rows, int H, int64_t cus) {
+  const int64_t wide = rows / kWideRows + H / 2, narrow = rows / kAttnTileRows + H / 2, rest = narrow % (2 * cus);
+  const int64_t time = (wide + cus - 1) / cus * 1462;
+  return narrow / (2 * cus) * 1517 + (rest == 0 ? 0 : rest <= cus ? 910 : 1517) < time;
+}
+
 hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* v, void* o, const DevTiles& dev,
                                       const int64_t* k_off_host, int H, float scale, bool log2_keys,
                                       hipStream_t stream, const UnmergeTarget* unmerge) {
@@ -1931,6 +1944,10 @@ hipError_t launch_attention_dev_tiles(const void* q, const void* k, const void* 
   a.q2 = a.q;
   a.o2 = a.o;
   HeadRows none = {};       // no whole tiles, no segments: every workgroup takes the device-side list
+  if ((AttnTiles)dev.kind == AttnTiles::kTiles512 && dev_tiles_in_halves((int64_t)(dev.max_tiles - H) * kWideRows, H, compute_units())) {
+    a.dev_halves = 1;
+    return launch_tiles(AttnTiles::kTiles256, a, log2_keys, none, k_off_host, H, stream, 2 * dev.max_tiles);
+  }
   return launch_tiles((AttnTiles)dev.kind, a, log2_keys, none, k_off_host, H, stream, dev.max_tiles);
 }
 

@@ -214,14 +214,15 @@ def test_the_library_s_own_scratch_gives_the_same_bits():
     assert torch.equal(own, out)
 
 
-@pytest.mark.parametrize("out_of_range", [False, True], ids=["in_range", "out_of_range"])
-def test_a_layer_s_outlier_queries_behind_wide_tiles(out_of_range):
-    """100 frames of 37 x 37, a tenth of the queries outliers: merged rows and outliers in one launch of 512-row tiles, the
-    pieces behind both.  The same bits as the separate calls (which are checked against the oracle elsewhere), also where
-    merged rows and outliers leave the range of their weights."""
+# outliers alone in 1.7 rounds of 512-row tiles; in 1.3 and 0.3, which run as 256-row tiles, two for each of the list's
+@pytest.mark.parametrize("frac,out_of_range", [(0.1, False), (0.1, True), (0.08, False), (0.08, True), (0.015, False)])
+def test_a_layer_s_outlier_queries_behind_wide_tiles(frac, out_of_range):
+    """100 frames of 37 x 37: merged rows and outliers in one launch of 512-row tiles, the pieces behind both.  The same
+    bits as the separate calls (which are checked against the oracle elsewhere), also where merged rows and outliers leave
+    the range of their weights."""
     require_gpu()
     S, H = 100, 16
-    plan = httm.Plan(httm.make_geom(S, 37, 37, 4, 4, 0.8, 0.8, H=H, log2_keys=True, outlier_frac=0.1))
+    plan = httm.Plan(httm.make_geom(S, 37, 37, 4, 4, 0.8, 0.8, H=H, log2_keys=True, outlier_frac=frac))
     off = [h * plan.M_q for h in range(H + 1)]
     assert httm.attention_wide_plan(off, [h * plan.M_k for h in range(H + 1)])["n_tiles"] > 0
     gen = torch.Generator(device="cuda").manual_seed(6400)
@@ -257,6 +258,35 @@ def test_a_layer_s_outlier_queries_behind_wide_tiles(out_of_range):
                 pick = sorted({x for r in far[:6] for x in (r - 1, r, r + 1, r // 256 * 256) if 0 <= x < len(rows)})
                 check_output(f32(res[pick]), orc.attention(f32(rows[pick]), kk, vv), f"head {h}, {name}", relative_to_magnitude=True)
     plan.close()
+
+
+def test_outlier_queries_alone_do_not_wait_for_long_tiles():
+    """32 976 outliers are 72 tiles of 512 rows on 256 CUs: as 256-row tiles they take about 1.2 of the time of
+    attention_log2 on the same rows (which shares the keys among waves), as 512-row tiles 1.7."""
+    require_gpu()
+    S, H = 100, 16
+    plan = httm.Plan(httm.make_geom(S, 37, 37, 4, 4, 0.8, 0.8, H=H, log2_keys=True, outlier_frac=0.015))
+    gen = torch.Generator(device="cuda").manual_seed(6450)
+    q, k, v = (torch.randn((H, plan.N, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    ws = httm.alloc_workspace(plan)
+    httm.layer_forward(plan, q, k, v, torch.empty((plan.N, H * 64), dtype=torch.bfloat16, device="cuda"), ws)
+    w = httm.workspace_views(plan, ws)
+    n = plan.outlier_cap // H
+    rows, out = w["q_out"][:n * H].contiguous(), torch.empty_like(w["o_out"])
+    qo, ko = [h * n for h in range(H + 1)], [h * plan.M_k for h in range(H + 1)]
+    calls = (lambda: httm.attention_outliers(plan, w["q_out"], w["k_m"], w["v_m"], out),
+             lambda: httm.attention_log2(rows, w["k_m"].view(-1, 64), w["v_m"].view(-1, 64), torch.empty_like(rows), qo, ko))
+    times = ([], [])
+    for _ in range(8):
+        for call, t in zip(calls, times):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+    plan.close()
+    assert min(times[0]) < 1.45 * min(times[1]), times
 
 
 @pytest.mark.parametrize("frac", [0.0, 0.1], ids=["layer", "filtered"])
