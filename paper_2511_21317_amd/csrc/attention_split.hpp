@@ -48,7 +48,7 @@ constexpr int64_t kAttnScratchBytes = (int64_t)(kAttnMaxShares + kAttnMaxExcess)
 
 // `count` consecutive tiles of one head in the excess set: tile e of the set (tile0 <= e < tile0 +
 // count) covers the query rows from q0 + (e - tile0) * tile_rows and the units [cum + (e - tile0) * kt,
-// ... + kt), kt = key tiles of the head (half of them where a unit is two: see narrow_tiles).
+// ... + kt), kt = units of one tile of the head: its key tiles, fewer where a unit is more of them (see narrow_tiles).
 struct SplitGroup {
   int32_t head, q0, tile0, cum, kt;
 };
@@ -63,7 +63,8 @@ struct SplitPlan {
   int32_t slots;        // 256-row tiles: shares + n_tiles - 1 (a few slots stay unused: a share and a tile that end together)
   int32_t tile_rows;    // 256 or 512
   // 512-row tiles: the first narrow_tiles ones are partial ones of at most 256 rows, whose segments have one slot of scratch
-  // instead of two and whose units are two key tiles, because they walk twice as fast
+  // instead of two and whose units are 1.6 key tiles: alone on a CU they take 0.62 of the time.  (With units of two the shares
+  // that hold them end last: 20 heads of 8942 x 50208 in 1.06 of the time of 256-row tiles.)
   int32_t narrow_tiles;
   int32_t slot_shift;   // what makes the slots of the other ones follow those
   SplitGroup grp[kAttnSplitGroups];
@@ -106,6 +107,9 @@ __host__ __device__ inline int split_tile_of_unit(const SplitPlan& p, int unit) 
 // second one for their rows from 256 on, but for the partial tiles that need one only: those come first.
 template <bool WIDE>
 __host__ __device__ inline int slots_per_segment(const SplitPlan& p, int tile) { return WIDE && tile >= p.narrow_tiles ? 2 : 1; }
+// Key tile at which unit u of a tile begins.
+template <bool WIDE>
+__host__ __device__ inline int first_key_tile(const SplitPlan& p, int tile, int u) { return WIDE && tile < p.narrow_tiles ? u * 8 / 5 : u; }
 template <bool WIDE>
 __host__ __device__ inline int split_slot(const SplitPlan& p, int share, int tile) {
   return slots_per_segment<WIDE>(p, tile) == 1 ? share + tile : 2 * (share + tile) - p.slot_shift;
@@ -130,9 +134,8 @@ __host__ __device__ inline SplitSegment split_segment(const SplitPlan& p, int sh
   SplitSegment s;
   s.head = g.head;
   s.q0 = g.q0 + (e - g.tile0) * (WIDE ? kWideRows : kAttnTileRows);
-  const int per_unit = slots_per_segment<WIDE>(p, e) == 1 && WIDE ? 2 : 1;       // key tiles
-  s.t0 = per_unit * ((u0 > tu0 ? u0 : tu0) - tu0);
-  s.t1 = per_unit * ((u1 < tu0 + g.kt ? u1 : tu0 + g.kt) - tu0);      // (may be one more than there are)
+  s.t0 = first_key_tile<WIDE>(p, e, (u0 > tu0 ? u0 : tu0) - tu0);
+  s.t1 = first_key_tile<WIDE>(p, e, (u1 < tu0 + g.kt ? u1 : tu0 + g.kt) - tu0);      // (may be one more than there are)
   s.slot = split_slot<WIDE>(p, share, e);
   return s;
 }
@@ -183,7 +186,7 @@ inline void plan_attention_split(const int64_t* q_off, const int64_t* k_off, int
     const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h];
     if (mq % tile_rows == 0) continue;
     if (n_groups == kAttnSplitGroups) return;
-    const int32_t tile = narrow ? 2 * kAttnKeyTile : kAttnKeyTile, kt = (int32_t)((mk + tile - 1) / tile);
+    const int32_t tiles = (int32_t)((mk + kAttnKeyTile - 1) / kAttnKeyTile), kt = narrow ? (5 * tiles + 7) / 8 : tiles;
     p.grp[n_groups++] = {h, (int32_t)(mq / tile_rows) * tile_rows, n_tiles, (int32_t)units, kt};
     n_tiles += 1;
     units += kt;

@@ -60,15 +60,27 @@ def test_without_scratch_only_whole_rounds():
     assert check_wide_plan([16384] * 16, [16384] * 16, 0)["n_tiles"] == 0
 
 
-@pytest.mark.parametrize("rows,n_tiles,slots", [(28650, 128, 766), (28700, 144, 767), (29142, 144, 798), (30166, 176, 862), (31190, 208, 926), (23500, 224, 958)])
+@pytest.mark.parametrize("H,mq,mk", [(20, 8942, 50208), (16, 12404, 72887), (48, 3762, 63618), (16, 28700, 28700), (16, 28650, 28650), (16, 17600, 17600)])
+def test_shares_take_equal_times(H, mq, mk):
+    """A tile of at most 256 rows takes 0.62 of the time of a larger one per key tile (alone on a CU): shares of such tiles
+    have that many key tiles more."""
+    p = check_wide_plan([mq] * H, [mk] * H)
+    time = np.zeros(p["shares"])
+    for share, _, q0, t0, t1, _ in p["segments"].tolist():
+        time[share] += (t1 - t0) * (0.62 if mq - q0 <= SLOT_ROWS else 1.0)
+    assert time[:-1].max() <= 1.02 * time[:-1].mean() + 1, (time.max(), time[:-1].mean())
+
+
+@pytest.mark.parametrize("rows,n_tiles,slots", [(28650, 128, 766), (28700, 144, 764), (29142, 144, 798), (30166, 176, 862), (31190, 208, 926), (23500, 224, 958)])
 def test_a_plan_needs_room_for_all_its_slots(rows, n_tiles, slots):
-    """Tiles in excess are cut if there is room for all of the plan's slots and not otherwise; what the library asks for holds
-    767, which the plans of about a third of the long launches exceed."""
+    """Tiles in excess are cut if there is room for all of the plan's slots and not otherwise (then all tiles run whole, or none has
+    512 rows); what the library asks for holds 767, which the plans of about a third of the long launches exceed."""
     off = [h * rows for h in range(17)]
     p = check_wide_plan([rows] * 16, [rows] * 16, slots * SLOT_BYTES)
     assert (p["n_tiles"], p["slots"]) == (n_tiles, slots)
-    assert check_wide_plan([rows] * 16, [rows] * 16, slots * SLOT_BYTES - 1) is None
-    assert (httm.attention_wide_plan(off, off) is not None) == (slots <= 767)
+    cut = lambda q: q is not None and q["n_tiles"] > 0      # noqa: E731
+    assert not cut(check_wide_plan([rows] * 16, [rows] * 16, slots * SLOT_BYTES - 1))
+    assert cut(httm.attention_wide_plan(off, off)) == (slots <= 767)
     assert httm.attention_scratch_bytes(16) == 767 * SLOT_BYTES
 
 
