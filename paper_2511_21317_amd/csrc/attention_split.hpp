@@ -39,11 +39,10 @@ constexpr int kAttnMaxPiecesPerTile = 32; // bounds what one workgroup of the se
 constexpr int64_t kAttnSlotWords = (int64_t)kAttnTileRows * (64 + 2);   // 64 sums of weight * v, sum of weights, shift
 
 // Scratch that covers any launch in 256-row tiles: a slot per (share, tile) pair that can occur.  A segment of a 512-row tile
-// has two slots, so a plan of those may need 1020; one that needs more than these 767 is dropped (choose_wide_tiles()), mostly
-// for 256-row tiles: with 16 equal heads those of 20 500 to 23 500, 29 000 to 31 500 and 37 000 to 39 500 rows, about a third of
-// the long launches.  What that leaves, us, so / with room for 1020 slots (17 MB more in every workspace and on every GPU):
-// 16 heads of 21000 x 21000 1356 / 1317, 23500 x 23500 1697 / 1636, 29142 x 29142 2582 / 2497, 31190 x 31190 3018 / 2858, 39600 x 39600
-// 4826 / 4584, 22000 x 60000 3976 / 3861.
+// has two slots, so a plan of those may need 1020; one that needs more than these 767 is dropped (choose_wide_tiles()) for whole
+// rounds or 256-row tiles: with 16 equal heads those of 20 800 to 23 300, 29 000 to 30 900 and 37 200 to 38 900 rows run in the
+// latter, a quarter of the long launches.  What that leaves, us, so / with room for 1020 slots (17 MB more in every workspace
+// and on every GPU): 16 heads of 21000 x 21000 1356 / 1317, 29142 x 29142 2582 / 2497, 30166 x 30166 2737 / 2678, 22000 x 60000 3976 / 3861.
 constexpr int64_t kAttnScratchBytes = (int64_t)(kAttnMaxShares + kAttnMaxExcess) * kAttnSlotWords * 4;
 
 // `count` consecutive tiles of one head in the excess set: tile e of the set (tile0 <= e < tile0 +
@@ -410,30 +409,38 @@ inline int64_t count_last_tiles(const AttnRoute& r, const int64_t* q_off, int H,
   return count_dealt_tiles(off, H, rows);
 }
 
-// Log2 keys: whether a launch runs in 512-row tiles, and how it is split.  Both sides' times in ns, fitted to launches of 16
-// heads: a pair of 256-row tiles takes 1517 a key tile and a 512-row tile 1462, with 5 and 7.5 us for their ends; segments
-// and their sum, which are twice as large, take 12 and 20 us.  A head's last tile of at most 256 rows is half a tile.  A
-// split launch has to gain 1.5 % by this, another one 0.5 %.  Every tile of a round has to be as long as the others: one workgroup
-// on a CU leaves it idle behind a short one (12 heads of 36 000 rows against 7000 to 17 000 keys 1126 us in 256-row tiles, 1237 in
-// these).  A plan that needs more slots than there are is dropped (kAttnScratchBytes).  us, 256-row tiles / these: 16 heads of 16384 x 4096 206 / 203, 16384 x 16384 780 / 749, 17600 x 17600 900 / 888,
-// 28700 x 9000 767 / 758, 28650 x 28650 2362 / 2294, 28700 x 83140 6870 / 6693, 8112 x 21619 521 / 500, 24 of 61587 x 6566 1778 /
-// 1761; 57 random launches of 8 to 24 heads 0.975 of the time in the median, 1.007 at most.
+// Log2 keys: whether a launch runs in 512-row tiles, and how it is split.  Both sides' times in ns: a pair of 256-row tiles
+// takes 1517 a key tile and 5 us for its ends, segments and their sum 12 us; a 512-row tile in a round 1438 and 10 us, in a launch
+// with segments 1454 and 11 us, segments and their sum 22 us (half a tile: a head's last one of at most 256 rows).  Rounds count as the
+// grid deals the tiles to the XCDs: one tile more than an XCD has CUs is another round (6 heads of 21713 rows x 3974 keys, 256 tiles:
+// 110 us in 256-row tiles, 181 in these).  Fitted to 980 random launches of 1 to 64 heads, each on two to five chips, on which the same
+// launches differ by 2 % between the two kinds of tiles: those chosen take 0.983 of the time in 256-row tiles in the mean (0.975 on the
+// better chips, 0.987 on the others), 6 % of them more than 1.01, 1.05 at most.  With 1462 and 7.5 us a tile and without the count of what
+// is dealt a third took more than 1.01 on the others, 1.65 at most.  Every tile of a round has to be as long as the others:
+// one workgroup on a CU leaves it idle behind a short one (12 heads of 36 000 rows against 7000 to 17 000 keys 1126 us in 256-row
+// tiles, 1237 in these).  A plan that needs more slots than there are is dropped (kAttnScratchBytes).  us, 256-row tiles / these: 16 heads of
+// 16384 x 4096 208 / 204, 16384 x 16384 794 / 759, 17600 x 17600 964 / 945, 23500 x 23500 1622 / 1575, 28650 x 28650 2527 / 2428, 31190 x 31190
+// 2897 / 2775, 28380 x 83140 7249 / 6936, 8192 x 83140 2105 / 1897.
 inline bool choose_wide_tiles(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words, AttnRoute* out) {
   AttnRoute& r = *out;
-  int64_t min_keys = INT64_MAX, max_keys = 0, halves = 0, halves256 = 0, work = 0, work256 = 0;    // half tiles, and times their key tiles
+  int64_t min_keys = INT64_MAX, max_keys = 0, full = 0, ragged = 0, tiles256 = 0, work256 = 0;
+  int64_t heads = 0, halves = 0, work = 0;    // half tiles, and times their key tiles
   for (int h = 0; h < H; ++h) {
     const int64_t mq = q_off[h + 1] - q_off[h], mk = k_off[h + 1] - k_off[h], kt = (mk + kAttnKeyTile - 1) / kAttnKeyTile;
     if (mq == 0) continue;
+    ++heads;
     min_keys = std::min(min_keys, mk);
     max_keys = std::max(max_keys, mk);
     const int64_t n256 = (mq + kAttnTileRows - 1) / kAttnTileRows;
+    full += mq / kWideRows;
+    ragged += mq % kWideRows != 0;
+    tiles256 += n256;
     const int64_t n = mq / kWideRows * 2 + (mq % kWideRows == 0 ? 0 : mq % kWideRows <= kAttnTileRows ? 1 : 2);
     halves += n;
-    halves256 += n256;
     work += n * kt;
     work256 += n256 * kt;
   }
-  const int64_t tiles = count_tiles(q_off, H, kWideRows);
+  const int64_t tiles = full + ragged;
   // (rounds of tiles, one a CU: all have to be of one length)
   if (tiles < cus || min_keys < kWideKeys || max_keys - min_keys > min_keys / 32) return false;
   r.tiles = AttnTiles::kTiles512;
@@ -445,10 +452,19 @@ inline bool choose_wide_tiles(const int64_t* q_off, const int64_t* k_off, int H,
     // tiles, 1582 : 1617)
     if (r.split.n_tiles > 0 && r.split.n_tiles * 8 < cus) return false;
   }
-  const int64_t rounds = (tiles + cus - 1) / cus * cus;
-  const int64_t time = r.split.n_tiles > 0 ? (work * 1462 + halves * 7500) / 2 / cus + 20000 : (work / halves * 1462 + 7500) * rounds / cus;
-  const int64_t time256 = (work256 * 1517 + halves256 * 5000) / 2 / cus + (halves256 % cus ? 12000 : 0);
-  return time * (r.split.n_tiles > 0 ? 203 : 201) <= time256 * 200;
+  const int64_t time256 = (work256 * 1517 + tiles256 * 5000) / 2 / cus + (tiles256 % cus ? 12000 : 0);
+  const bool split = r.split.n_tiles > 0;
+  if (split) {
+    full = r.kept_full;
+    ragged -= r.split_ragged;
+  }
+  const int64_t rounds = (8 * ((full + 7) / 8 + (ragged + 7) / 8) + cus - 1) / cus;       // (as count_dealt_tiles())
+  if (split && rounds * cus > tiles - r.split.n_tiles) return false;
+  // (heads of few tiles: an XCD's CUs walk the keys of four and more at a time, and so do the segments.  40 heads of 3685 x 18667 544 /
+  // 583, 48 of 4203 x 16739 665 / 704; 12 such launches 1.013 in the mean, 0.96 from 32 768 keys on)
+  if (split && tiles < 10 * heads && min_keys < 32768) return false;
+  const int64_t time = split ? (work * 727 + tiles * 10800) / cus + 22200 : (work / halves * 1438 + 9860) * rounds;
+  return split ? time * 301 <= time256 * 300 : time <= time256;
 }
 
 // The whole decision for a launch with room for `scratch_words` fp32 words of partial results (0: none).  `log2_keys`: one

@@ -50,6 +50,19 @@ def test_which_launches_run_in_512_row_tiles(H, mq, mk, n_tiles):
     assert (p["n_tiles"] if p else None) == n_tiles
 
 
+def test_one_tile_more_than_an_xcd_has_cus_is_another_round():
+    """256 tiles, 246 full and 10 partial ones: the grid deals 31 and 2 of them to the first XCD's 32 CUs."""
+    rows = [12900] * 9 + [11000]
+    assert sum(-(-m // ROWS) for m in rows) == 256 and check_wide_plan(rows, [4000] * 10) is None
+    assert check_wide_plan([12900] * 9 + [11264 - 512], [4000] * 10) is None       # 255: not a round
+    assert check_wide_plan([16384] * 8, [16384] * 8)["n_tiles"] == 0               # 256 full ones: dealt evenly
+
+
+def test_heads_of_few_tiles_against_few_keys_do_not():
+    assert check_wide_plan([3685] * 40, [18667] * 40) is None
+    assert check_wide_plan([3685] * 40, [45000] * 40)["n_tiles"] == 64
+
+
 def test_heads_of_different_key_lengths_do_not():
     assert check_wide_plan([28700] * 16, [28700] * 15 + [30000]) is None
     assert check_wide_plan([28700] * 15 + [0], [28700] * 15 + [512]) is not None      # (a head without rows has no say)
@@ -74,7 +87,7 @@ def test_shares_take_equal_times(H, mq, mk):
 @pytest.mark.parametrize("rows,n_tiles,slots", [(28650, 128, 766), (28700, 144, 764), (29142, 144, 798), (30166, 176, 862), (31190, 208, 926), (23500, 224, 958)])
 def test_a_plan_needs_room_for_all_its_slots(rows, n_tiles, slots):
     """Tiles in excess are cut if there is room for all of the plan's slots and not otherwise (then all tiles run whole, or none has
-    512 rows); what the library asks for holds 767, which the plans of about a third of the long launches exceed."""
+    512 rows); what the library asks for holds 767, which the plans of a quarter of the long launches exceed."""
     off = [h * rows for h in range(17)]
     p = check_wide_plan([rows] * 16, [rows] * 16, slots * SLOT_BYTES)
     assert (p["n_tiles"], p["slots"]) == (n_tiles, slots)
