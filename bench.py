@@ -119,6 +119,19 @@ def mfma_sustained_tflops():
             "what": "register-only loop of v_mfma_f32_16x16x32_bf16, pseudo-random operands, 512 workgroups of 4 waves"}
 
 
+def stage3_kernel(httm, H, M_q, M_k, log2_keys):
+    """The kernel that runs the merged rows' whole tiles in stage 3 (the plan the library itself evaluates)."""
+    import torch
+    q_off, k_off = ([h * m for h in range(H + 1)] for m in (M_q, M_k))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if log2_keys and httm.attention_wide_plan(q_off, k_off, cus) is not None:
+        return "attention_wide_kernel"
+    tiles = httm.attention_route(q_off, k_off, cus)["tiles"][0]
+    shape = {"tiles256": "4, 4, 1", "tiles128": "2, 4, 1", "groups32": "2, 4, 4", "groups64": "2, 8, 4", "groups128": "2, 8, 2",
+             "groups128_wide": "4, 8, 4", "groups256": "4, 8, 2"}[tiles]
+    return f"attention_kernel<{shape}, {'false' if log2_keys else 'true'}>"
+
+
 def pmc_traffic_bytes(kernel: str, workload_index: int):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 --pmc summary of this workload
     (FETCH_SIZE + WRITE_SIZE, already scaled by the copy-kernel calibration), and the file, or None."""
@@ -290,8 +303,9 @@ def main():
     clocks["after_headline"] = shader_clock_mhz()
 
     a = headline["stages"]["attention"]
-    traffic, traffic_file = pmc_traffic_bytes("attention_kernel<4, 4, 1, false>" if LK else "attention_kernel<4, 4, 1, true>", w.index)
-    roofline = {"kernel": "attention_kernel", "bound": "mfma", "achieved": a["TFLOP/s"],
+    kernel = stage3_kernel(httm, H, plan_desc["M_q"], plan_desc["M_k"], LK)
+    traffic, traffic_file = pmc_traffic_bytes(kernel, w.index)
+    roofline = {"kernel": kernel, "bound": "mfma", "achieved": a["TFLOP/s"],
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": a["TFLOP/s"] / PEAK_BF16_TFLOPS,
                 "traffic": None if special else traffic,
                 "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated; not measured in this "
