@@ -1602,13 +1602,17 @@ void attention_kernel(const AttnArgs a) {
   const int pos = block >> 3, whole_per_xcd = a.full_per_xcd + a.ragged_per_xcd;
   if (dev_tile) {
     if (!a.dev_tiles) return;
-    const int half = (block - a.main_blocks) & a.dev_halves, t = (block - a.main_blocks) >> a.dev_halves;
+    int t = block - a.main_blocks, half = 0;
+    if constexpr (KS == 1 && BQ == kAttnTileRows) {
+      half = t & a.dev_halves;
+      t >>= a.dev_halves;
+    }
     if (t >= a.dev_tiles[0]) return;
     h = a.dev_tiles[1 + 2 * t];
     q0 = a.dev_tiles[2 + 2 * t] + half * kAttnTileRows;
     q_base_dev = a.dev_q_off[h];
     mq_dev = a.dev_q_off[h + 1] - a.dev_q_off[h];
-    if (q0 >= mq_dev) return;
+    if (half && q0 >= mq_dev) return;
   } else if (KS == 1 && pos >= whole_per_xcd) {
     const int item = pos - whole_per_xcd;
     share = xcd * a.split_per_xcd + item;

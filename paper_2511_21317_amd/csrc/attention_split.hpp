@@ -423,6 +423,7 @@ inline int64_t count_last_tiles(const AttnRoute& r, const int64_t* q_off, int H,
 // 2897 / 2775, 28380 x 83140 7249 / 6936, 8192 x 83140 2105 / 1897.
 inline bool choose_wide_tiles(const int64_t* q_off, const int64_t* k_off, int H, int64_t cus, int64_t scratch_words, AttnRoute* out) {
   AttnRoute& r = *out;
+  if ((q_off[H] - q_off[0]) / kWideRows + H < cus) return false;       // (the small launches, which the host's time is most of)
   int64_t min_keys = INT64_MAX, max_keys = 0, full = 0, ragged = 0, tiles256 = 0, work256 = 0;
   int64_t heads = 0, halves = 0, work = 0;    // half tiles, and times their key tiles
   for (int h = 0; h < H; ++h) {
