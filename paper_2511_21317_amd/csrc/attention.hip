@@ -1260,7 +1260,7 @@ __device__ __forceinline__ void attention_tile(const AttnArgs& a, bf16_t (*lds)[
 // tile's requests have one and a half tiles until that barrier - three buffers each of K and V, LDS objects of their own, so
 // that reads of one do not wait for the requests to another.  Products, their order and the sums of a row are
 // those of the 256-row tiles, bit for bit.  16 heads of 24576 rows x 28700 keys: 1.855 GHz with the matrix cores busy 75 % of
-// the cycles in 256-row tiles; with bursts of reads 2.07 GHz and 69 % here.  us, 256-row tiles / two buffers and the reads in
+// the cycles in 256-row tiles; 16 of 28650 x 28650 here 1.95 to 2.01 GHz and 71 %.  us, 256-row tiles / two buffers and the reads in
 // bursts at the ends of a step's halves / two buffers / three: 16 x 16384 x 16384 780 / 775 / 754 / 749, 24576 x 28700 2040 / 2020 /
 // 1965 / 1950, 24 x 37477 x 9201 1517 / - / 1515 / 1473 (later rounds are not in step any more: K and V come from further away).
 // A half with a row out of the range of its weights is taken again as a 256-row tile with shifts: a workgroup alone on its CU,
