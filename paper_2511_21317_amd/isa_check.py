@@ -47,7 +47,7 @@ class _Instr:
 
 def _functions(asm: str):
     """(name, instructions) of every function of an assembly file, with the edges of its control flow."""
-    name, body, labels, pending, in_asm = None, [], {}, [], False
+    name, body, labels, in_asm = None, [], {}, False
 
     def finish():
         target = None
@@ -72,13 +72,12 @@ def _functions(asm: str):
         line = re.sub(r"\s+", " ", raw.split(";")[0]).strip()
         m = re.match(r"([\w.$]+):", line)
         if m:
-            if not m.group(1).startswith("."):
-                name, body, labels = m.group(1), [], {}
-            else:
+            if m.group(1).startswith("."):
                 labels[m.group(1)] = len(body)
-        elif name and line.startswith(".end_amdhsa_kernel") or name and line.startswith(".Lfunc_end"):
-            yield finish()
-            name = None
+                continue
+            if name and body:
+                yield finish()
+            name, body, labels = m.group(1), [], {}
         elif name and re.match(r"[a-z]+_", line):
             body.append(_Instr(line, in_asm))
     if name and body:

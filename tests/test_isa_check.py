@@ -59,6 +59,14 @@ def test_every_path_is_followed():
     assert hazards(kernel(*far))[1]
 
 
+def test_every_function_is_looked_at():
+    bad, good = kernel("v_mov_b32_e32 v4, v0", PRODUCT), kernel(PRODUCT)
+    function = bad.replace("kernel", "function").replace("\ts_endpgm\n\t.end_amdhsa_kernel function\n", "\ts_setpc_b64 s[30:31]\n")
+    for asm in (bad + good, good + bad, function + good, good + function):
+        n, found = hazards(asm)
+        assert n == 2 and len(found) == 1
+
+
 def test_a_build_with_them_is_refused(tmp_path):
     path = tmp_path / "attention-hip-amdgcn-amd-amdhsa-gfx950.s"
     path.write_text(kernel(PRODUCT))
